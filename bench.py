@@ -213,8 +213,11 @@ def sweep_roofline(cfg, seed, iters=200, temperature=0.0, **over):
     recursion is bound by vector-instruction issue, so on the 1000-face pair
     at T = 0.1 (seed 0) its instructions per launch, from the committed SQ
     counter summary, are set against the VALU issue peak.
-    ``over`` changes the pair's spec (e.g. ``k=96``).  The working set is the
-    two record buffers, the routing words and the row pointers."""
+    ``over`` changes the pair's spec (e.g. ``k=96``).  A hard iteration is two
+    kernels (the variable pass and the row pass), timed from the start of the
+    first to the end of the second.  The working set is one multiplier, one
+    variable word and one cell index per nonzero and the cost and residual of
+    every variable (padding not counted)."""
     w = Workload(cfg, seed, **over)
     c = w.ctx
     cxy, cyx = c.knn_candidates(w.DX, w.DY, w.spec.k, w.knn_prec)
@@ -242,7 +245,7 @@ def sweep_roofline(cfg, seed, iters=200, temperature=0.0, **over):
     nbytes = BYTES_PER_NNZ * info["nnz"] + BYTES_PER_ROW * info["n_rows"]
     gbs = nbytes / (us * 1e-6) / 1e9
     rec_bytes = 4 if w.msg == "fp32" else 8
-    working_set = 2 * 8 * rec_bytes * info["n_free"] + 4 * info["nnz"] + 4 * (info["n_rows"] + 1)
+    working_set = (rec_bytes + 8) * info["nnz"] + (2 * rec_bytes + 1) * info["n_free"]
     out = {"pair": f"{w.spec.faces_x}/{w.spec.faces_y} faces, K={w.spec.k}", "nnz": info["nnz"],
            "rows": info["n_rows"], "working_set_bytes": working_set,
            "avg_launch_us": round(us, 2), "bytes_per_launch": nbytes, "achieved_GBps": round(gbs, 1),
@@ -544,8 +547,9 @@ def copy_calibration(nbytes, reps=5):
 def summarize_counters(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, out_json, copy_bytes,
                        command="", workload="plain_fp32_500 (config 2, seed 0)"):
     """Turn rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE collections (KiB per
-    dispatch) of the sweep kernel and of a plain copy of ``copy_bytes`` bytes
-    into HBM bytes per sweep launch; writes the summary JSON used by the
+    dispatch) of the sweep kernels and of a plain copy of ``copy_bytes`` bytes
+    into HBM bytes per sweep (the row pass and, where the collection has one,
+    the variable pass before it); writes the summary JSON used by the
     roofline's ``traffic`` field."""
     import csv
     import hashlib
@@ -556,15 +560,17 @@ def summarize_counters(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, out
     def per_kernel(path, counter, name_has):
         rows = [r for r in csv.DictReader(open(path))
                 if r["Counter_Name"] == counter and name_has in r["Kernel_Name"]]
-        if name_has.startswith("k_sweep"):
+        if name_has.startswith("k_"):
             names.update(r["Kernel_Name"].strip() for r in rows)
-        return statistics.median(float(r["Counter_Value"]) for r in rows), len(rows)
+        return statistics.median([float(r["Counter_Value"]) for r in rows] or [0.0]), len(rows)
 
     cf, _ = per_kernel(copy_fetch_csv, "FETCH_SIZE", "copyBuffer")
     cw, _ = per_kernel(copy_write_csv, "WRITE_SIZE", "copyBuffer")
-    # the hard FP32 update sweep, with or without row tiles: k_sweep<float, false, 0, ...>
+    # the hard FP32 update sweep, k_sweep<float, false, 0, ...>, and its variable pass
     f, nf = per_kernel(fetch_csv, "FETCH_SIZE", "k_sweep<float, false, 0")
     wv, nw = per_kernel(write_csv, "WRITE_SIZE", "k_sweep<float, false, 0")
+    f += per_kernel(fetch_csv, "FETCH_SIZE", "k_vars<float>")[0]
+    wv += per_kernel(write_csv, "WRITE_SIZE", "k_vars<float>")[0]
     kib = copy_bytes / 1024.0
     ffac, wfac = kib / cf, kib / cw
     fetch_b = f * ffac * 1024.0
@@ -640,7 +646,7 @@ def main():
     info = w.ctx.info
     log(f"[bench] timed: {ms_per_step:.2f} ms/step, {value:.0f} dual it/s, gap={r['gap']:.2e}")
 
-    # dominant kernel: the sweep, timed per launch with HIP events on its stream
+    # dominant kernels: one sweep (variable pass and row pass), timed with HIP events on its stream
     c = w.ctx
     lam = c.init_lambda(w.msg)
     c.dual_solve(lam, 20, w.spec.omega, w.spec.temperature, trace=False)
@@ -663,7 +669,7 @@ def main():
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             # the committed counters describe the seed-0 pair at its own K
             "traffic": _traffic() if (a.config, a.seed, a.k) == (2, 0, None) and w.iters > 0 else None,
-            "kernel": "k_sweep<float,false,MODE_UPDATE>", "avg_launch_us": round(avg_s * 1e6, 3),
+            "kernel": "k_vars<float> + k_sweep<float,false,MODE_UPDATE>", "avg_launch_us": round(avg_s * 1e6, 3),
             "bytes_per_launch": bytes_per_launch}
     log(f"[bench] sweep kernel: {n_launch} launches, avg {avg_s * 1e6:.2f} us, {achieved:.0f} GB/s algorithmic")
 

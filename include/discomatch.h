@@ -106,10 +106,11 @@ dm_status dm_set_stream(dm_ctx* ctx, void* hip_stream);
  * (dm_build_product_space or dm_build_ilp, and after dm_fix_variables) the
  * Jacobi solver's state of one message precision has a known size:
  * dm_workspace_query gives it for stage DM_WS_SOLVE_FP32 or DM_WS_SOLVE_FP64
- * (two multiplier record buffers of n_free x 8 reals and the per-block bound
- * partials of a sweep).  dm_set_workspace hands the library a device buffer
+ * (the multipliers in the sweeps' own layouts: cells and variable vectors, or
+ * two record buffers of n_free x 8 reals, whichever is larger, and the
+ * per-block bound partials of a sweep).  dm_set_workspace hands the library a device buffer
  * of at least that many bytes, 256-byte aligned: from then on dm_dual_solve,
- * dm_lbfgs_solve and the sweeps of that precision keep their records and
+ * dm_lbfgs_solve and the sweeps of that precision keep their state and
  * partials there instead of allocating them.  The caller owns the buffer,
  * keeps it alive while it is attached and does not touch it between calls;
  * the library reads and writes it only on the context's stream.  ptr = NULL

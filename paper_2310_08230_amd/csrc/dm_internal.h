@@ -151,6 +151,12 @@ struct MeshDev {
   DArr<double> area;       // nv mixed areas (filled by costs)
 };
 
+// Cell word (hard sweep): [31:29] number of rows the variable lies in (1 to 5),
+// [26:0] variable in variable order; CHUNK_PAD marks padding.
+constexpr int CELL_DEG_SHIFT = 29;
+constexpr int TILE_NARROW = 5;   // entries of each sign a row of a narrow / wide tile holds
+constexpr int TILE_WIDE = 8;
+
 // Reduced-problem entry word: [31] coefficient is -1, [30] unused, [29:27]
 // slot of the entry in its variable's record, [26:0] variable.
 constexpr uint32_t W_NEG = 1u << 31;
@@ -161,7 +167,7 @@ constexpr int REC_COST = 5;
 constexpr int REC_RDEG = 6;
 constexpr int MAX_SHORT_ROW = 64;
 constexpr int SOFT_MAX_ROW = 24;
-constexpr uint32_t CHUNK_PAD = 0xFFFFFFFFu;   // entry word of an unused chunk slot
+constexpr uint32_t CHUNK_PAD = 0xFFFFFFFFu;   // cell word of an unused cell
 
 // Multipliers of free variable i from its record (slots 0-4 hold s_k, slot 5
 // the cost c_i, slot 6 the reciprocal 1/|J_i| of the number of rows the
@@ -245,6 +251,26 @@ __device__ inline double sum_partials_1024(const double* p, int n, double* red) 
 
 constexpr int HOST_SLOTS = 16;
 
+// state of the hard sweep: one multiplier per cell, the residual t and the
+// cost per variable (variable order); the second cell and t buffers hold the
+// new multipliers where the old ones are still needed
+struct CellState {
+  DArr<unsigned char> cell[2], t[2], cost;
+  template <typename R>
+  R* cells(int b) { return reinterpret_cast<R*>(cell[b].p); }
+  template <typename R>
+  R* ts(int b) { return reinterpret_cast<R*>(t[b].p); }
+  template <typename R>
+  R* costs() { return reinterpret_cast<R*>(cost.p); }
+  void release() {
+    for (int b = 0; b < 2; ++b) {
+      cell[b].release();
+      t[b].release();
+    }
+    cost.release();
+  }
+};
+
 struct dm_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -301,19 +327,22 @@ struct dm_ctx {
   int32_t n_chunks = 0;
   DArr<int4> chunk_desc;   // n_chunks wave chunks: (first row, rows, first entry, entries)
   DArr<unsigned long long> chunk_mask;  // per chunk: bit e set when entry e starts a row
-  DArr<uint32_t> chunk_word;  // 64 per chunk: the chunk's entry words, CHUNK_PAD past its end
+  DArr<unsigned long long> chunk_neg;   // per chunk: bit e set when entry e has coefficient -1
   DArr<int8_t> chunk_b;       // 64 per chunk: right-hand side of each entry's row
-  // launch layout of the hard sweep (layout.hip): short rows are packed into
-  // the chunks in region/key order; projection rows run in long_perm order;
-  // block b takes item xcd_item[(b % 8) * xcd_stride + b / 8] (-1: none)
+  // launch layout of the hard sweep (layout.hip): cells in row order (narrow
+  // tiles, wide tiles, chunks, projection rows, then one zero cell), variables
+  // in mesh order
+  int64_t n_cells = 0;        // without the zero cell, whose index it is
+  int32_t n_tiles[2] = {0, 0};   // narrow and wide 64-row tiles of short rows with b = 0
+  int64_t wide_cell0 = 0, chunk_cell0 = 0, long_cell0 = 0;
+  DArr<uint32_t> cell_word;   // n_cells
+  DArr<uint32_t> ent_cell;    // nnz: cell of every entry of the reduced rows
+  DArr<uint32_t> vpos;        // 5 planes of n_free: cell of slot k of variable v at k * n_free + v
+  DArr<int32_t> vperm, vinv;  // n_free: reduced variable of v, and back
+  DArr<uint8_t> vdeg;         // n_free: rows of v
   int32_t long_wpr = 1;       // waves per projection row: 1 or 4 (4 rows or 1 row per block)
-  int32_t n_long_items = 0;   // projection-row blocks
-  int32_t xcd_stride = 0;
-  int32_t n_tiles = 0;        // 64-row tiles of short rows with b = 0 (one lane per row)
-  int32_t n_tile_items = 0;   // blocks of four tiles
-  DArr<uint32_t> tile_word;   // per tile 16 x 64 entry words: 8 slots of +1 entries, 8 of -1 entries
+  int32_t n_long_y = 0;       // Y projection rows, the first in long_perm
   DArr<int32_t> long_perm;    // n_rows - n_short: projection rows (relative to n_short) in launch order
-  DArr<int32_t> xcd_item;     // 8 * xcd_stride
   DArr<int32_t> soft_row;     // short rows sorted (stably) by length, for the smoothed sweep
   int64_t soft_c8 = 0, soft_c16 = 0;   // how many of them have <= 7 / 8..15 entries
 
@@ -329,9 +358,9 @@ struct dm_ctx {
   DArr<int32_t> corner_list; // 3*nP
 
   // solver state (byte buffers reused for FP32 / FP64)
-  DArr<unsigned char> rec[2];    // records n_free * REC * sizeof(real)
-  DArr<unsigned char> rrec[2];   // rounding copy
-  DArr<unsigned char> mrec;      // min-marginals / marginals per slot
+  DArr<unsigned char> rec[2];    // smoothed sweep: records n_free * REC * sizeof(real)
+  CellState cells, rcells;       // hard sweep: solver and rounding copy
+  DArr<unsigned char> mrec;      // min-marginals per cell, or marginals per slot
   DArr<double> partial;          // per-block partial sums, two alternating halves
   int pend_half = 0;             // half written by the last sweep launch
   double* pend_partial = nullptr;
@@ -351,6 +380,7 @@ struct dm_ctx {
 
   // optional per-launch event timing of the sweep kernel
   bool timing = false;
+  bool timing_open = false;   // a start event waits for its row pass
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
 
@@ -390,40 +420,50 @@ dm_status check_finite(dm_ctx* ctx, const float* a, int64_t na, const float* b, 
 // takes this device's address of the scratch array of dm_knn_candidates_noalloc (once per device)
 dm_status knn_scratch_init(dm_ctx* ctx);
 dm_status dual_flush(dm_ctx* ctx);  // write the bound of the last sweep launch
-// layout of the Jacobi solver's state in a caller workspace: two record
-// buffers, then the sweep partials; sizes for the current problem
+// layout of the Jacobi solver's state in a caller workspace: two cell buffers
+// and three variable vectors (hard sweep) or two record buffers (smoothed) in
+// the same place, then the sweep partials; sizes for the current problem
 struct SolverLayout {
-  size_t rec_bytes, part_off, part_count, total;
+  size_t rec_bytes, cell_bytes, var_bytes, part_off, part_count, total;
 };
 SolverLayout solver_layout(const dm_ctx* ctx, size_t real_bytes);
 dm_status cost_offset(dm_ctx* ctx);   // offset = summed costs of elements fixed to 1 (synchronises)
 dm_status corner_lists(dm_ctx* ctx);  // corners per candidate pair (built once per product space)
 void fill_info(dm_ctx* ctx, dm_space_info* info);   // sizes of the current (reduced) problem
 dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix);  // presolve from fixings, reduced problem
-dm_status sweep_layout(dm_ctx* ctx);   // chunks, projection-row order and per-XCD items of the hard sweep
+dm_status sweep_layout(dm_ctx* ctx);   // cells, variable order and launch order of the hard sweep
 
-// One sweep over all rows of the presolved problem (dual.hip).  Modes: update
-// the multipliers (rin -> out), write min-marginals (or soft marginals) per
-// slot to out, bound only, or write each row's minimising assignment.
+// Sweeps over all rows of the presolved problem (dual.hip).  Modes: update the
+// multipliers, write min-marginals (or soft marginals), bound only, or write
+// each row's minimising assignment.
 enum SweepMode { SWEEP_UPDATE = 0, SWEEP_EVAL = 1, SWEEP_BOUND = 2, SWEEP_SUBGRAD = 3 };
 // Options of the hard sweep used by the quasi-Newton layer: rows see
 // lambda + (*gamma) * dir (gamma on the device); the launch does nothing while
-// *skip is nonzero; SWEEP_SUBGRAD writes 1 / 0 per slot to gsub.  dir and gsub
-// hold five slot planes of n_free values: slot k of variable i at
-// k * n_free + i.
+// *skip is nonzero; SWEEP_SUBGRAD writes 1 / 0 per entry to gsub.  dir and gsub
+// hold one value per cell.
 struct SweepExt {
   const void* dir = nullptr;
   const double* gamma = nullptr;
   const int32_t* skip = nullptr;
   uint8_t* gsub = nullptr;
 };
+// hard sweep: state from multipliers in entry order (two: both buffers), t of
+// every variable (after every change of the cells), a row pass, and back
 template <typename R>
-dm_status dual_import(dm_ctx* ctx, const R* lam, DArr<unsigned char>* bufs);
+dm_status cells_import(dm_ctx* ctx, const R* lam, CellState& S, bool two);
 template <typename R>
-dm_status dual_export(dm_ctx* ctx, const unsigned char* rec, R* lam);
+dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool timed);
 template <typename R>
-dm_status dual_sweep(dm_ctx* ctx, int mode, bool soft, const unsigned char* rin, unsigned char* out, R omega,
-                     R T, double* bound_out, const SweepExt* ext = nullptr);
+dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
+                     const SweepExt* ext);
+template <typename R>
+dm_status cells_export(dm_ctx* ctx, const R* cells, const R* t, R* lam);
+// smoothed sweep on records
+template <typename R>
+dm_status records_import(dm_ctx* ctx, const R* lam, DArr<unsigned char>* bufs);
+template <typename R>
+dm_status soft_sweep(dm_ctx* ctx, int mode, const unsigned char* rin, unsigned char* out, R omega, R T,
+                     double* bound_out);
 
 // grid size helper
 inline unsigned grid_for(int64_t n, int block) {

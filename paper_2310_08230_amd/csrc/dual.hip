@@ -1,33 +1,45 @@
 // Jacobi min-marginal averaging on the Lagrangean dual (Sec. 3.2, Eq. (D);
 // the MMA step of Alg. 1) and the dual bound.
 //
-// State layout.  The multipliers lambda^j_i of free variable i live in one
-// record of REC reals: slots 0-2 for its three closedness rows (edges k = 0,
-// 1, 2 of the element), slot 3 for its first projection row, slot 4 for its
-// Y projection row when the element is triangle-triangle, slot 5 for the cost
-// c_i, slot 6 for its number of rows (a generic problem's variable takes slots
-// 0 to |J_i| - 1 in row order).  Two record buffers alternate between
-// iterations.
+// State layout (hard minimum).  Every entry of the presolved rows owns one
+// cell with its multiplier s^j_i; the cells are in row order (layout.hip).  One
+// iteration is two passes:
+//   1. k_vars, one thread per variable: gathers the variable's s from its (at
+//      most five) cells and writes one value, the residual t_i = c_i - sum_k s_k;
+//   2. k_sweep, over the rows: each entry reads its cell and its variable's t
+//      and restores dual feasibility, lambda^j_i = s_j + t_i / |J_i|; the row
+//      computes its minimum and the min-marginal differences M^j_i =
+//      min_{s_i=1} - min_{s_i=0} (Appendix "Coarse-to-fine"); each entry writes
+//      s_j' = lambda^j_i - omega M^j_i back to its cell.  Row minima are summed
+//      into an FP64 bound in a fixed order.
+// Together they are lambda <- lambda - omega (M - mean_j M): the mean of the
+// min-marginals is exactly what the projection adds back.
 //
-// One iteration is one kernel launch over every row of the presolved problem:
-//   1. each entry reads its variable's record from the previous iteration and
-//      restores dual feasibility, lambda^j_i = s_j + (c_i - sum_k s_k)/|J_i|;
-//   2. each row computes its minimum and the min-marginal differences
-//      M^j_i = min_{s_i=1} - min_{s_i=0} (Appendix "Coarse-to-fine");
-//   3. each entry writes s_j' = lambda^j_i - omega M^j_i to the other buffer;
-//   4. row minima are summed into an FP64 bound in a fixed order.
-// Steps 1 and 3 together are lambda <- lambda - omega (M - mean_j M): the
-// mean of the min-marginals is exactly what the projection in step 1 adds
-// back, so the variable-averaging pass needs no separate launch.
+// What bounds an iteration and why two passes: an entry needs its variable's
+// sum, and a single pass has to gather the variable's whole 32-byte record for
+// it and scatter 4 bytes into another (measured: 3.7 times the algorithmic
+// bytes through the L2 at the 2000/3000-face pair, 253 us).  Split in two, the
+// row pass streams its cells coalesced, in place, and every random access is a
+// 4-byte read of a small array (t: 4 bytes per variable) or of cells that
+// neighbouring variables share.  Measured, one iteration before and after:
+// 13.2 -> 10.0 us at the 500-face pair (two launches of 2.4 us each are half of
+// it), 41.6 -> 25.0 at 1000 faces, 253 -> 121 at 2000/3000 (row pass 75, variable
+// pass 46; 4.7 and 5.0 TB/s through the L2s, a plain copy reaches 4.7), 837 -> 381
+// with K = 144 candidates.
 //
-// Rows: closedness rows (short, coefficients +-1, right-hand side b) are packed
-// into chunks of at most 255 entries, one 256-thread block per chunk, with the
-// row minimum from sorted prefix sums in LDS: choosing k entries with
-// coefficient +1 and k-b with -1 costs at least S+(k) + S-(k-b), the sums of
-// the k and k-b smallest multipliers.  Projection rows (all +1, b = 1) get one
-// block each and reduce (min, argmin, second min) across the block.  With a
-// temperature T > 0 every min becomes the soft-min -T log sum exp(-./T); short
-// rows then run a partial-sum recursion with one lane per partial sum.
+// Rows: closedness rows (short, coefficients +-1, right-hand side b) with b = 0
+// and few entries run one lane per row (tiles), the others one lane per entry
+// in wave chunks, with the row minimum from sorted prefix sums: choosing k
+// entries with coefficient +1 and k-b with -1 costs at least S+(k) + S-(k-b),
+// the sums of the k and k-b smallest multipliers.  Projection rows (all +1,
+// b = 1) get one wave or one block each and reduce (min, argmin, second min).
+//
+// With a temperature T > 0 every min becomes the soft-min -T log sum
+// exp(-./T); short rows then run a partial-sum recursion with one lane per
+// partial sum.  That sweep is bound by its arithmetic and keeps one record of
+// REC reals per variable (slots 0-2 for its three closedness rows, then its
+// projection rows, slot 5 the cost, slot 6 the reciprocal row count) in two
+// buffers that alternate between iterations, one launch per iteration.
 #include <hip/hip_ext.h>
 
 #include <cmath>
@@ -252,54 +264,79 @@ __device__ inline void reduce_partials(const double* partial, int n, double offs
 }
 
 struct SweepArgs {
-  const uint32_t* word;
-  const int32_t* rrow_ptr;
-  const int32_t* soft_row;  // short rows in order of length (smoothed form)
-  int32_t soft_c8, soft_c16;  // short rows of at most 7 / of 8 to 15 entries
-  const int32_t* rrow_b;
-  const int4* chunk_desc;   // (first row, rows, first entry, entries) per chunk
+  // ---- hard minimum: cells
+  const uint32_t* word;     // per cell: variable and row count, CHUNK_PAD for padding
+  int32_t n_tiles[2];       // narrow and wide 64-row tiles
+  uint32_t wide_cell0, chunk_cell0, long_cell0;   // first cells (narrow tiles start at 0)
+  int32_t n_chunks;         // wave chunks of short rows
   const unsigned long long* chunk_mask;   // bit e: entry e of the chunk starts a row
-  const uint32_t* chunk_word;   // 64 words per chunk, CHUNK_PAD past its end
-  const int8_t* chunk_b;        // 64 per chunk: right-hand side of the entry's row
-  int32_t n_short_blocks;   // items of short rows (hard form: row tiles, then chunks)
-  int32_t n_tile_items;     // hard form: blocks of four 64-row tiles
-  int32_t n_tiles;
-  const uint32_t* tile_word;  // per tile: 16 x 64 entry words (slot j of lane l at j * 64 + l), CHUNK_PAD
-  int32_t n_short;
-  int32_t n_rows;
-  int32_t n_items;          // short-row blocks + long-row blocks
-  int32_t n_chunks;         // wave chunks of short rows (hard form)
-  int32_t long_wpr;         // waves per projection row: 1 or 4
-  int32_t n_long;           // projection rows
-  const int32_t* long_perm; // projection rows (relative to n_short) in launch order
-  const int32_t* xcd_item;  // hard form: item of block b at (b % 8) * xcd_stride + b / 8, or -1
-  int32_t xcd_stride;
-  double* partial;          // this launch's per-block partials
-  const double* prev_partial; // previous launch's partials still to be summed, or NULL
-  int32_t prev_n;
-  double prev_offset;
-  double* prev_out;
-  // quasi-Newton extensions (hard min only): rows see lambda + gamma * dir
-  // when dir is set (dir in slot planes: slot k of variable i at
-  // k * plane + i; gamma a device scalar); the launch does nothing when
+  const unsigned long long* chunk_neg;    // bit e: entry e has coefficient -1
+  const int8_t* chunk_b;    // 64 per chunk: right-hand side of the entry's row
+  int32_t n_long_y;         // of the projection rows in launch order, the Y rows come first
+  int32_t per[5];           // blocks per XCD: Y rows, X rows, chunks, wide tiles, narrow tiles
+  int32_t n_entries_short;  // entries of the short rows
+  // quasi-Newton extensions: rows see lambda + gamma * dir when dir is set
+  // (one value per cell; gamma a device scalar); the launch does nothing when
   // *skip is nonzero; MODE_SUBGRAD writes the row's minimising assignment
-  // (1 / 0 per entry) to gsub in the same slot planes
-  int64_t plane;
+  // (1 / 0 per entry) to its cells of gsub
   const void* dir;
   const double* gamma;
   const int32_t* skip;
   uint8_t* gsub;
+  // ---- smoothed: records
+  const uint32_t* ent_word;   // per entry: sign, slot, variable
+  const int32_t* soft_row;  // short rows in order of length
+  int32_t soft_c8, soft_c16;  // short rows of at most 7 / of 8 to 15 entries
+  const int32_t* rrow_b;
+  int32_t n_short_blocks;   // blocks of short rows
+  int32_t n_items;          // short-row blocks + long-row blocks
+  // ---- both
+  const int32_t* rrow_ptr;
+  int32_t n_short;
+  int32_t long_wpr;         // waves per projection row: 1 or 4
+  int32_t n_long;           // projection rows
+  const int32_t* long_perm; // projection rows (relative to n_short) in launch order
+  double* partial;          // this launch's per-block partials
+  const double* prev_partial; // smoothed: previous launch's partials still to be summed, or NULL
+  int32_t prev_n;
+  double prev_offset;
+  double* prev_out;
 };
 
-__device__ inline size_t slot_index(const SweepArgs& A, uint32_t w) {
-  return size_t((w >> W_SLOT_SHIFT) & 7u) * size_t(A.plane) + size_t(w & W_VAR_MASK);
+// multiplier of a cell with dual feasibility restored: s + t (1/|J|) in one
+// rounding, as rec_lambdas forms it
+template <typename R>
+__device__ inline R feasible(R s, R t, R rdeg) {
+  if constexpr (sizeof(R) == 4) return __builtin_fmaf(t, rdeg, s);
+  else return __builtin_fma(t, rdeg, s);
 }
 
-// multiplier seen by the rows: the record's, moved along dir when one is set
 template <typename R>
-__device__ inline R row_lambda(const SweepArgs& A, const R* __restrict__ rin, uint32_t w, R gam) {
-  R v = cur_lambda<R>(rin, w);
-  if (A.dir) v += gam * static_cast<const R*>(A.dir)[slot_index(A, w)];
+__device__ inline R fma_r(R a, R b, R c) {
+  if constexpr (sizeof(R) == 4) return __builtin_fmaf(a, b, c);
+  else return __builtin_fma(a, b, c);
+}
+
+// 1/|J| of a cell word.  A product triangle lies in four or five rows; the
+// top bit of the count tells those from the fewer rows of a generic variable.
+template <typename R>
+__device__ inline R rdeg_hi(uint32_t w) {
+  return (w >> CELL_DEG_SHIFT) & 1u ? R(1) / R(5) : R(1) / R(4);
+}
+template <typename R>
+__device__ inline R rdeg_of(uint32_t w) {
+  const uint32_t d = w >> CELL_DEG_SHIFT;
+  const R lo = d == 1u ? R(1) : (d == 2u ? R(1) / R(2) : R(1) / R(3));
+  return (w >> 31) ? rdeg_hi<R>(w) : lo;
+}
+
+// multiplier of cell c (word w, not padding) as the rows see it: feasible, and
+// moved along dir when one is set
+template <typename R>
+__device__ inline R cell_lambda(const SweepArgs& A, const R* cells, const R* __restrict__ t, uint32_t c, uint32_t w,
+                                R gam) {
+  R v = feasible<R>(cells[c], t[w & W_VAR_MASK], rdeg_of<R>(w));
+  if (A.dir) v = fma_r<R>(gam, static_cast<const R*>(A.dir)[c], v);
   return v;
 }
 
@@ -342,20 +379,21 @@ __device__ inline R permute_to(int dst_lane, R v) {   // push v to lane dst_lane
 }
 
 template <typename R, int MODE>
-__device__ inline double short_chunk_hard(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out,
+__device__ inline double short_chunk_hard(const SweepArgs& A, const R* cells, const R* __restrict__ t_, R* out,
                                           R omega, R gam, int32_t wc, R* wave_vals) {
   const int lane = threadIdx.x & 63;
   double rowpart = 0.0;
   if (wc < A.n_chunks) {   // uniform across the wave
     // the padded chunk: words and right-hand sides straight from the chunk index
     const unsigned long long starts = A.chunk_mask[wc];
-    const uint32_t wp = A.chunk_word[size_t(wc) * 64 + lane];
+    const unsigned long long negm = A.chunk_neg[wc];
+    const uint32_t cell = A.chunk_cell0 + uint32_t(wc) * 64u + uint32_t(lane);
+    const uint32_t w = A.word[cell];
     const int32_t b = A.chunk_b[size_t(wc) * 64 + lane];
-    const bool act = wp != CHUNK_PAD;
-    const uint32_t w = act ? wp : 0u;
+    const bool act = w != CHUNK_PAD;
     const int32_t ne = __popcll(__ballot(act));
-    const R lam = act ? row_lambda<R>(A, rin, w, gam) : R(0);
-    const int g = int(w >> 31);
+    const R lam = act ? cell_lambda<R>(A, cells, t_, cell, w, gam) : R(0);
+    const int g = int((negm >> lane) & 1ull);
     // my row from the chunk's row-start mask: its start is the last set bit at
     // or below this lane, its end the next set bit (or the chunk's end)
     const unsigned long long le = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
@@ -363,7 +401,6 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* __restric
     const int32_t s = 63 - __clzll(static_cast<long long>(below));   // entry 0 always starts a row
     const int32_t n = (above ? __ffsll(static_cast<long long>(above)) - 1 : ne) - s;
 
-    const unsigned long long negm = __ballot(act && g);
     const unsigned long long rowm = act ? (((n >= 64) ? ~0ull : ((1ull << n) - 1ull)) << s) : 0ull;
     const int32_t P = __popcll(rowm & ~negm);
     const int32_t N = n - P;
@@ -433,10 +470,10 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* __restric
           }
           const R Wm = g == int(sel) ? Vv : U;
           const R M = sel ? lam - Wm : lam + Wm;
-          if (MODE == MODE_UPDATE) write_out<R>(out, w, lam - omega * M);
-          if (MODE == MODE_EVAL) write_out<R>(out, w, M);
+          if (MODE == MODE_UPDATE) out[cell] = fma_r<R>(-omega, M, lam);
+          if (MODE == MODE_EVAL) out[cell] = M;
         }
-        if (MODE == MODE_SUBGRAD) A.gsub[slot_index(A, w)] = uint8_t(sel ? 1 : 0);
+        if (MODE == MODE_SUBGRAD) A.gsub[cell] = uint8_t(sel ? 1 : 0);
         if (sel) rowpart = double(lam);
       }
       return rowpart;
@@ -542,10 +579,10 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* __restric
     }
     if (act) {
       const R M = m1 - m0;
-      if (MODE == MODE_UPDATE) write_out<R>(out, w, lam - omega * M);
-      if (MODE == MODE_EVAL) write_out<R>(out, w, M);
+      if (MODE == MODE_UPDATE) out[cell] = fma_r<R>(-omega, M, lam);
+      if (MODE == MODE_EVAL) out[cell] = M;
       if (MODE == MODE_SUBGRAD)
-        A.gsub[slot_index(A, w)] = uint8_t(rank < kbest ? 1 : 0);
+        A.gsub[cell] = uint8_t(rank < kbest ? 1 : 0);
       if (lane == s) rowpart = double(rmin);
     }
   }
@@ -554,109 +591,91 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* __restric
 
 // the four waves of a block take four adjacent chunks
 template <typename R, int MODE>
-__device__ void short_wave_hard(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out, R omega,
-                                R gam, unsigned char* smem, double* red, int32_t item) {
+__device__ double chunk_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega, R gam,
+                              unsigned char* smem, int32_t item) {
   const int wave = threadIdx.x >> 6;
   R* wave_vals = reinterpret_cast<R*>(smem) + wave * 192;   // three 64-value slices per wave
-  const int32_t wc = (item - A.n_tile_items) * 4 + wave;
-  const double rowpart = short_chunk_hard<R, MODE>(A, rin, out, omega, gam, wc, wave_vals);
-  double part = block_sum(rowpart, red);
-  store_partial(part, A.partial, item);
+  return short_chunk_hard<R, MODE>(A, cells, t, out, omega, gam, item * 4 + wave, wave_vals);
 }
 
 // ---------------------------------------------------------------- short rows with b = 0, one lane per row
-// Rows with right-hand side 0 and at most TILE_HALF entries of each sign run
-// one lane per row, 64 rows per wave (a tile): the row's +1 entries sit in
-// slots 0 to TILE_HALF - 1 and its -1 entries in the next TILE_HALF slots,
-// each group in row order; slot j of lane l is word j * 64 + l of the tile,
-// CHUNK_PAD where the group has ended.  The multipliers stay in registers and
-// the closed form of the b = 0 rows (see short_chunk_hard) is evaluated over
-// pairs: within a group the earlier entry's rank rises if it is larger, the
-// later one's if it is not smaller; across the groups both counts rise if the
-// pair sums to a negative value.  d = count - rank decides whether an entry
-// is taken (d > 0).  A missing entry holds +inf: it is never taken, never
-// ranked before a value and never pairs to a negative sum.
-constexpr int TILE_HALF = 8;
-
-// a multiplier record as loaded (two 16-byte loads for FP32, four for FP64)
+// Rows with right-hand side 0 and at most H entries of each sign run one lane
+// per row, 64 rows per wave (a tile).  Pair j of lane l holds the row's j-th +1
+// and j-th -1 entry, each group in row order, in cells j * 128 + 2 l and the
+// next one (one 8-byte access per pair and lane, 512 bytes per wave).  The
+// multipliers stay in registers and the closed form of the b = 0 rows (see
+// short_chunk_hard) is evaluated over pairs: within a group the earlier
+// entry's rank rises if it is larger, the later one's if it is not smaller;
+// across the groups both counts rise if the pair sums to a negative value.
+// d = count - rank decides whether an entry is taken (d > 0).  A missing entry
+// holds +inf: it is never taken, never ranked before a value and never pairs
+// to a negative sum.
+// Two widths, because the cells of a tile are streamed whether they are used
+// or not and the comparisons grow with the square of the width: 77 % of the
+// rows of the 2000/3000-face pair have at most TILE_NARROW = 5 entries of each
+// sign, 99.4 % at most TILE_WIDE = 8; the mean is 9.7 entries in 11.4 cells.
 template <typename R>
-struct RecRaw;
+struct Pair2;
 template <>
-struct RecRaw<float> {
-  float4 lo, hi;
-  __device__ void load(const float* __restrict__ rec, uint32_t i) {
-    lo = *reinterpret_cast<const float4*>(rec + size_t(i) * REC);
-    hi = *reinterpret_cast<const float4*>(rec + size_t(i) * REC + 4);
-  }
-  // lambda of slot k with dual feasibility restored, in the arithmetic of rec_lambdas
-  __device__ float lambda(int k) const {
-    const float sum = (((lo.x + lo.y) + lo.z) + lo.w) + hi.x;
-    const float corr = (hi.y - sum) * hi.z;
-    const float sk = k == 0 ? lo.x : k == 1 ? lo.y : k == 2 ? lo.z : k == 3 ? lo.w : hi.x;
-    return sk + corr;
-  }
+struct Pair2<float> {
+  using type = float2;
 };
 template <>
-struct RecRaw<double> {
-  double2 a, b, c, d;
-  __device__ void load(const double* __restrict__ rec, uint32_t i) {
-    const double* r = rec + size_t(i) * REC;
-    a = *reinterpret_cast<const double2*>(r);
-    b = *reinterpret_cast<const double2*>(r + 2);
-    c = *reinterpret_cast<const double2*>(r + 4);
-    d = *reinterpret_cast<const double2*>(r + 6);
-  }
-  __device__ double lambda(int k) const {
-    const double sum = (((a.x + a.y) + b.x) + b.y) + c.x;
-    const double corr = (c.y - sum) * d.x;
-    const double sk = k == 0 ? a.x : k == 1 ? a.y : k == 2 ? b.x : k == 3 ? b.y : c.x;
-    return sk + corr;
-  }
+struct Pair2<double> {
+  using type = double2;
 };
 
-// TB: FP32 records in flight per batch (8 or 16); every load of a batch is
-// issued before the first one is used (a missing entry loads record 0 and is
-// then replaced).  FP64 records are twice as wide and go two at a time.
-template <typename R, int MODE, int TB>
-__device__ inline double tile_rows(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out, R omega,
-                                   R gam, const uint32_t* __restrict__ tw) {
-  constexpr int H = TILE_HALF;
-  constexpr int B = sizeof(R) == 4 ? TB : 2;
-  const int lane = threadIdx.x & 63;
-  uint32_t wv[2 * H];
+template <typename R, int MODE, int H>
+__device__ inline double tile_rows(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega,
+                                   R gam, uint32_t cell0) {
+  using P2 = typename Pair2<R>::type;
+  const uint32_t c0 = cell0 + 2u * (threadIdx.x & 63u);
+  uint2 wv[H];
+  P2 sv[H];
 #pragma unroll
-  for (int j = 0; j < 2 * H; ++j) wv[j] = tw[j * 64 + lane];
-  R lam[2 * H];   // slots 0 to H - 1: +1 entries, H to 2H - 1: -1 entries
+  for (int j = 0; j < H; ++j) wv[j] = *reinterpret_cast<const uint2*>(A.word + c0 + 128u * j);
 #pragma unroll
-  for (int j0 = 0; j0 < 2 * H; j0 += B) {
-    RecRaw<R> raw[B];
+  for (int j = 0; j < H; ++j) sv[j] = *reinterpret_cast<const P2*>(cells + c0 + 128u * j);
+  R lp[H], lq[H];
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const uint32_t w = wv[j0 + u] != CHUNK_PAD ? wv[j0 + u] : 0u;
-      raw[u].load(rin, w & W_VAR_MASK);
+  for (int j = 0; j < H; ++j) {   // a missing entry reads t of variable 0 and is replaced below
+    lp[j] = t[wv[j].x != CHUNK_PAD ? wv[j].x & W_VAR_MASK : 0u];
+    lq[j] = t[wv[j].y != CHUNK_PAD ? wv[j].y & W_VAR_MASK : 0u];
+  }
+  uint32_t all = 0xFFFFFFFFu;
+#pragma unroll
+  for (int j = 0; j < H; ++j) all &= wv[j].x & wv[j].y;
+  if (__all(int(all >> 31))) {   // every variable in four or five rows (padding reads as seven)
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      lp[j] = feasible<R>(sv[j].x, lp[j], rdeg_hi<R>(wv[j].x));
+      lq[j] = feasible<R>(sv[j].y, lq[j], rdeg_hi<R>(wv[j].y));
     }
+  } else {
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const uint32_t w = wv[j0 + u];
-      lam[j0 + u] = w != CHUNK_PAD ? raw[u].lambda(int((w >> W_SLOT_SHIFT) & 7u)) : rinf<R>();
+    for (int j = 0; j < H; ++j) {
+      lp[j] = feasible<R>(sv[j].x, lp[j], rdeg_of<R>(wv[j].x));
+      lq[j] = feasible<R>(sv[j].y, lq[j], rdeg_of<R>(wv[j].y));
     }
   }
   if (A.dir) {   // uniform: rows see lambda + gamma * dir
-    R dv[2 * H];
+    P2 dv[H];
 #pragma unroll
-    for (int j = 0; j < 2 * H; ++j)
-      dv[j] = static_cast<const R*>(A.dir)[slot_index(A, wv[j] != CHUNK_PAD ? wv[j] : 0u)];
+    for (int j = 0; j < H; ++j) dv[j] = *reinterpret_cast<const P2*>(static_cast<const R*>(A.dir) + c0 + 128u * j);
 #pragma unroll
-    for (int j = 0; j < 2 * H; ++j)
-      if (wv[j] != CHUNK_PAD) lam[j] += gam * dv[j];
+    for (int j = 0; j < H; ++j) {
+      lp[j] = fma_r<R>(gam, dv[j].x, lp[j]);
+      lq[j] = fma_r<R>(gam, dv[j].y, lq[j]);
+    }
   }
-  R* lp = lam;
-  R* lq = lam + H;
-  int32_t d[2 * H];
 #pragma unroll
-  for (int j = 0; j < 2 * H; ++j) d[j] = 0;
-  int32_t* dp = d;
-  int32_t* dq = d + H;
+  for (int j = 0; j < H; ++j) {
+    lp[j] = wv[j].x != CHUNK_PAD ? lp[j] : rinf<R>();
+    lq[j] = wv[j].y != CHUNK_PAD ? lq[j] : rinf<R>();
+  }
+  int32_t dp[H], dq[H];
+#pragma unroll
+  for (int j = 0; j < H; ++j) dp[j] = dq[j] = 0;
 #pragma unroll
   for (int j = 1; j < H; ++j)
 #pragma unroll
@@ -693,37 +712,27 @@ __device__ inline double tile_rows(const SweepArgs& A, const R* __restrict__ rin
       V = fmin(V, lq[j]);
     }
   }
-  if (MODE == MODE_UPDATE || MODE == MODE_EVAL || MODE == MODE_SUBGRAD) {
+  if (MODE == MODE_SUBGRAD) {
 #pragma unroll
-    for (int j = 0; j < 2 * H; ++j) {
-      const uint32_t w = wv[j];
-      if (w == CHUNK_PAD) continue;
-      const bool neg = j >= H;
-      const R lv = lam[j];
-      const bool sel = d[j] > 0;
-      if (MODE == MODE_SUBGRAD) {
-        A.gsub[slot_index(A, w)] = uint8_t(sel ? 1 : 0);
-      } else {
-        // taken +1: p - U, left +1: p + V, taken -1: q - V, left -1: q + U
-        const R Wm = neg == sel ? V : U;
-        const R M = sel ? lv - Wm : lv + Wm;
-        if (MODE == MODE_UPDATE) write_out<R>(out, w, lv - omega * M);
-        if (MODE == MODE_EVAL) write_out<R>(out, w, M);
+    for (int j = 0; j < H; ++j)
+      *reinterpret_cast<uchar2*>(A.gsub + c0 + 128u * j) = make_uchar2(dp[j] > 0 ? 1 : 0, dq[j] > 0 ? 1 : 0);
+  }
+  if (MODE == MODE_UPDATE || MODE == MODE_EVAL) {
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      // taken +1: p - U, left +1: p + V, taken -1: q - V, left -1: q + U;
+      // padding cells take what comes out, they are never read
+      P2 m;
+      m.x = dp[j] > 0 ? lp[j] - U : lp[j] + V;
+      m.y = dq[j] > 0 ? lq[j] - V : lq[j] + U;
+      if (MODE == MODE_UPDATE) {
+        m.x = fma_r<R>(-omega, m.x, lp[j]);
+        m.y = fma_r<R>(-omega, m.y, lq[j]);
       }
+      *reinterpret_cast<P2*>(out + c0 + 128u * j) = m;
     }
   }
   return rowmin;
-}
-
-template <typename R, int MODE, int TB>
-__device__ void tile_block(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out, R omega, R gam,
-                           double* red, int32_t item) {
-  const int32_t t = item * 4 + int32_t(threadIdx.x >> 6);
-  double rowpart = 0.0;
-  if (t < A.n_tiles)   // uniform across the wave
-    rowpart = tile_rows<R, MODE, TB>(A, rin, out, omega, gam, A.tile_word + size_t(t) * (2 * TILE_HALF * 64));
-  const double part = block_sum(rowpart, red);
-  store_partial(part, A.partial, item);
 }
 
 // ---------------------------------------------------------------- short rows, soft min
@@ -769,7 +778,7 @@ __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R
     n = A.rrow_ptr[j + 1] - s;
     b = A.rrow_b[j];
     if (lane < n) {
-      w = A.word[s + lane];
+      w = A.ent_word[s + lane];
       mylam = cur_lambda<R>(rin, w);
       lamL[lane] = mylam * inv_unit;
       aL[lane] = (w >> 31) ? int8_t(-1) : int8_t(1);
@@ -830,6 +839,42 @@ __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R
   store_partial(part, A.partial, item);
 }
 
+// a multiplier record as loaded (two 16-byte loads for FP32, four for FP64)
+template <typename R>
+struct RecRaw;
+template <>
+struct RecRaw<float> {
+  float4 lo, hi;
+  __device__ void load(const float* __restrict__ rec, uint32_t i) {
+    lo = *reinterpret_cast<const float4*>(rec + size_t(i) * REC);
+    hi = *reinterpret_cast<const float4*>(rec + size_t(i) * REC + 4);
+  }
+  // lambda of slot k with dual feasibility restored, in the arithmetic of rec_lambdas
+  __device__ float lambda(int k) const {
+    const float sum = (((lo.x + lo.y) + lo.z) + lo.w) + hi.x;
+    const float corr = (hi.y - sum) * hi.z;
+    const float sk = k == 0 ? lo.x : k == 1 ? lo.y : k == 2 ? lo.z : k == 3 ? lo.w : hi.x;
+    return sk + corr;
+  }
+};
+template <>
+struct RecRaw<double> {
+  double2 a, b, c, d;
+  __device__ void load(const double* __restrict__ rec, uint32_t i) {
+    const double* r = rec + size_t(i) * REC;
+    a = *reinterpret_cast<const double2*>(r);
+    b = *reinterpret_cast<const double2*>(r + 2);
+    c = *reinterpret_cast<const double2*>(r + 4);
+    d = *reinterpret_cast<const double2*>(r + 6);
+  }
+  __device__ double lambda(int k) const {
+    const double sum = (((a.x + a.y) + b.x) + b.y) + c.x;
+    const double corr = (c.y - sum) * d.x;
+    const double sk = k == 0 ? a.x : k == 1 ? a.y : k == 2 ? b.x : k == 3 ? b.y : c.x;
+    return sk + corr;
+  }
+};
+
 // ---------------------------------------------------------------- long rows (exactly one)
 template <typename R>
 struct MinState {   // hard: (m, a, m2); soft adds s = sum_{k != a} exp(-(lam_k - m2)/T)
@@ -872,19 +917,20 @@ __device__ inline MinState<R> ms_shfl_xor(MinState<R> v, int off) {
 // block per row (long_wpr = 4); each lane keeps up to LONG_REG of its row's
 // multipliers in registers between the two passes
 constexpr int LONG_REG = 8;
-constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD turn
+constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD turn (smoothed)
 
-// LONG_BATCH: record loads in flight per lane
-template <typename R, bool SOFT, int MODE, int LONG_BATCH>
-__device__ void long_rows(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out, R omega, R T,
-                          R gam, double* red, int32_t item) {
+// Row lr of the launch order.  Hard: src holds the cells, t the residuals per
+// variable, dst takes the cells' new values (src and dst may be one array: a
+// lane reads its own cells before it writes them).  Smoothed: src and dst are
+// records.  Returns the row minimum on one lane of the row.
+template <typename R, bool SOFT, int MODE>
+__device__ double long_rows(const SweepArgs& A, const R* src, const R* __restrict__ t, R* dst, R omega, R T, R gam,
+                            int32_t lr, bool has) {
   __shared__ R xm[4], xm2[4], xs[4];
   __shared__ int32_t xa[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wpr = A.long_wpr;   // uniform
   const int sub = wave & (wpr - 1);
-  const int32_t lr = (item - A.n_short_blocks) * (4 / wpr) + wave / wpr;
-  const bool has = lr < A.n_long;
   const int32_t j = has ? A.n_short + A.long_perm[lr] : 0;
   const int32_t step = 64 * wpr, i0 = sub * 64 + lane;
   const int32_t s = has ? A.rrow_ptr[j] : 0;
@@ -896,49 +942,53 @@ __device__ void long_rows(const SweepArgs& A, const R* __restrict__ rin, R* __re
   st.a = INT32_MAX;
   // The first LONG_REG entries of every lane are loaded without branches
   // (past the row's end a lane loads the row's first entry and ignores it), so
-  // that all loads of a batch are in flight together: the words, then the
-  // records in batches of LONG_BATCH.
+  // that all loads of a batch are in flight together: the words, then what
+  // they point at.
+  const uint32_t c0 = A.long_cell0 + uint32_t(s - (has ? A.n_entries_short : 0));   // hard: the row's first cell
+  const uint32_t* words = SOFT ? A.ent_word + s : A.word + c0;
+  auto value = [&](int32_t i, uint32_t w) {
+    if constexpr (SOFT) return cur_lambda<R>(src, w);
+    else return cell_lambda<R>(A, src, t, c0 + uint32_t(i), w, gam);
+  };
+  auto take = [&](int32_t i, R v) {
+    MinState<R> one;
+    one.m = v;
+    one.m2 = rinf<R>();
+    one.s = R(0);
+    one.a = i;
+    st = ms_combine<R, SOFT>(st, one, T);
+  };
+  constexpr int LONG_BATCH = SOFT ? 2 : 4;   // loads in flight together
   uint32_t wv[LONG_REG];
   R lv[LONG_REG];
 #pragma unroll
   for (int u = 0; u < LONG_REG; ++u) {
     const int32_t i = i0 + step * u;
-    wv[u] = n > 0 ? A.word[s + (i < n ? i : 0)] : 0u;
+    wv[u] = n > 0 ? words[i < n ? i : 0] : 0u;
   }
 #pragma unroll
   for (int u0 = 0; u0 < LONG_REG; u0 += LONG_BATCH) {
     if (sub * 64 + step * u0 >= n) break;   // uniform: no lane of the wave has entries left
-    RecRaw<R> raw[LONG_BATCH];
+    if constexpr (SOFT) {
+      RecRaw<R> raw[LONG_BATCH];
 #pragma unroll
-    for (int u = 0; u < LONG_BATCH; ++u) raw[u].load(rin, wv[u0 + u] & W_VAR_MASK);
-    R dv[LONG_BATCH];
-    if (A.dir)
+      for (int u = 0; u < LONG_BATCH; ++u) raw[u].load(src, wv[u0 + u] & W_VAR_MASK);
 #pragma unroll
-      for (int u = 0; u < LONG_BATCH; ++u) dv[u] = static_cast<const R*>(A.dir)[slot_index(A, wv[u0 + u])];
+      for (int u = 0; u < LONG_BATCH; ++u) lv[u0 + u] = raw[u].lambda(int((wv[u0 + u] >> W_SLOT_SHIFT) & 7u));
+    } else {
+#pragma unroll
+      for (int u = 0; u < LONG_BATCH; ++u) {
+        const int32_t i = i0 + step * (u0 + u);
+        lv[u0 + u] = value(i < n ? i : 0, wv[u0 + u]);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < LONG_BATCH; ++u) {
       const int32_t i = i0 + step * (u0 + u);
-      R v = raw[u].lambda(int((wv[u0 + u] >> W_SLOT_SHIFT) & 7u));
-      if (A.dir) v += gam * dv[u];
-      lv[u0 + u] = v;
-      if (i < n) {
-        MinState<R> one;
-        one.m = v;
-        one.m2 = rinf<R>();
-        one.s = R(0);
-        one.a = i;
-        st = ms_combine<R, SOFT>(st, one, T);
-      }
+      if (i < n) take(i, lv[u0 + u]);
     }
   }
-  for (int32_t i = i0 + step * LONG_REG; i < n; i += step) {   // rows longer than step * LONG_REG
-    MinState<R> one;
-    one.m = row_lambda<R>(A, rin, A.word[s + i], gam);
-    one.m2 = rinf<R>();
-    one.s = R(0);
-    one.a = i;
-    st = ms_combine<R, SOFT>(st, one, T);
-  }
+  for (int32_t i = i0 + step * LONG_REG; i < n; i += step) take(i, value(i, words[i]));   // longer rows
   for (int off = 32; off > 0; off >>= 1) st = ms_combine<R, SOFT>(st, ms_shfl_xor<R, SOFT>(st, off), T);
   if (wpr > 1) {
     // the row's waves combine their states in index order: every wave of
@@ -990,10 +1040,14 @@ __device__ void long_rows(const SweepArgs& A, const R* __restrict__ rin, R* __re
           M = lam - others;
           mu = r_exp<R>(-(lam - rowv) / T);
         }
-        if (MODE == MODE_UPDATE) write_out<R>(out, w, lam - omega * M);
-        if (MODE == MODE_EVAL) write_out<R>(out, w, SOFT ? mu : M);
-        if (MODE == MODE_SUBGRAD)
-          A.gsub[slot_index(A, w)] = uint8_t(i == st.a ? 1 : 0);
+        if constexpr (SOFT) {
+          if (MODE == MODE_UPDATE) write_out<R>(dst, w, lam - omega * M);
+          if (MODE == MODE_EVAL) write_out<R>(dst, w, mu);
+        } else {
+          if (MODE == MODE_UPDATE) dst[c0 + uint32_t(i)] = fma_r<R>(-omega, M, lam);
+          if (MODE == MODE_EVAL) dst[c0 + uint32_t(i)] = M;
+          if (MODE == MODE_SUBGRAD) A.gsub[c0 + uint32_t(i)] = uint8_t(i == st.a ? 1 : 0);
+        }
       };
 #pragma unroll
       for (int u = 0; u < LONG_REG; ++u) {
@@ -1001,14 +1055,13 @@ __device__ void long_rows(const SweepArgs& A, const R* __restrict__ rin, R* __re
         if (i < n) finish(i, wv[u], lv[u]);
       }
       for (int32_t i = i0 + step * LONG_REG; i < n; i += step) {
-        const uint32_t w = A.word[s + i];
-        finish(i, w, row_lambda<R>(A, rin, w, gam));
+        const uint32_t w = words[i];
+        finish(i, w, value(i, w));
       }
     }
     if (lane == 0 && sub == 0) rowpart = double(rowv);
   }
-  double part = block_sum(rowpart, red);
-  store_partial(part, A.partial, item);
+  return rowpart;
 }
 
 template <typename R, bool SOFT>
@@ -1016,40 +1069,77 @@ constexpr size_t smem_bytes() {
   return SOFT ? (SOFT_FTAB + 256) * sizeof(R) + 256 : 768 * sizeof(R);
 }
 
-// TB > 0: the hard form's launch has one-lane-per-row tiles, whose record
-// loads go TB at a time (their register use sets the occupancy of the whole
-// kernel, so launches without tiles take the instantiation TB = 0)
-template <typename R, bool SOFT, int MODE, int TB>
-__global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* __restrict__ rin, R* __restrict__ out,
-                                               R omega, R T) {
+// First pass of a hard iteration: t_i = c_i - sum_k s_k, one thread per
+// variable in variable order; unused slots read the zero cell.  Bound by the
+// index planes and the gathered lines (2000/3000-face pair: 20 + 16 bytes per
+// variable, 38 us, 5 TB/s; with the variables in canonical order 47 us).
+// Blocks 8 and up take the variables, each XCD a contiguous eighth; block 0
+// sums the previous row pass's partials, so that no other launch has to.
+template <typename R>
+__global__ __launch_bounds__(256) void k_vars(const uint32_t* __restrict__ vpos, const R* __restrict__ cells,
+                                              const R* __restrict__ cost, int64_t n, int32_t per, R* __restrict__ t,
+                                              const double* prev_partial, int32_t prev_n, double prev_offset,
+                                              double* prev_out) {
+  __shared__ double red[4];
+  if (blockIdx.x < 8) {
+    if (blockIdx.x == 0 && prev_partial) reduce_partials(prev_partial, prev_n, prev_offset, prev_out, red);
+    return;
+  }
+  const int32_t k = int32_t(blockIdx.x / 8u) - 1;
+  const int64_t v = (int64_t(blockIdx.x % 8u) * per + k) * 256 + threadIdx.x;
+  if (v >= n) return;
+  uint32_t p[5];
+#pragma unroll
+  for (int q = 0; q < 5; ++q) p[q] = vpos[size_t(q) * n + v];
+  const R c = cost[v];
+  R s[5];
+#pragma unroll
+  for (int q = 0; q < 5; ++q) s[q] = cells[p[q]];
+  t[v] = c - ((((s[0] + s[1]) + s[2]) + s[3]) + s[4]);
+}
+
+template <typename R, bool SOFT, int MODE>
+__global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const R* __restrict__ t, R* out, R omega,
+                                               R T) {
   __shared__ __align__(16) unsigned char smem[smem_bytes<R, SOFT>()];
   __shared__ double red[256];
   if (A.skip && *A.skip) return;   // uniform across the grid
-  if (blockIdx.x == 0 && A.prev_partial) reduce_partials(A.prev_partial, A.prev_n, A.prev_offset, A.prev_out, red);
-  const R gam = A.gamma ? R(*A.gamma) : R(0);
+  if (SOFT && blockIdx.x == 0 && A.prev_partial)
+    reduce_partials(A.prev_partial, A.prev_n, A.prev_offset, A.prev_out, red);
   // Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8).
-  // The hard form takes the item of block b from the per-XCD table of the
-  // sweep layout (region b % 8, in key order).  The smoothed form gives each
-  // XCD a contiguous range of short-row blocks and projection-row blocks in
-  // groups of LONG_GROUP consecutive blocks, group g on XCD g % 8, the heavier
-  // projection-row blocks first.
   const int32_t x = int32_t(blockIdx.x % 8u), k0 = int32_t(blockIdx.x / 8u);
-  if (!SOFT) {
-    if (k0 >= A.xcd_stride) return;
-    const int32_t item = A.xcd_item[x * A.xcd_stride + k0];
-    if (item < 0) return;
-    if constexpr (TB > 0) {
-      if (item < A.n_tile_items) {
-        tile_block<R, MODE, TB>(A, rin, out, omega, gam, red, item);
-        return;
-      }
+  if constexpr (!SOFT) {
+    // Every XCD takes a contiguous eighth of each kind of rows, the heavier
+    // kinds first; Y projection rows span all variables and are dealt in turn.
+    const R gam = A.gamma ? R(*A.gamma) : R(0);
+    const int wave = threadIdx.x >> 6;
+    double part = 0.0;
+    int32_t k = k0;
+    if (k < A.per[0] + A.per[1]) {
+      const bool yrow = k < A.per[0];
+      const int32_t rpb = 4 / A.long_wpr;
+      const int32_t item = yrow ? k * 8 + x : x * A.per[1] + (k - A.per[0]);
+      const int32_t r = item * rpb + wave / A.long_wpr;
+      const int32_t lr = yrow ? r : A.n_long_y + r;
+      part = long_rows<R, false, MODE>(A, rin, t, out, omega, T, gam, lr, lr < (yrow ? A.n_long_y : A.n_long));
+    } else if ((k -= A.per[0] + A.per[1]) < A.per[2]) {
+      part = chunk_block<R, MODE>(A, rin, t, out, omega, gam, smem, x * A.per[2] + k);
+    } else if ((k -= A.per[2]) < A.per[3]) {
+      const int32_t tile = (x * A.per[3] + k) * 4 + wave;
+      if (tile < A.n_tiles[1])   // uniform across the wave
+        part = tile_rows<R, MODE, TILE_WIDE>(A, rin, t, out, omega, gam,
+                                             A.wide_cell0 + uint32_t(tile) * (128u * TILE_WIDE));
+    } else {
+      const int32_t tile = (x * A.per[4] + (k - A.per[3])) * 4 + wave;
+      if (tile < A.n_tiles[0])
+        part = tile_rows<R, MODE, TILE_NARROW>(A, rin, t, out, omega, gam, uint32_t(tile) * (128u * TILE_NARROW));
     }
-    if (item < A.n_short_blocks) short_wave_hard<R, MODE>(A, rin, out, omega, gam, smem, red, item);
-    else long_rows<R, false, MODE, (TB > 0 ? 4 : 2)>(A, rin, out, omega, T, gam, red, item);
-    return;
-  }
-  int32_t item;
-  {
+    store_partial(block_sum(part, red), A.partial, int32_t(blockIdx.x));
+  } else {
+    // The smoothed form gives each XCD a contiguous range of short-row blocks
+    // and projection-row blocks in groups of LONG_GROUP consecutive blocks,
+    // group g on XCD g % 8, the heavier projection-row blocks first.
+    int32_t item;
     const int32_t n_long_blocks = A.n_items - A.n_short_blocks;
     const int32_t lx = (n_long_blocks + 8 * LONG_GROUP - 1) / (8 * LONG_GROUP) * LONG_GROUP;
     if (k0 < lx) {
@@ -1062,32 +1152,33 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* __restrict_
       if (k0 - lx >= pc || c >= A.n_short_blocks) return;
       item = c;
     }
-  }
-  if (item < A.n_short_blocks) {
-    const int32_t nb8 = (A.soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>();
-    const int32_t nb16 = (A.soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>();
-    const int32_t c816 = A.soft_c8 + A.soft_c16;
-    if (item < nb8)
-      short_rows_soft<R, MODE, 8>(A, rin, out, omega, T, smem, red, item, item, 0, A.soft_c8);
-    else if (item < nb8 + nb16)
-      short_rows_soft<R, MODE, 16>(A, rin, out, omega, T, smem, red, item, item - nb8, A.soft_c8, c816);
-    else
-      short_rows_soft<R, MODE, 32>(A, rin, out, omega, T, smem, red, item, item - nb8 - nb16, c816,
-                                   A.n_short);
-  } else {
-    long_rows<R, true, MODE, 2>(A, rin, out, omega, T, gam, red, item);
+    if (item < A.n_short_blocks) {
+      const int32_t nb8 = (A.soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>();
+      const int32_t nb16 = (A.soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>();
+      const int32_t c816 = A.soft_c8 + A.soft_c16;
+      if (item < nb8)
+        short_rows_soft<R, MODE, 8>(A, rin, out, omega, T, smem, red, item, item, 0, A.soft_c8);
+      else if (item < nb8 + nb16)
+        short_rows_soft<R, MODE, 16>(A, rin, out, omega, T, smem, red, item, item - nb8, A.soft_c8, c816);
+      else
+        short_rows_soft<R, MODE, 32>(A, rin, out, omega, T, smem, red, item, item - nb8 - nb16, c816, A.n_short);
+    } else {
+      const int32_t lr = (item - A.n_short_blocks) * (4 / A.long_wpr) + int32_t(threadIdx.x >> 6) / A.long_wpr;
+      const double part = long_rows<R, true, MODE>(A, rin, nullptr, out, omega, T, R(0), lr, lr < A.n_long);
+      store_partial(block_sum(part, red), A.partial, item);
+    }
   }
 }
 
-// ---------------------------------------------------------------- state import / export
+// ---------------------------------------------------------------- state import / export (records)
 template <typename R>
-__global__ void k_import(const R* lam, const uint32_t* word, int64_t nnz, R* rec) {
+__global__ void k_rec_import(const R* lam, const uint32_t* word, int64_t nnz, R* rec) {
   int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e < nnz) write_out<R>(rec, word[e], lam[e]);
 }
 
 template <typename R>
-__global__ void k_set_cost(const int32_t* free_var, const double* c64, const uint8_t* deg, int64_t nfree, R* rec0,
+__global__ void k_rec_cost(const int32_t* free_var, const double* c64, const uint8_t* deg, int64_t nfree, R* rec0,
                            R* rec1) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= nfree) return;
@@ -1101,9 +1192,35 @@ __global__ void k_set_cost(const int32_t* free_var, const double* c64, const uin
 }
 
 template <typename R>
-__global__ void k_export(const R* rec, const uint32_t* word, int64_t nnz, R* lam) {
+__global__ void k_rec_export(const R* rec, const uint32_t* word, int64_t nnz, R* lam) {
   int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e < nnz) lam[e] = cur_lambda<R>(rec, word[e]);
+}
+
+// ---------------------------------------------------------------- state import / export (cells)
+// entries' multipliers into their cells, costs in variable order, the zero cell
+template <typename R>
+__global__ void k_cell_import(const R* lam, const uint32_t* ent_cell, int64_t nnz, const int32_t* vperm,
+                              const int32_t* free_var, const double* c64, int64_t n, uint32_t zero_cell, R* cells,
+                              R* cost) {
+  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e < nnz) cells[ent_cell[e]] = lam[e];
+  if (e < n) cost[e] = R(c64[free_var[vperm[e]]]);
+  if (e == 0) cells[zero_cell] = R(0);
+}
+
+template <typename R>
+__global__ void k_zero_cell(R* cells, uint32_t zero_cell) {
+  cells[zero_cell] = R(0);
+}
+
+template <typename R>
+__global__ void k_cell_export(const R* cells, const R* t, const uint32_t* ent_cell, const uint32_t* word, int64_t nnz,
+                              R* lam) {
+  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e >= nnz) return;
+  const uint32_t c = ent_cell[e], w = word[c];
+  lam[e] = feasible<R>(cells[c], t[w & W_VAR_MASK], rdeg_of<R>(w));
 }
 
 template <typename R>
@@ -1123,53 +1240,54 @@ __global__ __launch_bounds__(256) void k_reduce_last(const double* partial, int 
   reduce_partials(partial, n, offset, out, red);
 }
 
-// one sweep launch; with timing events the launch records the kernel's own
-// start and end (hipExtLaunchKernelGGL), as a kernel trace does
-template <typename R, bool SOFT, int MODE, int TB = 0>
-void launch_sweep(hipStream_t st, unsigned grid, hipEvent_t e0, hipEvent_t e1, const SweepArgs& A, const R* ri,
-                  R* ro, R omega, R T) {
-  if (e0)
-    hipExtLaunchKernelGGL(k_sweep<R, SOFT, MODE, TB>, dim3(grid), dim3(256), 0, st, e0, e1, 0, A, ri, ro, omega, T);
-  else
-    k_sweep<R, SOFT, MODE, TB><<<grid, 256, 0, st>>>(A, ri, ro, omega, T);
-}
-
-// Tile record loads: 16 in flight per lane once there are at least
-// TILE_WIDE_BATCH tiles (more latency hidden per wave, 1000-face pair 46 ->
-// 42 us), 8 below (the 500-face pair's 900 tiles are 1 % faster so); FP64
-// sweeps take one instantiation (their batches are two records).
-constexpr int32_t TILE_WIDE_BATCH = 2048;
-template <typename R, int MODE>
-void launch_hard(int32_t n_tiles, hipStream_t st, unsigned grid, hipEvent_t e0, hipEvent_t e1, const SweepArgs& A,
-                 const R* ri, R* ro, R omega, R T) {
-  if (n_tiles <= 0) launch_sweep<R, false, MODE, 0>(st, grid, e0, e1, A, ri, ro, omega, T);
-  else if (sizeof(R) == 4 && n_tiles >= TILE_WIDE_BATCH)
-    launch_sweep<R, false, MODE, 16>(st, grid, e0, e1, A, ri, ro, omega, T);
-  else launch_sweep<R, false, MODE, 8>(st, grid, e0, e1, A, ri, ro, omega, T);
-}
-
 }  // namespace
 
 // ============================================================================
-// host side (shared with rounding and the backward pass)
+// host side (shared with rounding, the quasi-Newton layer and the backward pass)
 // ============================================================================
+// blocks per XCD of each kind of rows of the hard sweep, in launch order
+static void hard_blocks(const dm_ctx* ctx, int32_t per[5]) {
+  const int64_t n_long = ctx->n_rows - ctx->n_short, rpb = 4 / ctx->long_wpr;
+  const auto xcd = [](int64_t items) { return int32_t((items + 7) / 8); };
+  per[0] = xcd((ctx->n_long_y + rpb - 1) / rpb);
+  per[1] = xcd((n_long - ctx->n_long_y + rpb - 1) / rpb);
+  per[2] = xcd((ctx->n_chunks + 3) / 4);
+  per[3] = xcd((ctx->n_tiles[1] + 3) / 4);
+  per[4] = xcd((ctx->n_tiles[0] + 3) / 4);
+}
+
+static int64_t hard_grid(const dm_ctx* ctx) {
+  int32_t per[5];
+  hard_blocks(ctx, per);
+  return 8 * (int64_t(per[0]) + per[1] + per[2] + per[3] + per[4]);
+}
+
+static int64_t soft_short_blocks(const dm_ctx* ctx) {
+  const int64_t c32 = ctx->n_short - ctx->soft_c8 - ctx->soft_c16;
+  return (ctx->soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>() + (ctx->soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>() +
+         (c32 + soft_rpb<32>() - 1) / soft_rpb<32>();
+}
+
+static int64_t long_blocks(const dm_ctx* ctx) {
+  const int64_t rpb = 4 / ctx->long_wpr;
+  return (ctx->n_rows - ctx->n_short + rpb - 1) / rpb;
+}
+
 // per-launch partials of one sweep (hard and smoothed forms): the partial
 // buffer holds two halves of this many doubles
 static int64_t sweep_partial_cap(const dm_ctx* ctx) {
-  const int64_t c32 = ctx->n_short - ctx->soft_c8 - ctx->soft_c16;
-  const int64_t soft_blocks = (ctx->soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>() +
-                              (ctx->soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>() +
-                              (c32 + soft_rpb<32>() - 1) / soft_rpb<32>();
-  return std::max<int64_t>(int64_t(ctx->n_tile_items) + (ctx->n_chunks + 3) / 4, soft_blocks) +
-         ctx->n_long_items;
+  return std::max<int64_t>(hard_grid(ctx), soft_short_blocks(ctx) + long_blocks(ctx));
 }
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 SolverLayout solver_layout(const dm_ctx* ctx, size_t real_bytes) {
   SolverLayout L;
-  L.rec_bytes = align256(size_t(std::max<int64_t>(ctx->n_free, 1)) * REC * real_bytes);
-  L.part_off = 2 * L.rec_bytes;
+  const size_t n = size_t(std::max<int64_t>(ctx->n_free, 1));
+  L.rec_bytes = align256(n * REC * real_bytes);
+  L.cell_bytes = align256(size_t(ctx->n_cells + 1) * real_bytes);
+  L.var_bytes = align256(n * real_bytes);
+  L.part_off = std::max(2 * L.rec_bytes, 2 * L.cell_bytes + 3 * L.var_bytes);
   L.part_count = size_t(2 * std::max<int64_t>(sweep_partial_cap(ctx), 1));
   L.total = L.part_off + align256(L.part_count * sizeof(double));
   return L;
@@ -1188,7 +1306,44 @@ static dm_status solver_workspace(dm_ctx* ctx, size_t real_bytes, unsigned char*
 }
 
 template <typename R>
-dm_status dual_import(dm_ctx* ctx, const R* lam, DArr<unsigned char>* bufs) {
+dm_status cells_import(dm_ctx* ctx, const R* lam, CellState& S, bool two) {
+  const int64_t n = ctx->n_free;
+  const size_t cb = size_t(ctx->n_cells + 1) * sizeof(R), vb = size_t(std::max<int64_t>(n, 1)) * sizeof(R);
+  unsigned char* ws = nullptr;
+  SolverLayout L;
+  if (&S == &ctx->cells) DM_TRY(solver_workspace(ctx, sizeof(R), &ws, &L));
+  for (int b = 0; b < (two ? 2 : 1); ++b) {
+    if (ws) {   // the solver's state lives in the caller's workspace
+      S.cell[b].attach(ws + b * L.cell_bytes, cb);
+      S.t[b].attach(ws + 2 * L.cell_bytes + b * L.var_bytes, vb);
+    } else {
+      DM_ALLOC(ctx, S.cell[b], cb);
+      DM_ALLOC(ctx, S.t[b], vb);
+    }
+  }
+  if (ws) S.cost.attach(ws + 2 * L.cell_bytes + 2 * L.var_bytes, vb);
+  else DM_ALLOC(ctx, S.cost, vb);
+  const int64_t m = std::max<int64_t>(std::max<int64_t>(ctx->nnz, n), 1);
+  k_cell_import<R><<<grid_for(m, 256), 256, 0, ctx->stream>>>(
+      lam, ctx->ent_cell.p, ctx->nnz, ctx->vperm.p, ctx->free_var.p, ctx->cost64.p, n, uint32_t(ctx->n_cells),
+      S.cells<R>(0), S.costs<R>());
+  // the other buffer's zero cell: its other cells are written before they are read
+  if (two) k_zero_cell<R><<<1, 1, 0, ctx->stream>>>(S.cells<R>(1), uint32_t(ctx->n_cells));
+  DM_LAUNCH_CHECK(ctx);
+  return DM_OK;
+}
+
+template <typename R>
+dm_status cells_export(dm_ctx* ctx, const R* cells, const R* t, R* lam) {
+  if (ctx->nnz > 0)
+    k_cell_export<R><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(cells, t, ctx->ent_cell.p, ctx->cell_word.p,
+                                                                       ctx->nnz, lam);
+  DM_LAUNCH_CHECK(ctx);
+  return DM_OK;
+}
+
+template <typename R>
+dm_status records_import(dm_ctx* ctx, const R* lam, DArr<unsigned char>* bufs) {
   const size_t bytes = size_t(std::max<int64_t>(ctx->n_free, 1)) * REC * sizeof(R);
   unsigned char* ws = nullptr;
   SolverLayout L;
@@ -1205,81 +1360,31 @@ dm_status dual_import(dm_ctx* ctx, const R* lam, DArr<unsigned char>* bufs) {
   R* r0 = reinterpret_cast<R*>(bufs[0].p);
   R* r1 = reinterpret_cast<R*>(bufs[1].p);
   if (ctx->n_free > 0)
-    k_set_cost<R><<<grid_for(ctx->n_free, 256), 256, 0, ctx->stream>>>(ctx->free_var.p, ctx->cost64.p,
+    k_rec_cost<R><<<grid_for(ctx->n_free, 256), 256, 0, ctx->stream>>>(ctx->free_var.p, ctx->cost64.p,
                                                                        ctx->var_deg.p, ctx->n_free, r0, r1);
   if (ctx->nnz > 0)
-    k_import<R><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(lam, ctx->rent_word.p, ctx->nnz, r0);
+    k_rec_import<R><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(lam, ctx->rent_word.p, ctx->nnz, r0);
   DM_LAUNCH_CHECK(ctx);
   return DM_OK;
 }
 
 template <typename R>
-dm_status dual_export(dm_ctx* ctx, const unsigned char* rec, R* lam) {
+dm_status records_export(dm_ctx* ctx, const unsigned char* rec, R* lam) {
   if (ctx->nnz > 0)
-    k_export<R><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(reinterpret_cast<const R*>(rec),
+    k_rec_export<R><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(reinterpret_cast<const R*>(rec),
                                                                   ctx->rent_word.p, ctx->nnz, lam);
   DM_LAUNCH_CHECK(ctx);
   return DM_OK;
 }
 
-// one sweep over all rows; mode 0 update rec_in -> out, 1 write M (or mu) to
-// out per slot, 2 bound only; the bound goes to *bound_out (device)
-template <typename R>
-dm_status dual_sweep(dm_ctx* ctx, int mode, bool soft, const unsigned char* rin, unsigned char* out, R omega,
-                     R T, double* bound_out, const SweepExt* ext) {
-  if (soft && (ext || mode == MODE_SUBGRAD))
-    return dm_fail(ctx, DM_ERR_INVALID_ARG, "direction, skip and subgradient sweeps use the hard minimum");
-  if (soft && ctx->max_short > SOFT_MAX_ROW)
-    return dm_fail(ctx, DM_ERR_WORKSPACE, "smoothed rows support at most %d entries (found %d)", SOFT_MAX_ROW,
-                   ctx->max_short);
-  SweepArgs A;
-  A.word = ctx->rent_word.p;
-  A.rrow_ptr = ctx->rrow_ptr.p;
-  A.rrow_b = ctx->rrow_b.p;
-  A.chunk_desc = ctx->chunk_desc.p;
-  A.chunk_mask = ctx->chunk_mask.p;
-  A.chunk_word = ctx->chunk_word.p;
-  A.chunk_b = ctx->chunk_b.p;
-  A.n_chunks = ctx->n_chunks;
-  A.soft_row = ctx->soft_row.p;
-  A.soft_c8 = int32_t(ctx->soft_c8);
-  A.soft_c16 = int32_t(ctx->soft_c16);
-  const int64_t c32 = ctx->n_short - ctx->soft_c8 - ctx->soft_c16;
-  const int64_t soft_blocks = (ctx->soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>() +
-                              (ctx->soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>() +
-                              (c32 + soft_rpb<32>() - 1) / soft_rpb<32>();
-  A.n_tile_items = soft ? 0 : ctx->n_tile_items;
-  A.n_tiles = ctx->n_tiles;
-  A.tile_word = ctx->tile_word.p;
-  A.n_short_blocks = soft ? int32_t(soft_blocks) : ctx->n_tile_items + int32_t((ctx->n_chunks + 3) / 4);
-  // projection rows: a wave each, or a whole block each when they are long
-  const int64_t n_long = ctx->n_rows - ctx->n_short;
-  A.long_wpr = ctx->long_wpr;
-  A.n_long = int32_t(n_long);
-  A.long_perm = ctx->long_perm.p;
-  A.xcd_item = ctx->xcd_item.p;
-  A.xcd_stride = ctx->xcd_stride;
-  const int64_t n_long_blocks = ctx->n_long_items;
-  A.n_short = int32_t(ctx->n_short);
-  A.n_rows = int32_t(ctx->n_rows);
-  A.plane = ctx->n_free;
-  A.dir = ext ? ext->dir : nullptr;
-  A.gamma = ext ? ext->gamma : nullptr;
-  A.skip = ext ? ext->skip : nullptr;
-  A.gsub = ext ? ext->gsub : nullptr;
-  const int64_t nblocks = int64_t(A.n_short_blocks) + n_long_blocks;
-  if (nblocks == 0) {
-    DM_TRY(dual_flush(ctx));
-    if (bound_out) k_write_offset<<<1, 1, 0, ctx->stream>>>(bound_out, ctx->offset);
-    DM_LAUNCH_CHECK(ctx);
-    return DM_OK;
-  }
-  // two halves of the partial buffer alternate between consecutive launches;
-  // with a caller workspace of this precision they live there
+// the half of the partial buffer the next launch writes; two halves of it
+// alternate between consecutive launches, and with a caller workspace of this
+// precision they live there
+static dm_status next_partials(dm_ctx* ctx, size_t real_bytes, double** mine) {
   const int64_t cap = sweep_partial_cap(ctx);
   unsigned char* ws = nullptr;
   SolverLayout L;
-  DM_TRY(solver_workspace(ctx, sizeof(R), &ws, &L));
+  DM_TRY(solver_workspace(ctx, real_bytes, &ws, &L));
   if (ws) {
     double* want = reinterpret_cast<double*>(ws + L.part_off);
     if (ctx->partial.p != want || ctx->partial.n < size_t(2 * cap)) {
@@ -1290,48 +1395,167 @@ dm_status dual_sweep(dm_ctx* ctx, int mode, bool soft, const unsigned char* rin,
     DM_TRY(dual_flush(ctx));
     DM_ALLOC(ctx, ctx->partial, size_t(2 * cap));
   }
-  double* mine = ctx->partial.p + (ctx->pend_half ^ 1) * cap;
+  *mine = ctx->partial.p + (ctx->pend_half ^ 1) * cap;
+  return DM_OK;
+}
+
+static void pend(dm_ctx* ctx, double* mine, int64_t n, double* bound_out) {
+  ctx->pend_half ^= 1;
+  ctx->pend_partial = mine;
+  ctx->pend_n = int32_t(n);
+  ctx->pend_offset = ctx->offset;
+  ctx->pend_out = bound_out;
+}
+
+// timing: a start event for the first kernel of a sweep, a stop event for its
+// last (the runtime records the kernels' own start and end)
+static dm_status timing_events(dm_ctx* ctx, hipEvent_t* e0, hipEvent_t* e1) {
+  while (ctx->ev_pool.size() < ctx->ev_used + 2) {
+    hipEvent_t e;
+    DM_HIP(ctx, hipEventCreate(&e));
+    ctx->ev_pool.push_back(e);
+  }
+  if (e0) *e0 = ctx->ev_pool[ctx->ev_used];
+  if (e1) {
+    *e1 = ctx->ev_pool[ctx->ev_used + 1];
+    ctx->ev_used += 2;
+  }
+  return DM_OK;
+}
+
+// t of every variable from the cells; takes over the bound of the last row
+// pass that has not been summed yet
+template <typename R>
+dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool timed) {
+  const int64_t n = ctx->n_free;
+  const int32_t per = int32_t((n + 8 * 256 - 1) / (8 * 256));
+  hipEvent_t e0 = nullptr;
+  if (ctx->timing && timed) DM_TRY(timing_events(ctx, &e0, nullptr));
+  ctx->timing_open = e0 != nullptr;
+  const double* pp = ctx->pend_out ? ctx->pend_partial : nullptr;
+  const unsigned grid = 8u * unsigned(per + 1);
+  if (e0)
+    hipExtLaunchKernelGGL(k_vars<R>, dim3(grid), dim3(256), 0, ctx->stream, e0, nullptr, 0, ctx->vpos.p, cells, cost,
+                          n, per, t, pp, ctx->pend_n, ctx->pend_offset, ctx->pend_out);
+  else
+    k_vars<R><<<grid, 256, 0, ctx->stream>>>(ctx->vpos.p, cells, cost, n, per, t, pp, ctx->pend_n, ctx->pend_offset,
+                                             ctx->pend_out);
+  DM_LAUNCH_CHECK(ctx);
+  ctx->pend_out = nullptr;
+  return DM_OK;
+}
+
+template <typename R, bool SOFT, int MODE>
+static void launch_sweep(hipStream_t st, unsigned grid, hipEvent_t e0, hipEvent_t e1, const SweepArgs& A, const R* ri,
+                         const R* t, R* ro, R omega, R T) {
+  if (e0 || e1)
+    hipExtLaunchKernelGGL((k_sweep<R, SOFT, MODE>), dim3(grid), dim3(256), 0, st, e0, e1, 0, A, ri, t, ro, omega, T);
+  else
+    k_sweep<R, SOFT, MODE><<<grid, 256, 0, st>>>(A, ri, t, ro, omega, T);
+}
+
+static void common_args(const dm_ctx* ctx, SweepArgs& A) {
+  A = SweepArgs();
+  A.rrow_ptr = ctx->rrow_ptr.p;
+  A.n_short = int32_t(ctx->n_short);
+  A.long_wpr = ctx->long_wpr;
+  A.n_long = int32_t(ctx->n_rows - ctx->n_short);
+  A.long_perm = ctx->long_perm.p;
+}
+
+// no rows: the bound is the constant
+static dm_status empty_sweep(dm_ctx* ctx, double* bound_out) {
+  DM_TRY(dual_flush(ctx));
+  if (bound_out) k_write_offset<<<1, 1, 0, ctx->stream>>>(bound_out, ctx->offset);
+  DM_LAUNCH_CHECK(ctx);
+  return DM_OK;
+}
+
+// one hard row pass: mode update cells -> out (which may be cells itself),
+// write M per cell to out, bound only, or the minimising assignment to
+// ext->gsub; the bound goes to *bound_out (device)
+template <typename R>
+dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
+                     const SweepExt* ext) {
+  SweepArgs A;
+  common_args(ctx, A);
+  A.word = ctx->cell_word.p;
+  for (int f = 0; f < 2; ++f) A.n_tiles[f] = ctx->n_tiles[f];
+  A.wide_cell0 = uint32_t(ctx->wide_cell0);
+  A.chunk_cell0 = uint32_t(ctx->chunk_cell0);
+  A.long_cell0 = uint32_t(ctx->long_cell0);
+  A.n_chunks = ctx->n_chunks;
+  A.chunk_mask = ctx->chunk_mask.p;
+  A.chunk_neg = ctx->chunk_neg.p;
+  A.chunk_b = ctx->chunk_b.p;
+  A.n_long_y = ctx->n_long_y;
+  A.n_entries_short = int32_t(ctx->nnz_short);
+  hard_blocks(ctx, A.per);
+  if (ext) {
+    A.dir = ext->dir;
+    A.gamma = ext->gamma;
+    A.skip = ext->skip;
+    A.gsub = ext->gsub;
+  }
+  const int64_t grid = hard_grid(ctx);
+  if (grid == 0) return empty_sweep(ctx, bound_out);
+  DM_TRY(dual_flush(ctx));
+  double* mine = nullptr;
+  DM_TRY(next_partials(ctx, sizeof(R), &mine));
+  A.partial = mine;
+  hipEvent_t e1 = nullptr;
+  if (ctx->timing_open) DM_TRY(timing_events(ctx, nullptr, &e1));
+  ctx->timing_open = false;
+  hipStream_t st = ctx->stream;
+  const unsigned g = unsigned(grid);
+  if (mode == MODE_UPDATE) launch_sweep<R, false, MODE_UPDATE>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
+  else if (mode == MODE_EVAL) launch_sweep<R, false, MODE_EVAL>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
+  else if (mode == MODE_BOUND) launch_sweep<R, false, MODE_BOUND>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
+  else launch_sweep<R, false, MODE_SUBGRAD>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
+  DM_LAUNCH_CHECK(ctx);
+  pend(ctx, mine, grid, bound_out);
+  return DM_OK;
+}
+
+// one smoothed sweep over all rows: mode update rec_in -> out, write mu to out
+// per slot, or bound only; the bound goes to *bound_out (device)
+template <typename R>
+dm_status soft_sweep(dm_ctx* ctx, int mode, const unsigned char* rin, unsigned char* out, R omega, R T,
+                     double* bound_out) {
+  if (ctx->max_short > SOFT_MAX_ROW)
+    return dm_fail(ctx, DM_ERR_WORKSPACE, "smoothed rows support at most %d entries (found %d)", SOFT_MAX_ROW,
+                   ctx->max_short);
+  SweepArgs A;
+  common_args(ctx, A);
+  A.ent_word = ctx->rent_word.p;
+  A.rrow_b = ctx->rrow_b.p;
+  A.soft_row = ctx->soft_row.p;
+  A.soft_c8 = int32_t(ctx->soft_c8);
+  A.soft_c16 = int32_t(ctx->soft_c16);
+  A.n_short_blocks = int32_t(soft_short_blocks(ctx));
+  const int64_t nl = long_blocks(ctx), nblocks = int64_t(A.n_short_blocks) + nl;
+  A.n_items = int32_t(nblocks);
+  if (nblocks == 0) return empty_sweep(ctx, bound_out);
+  double* mine = nullptr;
+  DM_TRY(next_partials(ctx, sizeof(R), &mine));
   A.partial = mine;
   A.prev_partial = ctx->pend_out ? ctx->pend_partial : nullptr;
   A.prev_n = ctx->pend_n;
   A.prev_offset = ctx->pend_offset;
   A.prev_out = ctx->pend_out;
+  // 8 XCDs x blocks per XCD, see k_sweep
+  const int64_t long_slots = (nl + 8 * LONG_GROUP - 1) / (8 * LONG_GROUP) * LONG_GROUP;
+  const unsigned g = unsigned(8 * (long_slots + (A.n_short_blocks + 7) / 8));
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1));
   const R* ri = reinterpret_cast<const R*>(rin);
   R* ro = reinterpret_cast<R*>(out);
-  A.n_items = int32_t(nblocks);
-  // 8 XCDs x blocks per XCD, see k_sweep
-  const int64_t long_slots = (n_long_blocks + 8 * LONG_GROUP - 1) / (8 * LONG_GROUP) * LONG_GROUP;
-  const unsigned grid = soft ? unsigned(8 * (long_slots + (A.n_short_blocks + 7) / 8))
-                             : unsigned(8 * int64_t(ctx->xcd_stride));
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  if (ctx->timing) {
-    while (ctx->ev_pool.size() < ctx->ev_used + 2) {
-      hipEvent_t e;
-      DM_HIP(ctx, hipEventCreate(&e));
-      ctx->ev_pool.push_back(e);
-    }
-    e0 = ctx->ev_pool[ctx->ev_used];
-    e1 = ctx->ev_pool[ctx->ev_used + 1];
-    ctx->ev_used += 2;
-  }
   hipStream_t st = ctx->stream;
-  if (soft) {
-    if (mode == MODE_UPDATE) launch_sweep<R, true, MODE_UPDATE>(st, grid, e0, e1, A, ri, ro, omega, T);
-    else if (mode == MODE_EVAL) launch_sweep<R, true, MODE_EVAL>(st, grid, e0, e1, A, ri, ro, omega, T);
-    else launch_sweep<R, true, MODE_BOUND>(st, grid, e0, e1, A, ri, ro, omega, T);
-  } else {
-    const int32_t tiles = ctx->n_tiles;
-    if (mode == MODE_UPDATE) launch_hard<R, MODE_UPDATE>(tiles, st, grid, e0, e1, A, ri, ro, omega, T);
-    else if (mode == MODE_EVAL) launch_hard<R, MODE_EVAL>(tiles, st, grid, e0, e1, A, ri, ro, omega, T);
-    else if (mode == MODE_BOUND) launch_hard<R, MODE_BOUND>(tiles, st, grid, e0, e1, A, ri, ro, omega, T);
-    else launch_hard<R, MODE_SUBGRAD>(tiles, st, grid, e0, e1, A, ri, ro, omega, T);
-  }
+  if (mode == MODE_UPDATE) launch_sweep<R, true, MODE_UPDATE>(st, g, e0, e1, A, ri, nullptr, ro, omega, T);
+  else if (mode == MODE_EVAL) launch_sweep<R, true, MODE_EVAL>(st, g, e0, e1, A, ri, nullptr, ro, omega, T);
+  else launch_sweep<R, true, MODE_BOUND>(st, g, e0, e1, A, ri, nullptr, ro, omega, T);
   DM_LAUNCH_CHECK(ctx);
-  ctx->pend_half ^= 1;
-  ctx->pend_partial = mine;
-  ctx->pend_n = int32_t(nblocks);
-  ctx->pend_offset = ctx->offset;
-  ctx->pend_out = bound_out;
+  pend(ctx, mine, nblocks, bound_out);
   return DM_OK;
 }
 
@@ -1367,14 +1591,16 @@ extern "C" dm_status dm_timing_read(dm_ctx* ctx, int64_t* launches, double* tota
   return DM_OK;
 }
 
-template dm_status dual_import<float>(dm_ctx*, const float*, DArr<unsigned char>*);
-template dm_status dual_import<double>(dm_ctx*, const double*, DArr<unsigned char>*);
-template dm_status dual_export<float>(dm_ctx*, const unsigned char*, float*);
-template dm_status dual_export<double>(dm_ctx*, const unsigned char*, double*);
-template dm_status dual_sweep<float>(dm_ctx*, int, bool, const unsigned char*, unsigned char*, float, float, double*,
-                                     const SweepExt*);
-template dm_status dual_sweep<double>(dm_ctx*, int, bool, const unsigned char*, unsigned char*, double, double,
-                                      double*, const SweepExt*);
+#define DM_INSTANTIATE(R)                                                                                            \
+  template dm_status records_import<R>(dm_ctx*, const R*, DArr<unsigned char>*);                                      \
+  template dm_status cells_import<R>(dm_ctx*, const R*, CellState&, bool);                                            \
+  template dm_status cells_export<R>(dm_ctx*, const R*, const R*, R*);                                                \
+  template dm_status cells_vars<R>(dm_ctx*, const R*, const R*, R*, bool);                                            \
+  template dm_status cells_rows<R>(dm_ctx*, int, const R*, const R*, R*, R, double*, const SweepExt*);                \
+  template dm_status soft_sweep<R>(dm_ctx*, int, const unsigned char*, unsigned char*, R, R, double*);
+DM_INSTANTIATE(float)
+DM_INSTANTIATE(double)
+#undef DM_INSTANTIATE
 
 static dm_status check_solver(dm_ctx* ctx, int32_t msg_prec) {
   if (!ctx) return DM_ERR_INVALID_ARG;
@@ -1387,14 +1613,23 @@ static dm_status check_solver(dm_ctx* ctx, int32_t msg_prec) {
 
 template <typename R>
 static dm_status solve_impl(dm_ctx* ctx, int32_t iters, R omega, R T, R* lam, double* trace) {
-  DM_TRY(dual_import<R>(ctx, lam, ctx->rec));
-  const bool soft = T > R(0);
-  for (int32_t t = 0; t < iters; ++t)
-    DM_TRY(dual_sweep<R>(ctx, MODE_UPDATE, soft, ctx->rec[t & 1].p, ctx->rec[(t + 1) & 1].p, omega, T,
-                         trace ? trace + t : nullptr));
-  DM_TRY(dual_flush(ctx));
-  DM_TRY(dual_export<R>(ctx, ctx->rec[iters & 1].p, lam));
-  return DM_OK;
+  if (T > R(0)) {
+    DM_TRY(records_import<R>(ctx, lam, ctx->rec));
+    for (int32_t t = 0; t < iters; ++t)
+      DM_TRY(soft_sweep<R>(ctx, MODE_UPDATE, ctx->rec[t & 1].p, ctx->rec[(t + 1) & 1].p, omega, T,
+                           trace ? trace + t : nullptr));
+    DM_TRY(dual_flush(ctx));
+    return records_export<R>(ctx, ctx->rec[iters & 1].p, lam);
+  }
+  CellState& S = ctx->cells;
+  DM_TRY(cells_import<R>(ctx, lam, S, false));
+  R *cells = S.cells<R>(0), *t = S.ts<R>(0);
+  for (int32_t k = 0; k < iters; ++k) {
+    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
+    DM_TRY(cells_rows<R>(ctx, MODE_UPDATE, cells, t, cells, omega, trace ? trace + k : nullptr, nullptr));
+  }
+  DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, false));   // also sums the last bound
+  return cells_export<R>(ctx, cells, t, lam);
 }
 
 extern "C" dm_status dm_dual_solve(dm_ctx* ctx, int32_t iters, double omega, double temperature,
@@ -1428,11 +1663,20 @@ extern "C" dm_status dm_init_lambda(dm_ctx* ctx, int32_t msg_prec, void* lambda)
 
 template <typename R>
 static dm_status bound_impl(dm_ctx* ctx, const R* lam, R T, double* out) {
-  DArr<unsigned char> bufs[2];
-  DM_TRY(dual_import<R>(ctx, lam, bufs));
   DM_ALLOC(ctx, ctx->scal, 16);
-  DM_TRY(dual_sweep<R>(ctx, MODE_BOUND, T > R(0), bufs[0].p, nullptr, R(0), T, ctx->scal.p));
-  DM_TRY(dual_flush(ctx));
+  if (T > R(0)) {
+    DArr<unsigned char> bufs[2];
+    DM_TRY(records_import<R>(ctx, lam, bufs));
+    DM_TRY(soft_sweep<R>(ctx, MODE_BOUND, bufs[0].p, nullptr, R(0), T, ctx->scal.p));
+    DM_TRY(dual_flush(ctx));
+  } else {
+    CellState S;
+    DM_TRY(cells_import<R>(ctx, lam, S, false));
+    DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), false));
+    DM_TRY(cells_rows<R>(ctx, MODE_BOUND, S.cells<R>(0), S.ts<R>(0), static_cast<R*>(nullptr), R(0), ctx->scal.p,
+                         nullptr));
+    DM_TRY(dual_flush(ctx));
+  }
   DM_HIP(ctx, hipMemcpyAsync(out, ctx->scal.p, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
   DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
   return DM_OK;
@@ -1476,6 +1720,7 @@ extern "C" dm_status dm_set_workspace(dm_ctx* ctx, int32_t stage, void* ptr, siz
   // the solver's state moves: its own arrays (or views of the old buffer) go
   ctx->rec[0].release();
   ctx->rec[1].release();
+  ctx->cells.release();
   ctx->partial.release();
   ctx->ws_ptr[k] = ptr;
   ctx->ws_bytes[k] = ptr ? bytes : 0;

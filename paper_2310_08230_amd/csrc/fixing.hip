@@ -16,20 +16,20 @@ namespace {
 
 // per variable: preference and score key; agreeing variables flagged
 template <typename R>
-__global__ void k_agree_score(const R* mrec, const uint8_t* deg, int64_t nfree, uint8_t* flag, int8_t* pref,
-                              uint64_t* key) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nfree) return;
-  const R* m = mrec + size_t(i) * REC;
-  const int d = deg[i];
+__global__ void k_agree_score(const R* mcell, const uint32_t* vpos, const uint8_t* vdeg, const int32_t* vperm,
+                              int64_t nfree, uint8_t* flag, int8_t* pref, uint64_t* key) {
+  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (v >= nfree) return;
+  const int d = vdeg[v];
   bool neg = true, pos = true;
   double sum = 0.0;
   for (int k = 0; k < d; ++k) {
-    const R v = m[k];
-    neg = neg && v < R(0);
-    pos = pos && v > R(0);
-    sum += double(v);
+    const R m = mcell[vpos[size_t(k) * nfree + v]];
+    neg = neg && m < R(0);
+    pos = pos && m > R(0);
+    sum += double(m);
   }
+  const int32_t i = vperm[v];
   flag[i] = (neg || pos) ? 1 : 0;
   pref[i] = neg ? 1 : 0;
   // scores are >= 0, whose IEEE bits order like the values; complementing
@@ -68,13 +68,13 @@ dm_status confident_impl(dm_ctx* ctx, const R* lam, double frac, int8_t* fix, in
   int32_t na = 0;
   int64_t take = 0;
   if (nf > 0) {
-    DArr<unsigned char> bufs[2];
+    CellState S;
     DM_TRY(dual_flush(ctx));
-    DM_TRY(dual_import<R>(ctx, lam, bufs));
-    const size_t bytes = size_t(nf) * REC * sizeof(R);
-    DM_ALLOC(ctx, ctx->mrec, bytes);
-    DM_HIP(ctx, hipMemsetAsync(ctx->mrec.p, 0, bytes, st));
-    DM_TRY(dual_sweep<R>(ctx, SWEEP_EVAL, false, bufs[0].p, ctx->mrec.p, R(0), R(0), nullptr));
+    DM_TRY(cells_import<R>(ctx, lam, S, false));
+    DM_ALLOC(ctx, ctx->mrec, size_t(ctx->n_cells + 1) * sizeof(R));
+    R* m = reinterpret_cast<R*>(ctx->mrec.p);
+    DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), false));
+    DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, S.cells<R>(0), S.ts<R>(0), m, R(0), nullptr, nullptr));
     DArr<uint8_t> flag;
     DArr<int8_t> pref;
     DArr<uint64_t> key, key_c;
@@ -83,8 +83,8 @@ dm_status confident_impl(dm_ctx* ctx, const R* lam, double frac, int8_t* fix, in
     DM_ALLOC(ctx, pref, size_t(nf));
     DM_ALLOC(ctx, key, size_t(nf));
     DM_ALLOC(ctx, pos, size_t(nf) + 1);
-    k_agree_score<R><<<grid_for(nf, 256), 256, 0, st>>>(reinterpret_cast<const R*>(ctx->mrec.p), ctx->var_deg.p,
-                                                         nf, flag.p, pref.p, key.p);
+    k_agree_score<R><<<grid_for(nf, 256), 256, 0, st>>>(m, ctx->vpos.p, ctx->vdeg.p, ctx->vperm.p, nf, flag.p,
+                                                         pref.p, key.p);
     DM_LAUNCH_CHECK(ctx);
     DM_TRY(scan_u8(ctx, flag.p, pos.p, size_t(nf)));
     DM_TRY(read_i32(ctx, pos.p + nf, &na));

@@ -3,9 +3,12 @@
 //
 // Vectors with one value per multiplier (the subgradient g, the history pairs
 // s and y, the direction q / d) are five slot planes of n_free values: slot k
-// of variable i (k as in the records; slots at or above the variable's row
-// count are zero) at k * n_free + i, so every pass reads and writes
-// whole planes coalesced.  g and y only take the values 0/1 and -1/0/1 and
+// of variable i (i counts in variable order, layout.hip; slots at or above the
+// variable's row count are zero) at k * n_free + i, so every pass reads and
+// writes whole planes coalesced.  What the row passes read and write (the
+// direction, the row minimisers) is one value per cell: the last direction
+// pass also scatters d to the cells, which up to seven row passes then read in
+// order, and the history pass gathers the new g.  g and y only take the values 0/1 and -1/0/1 and
 // are stored as bytes, so a history pair costs 5 reals and 5 bytes per
 // variable.
 //
@@ -89,14 +92,34 @@ __device__ inline void project5(double v[5], int d) {
 }
 
 // ---------------------------------------------------------------- direction passes
+// the used slots of d into the variable's cells
+template <typename R>
+__device__ inline void scatter5(const uint32_t* vpos, int64_t i, int64_t n, const double v[5], int d, R* cells) {
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    if (k < d) cells[vpos[k * n + i]] = R(v[k]);
+}
+
+// row minimisers of the cells into slot planes (zero in unused slots)
+__global__ __launch_bounds__(VB) void k_qn_gather_g(const uint8_t* gcell, const uint32_t* vpos, const uint8_t* deg,
+                                                    int64_t n, uint8_t* g8) {
+  for (int64_t i = int64_t(blockIdx.x) * VB + threadIdx.x; i < n; i += int64_t(gridDim.x) * VB) {
+    const int d = deg[i];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) g8[k * n + i] = k < d ? gcell[vpos[k * n + i]] : 0;
+  }
+}
+
 // h = 0: d = g minus its per-variable mean
 template <typename R>
-__global__ __launch_bounds__(VB) void k_qn_project_g(const uint8_t* g8, const uint8_t* deg, int64_t n, R* d) {
+__global__ __launch_bounds__(VB) void k_qn_project_g(const uint8_t* g8, const uint8_t* deg, int64_t n, R* d,
+                                                     const uint32_t* vpos, R* dcell) {
   for (int64_t i = int64_t(blockIdx.x) * VB + threadIdx.x; i < n; i += int64_t(gridDim.x) * VB) {
     double v[5];
     load5_u8(g8, i, n, v);
     project5(v, deg[i]);
     store5<R>(d, i, n, v);
+    if (dcell) scatter5<R>(vpos, i, n, v, deg[i], dcell);
   }
 }
 
@@ -149,7 +172,8 @@ template <typename R>
 __global__ __launch_bounds__(VB) void k_qn_loop2(const R* q_in, const R* s, const int8_t* y_next,
                                                  const double* part_in, int32_t n_in, const double* sy,
                                                  const double* alpha, const double* h0_sy, const double* h0_yy,
-                                                 const uint8_t* deg, int64_t n, R* q_out, double* part_out) {
+                                                 const uint8_t* deg, int64_t n, R* q_out, double* part_out,
+                                                 const uint32_t* vpos, R* dcell) {
   __shared__ double red[4];
   const double h0 = h0_sy ? *h0_sy / *h0_yy : 1.0;
   const double beta = h0 * sum_partials(part_in, n_in, red) / *sy;
@@ -167,6 +191,7 @@ __global__ __launch_bounds__(VB) void k_qn_loop2(const R* q_in, const R* s, cons
       acc += dot5(yv, qv);
     } else {
       project5(qv, deg[i]);
+      if (dcell) scatter5<R>(vpos, i, n, qv, deg[i], dcell);
     }
     store5<R>(q_out, i, n, qv);
   }
@@ -177,25 +202,44 @@ __global__ __launch_bounds__(VB) void k_qn_loop2(const R* q_in, const R* s, cons
 }
 
 // ---------------------------------------------------------------- history
-// s = lambda_new - lambda_old (both with feasibility restored exactly as the
-// sweeps see them), y = g_old - g_new, and the partials of s^T y and y^T y
+// s + t / |J| in one rounding, as the row passes form it
 template <typename R>
-__global__ __launch_bounds__(VB) void k_qn_hist_pass(const R* rec_old, const R* rec_new, const uint8_t* g_old,
-                                                     const uint8_t* g_new, const uint8_t* deg, int64_t n, R* s_out,
-                                                     int8_t* y_out, double* part_sy, double* part_yy) {
+__device__ inline R restored(R s, R t, R rd) {
+  if constexpr (sizeof(R) == 4) return __builtin_fmaf(t, rd, s);
+  else return __builtin_fma(t, rd, s);
+}
+
+// s = lambda_new - lambda_old (both with feasibility restored exactly as the
+// sweeps see them), y = g_old - g_new, and the partials of s^T y and y^T y; the
+// new g comes from the cells and goes to its planes
+template <typename R>
+__global__ __launch_bounds__(VB) void k_qn_hist_pass(const R* cell_old, const R* t_old, const R* cell_new,
+                                                     const R* t_new, const uint32_t* vpos, const uint8_t* g_old,
+                                                     const uint8_t* gcell, const uint8_t* deg, int64_t n, uint8_t* g_new,
+                                                     R* s_out, int8_t* y_out, double* part_sy, double* part_yy) {
   __shared__ double red[4];
   double a_sy = 0.0, a_yy = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * VB + threadIdx.x; i < n; i += int64_t(gridDim.x) * VB) {
-    R lo[5], ln[5];
-    rec_lambdas<R>(rec_old, size_t(i), lo);
-    rec_lambdas<R>(rec_new, size_t(i), ln);
+    const int d = deg[i];
+    const R rd = R(1) / R(d), to = t_old[i], tn = t_new[i];
+    uint32_t p[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) p[k] = vpos[k * n + i];
+    R so[5], sn[5];
     double go[5], gn[5], sv[5], yv[5];
-    load5_u8(g_old, i, n, go);
-    load5_u8(g_new, i, n, gn);
+#pragma unroll
     for (int k = 0; k < 5; ++k) {
-      sv[k] = double(R(ln[k] - lo[k]));
+      so[k] = cell_old[p[k]];
+      sn[k] = cell_new[p[k]];
+      gn[k] = k < d ? double(gcell[p[k]]) : 0.0;
+    }
+    load5_u8(g_old, i, n, go);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      sv[k] = k < d ? double(R(restored<R>(sn[k], tn, rd) - restored<R>(so[k], to, rd))) : 0.0;
       yv[k] = go[k] - gn[k];
       y_out[k * n + i] = int8_t(yv[k]);
+      g_new[k * n + i] = uint8_t(gn[k]);
     }
     store5<R>(s_out, i, n, sv);
     a_sy += dot5(sv, yv);
@@ -317,15 +361,21 @@ __global__ __launch_bounds__(1024) void k_qn_hist(const double* sp, int32_t sn, 
 // ---------------------------------------------------------------- layout conversion
 // entry order <-> slot planes
 template <typename T>
-__global__ void k_scatter(const T* v, const uint32_t* word, int64_t nnz, int64_t n, T* planes) {
+__global__ void k_scatter(const T* v, const uint32_t* word, const int32_t* vinv, int64_t nnz, int64_t n, T* planes) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e < nnz) planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + (word[e] & W_VAR_MASK)] = v[e];
+  if (e < nnz) planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + vinv[word[e] & W_VAR_MASK]] = v[e];
 }
 
 template <typename T>
-__global__ void k_gather(const T* planes, const uint32_t* word, int64_t nnz, int64_t n, T* v) {
+__global__ void k_gather(const T* planes, const uint32_t* word, const int32_t* vinv, int64_t nnz, int64_t n, T* v) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e < nnz) v[e] = planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + (word[e] & W_VAR_MASK)];
+  if (e < nnz) v[e] = planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + vinv[word[e] & W_VAR_MASK]];
+}
+
+// entry order from cells
+__global__ void k_gather_cells(const uint8_t* cells, const uint32_t* ent_cell, int64_t nnz, uint8_t* v) {
+  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e < nnz) v[e] = cells[ent_cell[e]];
 }
 
 __global__ void k_fill_f64(double* a, int64_t n, double v) {
@@ -352,17 +402,17 @@ unsigned vgrid(int64_t n) {
 }
 
 // d = projected H g into q, over the pairs in `order` (oldest first); part
-// holds two VGRID halves
+// holds two VGRID halves; dcell (optional) takes d per cell as well
 template <typename R>
 dm_status direction(dm_ctx* ctx, const std::vector<int>& order, R* const* S, int8_t* const* Y, const uint8_t* g8,
-                    R* q, const Scal& sc, double* part) {
+                    R* q, const Scal& sc, double* part, R* dcell) {
   const int64_t n = ctx->n_free;
   const unsigned G = vgrid(n);
-  const uint8_t* deg = ctx->var_deg.p;
+  const uint8_t* deg = ctx->vdeg.p;
   hipStream_t st = ctx->stream;
   const int h = int(order.size());
   if (h == 0) {
-    k_qn_project_g<R><<<G, VB, 0, st>>>(g8, deg, n, q);
+    k_qn_project_g<R><<<G, VB, 0, st>>>(g8, deg, n, q, ctx->vpos.p, dcell);
     DM_LAUNCH_CHECK(ctx);
     return DM_OK;
   }
@@ -383,7 +433,7 @@ dm_status direction(dm_ctx* ctx, const std::vector<int>& order, R* const* S, int
     const int8_t* y_next = i + 1 < h ? Y[order[i + 1]] : nullptr;
     k_qn_loop2<R><<<G, VB, 0, st>>>(q, S[b], y_next, pin, int32_t(G), sc.sy(b), sc.alpha(b),
                                      i == 0 ? sc.sy(newest) : nullptr, i == 0 ? sc.yy(newest) : nullptr, deg, n,
-                                     q, pout);
+                                     q, pout, ctx->vpos.p, y_next ? nullptr : dcell);
     std::swap(pin, pout);
   }
   DM_LAUNCH_CHECK(ctx);
@@ -494,22 +544,30 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
   const int64_t n = ctx->n_free;
   const unsigned G = vgrid(n);
   DM_TRY(dual_flush(ctx));
-  DM_TRY(dual_import<R>(ctx, lam, ctx->rec));
+  CellState& C = ctx->cells;
+  DM_TRY(cells_import<R>(ctx, lam, C, true));
+  DArr<uint8_t> gcell;   // row minimisers and direction, one value per cell
+  DArr<R> dcell;
+  DM_ALLOC(ctx, gcell, size_t(ctx->n_cells) + 1);
+  DM_ALLOC(ctx, dcell, size_t(ctx->n_cells) + 1);
   int cur = 0, gc = 0;
+  R* none = nullptr;
   SweepExt sub;
-  sub.gsub = B.g[0].p;
-  DM_TRY(dual_sweep<R>(ctx, SWEEP_SUBGRAD, false, ctx->rec[0].p, nullptr, R(0), R(0), nullptr, &sub));
+  sub.gsub = gcell.p;
+  DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), false));
+  DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(0), C.ts<R>(0), none, R(0), nullptr, &sub));
   k_qn_begin<<<1, 1024, 0, stream>>>(ctx->pend_partial, ctx->pend_n, ctx->offset, st, etrace.p, P.gamma0,
                                    resume ? 1 : 0);
+  k_qn_gather_g<<<G, VB, 0, stream>>>(gcell.p, ctx->vpos.p, ctx->vdeg.p, n, B.g[0].p);
   DM_LAUNCH_CHECK(ctx);
   for (int32_t k = 0; k < iters; ++k) {
-    DM_TRY(direction<R>(ctx, S.order, B.Sp.data(), B.Yp.data(), B.g[gc].p, B.q.p, sc, B.part.p));
+    DM_TRY(direction<R>(ctx, S.order, B.Sp.data(), B.Yp.data(), B.g[gc].p, B.q.p, sc, B.part.p, dcell.p));
     SweepExt pe;
-    pe.dir = B.q.p;
+    pe.dir = dcell.p;
     pe.gamma = &st->gamma;
     pe.skip = &st->done;
     for (int t = 0; t <= P.max_search; ++t) {
-      DM_TRY(dual_sweep<R>(ctx, SWEEP_BOUND, false, ctx->rec[cur].p, nullptr, R(0), R(0), nullptr, &pe));
+      DM_TRY(cells_rows<R>(ctx, SWEEP_BOUND, C.cells<R>(cur), C.ts<R>(cur), none, R(0), nullptr, &pe));
       k_qn_probe<<<1, 1024, 0, stream>>>(ctx->pend_partial, ctx->pend_n, ctx->offset, t, P.max_search, P.step_up,
                                          P.step_down, st, gamma_trace ? gamma_trace + k : nullptr,
                                          taken ? taken + k : nullptr);
@@ -525,22 +583,23 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
       }
     }
     SweepExt me;
-    me.dir = B.q.p;
+    me.dir = dcell.p;
     me.gamma = &st->step;
-    DM_TRY(dual_sweep<R>(ctx, SWEEP_UPDATE, false, ctx->rec[cur].p, ctx->rec[cur ^ 1].p, R(P.omega), R(0),
-                         nullptr, &me));
-    sub.gsub = B.g[gc ^ 1].p;
-    DM_TRY(dual_sweep<R>(ctx, SWEEP_SUBGRAD, false, ctx->rec[cur ^ 1].p, nullptr, R(0), R(0), nullptr, &sub));
+    const int nxt = cur ^ 1;
+    DM_TRY(cells_rows<R>(ctx, SWEEP_UPDATE, C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), R(P.omega), nullptr, &me));
+    DM_TRY(cells_vars<R>(ctx, C.cells<R>(nxt), C.costs<R>(), C.ts<R>(nxt), false));
+    DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(nxt), C.ts<R>(nxt), none, R(0), nullptr, &sub));
     const double* sp = ctx->pend_partial;
     const int32_t sn = ctx->pend_n;
     double* psy = B.part.p + 2 * VGRID;
     double* pyy = B.part.p + 3 * VGRID;
     const int spare = S.spare;
     if (m > 0)
-      k_qn_hist_pass<R><<<G, VB, 0, stream>>>(reinterpret_cast<const R*>(ctx->rec[cur].p),
-                                               reinterpret_cast<const R*>(ctx->rec[cur ^ 1].p), B.g[gc].p,
-                                               B.g[gc ^ 1].p, ctx->var_deg.p, n, B.Sp[spare], B.Yp[spare], psy,
-                                               pyy);
+      k_qn_hist_pass<R><<<G, VB, 0, stream>>>(C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), C.ts<R>(nxt), ctx->vpos.p,
+                                               B.g[gc].p, gcell.p, ctx->vdeg.p, n, B.g[gc ^ 1].p, B.Sp[spare],
+                                               B.Yp[spare], psy, pyy);
+    else
+      k_qn_gather_g<<<G, VB, 0, stream>>>(gcell.p, ctx->vpos.p, ctx->vdeg.p, n, B.g[gc ^ 1].p);
     k_qn_hist<<<1, 1024, 0, stream>>>(sp, sn, ctx->offset, psy, pyy, m > 0 ? int32_t(G) : 0, k,
                                     (k == 0 && !resume) ? 1 : 0, P.eps, st, etrace.p, sc.sy(spare),
                                     sc.yy(spare), S.flag.p);
@@ -569,7 +628,7 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
   if (lb_trace)
     DM_HIP(ctx, hipMemcpyAsync(lb_trace, etrace.p, (size_t(iters) + 1) * sizeof(double), hipMemcpyDeviceToDevice,
                                stream));
-  DM_TRY(dual_export<R>(ctx, ctx->rec[cur].p, lam));
+  DM_TRY(cells_export<R>(ctx, C.cells<R>(cur), C.ts<R>(cur), lam));
   // the per-call trace buffer is freed on return: wait for the queued work
   DM_HIP(ctx, hipStreamSynchronize(stream));
   return DM_OK;
@@ -577,20 +636,20 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
 
 template <typename R>
 dm_status subgradient_impl(dm_ctx* ctx, const R* lam, uint8_t* g, double* lb) {
-  DArr<unsigned char> bufs[2];
-  DArr<uint8_t> g8;
+  CellState C;
+  DArr<uint8_t> gcell;
   DM_TRY(dual_flush(ctx));
-  DM_TRY(dual_import<R>(ctx, lam, bufs));
-  DM_ALLOC(ctx, g8, size_t(std::max<int64_t>(ctx->n_free, 1)) * 5);
-  DM_HIP(ctx, hipMemsetAsync(g8.p, 0, g8.n, ctx->stream));
+  DM_TRY(cells_import<R>(ctx, lam, C, false));
+  DM_ALLOC(ctx, gcell, size_t(ctx->n_cells) + 1);
   DM_ALLOC(ctx, ctx->scal, 16);
   SweepExt sub;
-  sub.gsub = g8.p;
-  DM_TRY(dual_sweep<R>(ctx, SWEEP_SUBGRAD, false, bufs[0].p, nullptr, R(0), R(0), ctx->scal.p, &sub));
+  sub.gsub = gcell.p;
+  DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), false));
+  DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(0), C.ts<R>(0), static_cast<R*>(nullptr), R(0), ctx->scal.p,
+                       &sub));
   DM_TRY(dual_flush(ctx));
   if (ctx->nnz > 0)
-    k_gather<uint8_t><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(g8.p, ctx->rent_word.p, ctx->nnz,
-                                                                        ctx->n_free, g);
+    k_gather_cells<<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(gcell.p, ctx->ent_cell.p, ctx->nnz, g);
   DM_LAUNCH_CHECK(ctx);
   double v = 0.0;
   DM_HIP(ctx, hipMemcpyAsync(&v, ctx->scal.p, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
@@ -609,17 +668,18 @@ dm_status direction_impl(dm_ctx* ctx, int32_t h, const R* S, const int8_t* Y, co
   const unsigned G = vgrid(n);
   const unsigned E = grid_for(nnz, 256);
   std::vector<int> order;
-  k_scatter<uint8_t><<<E, 256, 0, ctx->stream>>>(g, ctx->rent_word.p, nnz, n, B.g[0].p);
+  k_scatter<uint8_t><<<E, 256, 0, ctx->stream>>>(g, ctx->rent_word.p, ctx->vinv.p, nnz, n, B.g[0].p);
   for (int b = 0; b < h; ++b) {
-    k_scatter<R><<<E, 256, 0, ctx->stream>>>(S + size_t(b) * nnz, ctx->rent_word.p, nnz, n, B.Sp[b]);
-    k_scatter<int8_t><<<E, 256, 0, ctx->stream>>>(Y + size_t(b) * nnz, ctx->rent_word.p, nnz, n, B.Yp[b]);
+    k_scatter<R><<<E, 256, 0, ctx->stream>>>(S + size_t(b) * nnz, ctx->rent_word.p, ctx->vinv.p, nnz, n, B.Sp[b]);
+    k_scatter<int8_t><<<E, 256, 0, ctx->stream>>>(Y + size_t(b) * nnz, ctx->rent_word.p, ctx->vinv.p, nnz, n, B.Yp[b]);
     k_qn_pair_dots<R><<<G, VB, 0, ctx->stream>>>(B.Sp[b], B.Yp[b], n, B.part.p, B.part.p + VGRID);
     k_qn_pair_fin<<<1, 1024, 0, ctx->stream>>>(B.part.p, B.part.p + VGRID, int32_t(G), sc.sy(b), sc.yy(b));
     order.push_back(b);
   }
   DM_LAUNCH_CHECK(ctx);
-  DM_TRY(direction<R>(ctx, order, B.Sp.data(), B.Yp.data(), B.g[0].p, B.q.p, sc, B.part.p));
-  k_gather<R><<<E, 256, 0, ctx->stream>>>(B.q.p, ctx->rent_word.p, nnz, n, d);
+  DM_TRY(direction<R>(ctx, order, B.Sp.data(), B.Yp.data(), B.g[0].p, B.q.p, sc, B.part.p,
+                         static_cast<R*>(nullptr)));
+  k_gather<R><<<E, 256, 0, ctx->stream>>>(B.q.p, ctx->rent_word.p, ctx->vinv.p, nnz, n, d);
   DM_LAUNCH_CHECK(ctx);
   DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
   return DM_OK;

@@ -29,25 +29,32 @@ __device__ inline double counter_uniform(uint64_t seed, uint32_t round, uint32_t
   return double(z >> 11) * (1.0 / 9007199254740992.0) * 2.0 - 1.0;
 }
 
+// per variable v: its preference, the summed |M| (when absm is given) and the
+// number of undecided variables, one atomic per wave
 template <typename R>
-__global__ void k_agree(const R* mrec, const uint8_t* deg, int64_t nfree, int8_t* pref, int64_t* count,
-                        double* absm) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nfree) return;
-  const R* m = mrec + size_t(i) * REC;
-  const int d = deg[i];
-  bool neg = true, pos = true;
-  double a = 0.0;
-  for (int k = 0; k < d; ++k) {
-    R v = m[k];
-    neg = neg && (v < R(0));
-    pos = pos && (v > R(0));
-    a += fabs(double(v));
+__global__ void k_agree(const R* mcell, const uint32_t* vpos, const uint8_t* vdeg, const int32_t* vperm,
+                        int64_t nfree, int8_t* pref, int64_t* count, double* absm) {
+  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  bool undecided = false;
+  if (v < nfree) {
+    const int d = vdeg[v];
+    bool neg = true, pos = true;
+    double a = 0.0;
+    for (int k = 0; k < d; ++k) {
+      const R m = mcell[vpos[size_t(k) * nfree + v]];
+      neg = neg && (m < R(0));
+      pos = pos && (m > R(0));
+      a += fabs(double(m));
+    }
+    const int8_t p = neg ? 1 : (pos ? 0 : -1);
+    const int32_t i = vperm[v];
+    pref[i] = p;
+    if (absm) absm[i] = a;
+    undecided = p < 0;
   }
-  int8_t p = neg ? 1 : (pos ? 0 : -1);
-  pref[i] = p;
-  absm[i] = a;
-  if (p < 0) atomicAdd(reinterpret_cast<unsigned long long*>(count), 1ull);
+  const unsigned long long m = __ballot(undecided);
+  if (m && (threadIdx.x & 63) == 0)
+    atomicAdd(reinterpret_cast<unsigned long long*>(count), static_cast<unsigned long long>(__popcll(m)));
 }
 
 // one-block sums in a fixed order; eight independent accumulators per thread
@@ -83,17 +90,17 @@ __global__ __launch_bounds__(256) void k_violations_proj(const int32_t* row_ptr,
     atomicAdd(reinterpret_cast<unsigned long long*>(count), 1ull);
 }
 
-// c~_i += Delta_i in both record buffers; the next projection spreads
-// Delta_i / |J_i| over the multipliers of i
+// c~_i += Delta_i; the next projection spreads Delta_i / |J_i| over the
+// multipliers of i
 template <typename R>
-__global__ void k_perturb(const int8_t* pref, int64_t nfree, double delta, uint64_t seed, uint32_t round, R* r0,
-                          R* r1) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nfree) return;
-  int8_t p = pref[i];
-  double d = p == 1 ? -delta : (p == 0 ? delta : delta * counter_uniform(seed, round, uint32_t(i)));
-  r0[size_t(i) * REC + REC_COST] += R(d);
-  r1[size_t(i) * REC + REC_COST] += R(d);
+__global__ void k_perturb(const int8_t* pref, const int32_t* vperm, int64_t nfree, double delta, uint64_t seed,
+                          uint32_t round, R* cost) {
+  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (v >= nfree) return;
+  const int32_t i = vperm[v];
+  const int8_t p = pref[i];
+  const double d = p == 1 ? -delta : (p == 0 ? delta : delta * counter_uniform(seed, round, uint32_t(i)));
+  cost[v] += R(d);
 }
 
 }  // namespace
@@ -125,28 +132,30 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
                             int32_t* feasible, int32_t* rounds_used) {
   hipStream_t st = ctx->stream;
   const int64_t nfree = ctx->n_free;
-  DM_TRY(dual_import<R>(ctx, lam, ctx->rrec));
-  const size_t bytes = size_t(std::max<int64_t>(nfree, 1)) * REC * sizeof(R);
-  DM_ALLOC(ctx, ctx->mrec, bytes);
-  DM_HIP(ctx, hipMemsetAsync(ctx->mrec.p, 0, bytes, st));
+  CellState& S = ctx->rcells;
+  DM_TRY(dual_flush(ctx));
+  DM_TRY(cells_import<R>(ctx, lam, S, false));
+  R *cells = S.cells<R>(0), *t = S.ts<R>(0);
+  DM_ALLOC(ctx, ctx->mrec, size_t(ctx->n_cells + 1) * sizeof(R));
+  R* m = reinterpret_cast<R*>(ctx->mrec.p);
   DM_ALLOC(ctx, ctx->pref, size_t(std::max<int64_t>(nfree, 1)));
   DM_ALLOC(ctx, ctx->icount, 4);
   DM_ALLOC(ctx, ctx->scal, 16);
   DArr<double> absm;
   DM_ALLOC(ctx, absm, size_t(std::max<int64_t>(nfree, 1)));
   double delta = P.delta0;
-  int cur = 0;
   *feasible = 0;
   for (int32_t r = 0; r <= P.rounds; ++r) {
-    DM_TRY(dual_sweep<R>(ctx, SWEEP_EVAL, false, ctx->rrec[cur].p, ctx->mrec.p, R(0), R(0), nullptr));
+    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, false));
+    DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, cells, t, m, R(0), nullptr, nullptr));
     DM_HIP(ctx, hipMemsetAsync(ctx->icount.p, 0, sizeof(int64_t), st));
+    const bool auto_delta = r == 0 && delta <= 0.0;
     if (nfree > 0)
-      k_agree<R><<<grid_for(nfree, 256), 256, 0, st>>>(reinterpret_cast<const R*>(ctx->mrec.p), ctx->var_deg.p,
-                                                      nfree, ctx->pref.p, ctx->icount.p, absm.p);
+      k_agree<R><<<grid_for(nfree, 256), 256, 0, st>>>(m, ctx->vpos.p, ctx->vdeg.p, ctx->vperm.p, nfree, ctx->pref.p,
+                                                      ctx->icount.p, auto_delta ? absm.p : nullptr);
     DM_LAUNCH_CHECK(ctx);
     // the undecided count and, on the first round, the automatic perturbation
     // scale (from the summed |M|) come back with one wait
-    const bool auto_delta = r == 0 && delta <= 0.0;
     if (auto_delta) DM_TRY(sum_f64(ctx, absm.p, nfree, nullptr, SUM_ALL, ctx->scal.p));
     int64_t undecided = 0;
     double sum_absm = 0.0;
@@ -172,13 +181,13 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
       }
     }
     if (r == P.rounds) break;
-    k_perturb<R><<<grid_for(std::max<int64_t>(nfree, 1), 256), 256, 0, st>>>(
-        ctx->pref.p, nfree, delta, P.seed, uint32_t(r), reinterpret_cast<R*>(ctx->rrec[0].p),
-        reinterpret_cast<R*>(ctx->rrec[1].p));
+    if (nfree > 0)
+      k_perturb<R><<<grid_for(nfree, 256), 256, 0, st>>>(ctx->pref.p, ctx->vperm.p, nfree, delta, P.seed, uint32_t(r),
+                                                        S.costs<R>());
     DM_LAUNCH_CHECK(ctx);
-    for (int32_t t = 0; t < P.iters_per_round; ++t) {
-      DM_TRY(dual_sweep<R>(ctx, SWEEP_UPDATE, false, ctx->rrec[cur].p, ctx->rrec[cur ^ 1].p, R(P.omega), R(0), nullptr));
-      cur ^= 1;
+    for (int32_t k = 0; k < P.iters_per_round; ++k) {
+      DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
+      DM_TRY(cells_rows<R>(ctx, SWEEP_UPDATE, cells, t, cells, R(P.omega), nullptr, nullptr));
     }
     delta *= P.gamma;
   }

@@ -22,18 +22,23 @@
 
 namespace {
 
+template <typename R>
+__device__ inline double summed_m(const R* mcell, const uint32_t* vpos, const uint8_t* vdeg, int64_t nfree, int64_t v) {
+  double sum = 0.0;
+  for (int k = 0; k < vdeg[v]; ++k) sum += double(mcell[vpos[size_t(k) * nfree + v]]);
+  return sum;
+}
+
 // key of free variable i: (|sum_j M^j_i| as FP32 bits) << 32 | i, so the
 // smallest key is the least confident variable, ties to the lower index
 template <typename R>
-__global__ void k_branch_keys(const R* mrec, const uint8_t* deg, int64_t nfree, unsigned long long* best) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+__global__ void k_branch_keys(const R* mcell, const uint32_t* vpos, const uint8_t* vdeg, const int32_t* vperm,
+                              int64_t nfree, unsigned long long* best) {
+  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   unsigned long long key = ~0ull;
-  if (i < nfree) {
-    const R* m = mrec + size_t(i) * REC;
-    double sum = 0.0;
-    for (int k = 0; k < deg[i]; ++k) sum += double(m[k]);
-    const float a = float(fabs(sum));   // >= 0: its bits order like its value
-    key = (static_cast<unsigned long long>(__float_as_uint(a)) << 32) | static_cast<unsigned long long>(i);
+  if (v < nfree) {
+    const float a = float(fabs(summed_m<R>(mcell, vpos, vdeg, nfree, v)));   // >= 0: its bits order like its value
+    key = (static_cast<unsigned long long>(__float_as_uint(a)) << 32) | static_cast<unsigned long long>(vperm[v]);
   }
   for (int o = 32; o > 0; o >>= 1) {
     const unsigned long long other = __shfl_xor(key, o);
@@ -45,14 +50,11 @@ __global__ void k_branch_keys(const R* mrec, const uint8_t* deg, int64_t nfree, 
 // preferred value of free variable i: 1 when its summed min-marginal
 // differences are negative
 template <typename R>
-__global__ void k_branch_pref(const R* mrec, const uint8_t* deg, const unsigned long long* best,
-                              const int32_t* free_var, int32_t* out) {
+__global__ void k_branch_pref(const R* mcell, const uint32_t* vpos, const uint8_t* vdeg, const int32_t* vinv,
+                              int64_t nfree, const unsigned long long* best, const int32_t* free_var, int32_t* out) {
   const int32_t i = int32_t(*best & 0xFFFFFFFFull);
-  const R* m = mrec + size_t(i) * REC;
-  double sum = 0.0;
-  for (int k = 0; k < deg[i]; ++k) sum += double(m[k]);
   out[0] = free_var[i];
-  out[1] = sum < 0.0 ? 1 : 0;
+  out[1] = summed_m<R>(mcell, vpos, vdeg, nfree, vinv[i]) < 0.0 ? 1 : 0;
 }
 
 __global__ void k_apply_path(const int32_t* path, int32_t n, int8_t* fix) {
@@ -143,22 +145,20 @@ dm_status node_bound_and_branch(dm_ctx* ctx, const dm_search_params& P, DArr<uns
   *branch = nf > 0;
   if (!*branch) return DM_OK;
   // min-marginal differences at the final multipliers
-  DArr<unsigned char> bufs[2];
+  CellState S;
   DM_TRY(dual_flush(ctx));
-  DM_TRY(dual_import<R>(ctx, lam, bufs));
-  const size_t bytes = size_t(nf) * REC * sizeof(R);
-  DM_ALLOC(ctx, ctx->mrec, bytes);
-  DM_HIP(ctx, hipMemsetAsync(ctx->mrec.p, 0, bytes, st));
-  DM_TRY(dual_sweep<R>(ctx, SWEEP_EVAL, false, bufs[0].p, ctx->mrec.p, R(0), R(0), nullptr));
+  DM_TRY(cells_import<R>(ctx, lam, S, false));
+  DM_ALLOC(ctx, ctx->mrec, size_t(ctx->n_cells + 1) * sizeof(R));
+  R* m = reinterpret_cast<R*>(ctx->mrec.p);
+  DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), false));
+  DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, S.cells<R>(0), S.ts<R>(0), m, R(0), nullptr, nullptr));
   DArr<unsigned long long> key;
   DArr<int32_t> out;
   DM_ALLOC(ctx, key, 1);
   DM_ALLOC(ctx, out, 2);
   DM_HIP(ctx, hipMemsetAsync(key.p, 0xFF, sizeof(unsigned long long), st));
-  k_branch_keys<R><<<grid_for(nf, 256), 256, 0, st>>>(reinterpret_cast<const R*>(ctx->mrec.p), ctx->var_deg.p, nf,
-                                                       key.p);
-  k_branch_pref<R><<<1, 1, 0, st>>>(reinterpret_cast<const R*>(ctx->mrec.p), ctx->var_deg.p, key.p,
-                                    ctx->free_var.p, out.p);
+  k_branch_keys<R><<<grid_for(nf, 256), 256, 0, st>>>(m, ctx->vpos.p, ctx->vdeg.p, ctx->vperm.p, nf, key.p);
+  k_branch_pref<R><<<1, 1, 0, st>>>(m, ctx->vpos.p, ctx->vdeg.p, ctx->vinv.p, nf, key.p, ctx->free_var.p, out.p);
   DM_LAUNCH_CHECK(ctx);
   const int32_t* src[2] = {out.p, out.p + 1};
   int32_t v[2];

@@ -93,12 +93,12 @@ static dm_status backward_impl(dm_ctx* ctx, const R* lam, R T, double scale, con
                                int32_t D, float* gcost, float* gFX, float* gFY, double* value) {
   hipStream_t st = ctx->stream;
   DArr<unsigned char> bufs[2];
-  DM_TRY(dual_import<R>(ctx, lam, bufs));
+  DM_TRY(records_import<R>(ctx, lam, bufs));
   const size_t bytes = size_t(std::max<int64_t>(ctx->n_free, 1)) * REC * sizeof(R);
   DM_ALLOC(ctx, ctx->mrec, bytes);
   DM_HIP(ctx, hipMemsetAsync(ctx->mrec.p, 0, bytes, st));
   DM_ALLOC(ctx, ctx->scal, 16);
-  DM_TRY(dual_sweep<R>(ctx, SWEEP_EVAL, true, bufs[0].p, ctx->mrec.p, R(0), T, ctx->scal.p + 2));
+  DM_TRY(soft_sweep<R>(ctx, SWEEP_EVAL, bufs[0].p, ctx->mrec.p, R(0), T, ctx->scal.p + 2));
   DM_TRY(dual_flush(ctx));
   DM_ALLOC(ctx, ctx->gcost_tmp, size_t(ctx->nP));
   DM_TRY(corner_lists(ctx));
