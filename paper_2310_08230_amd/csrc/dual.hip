@@ -275,6 +275,7 @@ struct SweepArgs {
   int32_t n_long_y;         // of the projection rows in launch order, the Y rows come first
   int32_t per[5];           // blocks per XCD: Y rows, X rows, chunks, wide tiles, narrow tiles
   int32_t n_entries_short;  // entries of the short rows
+  const int32_t* long_ent;  // entry of each projection-row cell (ties in MODE_SUBGRAD), or NULL: in order
   // quasi-Newton extensions: rows see lambda + gamma * dir when dir is set
   // (one value per cell; gamma a device scalar); the launch does nothing when
   // *skip is nonzero; MODE_SUBGRAD writes the row's minimising assignment
@@ -950,12 +951,16 @@ __device__ double long_rows(const SweepArgs& A, const R* src, const R* __restric
     if constexpr (SOFT) return cur_lambda<R>(src, w);
     else return cell_lambda<R>(A, src, t, c0 + uint32_t(i), w, gam);
   };
+  // which of several equal minima a row takes shows only in its assignment
+  // (the min-marginals are the same): the first in the row's entry order
+  const int32_t* ent = !SOFT && MODE == MODE_SUBGRAD && A.long_ent && n > 0 ? A.long_ent + (s - A.n_entries_short) : nullptr;
+  auto place = [&](int32_t i) { return ent ? ent[i] : i; };
   auto take = [&](int32_t i, R v) {
     MinState<R> one;
     one.m = v;
     one.m2 = rinf<R>();
     one.s = R(0);
-    one.a = i;
+    one.a = place(i);
     st = ms_combine<R, SOFT>(st, one, T);
   };
   constexpr int LONG_BATCH = SOFT ? 2 : 4;   // loads in flight together
@@ -1046,7 +1051,7 @@ __device__ double long_rows(const SweepArgs& A, const R* src, const R* __restric
         } else {
           if (MODE == MODE_UPDATE) dst[c0 + uint32_t(i)] = fma_r<R>(-omega, M, lam);
           if (MODE == MODE_EVAL) dst[c0 + uint32_t(i)] = M;
-          if (MODE == MODE_SUBGRAD) A.gsub[c0 + uint32_t(i)] = uint8_t(i == st.a ? 1 : 0);
+          if (MODE == MODE_SUBGRAD) A.gsub[c0 + uint32_t(i)] = uint8_t(place(i) == st.a ? 1 : 0);
         }
       };
 #pragma unroll
@@ -1110,7 +1115,8 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
   const int32_t x = int32_t(blockIdx.x % 8u), k0 = int32_t(blockIdx.x / 8u);
   if constexpr (!SOFT) {
     // Every XCD takes a contiguous eighth of each kind of rows, the heavier
-    // kinds first; Y projection rows span all variables and are dealt in turn.
+    // kinds first.  (Y projection rows too: they span all variables, but
+    // neighbouring rows need neighbouring ones of them.)
     const R gam = A.gamma ? R(*A.gamma) : R(0);
     const int wave = threadIdx.x >> 6;
     double part = 0.0;
@@ -1118,7 +1124,7 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
     if (k < A.per[0] + A.per[1]) {
       const bool yrow = k < A.per[0];
       const int32_t rpb = 4 / A.long_wpr;
-      const int32_t item = yrow ? k * 8 + x : x * A.per[1] + (k - A.per[0]);
+      const int32_t item = yrow ? x * A.per[0] + k : x * A.per[1] + (k - A.per[0]);
       const int32_t r = item * rpb + wave / A.long_wpr;
       const int32_t lr = yrow ? r : A.n_long_y + r;
       part = long_rows<R, false, MODE>(A, rin, t, out, omega, T, gam, lr, lr < (yrow ? A.n_long_y : A.n_long));
@@ -1490,6 +1496,7 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
   A.chunk_b = ctx->chunk_b.p;
   A.n_long_y = ctx->n_long_y;
   A.n_entries_short = int32_t(ctx->nnz_short);
+  A.long_ent = ctx->long_ent.p;
   hard_blocks(ctx, A.per);
   if (ext) {
     A.dir = ext->dir;
