@@ -154,8 +154,8 @@ struct MeshDev {
 // Cell word (hard sweep): [31:29] number of rows the variable lies in (1 to 5),
 // [26:0] variable in variable order; CHUNK_PAD marks padding.
 constexpr int CELL_DEG_SHIFT = 29;
-constexpr int TILE_NARROW = 5;   // entries of each sign a row of a narrow / wide tile holds
-constexpr int TILE_WIDE = 8;
+constexpr int TILE_FORMS = 3;
+constexpr int TILE_HALF[TILE_FORMS] = {3, 5, 8};   // entries of each sign a row of a tile of each form holds
 
 // Reduced-problem entry word: [31] coefficient is -1, [30] unused, [29:27]
 // slot of the entry in its variable's record, [26:0] variable.
@@ -167,6 +167,8 @@ constexpr int REC_COST = 5;
 constexpr int REC_RDEG = 6;
 constexpr int MAX_SHORT_ROW = 64;
 constexpr int SOFT_MAX_ROW = 24;
+constexpr int64_t SMALL_LDS = 150 * 1024;   // the one-workgroup form: at most so many bytes of state
+constexpr int64_t SMALL_NNZ = 5000;         // and entries
 constexpr uint32_t CHUNK_PAD = 0xFFFFFFFFu;   // cell word of an unused cell
 
 // Multipliers of free variable i from its record (slots 0-4 hold s_k, slot 5
@@ -329,12 +331,12 @@ struct dm_ctx {
   DArr<unsigned long long> chunk_mask;  // per chunk: bit e set when entry e starts a row
   DArr<unsigned long long> chunk_neg;   // per chunk: bit e set when entry e has coefficient -1
   DArr<int8_t> chunk_b;       // 64 per chunk: right-hand side of each entry's row
-  // launch layout of the hard sweep (layout.hip): cells in row order (narrow
-  // tiles, wide tiles, chunks, projection rows, then one zero cell), variables
+  // launch layout of the hard sweep (layout.hip): cells in row order (tiles
+  // by form, chunks, projection rows, then one zero cell), variables
   // in mesh order
   int64_t n_cells = 0;        // without the zero cell, whose index it is
-  int32_t n_tiles[2] = {0, 0};   // narrow and wide 64-row tiles of short rows with b = 0
-  int64_t wide_cell0 = 0, chunk_cell0 = 0, long_cell0 = 0;
+  int32_t n_tiles[TILE_FORMS] = {0, 0, 0};   // 64-row tiles of short rows with b = 0, by form
+  int64_t tile_cell0[TILE_FORMS] = {0, 0, 0}, chunk_cell0 = 0, long_cell0 = 0;
   DArr<uint32_t> cell_word;   // n_cells
   DArr<uint32_t> ent_cell;    // nnz: cell of every entry of the reduced rows
   DArr<uint32_t> vpos;        // 5 planes of n_free: cell of slot k of variable v at k * n_free + v
@@ -384,6 +386,7 @@ struct dm_ctx {
   bool timing_open = false;   // a start event waits for its row pass
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
+  int64_t ev_sweeps = 0;      // sweeps the recorded events span
 
   // quasi-Newton session kept between dm_lbfgs_solve calls (history, step
   // size, Delta_min), owned by lbfgs.hip; invalidated when the costs or the
@@ -457,6 +460,8 @@ dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool time
 template <typename R>
 dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
                      const SweepExt* ext);
+template <typename R>
+dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, double* trace);
 template <typename R>
 dm_status cells_export(dm_ctx* ctx, const R* cells, const R* t, R* lam);
 // smoothed sweep on records

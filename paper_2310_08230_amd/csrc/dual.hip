@@ -266,14 +266,14 @@ __device__ inline void reduce_partials(const double* partial, int n, double offs
 struct SweepArgs {
   // ---- hard minimum: cells
   const uint32_t* word;     // per cell: variable and row count, CHUNK_PAD for padding
-  int32_t n_tiles[2];       // narrow and wide 64-row tiles
-  uint32_t wide_cell0, chunk_cell0, long_cell0;   // first cells (narrow tiles start at 0)
+  int32_t n_tiles[TILE_FORMS];   // 64-row tiles of each form
+  uint32_t tile_cell0[TILE_FORMS], chunk_cell0, long_cell0;   // first cells
   int32_t n_chunks;         // wave chunks of short rows
   const unsigned long long* chunk_mask;   // bit e: entry e of the chunk starts a row
   const unsigned long long* chunk_neg;    // bit e: entry e has coefficient -1
   const int8_t* chunk_b;    // 64 per chunk: right-hand side of the entry's row
   int32_t n_long_y;         // of the projection rows in launch order, the Y rows come first
-  int32_t per[5];           // blocks per XCD: Y rows, X rows, chunks, wide tiles, narrow tiles
+  int32_t per[3 + TILE_FORMS];   // blocks per XCD: Y rows, X rows, chunks, tiles from the widest form down
   int32_t n_entries_short;  // entries of the short rows
   const int32_t* long_ent;  // entry of each projection-row cell (ties in MODE_SUBGRAD), or NULL: in order
   // quasi-Newton extensions: rows see lambda + gamma * dir when dir is set
@@ -592,11 +592,11 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* cells, co
 
 // the four waves of a block take four adjacent chunks
 template <typename R, int MODE>
-__device__ double chunk_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega, R gam,
+__device__ __forceinline__ double chunk_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega, R gam,
                               unsigned char* smem, int32_t item) {
   const int wave = threadIdx.x >> 6;
   R* wave_vals = reinterpret_cast<R*>(smem) + wave * 192;   // three 64-value slices per wave
-  return short_chunk_hard<R, MODE>(A, cells, t, out, omega, gam, item * 4 + wave, wave_vals);
+  [[clang::always_inline]] return short_chunk_hard<R, MODE>(A, cells, t, out, omega, gam, item * 4 + wave, wave_vals);
 }
 
 // ---------------------------------------------------------------- short rows with b = 0, one lane per row
@@ -611,10 +611,10 @@ __device__ double chunk_block(const SweepArgs& A, const R* cells, const R* __res
 // d = count - rank decides whether an entry is taken (d > 0).  A missing entry
 // holds +inf: it is never taken, never ranked before a value and never pairs
 // to a negative sum.
-// Two widths, because the cells of a tile are streamed whether they are used
-// or not and the comparisons grow with the square of the width: 77 % of the
-// rows of the 2000/3000-face pair have at most TILE_NARROW = 5 entries of each
-// sign, 99.4 % at most TILE_WIDE = 8; the mean is 9.7 entries in 11.4 cells.
+// Several widths, because the cells of a tile are streamed whether they are
+// used or not and the comparisons grow with the square of the width: 76 % of
+// the rows of the 2000/3000-face pair have at most 5 entries of each sign,
+// 99.4 % at most 8; of the small pairs that the exact search meets, most have 3.
 template <typename R>
 struct Pair2;
 template <>
@@ -734,6 +734,19 @@ __device__ inline double tile_rows(const SweepArgs& A, const R* cells, const R* 
     }
   }
   return rowmin;
+}
+
+// the four waves of a block take four adjacent tiles of one form
+template <typename R, int MODE, int FORM>
+__device__ __forceinline__ double tile_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega,
+                                    R gam, int32_t item) {
+  constexpr int H = TILE_HALF[FORM];
+  const int32_t tile = item * 4 + int32_t(threadIdx.x >> 6);
+  if (tile >= A.n_tiles[FORM]) return 0.0;   // uniform across the wave
+  // inlined here whatever else calls it: as a function it costs the sweep 40
+  // registers and 6 % of its time
+  [[clang::always_inline]] return tile_rows<R, MODE, H>(A, cells, t, out, omega, gam,
+                                                         A.tile_cell0[FORM] + uint32_t(tile) * (128u * H));
 }
 
 // ---------------------------------------------------------------- short rows, soft min
@@ -925,7 +938,7 @@ constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD
 // lane reads its own cells before it writes them).  Smoothed: src and dst are
 // records.  Returns the row minimum on one lane of the row.
 template <typename R, bool SOFT, int MODE>
-__device__ double long_rows(const SweepArgs& A, const R* src, const R* __restrict__ t, R* dst, R omega, R T, R gam,
+__device__ __forceinline__ double long_rows(const SweepArgs& A, const R* src, const R* __restrict__ t, R* dst, R omega, R T, R gam,
                             int32_t lr, bool has) {
   __shared__ R xm[4], xm2[4], xs[4];
   __shared__ int32_t xa[4];
@@ -1131,14 +1144,11 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
     } else if ((k -= A.per[0] + A.per[1]) < A.per[2]) {
       part = chunk_block<R, MODE>(A, rin, t, out, omega, gam, smem, x * A.per[2] + k);
     } else if ((k -= A.per[2]) < A.per[3]) {
-      const int32_t tile = (x * A.per[3] + k) * 4 + wave;
-      if (tile < A.n_tiles[1])   // uniform across the wave
-        part = tile_rows<R, MODE, TILE_WIDE>(A, rin, t, out, omega, gam,
-                                             A.wide_cell0 + uint32_t(tile) * (128u * TILE_WIDE));
+      part = tile_block<R, MODE, 2>(A, rin, t, out, omega, gam, x * A.per[3] + k);
+    } else if ((k -= A.per[3]) < A.per[4]) {
+      part = tile_block<R, MODE, 1>(A, rin, t, out, omega, gam, x * A.per[4] + k);
     } else {
-      const int32_t tile = (x * A.per[4] + (k - A.per[3])) * 4 + wave;
-      if (tile < A.n_tiles[0])
-        part = tile_rows<R, MODE, TILE_NARROW>(A, rin, t, out, omega, gam, uint32_t(tile) * (128u * TILE_NARROW));
+      part = tile_block<R, MODE, 0>(A, rin, t, out, omega, gam, x * A.per[5] + (k - A.per[4]));
     }
     store_partial(block_sum(part, red), A.partial, int32_t(blockIdx.x));
   } else {
@@ -1174,6 +1184,142 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
       store_partial(block_sum(part, red), A.partial, item);
     }
   }
+}
+
+// ---------------------------------------------------------------- small problems: one workgroup
+// A problem whose cells and residuals fit one CU's LDS runs all its iterations
+// in one launch of one workgroup: the two passes alternate between barriers
+// (some 0.1 us) instead of launches (2.4 to 3 us each, which is nearly all of a
+// small problem's iteration).  The values are those of the two-launch form; the
+// bound sums the waves' row minima in wave order.
+// Exactly-one rows take a group of 4, 16 or 64 lanes each, a quarter of their
+// mean length, so that a lane holds about four entries of its row.
+// As many waves as their registers leave room for without spilling.
+template <typename R>
+constexpr int SMALL_THREADS = sizeof(R) == 4 ? 768 : 512;
+constexpr int SMALL_LREG = 4;
+
+template <typename R, int NT>
+__global__ __launch_bounds__(NT) void k_small(SweepArgs A, const uint32_t* __restrict__ vpos, R* gcells,
+                                              const R* __restrict__ cost, int32_t n, uint32_t n_cells, int32_t iters,
+                                              R omega, double offset, int32_t group, double* trace) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  A.dir = nullptr;   // a constant from here on
+  __shared__ double part[2][NT / 64];
+  R* cells = reinterpret_cast<R*>(lds);
+  R* t = cells + n_cells + 1;
+  R* wave_vals = t + n + (threadIdx.x >> 6) * 192;   // chunks only
+  constexpr int NW = NT / 64;
+  const int tid = int(threadIdx.x), wave = tid >> 6, lane = tid & 63;
+  for (uint32_t c = uint32_t(tid); c <= n_cells; c += NT) cells[c] = gcells[c];
+  // the first two variables of every thread keep their cell indices in registers
+  constexpr int KEEP = sizeof(R) == 4 ? 2 : 1;
+  uint32_t kp[KEEP][5];
+  R kc[KEEP];
+#pragma unroll
+  for (int u = 0; u < KEEP; ++u) {
+    const int32_t v = tid + u * NT;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) kp[u][q] = v < n ? vpos[size_t(q) * n + v] : n_cells;
+    kc[u] = v < n ? cost[v] : R(0);
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int32_t it = 0; it < iters; ++it) {
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u) {
+      const int32_t v = tid + u * NT;
+      R s[5];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) s[q] = cells[kp[u][q]];
+      if (v < n) t[v] = kc[u] - ((((s[0] + s[1]) + s[2]) + s[3]) + s[4]);
+    }
+    for (int32_t v = tid + KEEP * NT; v < n; v += NT) {
+      R s[5];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) s[q] = cells[vpos[size_t(q) * n + v]];
+      t[v] = cost[v] - ((((s[0] + s[1]) + s[2]) + s[3]) + s[4]);
+    }
+    __syncthreads();
+    double sum = 0.0;
+    int32_t w0 = wave;   // the waves take the items of all kinds in turn
+#pragma unroll 1
+    for (; w0 < A.n_tiles[2]; w0 += NW)
+      sum += tile_rows<R, MODE_UPDATE, TILE_HALF[2]>(A, cells, t, cells, omega, R(0),
+                                                     A.tile_cell0[2] + uint32_t(w0) * (128u * TILE_HALF[2]));
+    w0 -= A.n_tiles[2];
+#pragma unroll 1
+    for (; w0 < A.n_chunks; w0 += NW)
+      sum += short_chunk_hard<R, MODE_UPDATE>(A, cells, t, cells, omega, R(0), w0, wave_vals);
+    w0 -= A.n_chunks;
+#pragma unroll 1
+    for (; w0 < A.n_tiles[1]; w0 += NW)
+      sum += tile_rows<R, MODE_UPDATE, TILE_HALF[1]>(A, cells, t, cells, omega, R(0),
+                                                     A.tile_cell0[1] + uint32_t(w0) * (128u * TILE_HALF[1]));
+    w0 -= A.n_tiles[1];
+#pragma unroll 1
+    for (; w0 < A.n_tiles[0]; w0 += NW)
+      sum += tile_rows<R, MODE_UPDATE, TILE_HALF[0]>(A, cells, t, cells, omega, R(0),
+                                                     A.tile_cell0[0] + uint32_t(w0) * (128u * TILE_HALF[0]));
+    w0 -= A.n_tiles[0];
+    const int32_t rpw = 64 / group;
+#pragma unroll 1
+    for (; w0 * rpw < A.n_long; w0 += NW) {
+      const int32_t lr = w0 * rpw + lane / group, i0 = lane & (group - 1);
+      const bool has = lr < A.n_long;
+      const int32_t s0 = has ? A.rrow_ptr[A.n_short + lr] : 0;
+      const int32_t len = has ? A.rrow_ptr[A.n_short + lr + 1] - s0 : 0;
+      const uint32_t c0 = A.long_cell0 + uint32_t(has ? s0 - A.n_entries_short : 0);
+      auto value = [&](int32_t i) { return cell_lambda<R>(A, cells, t, c0 + uint32_t(i), A.word[c0 + uint32_t(i)], R(0)); };
+      R lv[SMALL_LREG];
+      MinState<R> st;
+      st.m = st.m2 = rinf<R>();
+      st.s = R(0);
+      st.a = INT32_MAX;
+      auto take = [&](int32_t i, R v) {
+        MinState<R> one;
+        one.m = v;
+        one.m2 = rinf<R>();
+        one.s = R(0);
+        one.a = i;
+        st = ms_combine<R, false>(st, one, R(0));
+      };
+#pragma unroll
+      for (int u = 0; u < SMALL_LREG; ++u) {
+        const int32_t i = i0 + u * group;
+        lv[u] = i < len ? value(i) : rinf<R>();
+      }
+#pragma unroll
+      for (int u = 0; u < SMALL_LREG; ++u) {
+        const int32_t i = i0 + u * group;
+        if (i < len) take(i, lv[u]);
+      }
+      for (int32_t i = i0 + SMALL_LREG * group; i < len; i += group) take(i, value(i));
+      for (int off = group / 2; off > 0; off >>= 1) st = ms_combine<R, false>(st, ms_shfl_xor<R, false>(st, off), R(0));
+      auto finish = [&](int32_t i, R v) {
+        cells[c0 + uint32_t(i)] = fma_r<R>(-omega, v - (i == st.a ? st.m2 : st.m), v);
+      };
+#pragma unroll
+      for (int u = 0; u < SMALL_LREG; ++u) {
+        const int32_t i = i0 + u * group;
+        if (i < len) finish(i, lv[u]);
+      }
+      for (int32_t i = i0 + SMALL_LREG * group; i < len; i += group) finish(i, value(i));
+      if (has && i0 == 0) sum += double(st.m);
+    }
+    if (trace) {
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+      if (lane == 0) part[it & 1][wave] = sum;
+    }
+    __syncthreads();
+    if (trace && tid == 0) {
+      double b = part[it & 1][0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) b += part[it & 1][w];
+      trace[it] = offset + b;
+    }
+  }
+  for (uint32_t c = uint32_t(tid); c < n_cells; c += NT) gcells[c] = cells[c];
 }
 
 // ---------------------------------------------------------------- state import / export (records)
@@ -1252,20 +1398,21 @@ __global__ __launch_bounds__(256) void k_reduce_last(const double* partial, int 
 // host side (shared with rounding, the quasi-Newton layer and the backward pass)
 // ============================================================================
 // blocks per XCD of each kind of rows of the hard sweep, in launch order
-static void hard_blocks(const dm_ctx* ctx, int32_t per[5]) {
+static void hard_blocks(const dm_ctx* ctx, int32_t per[3 + TILE_FORMS]) {
   const int64_t n_long = ctx->n_rows - ctx->n_short, rpb = 4 / ctx->long_wpr;
   const auto xcd = [](int64_t items) { return int32_t((items + 7) / 8); };
   per[0] = xcd((ctx->n_long_y + rpb - 1) / rpb);
   per[1] = xcd((n_long - ctx->n_long_y + rpb - 1) / rpb);
   per[2] = xcd((ctx->n_chunks + 3) / 4);
-  per[3] = xcd((ctx->n_tiles[1] + 3) / 4);
-  per[4] = xcd((ctx->n_tiles[0] + 3) / 4);
+  for (int f = 0; f < TILE_FORMS; ++f) per[3 + f] = xcd((ctx->n_tiles[TILE_FORMS - 1 - f] + 3) / 4);
 }
 
 static int64_t hard_grid(const dm_ctx* ctx) {
-  int32_t per[5];
+  int32_t per[3 + TILE_FORMS];
   hard_blocks(ctx, per);
-  return 8 * (int64_t(per[0]) + per[1] + per[2] + per[3] + per[4]);
+  int64_t n = 0;
+  for (int32_t p : per) n += p;
+  return 8 * n;
 }
 
 static int64_t soft_short_blocks(const dm_ctx* ctx) {
@@ -1415,7 +1562,7 @@ static void pend(dm_ctx* ctx, double* mine, int64_t n, double* bound_out) {
 
 // timing: a start event for the first kernel of a sweep, a stop event for its
 // last (the runtime records the kernels' own start and end)
-static dm_status timing_events(dm_ctx* ctx, hipEvent_t* e0, hipEvent_t* e1) {
+static dm_status timing_events(dm_ctx* ctx, hipEvent_t* e0, hipEvent_t* e1, int64_t sweeps = 1) {
   while (ctx->ev_pool.size() < ctx->ev_used + 2) {
     hipEvent_t e;
     DM_HIP(ctx, hipEventCreate(&e));
@@ -1425,6 +1572,7 @@ static dm_status timing_events(dm_ctx* ctx, hipEvent_t* e0, hipEvent_t* e1) {
   if (e1) {
     *e1 = ctx->ev_pool[ctx->ev_used + 1];
     ctx->ev_used += 2;
+    ctx->ev_sweeps += sweeps;
   }
   return DM_OK;
 }
@@ -1477,17 +1625,13 @@ static dm_status empty_sweep(dm_ctx* ctx, double* bound_out) {
   return DM_OK;
 }
 
-// one hard row pass: mode update cells -> out (which may be cells itself),
-// write M per cell to out, bound only, or the minimising assignment to
-// ext->gsub; the bound goes to *bound_out (device)
-template <typename R>
-dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
-                     const SweepExt* ext) {
-  SweepArgs A;
+static void hard_args(const dm_ctx* ctx, SweepArgs& A) {
   common_args(ctx, A);
   A.word = ctx->cell_word.p;
-  for (int f = 0; f < 2; ++f) A.n_tiles[f] = ctx->n_tiles[f];
-  A.wide_cell0 = uint32_t(ctx->wide_cell0);
+  for (int f = 0; f < TILE_FORMS; ++f) {
+    A.n_tiles[f] = ctx->n_tiles[f];
+    A.tile_cell0[f] = uint32_t(ctx->tile_cell0[f]);
+  }
   A.chunk_cell0 = uint32_t(ctx->chunk_cell0);
   A.long_cell0 = uint32_t(ctx->long_cell0);
   A.n_chunks = ctx->n_chunks;
@@ -1498,6 +1642,16 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
   A.n_entries_short = int32_t(ctx->nnz_short);
   A.long_ent = ctx->long_ent.p;
   hard_blocks(ctx, A.per);
+}
+
+// one hard row pass: mode update cells -> out (which may be cells itself),
+// write M per cell to out, bound only, or the minimising assignment to
+// ext->gsub; the bound goes to *bound_out (device)
+template <typename R>
+dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
+                     const SweepExt* ext) {
+  SweepArgs A;
+  hard_args(ctx, A);
   if (ext) {
     A.dir = ext->dir;
     A.gamma = ext->gamma;
@@ -1521,6 +1675,52 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
   else launch_sweep<R, false, MODE_SUBGRAD>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
   DM_LAUNCH_CHECK(ctx);
   pend(ctx, mine, grid, bound_out);
+  return DM_OK;
+}
+
+// LDS of the one-workgroup form, 0 where it does not apply.  One CU takes about
+// 1 us an iteration for every thousand entries on top of 2.4, the two launches
+// 7.1 to 7.5 us at any small size (measured, FP32 and FP64: 989 entries 3.7 and
+// 4.0 against 7.3 and 7.5 us, 2946 4.4 and 6.7 against 7.1 and 7.5, 7695 7.4 and
+// 9.1 against 7.3 and 7.5), so the line lies at SMALL_NNZ entries.
+template <typename R>
+static size_t small_lds(const dm_ctx* ctx) {
+  constexpr int64_t NW = SMALL_THREADS<R> / 64;
+  const int64_t reals = ctx->n_cells + 1 + ctx->n_free + (ctx->n_chunks > 0 ? NW * 192 : 0);
+  return ctx->nnz <= SMALL_NNZ && reals * int64_t(sizeof(R)) <= SMALL_LDS ? size_t(reals) * sizeof(R) : 0;
+}
+
+// iters hard iterations in place on S (their t is left to the next cells_vars);
+// the bounds go to trace (device, may be NULL)
+template <typename R>
+dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, double* trace) {
+  R *cells = S.cells<R>(0), *t = S.ts<R>(0);
+  const size_t lds = small_lds<R>(ctx);
+  if (lds > 0 && iters > 0 && hard_grid(ctx) > 0) {
+    DM_TRY(dual_flush(ctx));
+    SweepArgs A;
+    hard_args(ctx, A);
+    constexpr int NT = SMALL_THREADS<R>;
+    const int64_t n_long = ctx->n_rows - ctx->n_short, mean = (ctx->nnz - ctx->nnz_short) / std::max<int64_t>(n_long, 1);
+    const int32_t group = mean <= 16 ? 4 : (mean <= 64 ? 16 : 64);
+    if (lds > 48 * 1024)
+      DM_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small<R, NT>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1, iters));
+    if (e0)
+      hipExtLaunchKernelGGL((k_small<R, NT>), dim3(1), dim3(NT), lds, ctx->stream, e0, e1, 0, A, ctx->vpos.p, cells,
+                            S.costs<R>(), int32_t(ctx->n_free), uint32_t(ctx->n_cells), iters, omega, ctx->offset, group, trace);
+    else
+      k_small<R, NT><<<1, NT, lds, ctx->stream>>>(A, ctx->vpos.p, cells, S.costs<R>(), int32_t(ctx->n_free),
+                                                  uint32_t(ctx->n_cells), iters, omega, ctx->offset, group, trace);
+    DM_LAUNCH_CHECK(ctx);
+    return DM_OK;
+  }
+  for (int32_t k = 0; k < iters; ++k) {
+    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
+    DM_TRY(cells_rows<R>(ctx, MODE_UPDATE, cells, t, cells, omega, trace ? trace + k : nullptr, nullptr));
+  }
   return DM_OK;
 }
 
@@ -1592,9 +1792,10 @@ extern "C" dm_status dm_timing_read(dm_ctx* ctx, int64_t* launches, double* tota
     DM_HIP(ctx, hipEventElapsedTime(&ms, ctx->ev_pool[i], ctx->ev_pool[i + 1]));
     tot += ms;
   }
-  *launches = int64_t(ctx->ev_used / 2);
+  *launches = ctx->ev_sweeps;
   *total_ms = tot;
   ctx->ev_used = 0;
+  ctx->ev_sweeps = 0;
   return DM_OK;
 }
 
@@ -1604,6 +1805,7 @@ extern "C" dm_status dm_timing_read(dm_ctx* ctx, int64_t* launches, double* tota
   template dm_status cells_export<R>(dm_ctx*, const R*, const R*, R*);                                                \
   template dm_status cells_vars<R>(dm_ctx*, const R*, const R*, R*, bool);                                            \
   template dm_status cells_rows<R>(dm_ctx*, int, const R*, const R*, R*, R, double*, const SweepExt*);                \
+  template dm_status cells_iterate<R>(dm_ctx*, CellState&, int32_t, R, double*);                                     \
   template dm_status soft_sweep<R>(dm_ctx*, int, const unsigned char*, unsigned char*, R, R, double*);
 DM_INSTANTIATE(float)
 DM_INSTANTIATE(double)
@@ -1631,10 +1833,7 @@ static dm_status solve_impl(dm_ctx* ctx, int32_t iters, R omega, R T, R* lam, do
   CellState& S = ctx->cells;
   DM_TRY(cells_import<R>(ctx, lam, S, false));
   R *cells = S.cells<R>(0), *t = S.ts<R>(0);
-  for (int32_t k = 0; k < iters; ++k) {
-    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
-    DM_TRY(cells_rows<R>(ctx, MODE_UPDATE, cells, t, cells, omega, trace ? trace + k : nullptr, nullptr));
-  }
+  DM_TRY(cells_iterate<R>(ctx, S, iters, omega, trace));
   DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, false));   // also sums the last bound
   return cells_export<R>(ctx, cells, t, lam);
 }

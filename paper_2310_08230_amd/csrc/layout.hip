@@ -149,16 +149,16 @@ __global__ void k_unused_slots(const uint8_t* vdeg, int64_t n, uint32_t zero_cel
 constexpr int ROW_BATCH = 8;
 
 // Short rows: sort key (form, smallest X rank, smallest Y rank), sorted stably
-// so that equal keys keep the row order.  Forms: 0 and 1 are the narrow and
-// the wide tile (right-hand side 0 and at most TILE_NARROW or TILE_WIDE
-// entries of each sign), 2 the chunks.  count: rows of form 0, of form 1,
-// entries of both.
+// so that equal keys keep the row order.  Forms: 0 to 2 are the tiles
+// (right-hand side 0 and at most TILE_HALF entries of each sign, the narrowest
+// from form0 on), 3 the chunks.  count: rows of each tile form, entries of all
+// of them.
 __global__ __launch_bounds__(256) void k_short_keys(const int32_t* rrow_ptr, const int32_t* rrow_b,
                                                     const uint32_t* word, const uint32_t* vkey, int64_t n_short,
-                                                    int ybits, int ydrop, int kbits, uint32_t* key, int32_t* val,
-                                                    int32_t* count) {
-  __shared__ int32_t sh[3];
-  if (threadIdx.x < 3) sh[threadIdx.x] = 0;
+                                                    int ybits, int ydrop, int kbits, uint32_t form0, uint32_t* key,
+                                                    int32_t* val, int32_t* count) {
+  __shared__ int32_t sh[TILE_FORMS + 1];
+  if (threadIdx.x <= TILE_FORMS) sh[threadIdx.x] = 0;
   __syncthreads();
   const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (j < n_short) {
@@ -180,16 +180,19 @@ __global__ __launch_bounds__(256) void k_short_keys(const int32_t* rrow_ptr, con
       }
     }
     const int32_t m = max(nq, (t - s) - nq);
-    const uint32_t form = rrow_b[j] != 0 || m > TILE_WIDE ? 2u : (m > TILE_NARROW ? 1u : 0u);
-    key[j] = (form << kbits) | (x << (ybits - ydrop)) | (y >> ydrop);
+    uint32_t form = rrow_b[j] != 0 ? uint32_t(TILE_FORMS) : form0;
+    while (form < TILE_FORMS && m > TILE_HALF[form]) ++form;
+    // chunks by the X rank alone: which rows share a chunk decides which of two
+    // forms of the same minimum sweeps them
+    key[j] = (form << kbits) | (x << (ybits - ydrop)) | (form < TILE_FORMS ? y >> ydrop : 0u);
     val[j] = int32_t(j);
-    if (form < 2) {
+    if (form < TILE_FORMS) {
       atomicAdd(&sh[form], 1);
-      atomicAdd(&sh[2], t - s);
+      atomicAdd(&sh[TILE_FORMS], t - s);
     }
   }
   __syncthreads();
-  if (threadIdx.x < 3 && sh[threadIdx.x]) atomicAdd(&count[threadIdx.x], sh[threadIdx.x]);
+  if (threadIdx.x <= TILE_FORMS && sh[threadIdx.x]) atomicAdd(&count[threadIdx.x], sh[threadIdx.x]);
 }
 
 __device__ inline uint32_t cell_word_of(uint32_t w, const int32_t* vinv, const uint8_t* deg, int32_t* v) {
@@ -502,11 +505,17 @@ dm_status sweep_layout(dm_ctx* ctx) {
   DM_ALLOC(ctx, perm, size_t(std::max<int64_t>(nshort, 1)));
   DM_ALLOC(ctx, lkey, size_t(std::max<int64_t>(nlong, 1)));
   DM_ALLOC(ctx, ctx->long_perm, size_t(std::max<int64_t>(nlong, 1)));
-  DM_ALLOC(ctx, count, 4);
-  DM_HIP(ctx, hipMemsetAsync(count.p, 0, 4 * sizeof(int32_t), st));
+  constexpr int NC = TILE_FORMS + 2;
+  DM_ALLOC(ctx, count, NC);
+  DM_HIP(ctx, hipMemsetAsync(count.p, 0, NC * sizeof(int32_t), st));
   if (nshort > 0) {
+    // the narrowest tiles only where one workgroup sweeps the problem from LDS
+    // and its arithmetic counts: rows of one place spread over more tiles cost
+    // the variable pass cache lines (2000/3000-face pair 110 us an iteration
+    // without them, 117 with; 1000 faces 22.7 and 23.3)
+    const uint32_t form0 = rnnz <= SMALL_NNZ ? 0u : 1u;
     k_short_keys<<<grid_for(nshort, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rrow_b.p, ctx->rent_word.p, vkey.p,
-                                                        nshort, ybits, ydrop, kbits, skey.p, perm.p, count.p);
+                                                        nshort, ybits, ydrop, kbits, form0, skey.p, perm.p, count.p);
     DM_LAUNCH_CHECK(ctx);
     DM_TRY(sort_pairs_u32(ctx, skey.p, perm.p, size_t(nshort), kbits + 2));
   }
@@ -515,23 +524,26 @@ dm_status sweep_layout(dm_ctx* ctx) {
     const int64_t first_y_full = mesh ? ctx->n_closed_full + ctx->X.nf : INT64_MAX;
     k_long_keys<<<grid_for(nlong, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rrow_orig.p, ctx->rent_word.p, vkey.p,
                                                       nshort, nlong, first_y_full, ybits, lbits, lkey.p,
-                                                      ctx->long_perm.p, count.p + 3);
+                                                      ctx->long_perm.p, count.p + TILE_FORMS + 1);
     DM_LAUNCH_CHECK(ctx);
     DM_TRY(sort_pairs_u32(ctx, lkey.p, ctx->long_perm.p, size_t(nlong), lbits + 1));
   }
-  int32_t cnt[4];
+  int32_t cnt[NC];
   {
-    const int32_t* src[4] = {count.p, count.p + 1, count.p + 2, count.p + 3};
-    DM_TRY(read_i32s(ctx, 4, src, cnt));
+    const int32_t* src[NC];
+    for (int k = 0; k < NC; ++k) src[k] = count.p + k;
+    DM_TRY(read_i32s(ctx, NC, src, cnt));
   }
-  const int32_t n_tile_rows[2] = {cnt[0], cnt[1]};
-  const int32_t nnz_chunk = int32_t(ctx->nnz_short) - cnt[2];   // entries of the short rows left to the chunks
-  ctx->n_long_y = cnt[3];
+  const int32_t* n_tile_rows = cnt;
+  const int32_t nnz_chunk = int32_t(ctx->nnz_short) - cnt[TILE_FORMS];   // entries of the short rows left to the chunks
+  ctx->n_long_y = cnt[TILE_FORMS + 1];
   ctx->long_wpr = (nlong > 0 && (rnnz - ctx->nnz_short) / nlong > LONG_BLOCK_ROW) ? 4 : 1;
 
   // ---- the chunks: the remaining short rows in key order, packed greedily
-  const int64_t nchr = nshort - n_tile_rows[0] - n_tile_rows[1];
-  const int32_t* cperm = perm.p + n_tile_rows[0] + n_tile_rows[1];
+  int32_t form_row0[TILE_FORMS + 1] = {0};   // first row of each form in perm
+  for (int f = 0; f < TILE_FORMS; ++f) form_row0[f + 1] = form_row0[f] + n_tile_rows[f];
+  const int64_t nchr = nshort - form_row0[TILE_FORMS];
+  const int32_t* cperm = perm.p + form_row0[TILE_FORMS];
   DArr<int32_t> plen, prow_ptr, pb, pent;
   int32_t n_chunks = 0;
   if (nchr > 0) {
@@ -567,15 +579,17 @@ dm_status sweep_layout(dm_ctx* ctx) {
     DM_LAUNCH_CHECK(ctx);
   }
 
-  // ---- cells: narrow tiles, wide tiles, chunks, projection rows, the zero cell
+  // ---- cells: tiles by form, chunks, projection rows, the zero cell
   ctx->n_chunks = n_chunks;
-  for (int f = 0; f < 2; ++f) ctx->n_tiles[f] = (n_tile_rows[f] + 63) / 64;
-  const int64_t wide0 = int64_t(ctx->n_tiles[0]) * 128 * TILE_NARROW;
-  const int64_t chunk0 = wide0 + int64_t(ctx->n_tiles[1]) * 128 * TILE_WIDE;
+  int64_t chunk0 = 0;
+  for (int f = 0; f < TILE_FORMS; ++f) {
+    ctx->n_tiles[f] = (n_tile_rows[f] + 63) / 64;
+    ctx->tile_cell0[f] = chunk0;
+    chunk0 += int64_t(ctx->n_tiles[f]) * 128 * TILE_HALF[f];
+  }
   const int64_t long0 = chunk0 + int64_t(n_chunks) * 64;
   const int64_t ncell = long0 + (rnnz - ctx->nnz_short);
   if (ncell >= int64_t(CHUNK_PAD)) return dm_fail(ctx, DM_ERR_WORKSPACE, "sweep layout: too many cells");
-  ctx->wide_cell0 = wide0;
   ctx->chunk_cell0 = chunk0;
   ctx->long_cell0 = long0;
   ctx->n_cells = ncell;
@@ -585,12 +599,11 @@ dm_status sweep_layout(dm_ctx* ctx) {
   if (long0 > 0) DM_HIP(ctx, hipMemsetAsync(ctx->cell_word.p, 0xFF, sizeof(uint32_t) * size_t(long0), st));
   if (nfree > 0)
     k_unused_slots<<<grid_for(nfree, 256), 256, 0, st>>>(ctx->vdeg.p, nfree, uint32_t(ncell), ctx->vpos.p);
-  for (int f = 0; f < 2; ++f)
+  for (int f = 0; f < TILE_FORMS; ++f)
     if (n_tile_rows[f] > 0)
       k_tile_fill<<<grid_for(n_tile_rows[f], 256), 256, 0, st>>>(
-          perm.p + (f ? n_tile_rows[0] : 0), n_tile_rows[f], f ? TILE_WIDE : TILE_NARROW, uint32_t(f ? wide0 : 0),
-          ctx->rrow_ptr.p, ctx->rent_word.p, ctx->vinv.p, ctx->var_deg.p, nfree, ctx->cell_word.p, ctx->ent_cell.p,
-          ctx->vpos.p);
+          perm.p + form_row0[f], n_tile_rows[f], TILE_HALF[f], uint32_t(ctx->tile_cell0[f]), ctx->rrow_ptr.p,
+          ctx->rent_word.p, ctx->vinv.p, ctx->var_deg.p, nfree, ctx->cell_word.p, ctx->ent_cell.p, ctx->vpos.p);
   if (n_chunks > 0)
     k_chunk_fill<<<grid_for(n_chunks, 4), 256, 0, st>>>(ctx->chunk_desc.p, ctx->chunk_mask.p, pent.p, pb.p, n_chunks,
                                                         uint32_t(chunk0), ctx->rent_word.p, ctx->vinv.p,

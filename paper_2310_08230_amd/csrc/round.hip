@@ -185,10 +185,7 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
       k_perturb<R><<<grid_for(nfree, 256), 256, 0, st>>>(ctx->pref.p, ctx->vperm.p, nfree, delta, P.seed, uint32_t(r),
                                                         S.costs<R>());
     DM_LAUNCH_CHECK(ctx);
-    for (int32_t k = 0; k < P.iters_per_round; ++k) {
-      DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
-      DM_TRY(cells_rows<R>(ctx, SWEEP_UPDATE, cells, t, cells, R(P.omega), nullptr, nullptr));
-    }
+    DM_TRY(cells_iterate<R>(ctx, S, P.iters_per_round, R(P.omega), nullptr));
     delta *= P.gamma;
   }
   DM_TRY(sum_f64(ctx, ctx->cost64.p, ctx->nP, x, SUM_U8_NZ, ctx->scal.p + 1));

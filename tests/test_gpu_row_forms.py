@@ -3,7 +3,7 @@ lane per entry in chunks, projection rows, and variables in one to five rows.
 
 Generic 0-1 ILPs whose other rows all have one shape (p entries +1, q entries
 -1) on either side of the tile widths, in numbers that leave ragged 64-row
-tiles, against the FP64 oracle: multipliers and bounds after six Jacobi
+tiles and below and above the size that one workgroup takes, against the FP64 oracle: multipliers and bounds after six Jacobi
 iterations, the bound alone, and the row minimisers.  An iteration takes an
 entry through fewer than 100 roundings of values at most a few times the
 largest cost, so six leave at most 600 units in the last place, 2^-53 or 2^-24
@@ -57,7 +57,8 @@ def rows_of_one_shape(p, q, n_rows, b, seed):
 
 @pytest.mark.parametrize("p,q,n_rows,b", [(1, 1, 1, 0), (3, 3, 64, 0), (3, 4, 65, 0), (5, 2, 63, 0), (5, 5, 257, 0),
                                           (6, 5, 130, 0), (8, 8, 64, 0), (8, 9, 70, 0), (30, 30, 9, 0), (4, 4, 40, 1),
-                                          (3, 5, 40, -2), (2, 2, 3000, 0), (8, 7, 2100, 0)])
+                                          (3, 5, 40, -2), (3, 3, 800, 0), (3, 3, 560, 0),
+                                          (2, 2, 3000, 0), (8, 7, 2100, 0)])
 def test_rows_of_every_form_match_the_oracle(p, q, n_rows, b):
     n, ptr, cols, coefs, rhs, cost = rows_of_one_shape(p, q, n_rows, b, 1)
     S = O.Space.from_ilp(n, ptr, cols, coefs, rhs)
@@ -74,6 +75,12 @@ def test_rows_of_every_form_match_the_oracle(p, q, n_rows, b):
         rlam, rtr = S.dual_solve(6)
         assert np.abs(np_(lam) - rlam).max() <= tol * scale
         assert np.abs(np_(tr) - rtr).max() <= tol * scale * ctx.info["n_rows"]
+        again = ctx.dual_solve(ctx.init_lambda(prec), 6, trace=False)[0]
+        assert torch.equal(again, lam)
+        ctx.timing(True)
+        ctx.dual_solve(ctx.init_lambda(prec), 6)
+        assert ctx.timing_read()[0] == 6   # iterations, however they were launched
+        ctx.timing(False)
         assert abs(ctx.lower_bound(lam) - S.lower_bound(rlam)) <= tol * scale * ctx.info["n_rows"]
     g, _ = ctx.subgradient(ctx.init_lambda("fp64"))   # no two multipliers agree there
     assert np.array_equal(np_(g), S.subgradient(S.init_lambda()))
