@@ -46,7 +46,9 @@ extern "C" dm_status dm_create(int32_t device, void* hip_stream, dm_ctx** out) {
   c->cache.stream = c->stream;
   // pinned landing slots for small device-to-host reads
   if (hipHostMalloc(reinterpret_cast<void**>(&c->host_i32), HOST_SLOTS * sizeof(int32_t), hipHostMallocDefault) !=
-      hipSuccess) {
+          hipSuccess ||
+      hipEventCreateWithFlags(&c->landed, hipEventDisableTiming) != hipSuccess) {
+    if (c->host_i32) (void)hipHostFree(c->host_i32);
     delete c;
     (void)hipMemPoolDestroy(pool);
     return DM_ERR_HIP;
@@ -132,6 +134,13 @@ dm_status sort_pairs_u64(dm_ctx* ctx, uint64_t* keys, int32_t* vals, size_t n, i
   return sort_pairs_impl<uint64_t>(ctx, keys, vals, n, end_bit);
 }
 
+dm_status sort_pairs_k(dm_ctx* ctx, uint32_t* keys, int32_t* vals, size_t n, int end_bit) {
+  return sort_pairs_impl<uint32_t>(ctx, keys, vals, n, end_bit);
+}
+dm_status sort_pairs_k(dm_ctx* ctx, uint64_t* keys, int32_t* vals, size_t n, int end_bit) {
+  return sort_pairs_impl<uint64_t>(ctx, keys, vals, n, end_bit);
+}
+
 dm_status sort_pairs_u32(dm_ctx* ctx, uint32_t* keys, int32_t* vals, size_t n, int end_bit) {
   return sort_pairs_impl<uint32_t>(ctx, keys, vals, n, end_bit);
 }
@@ -180,49 +189,39 @@ dm_status sum_f64(dm_ctx* ctx, const double* a, int64_t n, const void* sel, int 
   return DM_OK;
 }
 
-__global__ void k_scan_tail(const int32_t* in_last, int32_t* out, size_t n, int is_u8,
-                            const uint8_t* u8_last) {
-  int32_t last = is_u8 ? int32_t(*u8_last) : *in_last;
-  out[n] = out[n - 1] + last;
-}
-
-struct U8ToI32 {
-  __host__ __device__ int32_t operator()(uint8_t v) const { return int32_t(v); }
+// input of a scan one longer than its array, with a zero at the end, so that
+// the exclusive scan's last value is the total
+template <typename T>
+struct PaddedInput {
+  const T* a;
+  size_t n;
+  __host__ __device__ int32_t operator()(size_t i) const { return i < n ? int32_t(a[i]) : 0; }
 };
 
-dm_status scan_i32(dm_ctx* ctx, const int32_t* in, int32_t* out, size_t n) {
-  if (n == 0) {
-    DM_HIP(ctx, hipMemsetAsync(out, 0, sizeof(int32_t), ctx->stream));
-    return DM_OK;
-  }
+template <typename T>
+static dm_status scan_impl(dm_ctx* ctx, const T* in, int32_t* out, size_t n) {
+  auto it = rocprim::make_transform_iterator(rocprim::make_counting_iterator(size_t(0)), PaddedInput<T>{in, n});
   size_t temp = 0;
-  DM_HIP(ctx, rocprim::exclusive_scan(nullptr, temp, in, out, int32_t(0), n,
-                                      rocprim::plus<int32_t>(), ctx->stream));
+  DM_HIP(ctx, rocprim::exclusive_scan(nullptr, temp, it, out, int32_t(0), n + 1, rocprim::plus<int32_t>(),
+                                      ctx->stream));
   DArr<unsigned char> tmp;
   DM_ALLOC(ctx, tmp, temp + 16);
-  DM_HIP(ctx, rocprim::exclusive_scan(tmp.p, temp, in, out, int32_t(0), n,
-                                      rocprim::plus<int32_t>(), ctx->stream));
-  k_scan_tail<<<1, 1, 0, ctx->stream>>>(in + n - 1, out, n, 0, nullptr);
-  DM_LAUNCH_CHECK(ctx);
+  DM_HIP(ctx, rocprim::exclusive_scan(tmp.p, temp, it, out, int32_t(0), n + 1, rocprim::plus<int32_t>(),
+                                      ctx->stream));
   return DM_OK;
 }
 
-dm_status scan_u8(dm_ctx* ctx, const uint8_t* in, int32_t* out, size_t n) {
-  if (n == 0) {
-    DM_HIP(ctx, hipMemsetAsync(out, 0, sizeof(int32_t), ctx->stream));
-    return DM_OK;
-  }
-  auto it = rocprim::make_transform_iterator(in, U8ToI32());
-  size_t temp = 0;
-  DM_HIP(ctx, rocprim::exclusive_scan(nullptr, temp, it, out, int32_t(0), n,
-                                      rocprim::plus<int32_t>(), ctx->stream));
-  DArr<unsigned char> tmp;
-  DM_ALLOC(ctx, tmp, temp + 16);
-  DM_HIP(ctx, rocprim::exclusive_scan(tmp.p, temp, it, out, int32_t(0), n,
-                                      rocprim::plus<int32_t>(), ctx->stream));
-  k_scan_tail<<<1, 1, 0, ctx->stream>>>(nullptr, out, n, 1, in + n - 1);
-  DM_LAUNCH_CHECK(ctx);
-  return DM_OK;
+dm_status scan_i32(dm_ctx* ctx, const int32_t* in, int32_t* out, size_t n) { return scan_impl(ctx, in, out, n); }
+dm_status scan_u8(dm_ctx* ctx, const uint8_t* in, int32_t* out, size_t n) { return scan_impl(ctx, in, out, n); }
+
+// values for the host: one small kernel writes them to the pinned slots
+// (a copy each costs the host as much as this launch)
+struct Collect {
+  const int32_t* p[HOST_SLOTS];
+};
+
+__global__ void k_collect(Collect c, int n, int32_t* host) {
+  if (int(threadIdx.x) < n) host[threadIdx.x] = *c.p[threadIdx.x];
 }
 
 dm_status read_i32(dm_ctx* ctx, const int32_t* dev, int32_t* host) {
@@ -231,10 +230,22 @@ dm_status read_i32(dm_ctx* ctx, const int32_t* dev, int32_t* host) {
 
 dm_status read_i32s(dm_ctx* ctx, int n, const int32_t* const* dev, int32_t* host) {
   if (n < 0 || n > HOST_SLOTS) return dm_fail(ctx, DM_ERR_STATE, "read_i32s: %d values (at most %d)", n, HOST_SLOTS);
-  for (int i = 0; i < n; ++i)
-    DM_HIP(ctx, hipMemcpyAsync(ctx->host_i32 + i, dev[i], sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
+  Collect c{};
+  for (int i = 0; i < n; ++i) c.p[i] = dev[i];
+  if (n > 0) k_collect<<<1, 64, 0, ctx->stream>>>(c, n, ctx->host_i32);
+  DM_LAUNCH_CHECK(ctx);
   DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
   for (int i = 0; i < n; ++i) host[i] = ctx->host_i32[i];
+  return DM_OK;
+}
+
+dm_status read_words(dm_ctx* ctx, int n, const void* dev, void* host) {
+  if (n < 0 || n > HOST_SLOTS) return dm_fail(ctx, DM_ERR_STATE, "read_words: %d words (at most %d)", n, HOST_SLOTS);
+  const int32_t* src[HOST_SLOTS];
+  int32_t v[HOST_SLOTS];
+  for (int i = 0; i < n; ++i) src[i] = static_cast<const int32_t*>(dev) + i;
+  DM_TRY(read_i32s(ctx, n, src, v));
+  std::memcpy(host, v, sizeof(int32_t) * size_t(n));
   return DM_OK;
 }
 

@@ -375,6 +375,7 @@ struct dm_ctx {
   bool corners_ready = false;    // corner_ptr / corner_list match the product space
   bool generic = false;          // the problem came from dm_build_ilp (no meshes, no candidates)
   bool desc_costs = false;       // the costs came from descriptors (dm_build_costs)
+  hipEvent_t landed = nullptr;   // a copy to host_i32 that is waited for by itself
   int32_t* host_i32 = nullptr;   // HOST_SLOTS pinned ints: landing slots of read_i32s
   DArr<int8_t> pref;             // per variable: 1, 0 or -1
   DArr<int64_t> icount;          // integer counters
@@ -397,6 +398,7 @@ struct dm_ctx {
 
   ~dm_ctx() {
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
+    if (landed) (void)hipEventDestroy(landed);
     if (qn && qn_free) qn_free(qn);
   }
 };
@@ -409,6 +411,8 @@ dm_status knn_distances(dm_ctx* ctx, const float* FX, int32_t nvx, const float* 
                         int32_t D, int32_t prec, float* d2 /* nvx*nvy */);
 dm_status sort_pairs_u64(dm_ctx* ctx, uint64_t* keys, int32_t* vals, size_t n, int end_bit);
 dm_status sort_pairs_u32(dm_ctx* ctx, uint32_t* keys, int32_t* vals, size_t n, int end_bit);
+dm_status sort_pairs_k(dm_ctx* ctx, uint32_t* keys, int32_t* vals, size_t n, int end_bit);   // by key type
+dm_status sort_pairs_k(dm_ctx* ctx, uint64_t* keys, int32_t* vals, size_t n, int end_bit);
 dm_status scan_i32(dm_ctx* ctx, const int32_t* in, int32_t* out, size_t n);  // exclusive, out[n] = total
 dm_status scan_u8(dm_ctx* ctx, const uint8_t* in, int32_t* out, size_t n);   // exclusive, out[n] = total
 // Deterministic FP64 sum of a[0..n) into *out (device), in an order fixed by
@@ -420,6 +424,8 @@ dm_status sum_f64(dm_ctx* ctx, const double* a, int64_t n, const void* sel, int 
 dm_status read_i32(dm_ctx* ctx, const int32_t* dev, int32_t* host);
 // n (<= HOST_SLOTS) device ints into host[0..n) with one wait for the stream
 dm_status read_i32s(dm_ctx* ctx, int n, const int32_t* const* dev, int32_t* host);
+// n (<= HOST_SLOTS) consecutive device ints (or words of wider values) from dev, likewise
+dm_status read_words(dm_ctx* ctx, int n, const void* dev, void* host);
 dm_status check_finite(dm_ctx* ctx, const float* a, int64_t na, const float* b, int64_t nb);
 // takes this device's address of the scratch array of dm_knn_candidates_noalloc (once per device)
 dm_status knn_scratch_init(dm_ctx* ctx);

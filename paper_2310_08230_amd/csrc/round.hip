@@ -10,6 +10,7 @@
 // rest by delta*u with u in [-1, 1) from a counter-based splitmix64 stream),
 // run a few Jacobi iterations and grow delta.
 #include <cmath>
+#include <cstring>
 
 #include "dm_internal.h"
 
@@ -127,6 +128,17 @@ dm_status count_violations(dm_ctx* ctx, const uint8_t* x, int64_t* out) {
   return DM_OK;
 }
 
+// a count and (when given) a sum with one wait
+static dm_status read_count_sum(dm_ctx* ctx, const int64_t* count, const double* sum, int64_t* c, double* v) {
+  const int32_t* src[4] = {reinterpret_cast<const int32_t*>(count), reinterpret_cast<const int32_t*>(count) + 1,
+                           reinterpret_cast<const int32_t*>(sum), sum ? reinterpret_cast<const int32_t*>(sum) + 1 : nullptr};
+  int32_t w[4];
+  DM_TRY(read_i32s(ctx, sum ? 4 : 2, src, w));
+  std::memcpy(c, w, sizeof(int64_t));
+  if (sum) std::memcpy(v, w + 2, sizeof(double));
+  return DM_OK;
+}
+
 template <typename R>
 static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam, uint8_t* x, double* pobj,
                             int32_t* feasible, int32_t* rounds_used) {
@@ -159,10 +171,7 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
     if (auto_delta) DM_TRY(sum_f64(ctx, absm.p, nfree, nullptr, SUM_ALL, ctx->scal.p));
     int64_t undecided = 0;
     double sum_absm = 0.0;
-    DM_HIP(ctx, hipMemcpyAsync(&undecided, ctx->icount.p, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    if (auto_delta)
-      DM_HIP(ctx, hipMemcpyAsync(&sum_absm, ctx->scal.p, sizeof(double), hipMemcpyDeviceToHost, st));
-    DM_HIP(ctx, hipStreamSynchronize(st));
+    DM_TRY(read_count_sum(ctx, ctx->icount.p, auto_delta ? ctx->scal.p : nullptr, &undecided, &sum_absm));
     if (auto_delta) delta = ctx->nnz ? 0.1 * sum_absm / double(ctx->nnz) : 0.0;
     k_make_x<<<grid_for(ctx->nP, 256), 256, 0, st>>>(ctx->state.p, ctx->var_red.p, ctx->pref.p, ctx->nP, x);
     DM_LAUNCH_CHECK(ctx);
@@ -172,9 +181,7 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
       DM_TRY(enqueue_violations(ctx, x));
       DM_TRY(sum_f64(ctx, ctx->cost64.p, ctx->nP, x, SUM_U8_NZ, ctx->scal.p + 1));
       int64_t viol = 0;
-      DM_HIP(ctx, hipMemcpyAsync(&viol, ctx->icount.p + 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      DM_HIP(ctx, hipMemcpyAsync(pobj, ctx->scal.p + 1, sizeof(double), hipMemcpyDeviceToHost, st));
-      DM_HIP(ctx, hipStreamSynchronize(st));
+      DM_TRY(read_count_sum(ctx, ctx->icount.p + 1, ctx->scal.p + 1, &viol, pobj));
       if (viol == 0) {
         *feasible = 1;
         return DM_OK;

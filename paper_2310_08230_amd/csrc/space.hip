@@ -20,6 +20,8 @@
 // pass (which variables can no longer take 0 or 1) and a variable pass.  The
 // fixpoint of a monotone propagation is unique, so the parallel rounds reach
 // the same fixings as any sequential order.
+#include <type_traits>
+
 #include "dm_internal.h"
 
 namespace {
@@ -30,67 +32,51 @@ struct Geo {
   int64_t W, QA, QB, Q;
 };
 
-__device__ inline void two_symbol(int pat, int32_t b, int32_t bp, int32_t out[3]) {
-  // bit k of the mask selects b' for position k
-  const int masks[6] = {4, 2, 1, 3, 5, 6};   // (b b b') (b b' b) (b' b b) (b' b' b) (b' b b') (b b' b')
-  int m = masks[pat];
-  out[0] = (m & 1) ? bp : b;
-  out[1] = (m & 2) ? bp : b;
-  out[2] = (m & 4) ? bp : b;
+// An enumeration slot: an X element with a Y element, both as up to three
+// vertices (a face's three, an edge's two, a vertex), and their classes and
+// ids.  Slots number fewer than 2^31, so 32-bit divisions decode them.
+struct Slot {
+  int32_t xc, x, yc, y;   // classes (0 face, 1 edge, 2 vertex) and ids
+  int32_t xv[3], yv[3];
+  int np;                 // rotations / patterns of the slot's classes
+};
+
+__device__ inline Slot decode_slot(const Geo& g, uint32_t q) {
+  Slot s;
+  if (q < uint32_t(g.QA)) {
+    const uint32_t W = uint32_t(g.W), f = q / W, j = q - f * W;
+    s.xc = 0;
+    s.x = int32_t(f);
+    s.yc = j < uint32_t(g.nfy) ? 0 : (j < uint32_t(g.nfy + g.ney) ? 1 : 2);
+    s.y = int32_t(j) - (s.yc == 0 ? 0 : (s.yc == 1 ? g.nfy : g.nfy + g.ney));
+    s.np = s.yc == 0 ? 3 : (s.yc == 1 ? 6 : 1);
+  } else {
+    const bool edge = q < uint32_t(g.QB);
+    const uint32_t r = q - uint32_t(edge ? g.QA : g.QB), nfy = uint32_t(g.nfy), e = r / nfy;
+    s.xc = edge ? 1 : 2;
+    s.x = int32_t(e);
+    s.yc = 0;
+    s.y = int32_t(r - e * nfy);
+    s.np = edge ? 6 : 1;
+  }
+  for (int k = 0; k < 3; ++k) {
+    s.xv[k] = s.xc == 0 ? g.FX[3 * s.x + k] : (s.xc == 1 ? g.EX[2 * s.x + (k & 1)] : s.x);
+    s.yv[k] = s.yc == 0 ? g.FY[3 * s.y + k] : (s.yc == 1 ? g.EY[2 * s.y + (k & 1)] : s.y);
+  }
+  return s;
 }
 
-// element sequences for enumeration slot q and rotation/pattern pat; returns
-// the number of patterns of the slot's class
-__device__ inline int slot_seq(const Geo& g, int64_t q, int pat, int32_t xs[3], int32_t ys[3],
-                               int32_t code[4]) {
-  if (q < g.QA) {
-    int32_t f = int32_t(q / g.W);
-    int64_t j = q % g.W;
-    xs[0] = g.FX[3 * f];
-    xs[1] = g.FX[3 * f + 1];
-    xs[2] = g.FX[3 * f + 2];
-    code[0] = 0;
-    code[1] = f;
-    if (j < g.nfy) {
-      int32_t gg = int32_t(j);
-      for (int k = 0; k < 3; ++k) ys[k] = g.FY[3 * gg + (k + pat) % 3];
-      code[2] = pat;
-      code[3] = gg;
-      return 3;
-    }
-    if (j < g.nfy + g.ney) {
-      int32_t e = int32_t(j - g.nfy);
-      two_symbol(pat, g.EY[2 * e], g.EY[2 * e + 1], ys);
-      code[2] = 8 + pat;
-      code[3] = e;
-      return 6;
-    }
-    int32_t n = int32_t(j - g.nfy - g.ney);
-    ys[0] = ys[1] = ys[2] = n;
-    code[2] = 16;
-    code[3] = n;
-    return 1;
-  }
-  if (q < g.QB) {
-    int64_t r = q - g.QA;
-    int32_t e = int32_t(r / g.nfy), gg = int32_t(r % g.nfy);
-    two_symbol(pat, g.EX[2 * e], g.EX[2 * e + 1], xs);
-    for (int k = 0; k < 3; ++k) ys[k] = g.FY[3 * gg + k];
-    code[0] = 1;
-    code[1] = e;
-    code[2] = pat;
-    code[3] = gg;
-    return 6;
-  }
-  int64_t r = q - g.QB;
-  int32_t m = int32_t(r / g.nfy), gg = int32_t(r % g.nfy);
-  xs[0] = xs[1] = xs[2] = m;
-  for (int k = 0; k < 3; ++k) ys[k] = g.FY[3 * gg + k];
-  code[0] = 2;
-  code[1] = m;
-  code[2] = 0;
-  code[3] = gg;
-  return 1;
+// which of a slot's vertices stands at corner k in rotation / pattern pat: a
+// face against a face is rotated on the Y side, against an edge (b b') it meets
+// the six two-symbol sequences (b b b') (b b' b) (b' b b) (b' b' b) (b' b b')
+// (b b' b'), whose bit k selects b'
+__device__ inline int x_corner(const Slot& s, int pat, int k) {
+  constexpr int masks[6] = {4, 2, 1, 3, 5, 6};
+  return s.xc == 0 ? k : (s.xc == 1 ? (masks[pat] >> k) & 1 : 0);
+}
+__device__ inline int y_corner(const Slot& s, int pat, int k) {
+  constexpr int masks[6] = {4, 2, 1, 3, 5, 6};
+  return s.yc == 0 ? (s.xc == 0 ? (k + pat) % 3 : k) : (s.yc == 1 ? (masks[pat] >> k) & 1 : 0);
 }
 
 __global__ void k_cand_mark(const int32_t* cand, int32_t nrows, int32_t K, int32_t nother, int dir,
@@ -142,72 +128,155 @@ __global__ void k_ystart(const uint32_t* key, int64_t nC, int32_t nvx, int32_t n
   ystart[n] = int32_t(lo);
 }
 
+// the rotations / patterns of each slot whose three corners are candidates: the
+// (at most nine) vertex pairs are looked up once
 __global__ void k_enum_mask(Geo g, const uint8_t* cand, uint8_t* mask, uint8_t* count) {
-  int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= g.Q) return;
-  int32_t xs[3], ys[3], code[4];
-  int np = slot_seq(g, q, 0, xs, ys, code);
-  uint8_t m = 0, c = 0;
-  for (int pat = 0; pat < np; ++pat) {
-    slot_seq(g, q, pat, xs, ys, code);
-    bool keep = true;
-    for (int k = 0; k < 3; ++k) keep = keep && cand[int64_t(xs[k]) * g.nvy + ys[k]];
-    if (keep) {
-      m |= uint8_t(1u << pat);
-      ++c;
-    }
+  const Slot s = decode_slot(g, uint32_t(q));
+  const int nx = 3 - s.xc, ny = 3 - s.yc;
+  // bit 3 a + b: vertex a of X with vertex b of Y; every X vertex needs one of
+  // Y's, so a slot whose first has none (most of them) is not looked at further
+  uint32_t ok = 0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (a > 0 && !ok) break;
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+      if (a < nx && b < ny && cand[int64_t(s.xv[a]) * g.nvy + s.yv[b]]) ok |= 1u << (3 * a + b);
   }
-  mask[q] = m;
-  count[q] = c;
+  uint32_t m = 0;
+#pragma unroll
+  for (int pat = 0; pat < 6; ++pat) {
+    uint32_t need = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) need |= 1u << (3 * x_corner(s, pat, k) + y_corner(s, pat, k));
+    if (pat < s.np && (ok & need) == need) m |= 1u << pat;
+  }
+  mask[q] = uint8_t(m);
+  count[q] = uint8_t(__popc(m));
 }
 
 __global__ void k_enum_fill(Geo g, const uint8_t* mask, const int32_t* off, int32_t* pv,
                             int32_t* code_out) {
-  int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= g.Q) return;
-  uint8_t m = mask[q];
+  const uint8_t m = mask[q];
   if (!m) return;
   int64_t o = off[q];
-  int32_t xs[3], ys[3], code[4];
+  const Slot s = decode_slot(g, uint32_t(q));
+#pragma unroll
   for (int pat = 0; pat < 6; ++pat) {
     if (!(m & (1u << pat))) continue;
-    slot_seq(g, q, pat, xs, ys, code);
-    for (int k = 0; k < 3; ++k) pv[3 * o + k] = xs[k] * g.nvy + ys[k];
-    for (int k = 0; k < 4; ++k) code_out[4 * o + k] = code[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int a = x_corner(s, pat, k), b = y_corner(s, pat, k);
+      const int32_t x = a == 0 ? s.xv[0] : (a == 1 ? s.xv[1] : s.xv[2]);
+      const int32_t y = b == 0 ? s.yv[0] : (b == 1 ? s.yv[1] : s.yv[2]);
+      pv[3 * o + k] = x * g.nvy + y;
+    }
+    reinterpret_cast<int4*>(code_out)[o] = make_int4(s.xc, s.x, 8 * s.yc + (s.yc == 2 ? 0 : pat), s.y);
     ++o;
   }
 }
 
-__global__ void k_edge_keys(const int32_t* pv, int64_t nP, uint64_t npv, uint64_t* key, int32_t* val) {
-  int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (s >= 3 * nP) return;
-  int64_t p = s / 3;
-  int k = int(s % 3);
-  uint64_t a = uint32_t(pv[3 * p + k]), b = uint32_t(pv[3 * p + (k + 1) % 3]);
-  key[s] = (a < b ? a : b) * npv + (a < b ? b : a);
-  val[s] = int32_t(s);
+// largest number of neighbours of a vertex, from the sorted directed edges a nv + b
+__global__ void k_max_degree(const uint64_t* dkey, int32_t nv, int32_t n, int* out) {
+  const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t a = dkey[i] / uint64_t(nv);
+  if (i > 0 && dkey[i - 1] / uint64_t(nv) == a) return;   // one thread per vertex: its first edge
+  int32_t d = 1;
+  while (i + d < n && dkey[i + d] / uint64_t(nv) == a) ++d;
+  atomicMax(out, d);
 }
 
-__global__ void k_row_flags(const uint64_t* key, int64_t n, uint8_t* flag) {
+// first directed edge of every vertex, and the edges' far ends: the sorted
+// neighbours of a are nbr[start[a] .. start[a + 1])
+__global__ void k_neighbours(const uint64_t* dkey, int32_t nv, int32_t n, int32_t* start, int32_t* nbr) {
+  const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) nbr[i] = int32_t(dkey[i] % uint64_t(nv));
+  if (i > nv) return;
+  int32_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (dkey[mid] < uint64_t(i) * uint64_t(nv)) lo = mid + 1;
+    else hi = mid;
+  }
+  start[i] = lo;
+}
+
+// place of b among a and its neighbours, in order (b is a or one of them)
+__device__ inline uint32_t near_rank(const int32_t* nbr, const int32_t* start, int32_t a, int32_t b) {
+  uint32_t r = b > a ? 1u : 0u;
+  for (int32_t i = start[a]; i < start[a + 1] && nbr[i] < b; ++i) ++r;
+  return r;
+}
+
+// Sort keys of the product edges, in the order of (smaller, larger) product
+// vertex.  Wide: min * npv + max (42 bits at the 2000/3000-face pair).  Compact,
+// where it fits 32 bits: the smaller vertex by its place among the candidate
+// pairs, the larger one by the places of its X and Y vertex among the smaller
+// one's and their neighbours (px and py places at most; 23 bits there), so that
+// the sort of the 13.4 M edges takes three passes over eight bytes, not six over
+// twelve (830 -> 350 us; the codes cost 120 more than the wide keys).
+struct EdgeCode {
+  const int32_t* cidx;
+  const int32_t *nx, *ny, *sx, *sy;   // neighbours
+  int32_t nvy;
+  uint32_t px, py;
+};
+
+template <typename K>
+__global__ void k_edge_keys(const int32_t* pv, int64_t nP, uint64_t npv, EdgeCode c, K* key, int32_t* val) {
+  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (p >= nP) return;
+  int32_t v[3], m[3], n[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    v[k] = pv[3 * p + k];
+    if constexpr (sizeof(K) == 4) {
+      m[k] = int32_t(uint32_t(v[k]) / uint32_t(c.nvy));
+      n[k] = v[k] - m[k] * c.nvy;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int l = (k + 1) % 3;
+    const bool up = v[k] < v[l];
+    const int32_t lo = up ? v[k] : v[l], hi = up ? v[l] : v[k];
+    if constexpr (sizeof(K) == 4) {
+      const uint32_t rx = near_rank(c.nx, c.sx, up ? m[k] : m[l], up ? m[l] : m[k]);
+      const uint32_t ry = near_rank(c.ny, c.sy, up ? n[k] : n[l], up ? n[l] : n[k]);
+      key[3 * p + k] = (uint32_t(c.cidx[lo]) * c.px + rx) * c.py + ry;
+    } else {
+      key[3 * p + k] = uint64_t(lo) * npv + uint64_t(hi);
+    }
+    val[3 * p + k] = int32_t(3 * p + k);
+  }
+}
+
+template <typename K>
+__global__ void k_row_flags(const K* key, int64_t n, uint8_t* flag) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) flag[i] = (i == 0 || key[i] != key[i - 1]) ? 1 : 0;
 }
 
-__global__ void k_closed_fill(const uint64_t* key, const int32_t* val, const uint8_t* flag,
+__global__ void k_closed_fill(uint64_t npv, const int32_t* val, const uint8_t* flag,
                               const int32_t* excl, const int32_t* pv, int64_t n, int32_t* row_ptr,
                               int64_t* row_key, int32_t* row_b, int32_t* ent_var, int8_t* ent_coef,
                               uint8_t* ent_slot) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  if (flag[i]) {
-    int32_t r = excl[i];
-    row_ptr[r] = int32_t(i);
-    row_key[r] = int64_t(key[i]);
-    row_b[r] = 0;
-  }
   int32_t s = val[i];
   int32_t p = s / 3, k = s % 3;
   int32_t a = pv[3 * p + k], b = pv[3 * p + (k + 1) % 3];
+  if (flag[i]) {
+    int32_t r = excl[i];
+    row_ptr[r] = int32_t(i);
+    row_key[r] = int64_t(uint64_t(a < b ? a : b) * npv + uint64_t(a < b ? b : a));
+    row_b[r] = 0;
+  }
   ent_var[i] = p;
   ent_coef[i] = a < b ? 1 : -1;
   ent_slot[i] = uint8_t(k);
@@ -277,65 +346,108 @@ __device__ inline bool presolve_done(const int* prev) {
   return prev && (prev[0] == 0 || prev[1] != 0);
 }
 
-// A row's entries are read PS_BATCH at a time, with indices clamped to the
-// row, so that the loads of a batch go out together and need no branch.
-constexpr int PS_BATCH = 8;
+// The short rows of the full problem in blocks of PS_ROWS: the block reads its
+// rows' entries coalesced, packs what a row needs of each (its sign and its
+// variable's state) into one byte of LDS, and one thread per row walks those.
+// A thread per row straight from memory touched some forty lines per load:
+// 106 us for the 13.4 M entries of the 2000/3000-face pair, against 50 staged
+// (what is left is the gather of the states, a byte each from 4.5 MB).  Rows that do not fit
+// the table (PS_CAP entries) are read from memory as they are walked.
+constexpr int PS_ROWS = 256;
+constexpr int PS_CAP = 12288;
 
-__global__ void k_presolve_rows(const int32_t* row_ptr, const int32_t* ent_var, const int8_t* ent_coef,
-                                const int32_t* row_b, int64_t nrows, const int8_t* state,
-                                uint32_t* force, int* flags, const int* prev) {
-  if (presolve_done(prev)) return;   // uniform across the grid
-  int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= nrows) return;
-  const int32_t s = row_ptr[j], e = row_ptr[j + 1];
-  int32_t r = row_b[j], P = 0, N = 0;
-  for (int32_t i0 = s; i0 < e; i0 += PS_BATCH) {
-    int32_t v[PS_BATCH];
-    int a[PS_BATCH];
+// bit 0: coefficient +1; bits 1-2: state + 1 (0 free, 1 fixed to 0, 2 fixed to 1)
+__device__ inline uint8_t ps_pack(int8_t coef, int8_t state) {
+  return uint8_t((coef > 0 ? 1 : 0) | ((state + 1) << 1));
+}
+
+struct RowStage {
+  const uint8_t* lds;   // the block's entries from e0 on, or NULL
+  int32_t e0;
+  const int32_t* ent_var;
+  const int8_t* ent_coef;
+  const int8_t* state;
+  __device__ uint8_t get(int32_t i) const { return lds ? lds[i - e0] : ps_pack(ent_coef[i], state[ent_var[i]]); }
+};
+
+__device__ inline RowStage stage_rows(const int32_t* row_ptr, int64_t r0, int64_t r1, const int32_t* ent_var,
+                                      const int8_t* ent_coef, const int8_t* state, uint8_t* table) {
+  const int32_t e0 = row_ptr[r0], n = row_ptr[r1] - e0;
+  const bool fits = n <= PS_CAP;   // uniform across the block
+  if (fits) {
+    constexpr int B = 4;   // entries per thread in flight
+    for (int32_t i0 = int32_t(threadIdx.x); i0 < n; i0 += B * PS_ROWS) {
+      int32_t v[B];
+      int8_t c[B], st[B];
 #pragma unroll
-    for (int u = 0; u < PS_BATCH; ++u) {
-      const int32_t i = i0 + u < e ? i0 + u : i0;
-      v[u] = ent_var[i];
-      a[u] = ent_coef[i];
-    }
-    int8_t st[PS_BATCH];
-#pragma unroll
-    for (int u = 0; u < PS_BATCH; ++u) st[u] = state[v[u]];
-#pragma unroll
-    for (int u = 0; u < PS_BATCH; ++u) {
-      if (i0 + u >= e) continue;
-      if (st[u] == 1) r -= a[u];
-      else if (st[u] < 0) {
-        if (a[u] > 0) ++P;
-        else ++N;
+      for (int u = 0; u < B; ++u) {
+        const int32_t i = e0 + (i0 + u * PS_ROWS < n ? i0 + u * PS_ROWS : i0);
+        v[u] = ent_var[i];
+        c[u] = ent_coef[i];
       }
+#pragma unroll
+      for (int u = 0; u < B; ++u) st[u] = state[v[u]];
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if (i0 + u * PS_ROWS < n) table[i0 + u * PS_ROWS] = ps_pack(c[u], st[u]);
     }
   }
+  __syncthreads();
+  return RowStage{fits ? table : nullptr, e0, ent_var, ent_coef, state};
+}
+
+// residual right-hand side and free entries of each sign of row j
+__device__ inline void row_counts(const RowStage& S, int32_t s, int32_t e, int32_t& r, int32_t& P, int32_t& N) {
+  for (int32_t i = s; i < e; ++i) {
+    const uint8_t c = S.get(i);
+    const int plus = c & 1, st = c >> 1;
+    if (st == 2) r -= plus ? 1 : -1;
+    else if (st == 0) {
+      P += plus;
+      N += 1 - plus;
+    }
+  }
+}
+
+// what the row forces on its free entries of one sign: bit 0 to 0, bit 1 to 1
+// (both: no value is possible); every entry of a sign gets the same
+__device__ inline uint32_t row_forces(int32_t r, int32_t P, int32_t N, int a) {
+  const int32_t Pr = P - (a > 0 ? 1 : 0), Nr = N - (a < 0 ? 1 : 0);
+  const bool one_ok = (r - a >= -Nr) && (r - a <= Pr);
+  const bool zero_ok = (r >= -Nr) && (r <= Pr);
+  return (one_ok ? 0u : 1u) | (zero_ok ? 0u : 2u);
+}
+
+// forced values, one byte per variable in words of four
+__device__ inline void force_var(uint32_t* force, int32_t v, uint32_t bits) {
+  atomicOr(&force[v >> 2], bits << (8 * (v & 3)));
+}
+
+__global__ __launch_bounds__(PS_ROWS) void k_presolve_rows(const int32_t* row_ptr, const int32_t* ent_var,
+                                                           const int8_t* ent_coef, const int32_t* row_b,
+                                                           int64_t nrows, const int8_t* state, uint32_t* force,
+                                                           int* flags, const int* prev) {
+  __shared__ uint8_t table[PS_CAP];
+  if (presolve_done(prev)) return;   // uniform across the grid
+  const int64_t r0 = int64_t(blockIdx.x) * PS_ROWS, r1 = r0 + PS_ROWS < nrows ? r0 + PS_ROWS : nrows;
+  const RowStage S = stage_rows(row_ptr, r0, r1, ent_var, ent_coef, state, table);
+  const int64_t j = r0 + threadIdx.x;
+  if (j >= r1) return;
+  const int32_t s = row_ptr[j], e = row_ptr[j + 1];
+  int32_t r = row_b[j], P = 0, N = 0;
+  row_counts(S, s, e, r, P, N);
   if (r < -N || r > P) {
     atomicOr(&flags[1], 1);
     return;
   }
-  for (int32_t i0 = s; i0 < e; i0 += PS_BATCH) {
-    int32_t v[PS_BATCH];
-    int a[PS_BATCH];
-#pragma unroll
-    for (int u = 0; u < PS_BATCH; ++u) {
-      const int32_t i = i0 + u < e ? i0 + u : i0;
-      v[u] = ent_var[i];
-      a[u] = ent_coef[i];
-    }
-    int8_t st[PS_BATCH];
-#pragma unroll
-    for (int u = 0; u < PS_BATCH; ++u) st[u] = state[v[u]];
-#pragma unroll
-    for (int u = 0; u < PS_BATCH; ++u) {
-      if (i0 + u >= e || st[u] >= 0) continue;
-      const int32_t Pr = P - (a[u] > 0 ? 1 : 0), Nr = N - (a[u] < 0 ? 1 : 0);
-      const bool one_ok = (r - a[u] >= -Nr) && (r - a[u] <= Pr);
-      const bool zero_ok = (r >= -Nr) && (r <= Pr);
-      if (!one_ok && !zero_ok) atomicOr(&flags[1], 1);
-      else if (!one_ok) atomicOr(&force[v[u]], 1u);
-      else if (!zero_ok) atomicOr(&force[v[u]], 2u);
+  const uint32_t fp = row_forces(r, P, N, 1), fn = row_forces(r, P, N, -1);
+  if ((fp && P) || (fn && N)) {
+    for (int32_t i = s; i < e; ++i) {
+      const uint8_t c = S.get(i);
+      if (c >> 1) continue;
+      const uint32_t f = (c & 1) ? fp : fn;
+      if (f == 3u) atomicOr(&flags[1], 1);
+      else if (f) force_var(force, ent_var[i], f);
     }
   }
 }
@@ -348,16 +460,20 @@ __global__ __launch_bounds__(256) void k_presolve_vars(int64_t nP, int8_t* state
   if (presolve_done(prev)) return;   // uniform across the grid
   if (threadIdx.x < 2) any[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p < nP) {
-    const uint32_t f = force[p];
-    if (f) {
-      force[p] = 0;
-      if (f == 3u) {
-        any[1] = 1;
-      } else if (state[p] < 0) {
-        state[p] = (f == 2u) ? 1 : 0;
-        any[0] = 1;
+  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;   // sixteen variables
+  if (16 * p < nP) {
+    const uint4 w4 = reinterpret_cast<const uint4*>(force)[p];
+    if (w4.x | w4.y | w4.z | w4.w) {
+      reinterpret_cast<uint4*>(force)[p] = make_uint4(0u, 0u, 0u, 0u);
+      for (int k = 0; k < 16; ++k) {
+        const uint32_t w = k < 4 ? w4.x : (k < 8 ? w4.y : (k < 12 ? w4.z : w4.w));
+        const uint32_t f = (w >> (8 * (k & 3))) & 3u;
+        if (f == 3u) {
+          any[1] = 1;
+        } else if (f && state[16 * p + k] < 0) {
+          state[16 * p + k] = (f == 2u) ? 1 : 0;
+          any[0] = 1;
+        }
       }
     }
   }
@@ -392,46 +508,67 @@ __global__ void k_free_fill(const int8_t* state, const int32_t* excl, int64_t nP
   }
 }
 
-__global__ void k_row_residual(const int32_t* row_ptr, const int32_t* ent_var, const int8_t* ent_coef,
-                               const int32_t* row_b, int64_t nrows, const int8_t* state,
-                               int32_t* nfree, int32_t* resid, uint8_t* keep, int* flags) {
-  int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= nrows) return;
-  int32_t r = row_b[j], c = 0;
-  for (int32_t i = row_ptr[j]; i < row_ptr[j + 1]; ++i) {
-    int8_t st = state[ent_var[i]];
-    if (st == 1) r -= ent_coef[i];
-    else if (st < 0) ++c;
-  }
+__global__ __launch_bounds__(PS_ROWS) void k_row_residual(const int32_t* row_ptr, const int32_t* ent_var,
+                                                          const int8_t* ent_coef, const int32_t* row_b, int64_t nrows,
+                                                          const int8_t* state, int32_t* nfree, int32_t* resid,
+                                                          uint8_t* keep, int* flags) {
+  __shared__ uint8_t table[PS_CAP];
+  const int64_t r0 = int64_t(blockIdx.x) * PS_ROWS, r1 = r0 + PS_ROWS < nrows ? r0 + PS_ROWS : nrows;
+  const RowStage S = stage_rows(row_ptr, r0, r1, ent_var, ent_coef, state, table);
+  const int64_t j = r0 + threadIdx.x;
+  if (j >= r1) return;
+  int32_t r = row_b[j], P = 0, N = 0;
+  row_counts(S, row_ptr[j], row_ptr[j + 1], r, P, N);
+  const int32_t c = P + N;
   if (c == 0 && r != 0) atomicOr(&flags[1], 1);
   nfree[j] = c;
   resid[j] = r;
   keep[j] = c > 0 ? 1 : 0;
 }
 
-__global__ void k_reduced_fill(const int32_t* row_ptr, const int32_t* ent_var, const int8_t* ent_coef,
-                               const uint8_t* ent_slot, int64_t nrows, const int8_t* state,
-                               const int32_t* var_red, const int32_t* free_var,
-                               const uint8_t* keep, const int32_t* new_id, const int32_t* cnt_excl,
-                               const int32_t* resid, int32_t* rrow_orig, int32_t* rrow_ptr,
-                               int32_t* rrow_b, int32_t* rent_var, int8_t* rent_coef,
-                               uint32_t* rent_word) {
-  int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= nrows || !keep[j]) return;
-  int32_t nr = new_id[j];
-  rrow_orig[nr] = int32_t(j);
-  rrow_b[nr] = resid[j];
-  int32_t pos = cnt_excl[j];
-  rrow_ptr[nr] = pos;
-  for (int32_t i = row_ptr[j]; i < row_ptr[j + 1]; ++i) {
-    int32_t v = ent_var[i];
-    if (state[v] >= 0) continue;
-    int32_t rv = var_red[v];
-    int a = ent_coef[i];
-    rent_var[pos] = rv;
-    rent_coef[pos] = int8_t(a);
-    rent_word[pos] = (a < 0 ? W_NEG : 0u) | (uint32_t(ent_slot[i]) << W_SLOT_SHIFT) | uint32_t(rv);
-    ++pos;
+__device__ inline int block_excl_flag(bool f, int* sh, int* total);
+
+// Reduced short rows in blocks of FILL_ROWS: one thread per row for its
+// pointers, then the block walks its entries 256 at a time, every free one
+// taking the next place (the rows of a block are contiguous in the full and in
+// the reduced entries alike), so that all reads and writes are coalesced.  One
+// thread per row writing its own entries took 557 us at the 2000/3000-face
+// pair, this takes 121.
+constexpr int FILL_ROWS = 128;
+
+__global__ __launch_bounds__(256) void k_reduced_fill(const int32_t* row_ptr, const int32_t* ent_var,
+                                                      const int8_t* ent_coef, const uint8_t* ent_slot, int64_t nrows,
+                                                      const int8_t* state, const int32_t* var_red,
+                                                      const uint8_t* keep, const int32_t* new_id,
+                                                      const int32_t* cnt_excl, const int32_t* resid,
+                                                      int32_t* rrow_orig, int32_t* rrow_ptr, int32_t* rrow_b,
+                                                      int32_t* rent_var, int8_t* rent_coef, uint32_t* rent_word) {
+  __shared__ int sh[4];
+  const int64_t r0 = int64_t(blockIdx.x) * FILL_ROWS, r1 = r0 + FILL_ROWS < nrows ? r0 + FILL_ROWS : nrows;
+  const int64_t j = r0 + threadIdx.x;
+  if (j < r1 && keep[j]) {
+    const int32_t nr = new_id[j];
+    rrow_orig[nr] = int32_t(j);
+    rrow_b[nr] = resid[j];
+    rrow_ptr[nr] = cnt_excl[j];
+  }
+  const int32_t e1 = row_ptr[r1];
+  int32_t pos = cnt_excl[r0];
+  for (int32_t t0 = row_ptr[r0]; t0 < e1; t0 += 256) {   // uniform across the block
+    const int32_t i = t0 + int32_t(threadIdx.x);
+    const bool in = i < e1;
+    const int32_t v = in ? ent_var[i] : 0;
+    const bool f = in && state[v] < 0;
+    int total = 0;
+    const int off = block_excl_flag(f, sh, &total);
+    if (f) {
+      const int32_t rv = var_red[v];
+      const int a = ent_coef[i];
+      rent_var[pos + off] = rv;
+      rent_coef[pos + off] = int8_t(a);
+      rent_word[pos + off] = (a < 0 ? W_NEG : 0u) | (uint32_t(ent_slot[i]) << W_SLOT_SHIFT) | uint32_t(rv);
+    }
+    pos += total;
   }
 }
 
@@ -483,7 +620,7 @@ __global__ __launch_bounds__(256) void k_presolve_proj(const int32_t* row_ptr, c
   if (r == 0 || P == 1)
     for (int32_t i = s + threadIdx.x; i < e; i += blockDim.x) {
       int32_t v = ent_var[i];
-      if (state[v] < 0) atomicOr(&force[v], r == 0 ? 1u : 2u);
+      if (state[v] < 0) force_var(force, v, r == 0 ? 1u : 2u);
     }
 }
 
@@ -641,8 +778,18 @@ dm_status space_build(dm_ctx* ctx, const int32_t* cand_xy, const int32_t* cand_y
   if (e0) return dm_fail(ctx, DM_ERR_INVALID_ARG, "candidate index out of range");
   DM_ALLOC(ctx, ctx->cidx, size_t(npv) + 1);
   DM_TRY(scan_u8(ctx, ctx->cand.p, ctx->cidx.p, size_t(npv)));
-  int32_t nC = 0;
-  DM_TRY(read_i32(ctx, ctx->cidx.p + npv, &nC));
+  k_max_degree<<<grid_for(3 * X.nf, 256), 256, 0, st>>>(X.dkey.p, nvx, 3 * X.nf, err.p + 1);
+  k_max_degree<<<grid_for(3 * Y.nf, 256), 256, 0, st>>>(Y.dkey.p, nvy, 3 * Y.nf, err.p + 2);
+  DM_LAUNCH_CHECK(ctx);
+  int32_t nC = 0, degree[2];
+  {
+    const int32_t* src[3] = {ctx->cidx.p + npv, err.p + 1, err.p + 2};
+    int32_t v[3];
+    DM_TRY(read_i32s(ctx, 3, src, v));
+    nC = v[0];
+    degree[0] = v[1];
+    degree[1] = v[2];
+  }
   ctx->nC = nC;
   DM_ALLOC(ctx, ctx->cpair, size_t(nC));
   DM_ALLOC(ctx, ctx->cand_xstart, size_t(nvx) + 1);
@@ -705,19 +852,38 @@ dm_status space_build(dm_ctx* ctx, const int32_t* cand_xy, const int32_t* cand_y
   const int64_t nP = ctx->nP;
 
   // ---- closedness rows: sort the 3|P| directed boundary edges by key
-  DArr<uint64_t> ekey;
   DArr<int32_t> eval_;
-  DM_ALLOC(ctx, ekey, size_t(3 * nP));
-  DM_ALLOC(ctx, eval_, size_t(3 * nP));
-  k_edge_keys<<<grid_for(3 * nP, 256), 256, 0, st>>>(ctx->pv.p, nP, uint64_t(npv), ekey.p, eval_.p);
-  DM_LAUNCH_CHECK(ctx);
-  DM_TRY(sort_pairs_u64(ctx, ekey.p, eval_.p, size_t(3 * nP), bits_for(uint64_t(npv) * uint64_t(npv))));
   DArr<uint8_t> rflag;
   DArr<int32_t> rexcl;
+  DM_ALLOC(ctx, eval_, size_t(3 * nP));
   DM_ALLOC(ctx, rflag, size_t(3 * nP));
   DM_ALLOC(ctx, rexcl, size_t(3 * nP) + 1);
-  k_row_flags<<<grid_for(3 * nP, 256), 256, 0, st>>>(ekey.p, 3 * nP, rflag.p);
-  DM_LAUNCH_CHECK(ctx);
+  const uint64_t px = uint64_t(degree[0]) + 1, py = uint64_t(degree[1]) + 1;
+  const int compact = bits_for(uint64_t(nC) * px * py);
+  const auto sorted_edges = [&](auto* type, int bits) -> dm_status {
+    using K = std::remove_pointer_t<decltype(type)>;
+    DArr<K> ekey;
+    DArr<int32_t> sx, sy, nx, ny;
+    EdgeCode code{};
+    DM_ALLOC(ctx, ekey, size_t(3 * nP));
+    if (sizeof(K) == 4) {
+      DM_ALLOC(ctx, sx, size_t(nvx) + 1);
+      DM_ALLOC(ctx, sy, size_t(nvy) + 1);
+      DM_ALLOC(ctx, nx, size_t(3 * X.nf));
+      DM_ALLOC(ctx, ny, size_t(3 * Y.nf));
+      k_neighbours<<<grid_for(std::max(nvx + 1, 3 * X.nf), 256), 256, 0, st>>>(X.dkey.p, nvx, 3 * X.nf, sx.p, nx.p);
+      k_neighbours<<<grid_for(std::max(nvy + 1, 3 * Y.nf), 256), 256, 0, st>>>(Y.dkey.p, nvy, 3 * Y.nf, sy.p, ny.p);
+      code = EdgeCode{ctx->cidx.p, nx.p, ny.p, sx.p, sy.p, nvy, uint32_t(px), uint32_t(py)};
+    }
+    k_edge_keys<K><<<grid_for(nP, 256), 256, 0, st>>>(ctx->pv.p, nP, uint64_t(npv), code, ekey.p, eval_.p);
+    DM_LAUNCH_CHECK(ctx);
+    DM_TRY(sort_pairs_k(ctx, ekey.p, eval_.p, size_t(3 * nP), bits));
+    k_row_flags<K><<<grid_for(3 * nP, 256), 256, 0, st>>>(ekey.p, 3 * nP, rflag.p);
+    DM_LAUNCH_CHECK(ctx);
+    return DM_OK;
+  };
+  if (compact <= 32) DM_TRY(sorted_edges(static_cast<uint32_t*>(nullptr), compact));
+  else DM_TRY(sorted_edges(static_cast<uint64_t*>(nullptr), bits_for(uint64_t(npv) * uint64_t(npv))));
   DM_TRY(scan_u8(ctx, rflag.p, rexcl.p, size_t(3 * nP)));
   int32_t nc = 0, nXf = 0;
   {
@@ -754,7 +920,7 @@ dm_status space_build(dm_ctx* ctx, const int32_t* cand_xy, const int32_t* cand_y
   DM_ALLOC(ctx, ctx->ent_var, size_t(nnz));
   DM_ALLOC(ctx, ctx->ent_coef, size_t(nnz));
   DM_ALLOC(ctx, ctx->ent_slot, size_t(nnz));
-  k_closed_fill<<<grid_for(3 * nP, 256), 256, 0, st>>>(ekey.p, eval_.p, rflag.p, rexcl.p, ctx->pv.p, 3 * nP,
+  k_closed_fill<<<grid_for(3 * nP, 256), 256, 0, st>>>(uint64_t(npv), eval_.p, rflag.p, rexcl.p, ctx->pv.p, 3 * nP,
                                                        ctx->row_ptr.p, ctx->row_key.p, ctx->row_b.p,
                                                        ctx->ent_var.p, ctx->ent_coef.p, ctx->ent_slot.p);
   k_xproj<<<grid_for(std::max<int64_t>(X.nf, nXf), 256), 256, 0, st>>>(
@@ -765,7 +931,6 @@ dm_status space_build(dm_ctx* ctx, const int32_t* cand_xy, const int32_t* cand_y
       ctx->row_b.p, ctx->ent_var.p, ctx->ent_coef.p, ctx->ent_slot.p);
   k_set_i32<<<1, 1, 0, st>>>(ctx->row_ptr.p, nrows, int32_t(nnz));
   DM_LAUNCH_CHECK(ctx);
-  ekey.release();
   eval_.release();
   rflag.release();
   rexcl.release();
@@ -794,8 +959,9 @@ dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix) {
     DM_HIP(ctx, hipMemsetAsync(ctx->state.p, 0xFF, size_t(nP), st));
   }
   DArr<uint32_t> force;
-  DM_ALLOC(ctx, force, size_t(nP));
-  DM_HIP(ctx, hipMemsetAsync(force.p, 0, sizeof(uint32_t) * nP, st));
+  const size_t nforce = std::max<size_t>(size_t(nP + 15) / 16 * 4, 4);   // one byte per variable, sixteen at a time
+  DM_ALLOC(ctx, force, nforce);
+  DM_HIP(ctx, hipMemsetAsync(force.p, 0, sizeof(uint32_t) * nforce, st));
   // Rounds run in batches of PRESOLVE_BATCH with one host read per batch:
   // round k writes its (changed, infeasible) flags to rflags[2k..2k+1], and
   // a round whose predecessor changed nothing (or found infeasibility) does
@@ -810,17 +976,16 @@ dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix) {
       int* fl = rflags.p + 2 * k;
       const int* prev = k > 0 ? rflags.p + 2 * (k - 1) : nullptr;
       if (nc > 0)
-        k_presolve_rows<<<grid_for(nc, 128), 128, 0, st>>>(ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_coef.p,
+        k_presolve_rows<<<grid_for(nc, PS_ROWS), PS_ROWS, 0, st>>>(ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_coef.p,
                                                            ctx->row_b.p, nc, ctx->state.p, force.p, fl, prev);
       if (nrows > nc)
         k_presolve_proj<<<unsigned(nrows - nc), 256, 0, st>>>(ctx->row_ptr.p, ctx->ent_var.p, nc, ctx->state.p,
                                                             force.p, fl, prev);
-      k_presolve_vars<<<grid_for(nP, 256), 256, 0, st>>>(nP, ctx->state.p, force.p, fl, prev);
+      k_presolve_vars<<<grid_for((nP + 15) / 16, 256), 256, 0, st>>>(nP, ctx->state.p, force.p, fl, prev);
     }
     DM_LAUNCH_CHECK(ctx);
     int flags[2 * PRESOLVE_BATCH];
-    DM_HIP(ctx, hipMemcpyAsync(flags, rflags.p, sizeof(flags), hipMemcpyDeviceToHost, st));
-    DM_HIP(ctx, hipStreamSynchronize(st));
+    DM_TRY(read_words(ctx, 2 * PRESOLVE_BATCH, rflags.p, flags));
     for (int k = 0; k < PRESOLVE_BATCH && !done; ++k) {
       ++rounds;
       if (flags[2 * k + 1])
@@ -864,7 +1029,7 @@ dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix) {
   DM_ALLOC(ctx, cnt_excl, size_t(nrows) + 1);
   DM_HIP(ctx, hipMemsetAsync(err.p, 0, 4 * sizeof(int), st));
   if (nc > 0)
-    k_row_residual<<<grid_for(nc, 128), 128, 0, st>>>(ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_coef.p,
+    k_row_residual<<<grid_for(nc, PS_ROWS), PS_ROWS, 0, st>>>(ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_coef.p,
                                                       ctx->row_b.p, nc, ctx->state.p, nfr.p, resid.p, keep.p,
                                                       err.p);
   if (nrows > nc)
@@ -894,10 +1059,10 @@ dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix) {
   DM_ALLOC(ctx, ctx->rent_coef, size_t(std::max(rnnz, 1)));
   DM_ALLOC(ctx, ctx->rent_word, size_t(std::max(rnnz, 1)));
   if (nc > 0)
-    k_reduced_fill<<<grid_for(nc, 128), 128, 0, st>>>(
-        ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_coef.p, ctx->ent_slot.p, nc, ctx->state.p, ctx->var_red.p,
-        ctx->free_var.p, keep.p, new_id.p, cnt_excl.p, resid.p, ctx->rrow_orig.p, ctx->rrow_ptr.p,
-        ctx->rrow_b.p, ctx->rent_var.p, ctx->rent_coef.p, ctx->rent_word.p);
+    k_reduced_fill<<<grid_for(nc, FILL_ROWS), 256, 0, st>>>(
+        ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_coef.p, ctx->ent_slot.p, nc, ctx->state.p, ctx->var_red.p, keep.p,
+        new_id.p, cnt_excl.p, resid.p, ctx->rrow_orig.p, ctx->rrow_ptr.p, ctx->rrow_b.p, ctx->rent_var.p,
+        ctx->rent_coef.p, ctx->rent_word.p);
   if (nrows > nc)
     k_reduced_fill_proj<<<unsigned(nrows - nc), 256, 0, st>>>(
       ctx->row_ptr.p, ctx->ent_var.p, ctx->ent_slot.p, nc, ctx->state.p, ctx->var_red.p, keep.p,
@@ -915,8 +1080,7 @@ dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix) {
     k_long_coefs<<<grid_for(rnnz, 256), 256, 0, st>>>(ctx->rrow_ptr.p, nshort, rnnz, ctx->rent_coef.p, err.p);
   DM_LAUNCH_CHECK(ctx);
   int stats[4];
-  DM_HIP(ctx, hipMemcpyAsync(stats, err.p, sizeof(stats), hipMemcpyDeviceToHost, st));
-  DM_HIP(ctx, hipStreamSynchronize(st));
+  DM_TRY(read_words(ctx, 4, err.p, stats));
   ctx->max_short = stats[2];
   if (stats[2] > MAX_SHORT_ROW)
     return dm_fail(ctx, DM_ERR_WORKSPACE, "a closedness row has %d > %d free entries", stats[2], MAX_SHORT_ROW);
@@ -942,8 +1106,7 @@ dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix) {
     DM_LAUNCH_CHECK(ctx);
   }
   int32_t bnd[2];
-  DM_HIP(ctx, hipMemcpyAsync(bnd, bound.p, sizeof(bnd), hipMemcpyDeviceToHost, st));
-  DM_HIP(ctx, hipStreamSynchronize(st));
+  DM_TRY(read_words(ctx, 2, bound.p, bnd));
   ctx->soft_c8 = bnd[0];
   ctx->soft_c16 = bnd[1] - bnd[0];
   return DM_OK;
