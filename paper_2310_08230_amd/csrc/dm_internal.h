@@ -345,6 +345,7 @@ struct dm_ctx {
   int32_t long_wpr = 1;       // waves per projection row: 1 or 4 (4 rows or 1 row per block)
   int32_t n_long_y = 0;       // Y projection rows, the first in long_perm
   DArr<int32_t> long_perm;    // n_rows - n_short: projection rows (relative to n_short) in launch order
+  DArr<int2> long_row;        // first cell and length of each, in launch order
   DArr<int32_t> long_ent;     // entry of each projection-row cell, relative to the first (none: in order)
   DArr<int32_t> soft_row;     // short rows sorted (stably) by length, for the smoothed sweep
   int64_t soft_c8 = 0, soft_c16 = 0;   // how many of them have <= 7 / 8..15 entries

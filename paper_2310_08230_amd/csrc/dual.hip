@@ -238,16 +238,25 @@ __device__ inline void write_out(R* __restrict__ out, uint32_t w, R v) {
   out[size_t(w & W_VAR_MASK) * REC + ((w >> W_SLOT_SHIFT) & 7u)] = v;
 }
 
-// block-wide FP64 sum of a 256-thread block in a fixed order: an xor butterfly
-// inside each wave (every lane ends with the same value, since a + b == b + a
-// exactly), then the four wave sums in index order
+// FP64 sum of a wave in a fixed order, the same value in every lane: DPP moves
+// inside rows of sixteen lanes (every pairing is symmetric), two shuffles across
+__device__ inline double wave_sum(double v) {
+  v += dpp_move<0xB1>(v);
+  v += dpp_move<0x4E>(v);
+  v += dpp_move<0x141>(v);
+  v += dpp_move<0x140>(v);
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+
+// block-wide FP64 sum of a 256-thread block in a fixed order (the waves in
+// index order); red is not reused after it
 __device__ inline double block_sum(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  double r = ((red[0] + red[1]) + red[2]) + red[3];
-  __syncthreads();
-  return r;
+  return ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 // Each block stores the sum of its row minima; the per-block partials of one
@@ -274,7 +283,7 @@ struct SweepArgs {
   const int8_t* chunk_b;    // 64 per chunk: right-hand side of the entry's row
   int32_t n_long_y;         // of the projection rows in launch order, the Y rows come first
   int32_t per[3 + TILE_FORMS];   // blocks per XCD: Y rows, X rows, chunks, tiles from the widest form down
-  int32_t n_entries_short;  // entries of the short rows
+  const int2* long_row;     // first cell and length of the projection rows in launch order
   const int32_t* long_ent;  // entry of each projection-row cell (ties in MODE_SUBGRAD), or NULL: in order
   // quasi-Newton extensions: rows see lambda + gamma * dir when dir is set
   // (one value per cell; gamma a device scalar); the launch does nothing when
@@ -927,19 +936,144 @@ __device__ inline MinState<R> ms_shfl_xor(MinState<R> v, int off) {
   return o;
 }
 
+// The hard minimum and second minimum alone.  Which entry holds the minimum
+// needs no index: an entry that equals it either is the only one, or the second
+// minimum equals it too.
+template <typename R>
+struct TwoMin {
+  R m, m2;
+  __device__ void take(R v) {   // a NaN is passed over
+    m2 = fmin(m2, m > v ? m : v);
+    m = fmin(m, v);
+  }
+  __device__ void join(R om, R om2) {
+    m2 = fmin(fmax(m, om), fmin(m2, om2));
+    m = fmin(m, om);
+  }
+  template <int CTRL>
+  __device__ void join_dpp() {
+    join(dpp_move<CTRL>(m), dpp_move<CTRL>(m2));
+  }
+  // over the first 4, 16 or 64 lanes of every aligned group
+  __device__ void join_group(int group) {
+    join_dpp<0xB1>();
+    join_dpp<0x4E>();
+    if (group > 4) {
+      join_dpp<0x141>();
+      join_dpp<0x140>();
+    }
+    if (group > 16) {
+      join(__shfl_xor(m, 16), __shfl_xor(m2, 16));
+      join(__shfl_xor(m, 32), __shfl_xor(m2, 32));
+    }
+  }
+};
+
 // one wave per projection row (four rows per block), or for long rows one
 // block per row (long_wpr = 4); each lane keeps up to LONG_REG of its row's
 // multipliers in registers between the two passes
 constexpr int LONG_REG = 8;
 constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD turn (smoothed)
 
-// Row lr of the launch order.  Hard: src holds the cells, t the residuals per
-// variable, dst takes the cells' new values (src and dst may be one array: a
-// lane reads its own cells before it writes them).  Smoothed: src and dst are
-// records.  Returns the row minimum on one lane of the row.
-template <typename R, bool SOFT, int MODE>
-__device__ __forceinline__ double long_rows(const SweepArgs& A, const R* src, const R* __restrict__ t, R* dst, R omega, R T, R gam,
-                            int32_t lr, bool has) {
+// Hard: the row's cells d.x .. d.x + d.y - 1 (d from long_row: first cell and
+// length, so that the words follow the descriptor at once).  A launch over few
+// blocks takes as long as its longest chain of loads and reductions: descriptor,
+// words, cells and residuals, six exchange steps of (m, m2), four of them as
+// register moves.  Against row number, offsets and an exchange of (m, m2, index)
+// through the LDS, an FP32 iteration takes 6.5-6.8 us (8.0) with 8k-30k entries,
+// 9.2 us (9.4) with 231k.  In place where
+// cells and dst are one array: a lane reads its own cells before it writes them.
+// Returns the row minimum on one lane of the row.
+template <typename R, int MODE>
+__device__ __forceinline__ double long_cells(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* dst,
+                                             R omega, R gam, int32_t lr, bool has) {
+  __shared__ R xm[4], xm2[4];
+  __shared__ int32_t xa[4];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wpr = A.long_wpr;   // uniform
+  const int sub = wave & (wpr - 1);
+  const int2 d = has ? A.long_row[lr] : make_int2(0, 0);
+  const uint32_t c0 = uint32_t(d.x);
+  const int32_t n = d.y, step = 64 * wpr, i0 = sub * 64 + lane;
+  const uint32_t* words = A.word + c0;
+  // the first LONG_REG entries of every lane without branches (past the row's
+  // end a lane reads the row's first entry and ignores it), the loads of a
+  // batch in flight together
+  constexpr int BATCH = 4;
+  uint32_t wv[LONG_REG];
+  R lv[LONG_REG];
+#pragma unroll
+  for (int u = 0; u < LONG_REG; ++u) {
+    const int32_t i = i0 + step * u;
+    wv[u] = n > 0 ? words[i < n ? i : 0] : 0u;
+  }
+  TwoMin<R> st{rinf<R>(), rinf<R>()};
+#pragma unroll
+  for (int u0 = 0; u0 < LONG_REG; u0 += BATCH) {
+    if (sub * 64 + step * u0 >= n) break;   // uniform: no lane of the wave has entries left
+#pragma unroll
+    for (int u = u0; u < u0 + BATCH; ++u) {
+      const int32_t i = i0 + step * u;
+      lv[u] = cell_lambda<R>(A, cells, t, c0 + uint32_t(i < n ? i : 0), wv[u], gam);
+    }
+#pragma unroll
+    for (int u = u0; u < u0 + BATCH; ++u)
+      if (i0 + step * u < n) st.take(lv[u]);
+  }
+  auto value = [&](int32_t i) { return cell_lambda<R>(A, cells, t, c0 + uint32_t(i), words[i], gam); };
+  for (int32_t i = i0 + step * LONG_REG; i < n; i += step) st.take(value(i));   // longer rows
+  st.join_group(64);
+  // which of several equal minima a row takes shows only in its assignment: the
+  // first in the row's entry order
+  int32_t first = INT32_MAX;
+  const int32_t* ent = A.long_ent ? A.long_ent + (c0 - A.long_cell0) : nullptr;
+  auto place = [&](int32_t i) { return ent ? ent[i] : i; };
+  if (wpr > 1) {   // the row's waves join: every wave ends with the same state
+    if (lane == 0) {
+      xm[wave] = st.m;
+      xm2[wave] = st.m2;
+    }
+    __syncthreads();
+    const int w0 = wave & ~(wpr - 1);
+    TwoMin<R> all{xm[w0], xm2[w0]};
+    for (int q = 1; q < wpr; ++q) all.join(xm[w0 + q], xm2[w0 + q]);
+    st = all;
+  }
+  if constexpr (MODE == MODE_SUBGRAD) {
+#pragma unroll
+    for (int u = 0; u < LONG_REG; ++u)
+      if (i0 + step * u < n && lv[u] == st.m) first = min(first, place(i0 + step * u));
+    for (int32_t i = i0 + step * LONG_REG; i < n; i += step)
+      if (value(i) == st.m) first = min(first, place(i));
+    for (int off = 32; off > 0; off >>= 1) first = min(first, __shfl_xor(first, off));
+    if (wpr > 1) {
+      if (lane == 0) xa[wave] = first;
+      __syncthreads();
+      for (int q = 0; q < wpr; ++q) first = min(first, xa[(wave & ~(wpr - 1)) + q]);
+    }
+  }
+  if (MODE != MODE_BOUND) {
+    auto finish = [&](int32_t i, R lam) {
+      const R M = lam - (lam == st.m ? st.m2 : st.m);
+      if (MODE == MODE_UPDATE) dst[c0 + uint32_t(i)] = fma_r<R>(-omega, M, lam);
+      if (MODE == MODE_EVAL) dst[c0 + uint32_t(i)] = M;
+      if (MODE == MODE_SUBGRAD) A.gsub[c0 + uint32_t(i)] = uint8_t(place(i) == first ? 1 : 0);
+    };
+#pragma unroll
+    for (int u = 0; u < LONG_REG; ++u) {
+      const int32_t i = i0 + step * u;
+      if (i < n) finish(i, lv[u]);
+    }
+    for (int32_t i = i0 + step * LONG_REG; i < n; i += step) finish(i, value(i));
+  }
+  return has && lane == 0 && sub == 0 ? double(st.m) : 0.0;
+}
+
+// Smoothed: row lr of the launch order on records; lanes stride the row's
+// entries as above.
+template <typename R, int MODE>
+__device__ double long_records(const SweepArgs& A, const R* __restrict__ src, R* __restrict__ dst, R omega, R T,
+                               int32_t lr, bool has) {
   __shared__ R xm[4], xm2[4], xs[4];
   __shared__ int32_t xa[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -954,29 +1088,16 @@ __device__ __forceinline__ double long_rows(const SweepArgs& A, const R* src, co
   st.m2 = rinf<R>();
   st.s = R(0);
   st.a = INT32_MAX;
-  // The first LONG_REG entries of every lane are loaded without branches
-  // (past the row's end a lane loads the row's first entry and ignores it), so
-  // that all loads of a batch are in flight together: the words, then what
-  // they point at.
-  const uint32_t c0 = A.long_cell0 + uint32_t(s - (has ? A.n_entries_short : 0));   // hard: the row's first cell
-  const uint32_t* words = SOFT ? A.ent_word + s : A.word + c0;
-  auto value = [&](int32_t i, uint32_t w) {
-    if constexpr (SOFT) return cur_lambda<R>(src, w);
-    else return cell_lambda<R>(A, src, t, c0 + uint32_t(i), w, gam);
-  };
-  // which of several equal minima a row takes shows only in its assignment
-  // (the min-marginals are the same): the first in the row's entry order
-  const int32_t* ent = !SOFT && MODE == MODE_SUBGRAD && A.long_ent && n > 0 ? A.long_ent + (s - A.n_entries_short) : nullptr;
-  auto place = [&](int32_t i) { return ent ? ent[i] : i; };
+  const uint32_t* words = A.ent_word + s;
   auto take = [&](int32_t i, R v) {
     MinState<R> one;
     one.m = v;
     one.m2 = rinf<R>();
     one.s = R(0);
-    one.a = place(i);
-    st = ms_combine<R, SOFT>(st, one, T);
+    one.a = i;
+    st = ms_combine<R, true>(st, one, T);
   };
-  constexpr int LONG_BATCH = SOFT ? 2 : 4;   // loads in flight together
+  constexpr int LONG_BATCH = 2;   // record loads in flight together
   uint32_t wv[LONG_REG];
   R lv[LONG_REG];
 #pragma unroll
@@ -987,27 +1108,19 @@ __device__ __forceinline__ double long_rows(const SweepArgs& A, const R* src, co
 #pragma unroll
   for (int u0 = 0; u0 < LONG_REG; u0 += LONG_BATCH) {
     if (sub * 64 + step * u0 >= n) break;   // uniform: no lane of the wave has entries left
-    if constexpr (SOFT) {
-      RecRaw<R> raw[LONG_BATCH];
+    RecRaw<R> raw[LONG_BATCH];
 #pragma unroll
-      for (int u = 0; u < LONG_BATCH; ++u) raw[u].load(src, wv[u0 + u] & W_VAR_MASK);
+    for (int u = 0; u < LONG_BATCH; ++u) raw[u].load(src, wv[u0 + u] & W_VAR_MASK);
 #pragma unroll
-      for (int u = 0; u < LONG_BATCH; ++u) lv[u0 + u] = raw[u].lambda(int((wv[u0 + u] >> W_SLOT_SHIFT) & 7u));
-    } else {
-#pragma unroll
-      for (int u = 0; u < LONG_BATCH; ++u) {
-        const int32_t i = i0 + step * (u0 + u);
-        lv[u0 + u] = value(i < n ? i : 0, wv[u0 + u]);
-      }
-    }
+    for (int u = 0; u < LONG_BATCH; ++u) lv[u0 + u] = raw[u].lambda(int((wv[u0 + u] >> W_SLOT_SHIFT) & 7u));
 #pragma unroll
     for (int u = 0; u < LONG_BATCH; ++u) {
       const int32_t i = i0 + step * (u0 + u);
       if (i < n) take(i, lv[u0 + u]);
     }
   }
-  for (int32_t i = i0 + step * LONG_REG; i < n; i += step) take(i, value(i, words[i]));   // longer rows
-  for (int off = 32; off > 0; off >>= 1) st = ms_combine<R, SOFT>(st, ms_shfl_xor<R, SOFT>(st, off), T);
+  for (int32_t i = i0 + step * LONG_REG; i < n; i += step) take(i, cur_lambda<R>(src, words[i]));   // longer rows
+  for (int off = 32; off > 0; off >>= 1) st = ms_combine<R, true>(st, ms_shfl_xor<R, true>(st, off), T);
   if (wpr > 1) {
     // the row's waves combine their states in index order: every wave of
     // the row ends with the same state
@@ -1030,42 +1143,26 @@ __device__ __forceinline__ double long_rows(const SweepArgs& A, const R* src, co
       o.m2 = xm2[w0 + q];
       o.s = xs[w0 + q];
       o.a = xa[w0 + q];
-      acc = ms_combine<R, SOFT>(acc, o, T);
+      acc = ms_combine<R, true>(acc, o, T);
     }
     st = acc;
   }
   double rowpart = 0.0;
   if (has) {
-    R rowv = st.m;
-    R tot = R(0);
-    if (SOFT) {
-      tot = (st.m2 == rinf<R>()) ? R(0) : st.s * r_exp<R>(-(st.m2 - st.m) / T);
-      rowv = st.m - T * r_log<R>(R(1) + tot);
-    }
+    const R tot = (st.m2 == rinf<R>()) ? R(0) : st.s * r_exp<R>(-(st.m2 - st.m) / T);
+    const R rowv = st.m - T * r_log<R>(R(1) + tot);
     if (MODE != MODE_BOUND) {
       auto finish = [&](int32_t i, uint32_t w, R lam) {
-        R M, mu = R(0);
-        if (!SOFT) {
-          M = lam - (i == st.a ? st.m2 : st.m);
+        R others;
+        if (i == st.a) {
+          others = st.m2 - T * r_log<R>(st.s);
         } else {
-          R others;
-          if (i == st.a) {
-            others = st.m2 - T * r_log<R>(st.s);
-          } else {
-            R e = r_exp<R>(-(lam - st.m) / T);
-            others = st.m - T * r_log<R>((R(1) + tot) - e);
-          }
-          M = lam - others;
-          mu = r_exp<R>(-(lam - rowv) / T);
+          R e = r_exp<R>(-(lam - st.m) / T);
+          others = st.m - T * r_log<R>((R(1) + tot) - e);
         }
-        if constexpr (SOFT) {
-          if (MODE == MODE_UPDATE) write_out<R>(dst, w, lam - omega * M);
-          if (MODE == MODE_EVAL) write_out<R>(dst, w, mu);
-        } else {
-          if (MODE == MODE_UPDATE) dst[c0 + uint32_t(i)] = fma_r<R>(-omega, M, lam);
-          if (MODE == MODE_EVAL) dst[c0 + uint32_t(i)] = M;
-          if (MODE == MODE_SUBGRAD) A.gsub[c0 + uint32_t(i)] = uint8_t(place(i) == st.a ? 1 : 0);
-        }
+        const R M = lam - others;
+        if (MODE == MODE_UPDATE) write_out<R>(dst, w, lam - omega * M);
+        if (MODE == MODE_EVAL) write_out<R>(dst, w, r_exp<R>(-(lam - rowv) / T));
       };
 #pragma unroll
       for (int u = 0; u < LONG_REG; ++u) {
@@ -1074,7 +1171,7 @@ __device__ __forceinline__ double long_rows(const SweepArgs& A, const R* src, co
       }
       for (int32_t i = i0 + step * LONG_REG; i < n; i += step) {
         const uint32_t w = words[i];
-        finish(i, w, value(i, w));
+        finish(i, w, cur_lambda<R>(src, w));
       }
     }
     if (lane == 0 && sub == 0) rowpart = double(rowv);
@@ -1140,7 +1237,7 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
       const int32_t item = yrow ? x * A.per[0] + k : x * A.per[1] + (k - A.per[0]);
       const int32_t r = item * rpb + wave / A.long_wpr;
       const int32_t lr = yrow ? r : A.n_long_y + r;
-      part = long_rows<R, false, MODE>(A, rin, t, out, omega, T, gam, lr, lr < (yrow ? A.n_long_y : A.n_long));
+      part = long_cells<R, MODE>(A, rin, t, out, omega, gam, lr, lr < (yrow ? A.n_long_y : A.n_long));
     } else if ((k -= A.per[0] + A.per[1]) < A.per[2]) {
       part = chunk_block<R, MODE>(A, rin, t, out, omega, gam, smem, x * A.per[2] + k);
     } else if ((k -= A.per[2]) < A.per[3]) {
@@ -1180,7 +1277,7 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
         short_rows_soft<R, MODE, 32>(A, rin, out, omega, T, smem, red, item, item - nb8 - nb16, c816, A.n_short);
     } else {
       const int32_t lr = (item - A.n_short_blocks) * (4 / A.long_wpr) + int32_t(threadIdx.x >> 6) / A.long_wpr;
-      const double part = long_rows<R, true, MODE>(A, rin, nullptr, out, omega, T, R(0), lr, lr < A.n_long);
+      const double part = long_records<R, MODE>(A, rin, out, omega, T, lr, lr < A.n_long);
       store_partial(block_sum(part, red), A.partial, item);
     }
   }
@@ -1267,37 +1364,23 @@ __global__ __launch_bounds__(NT) void k_small(SweepArgs A, const uint32_t* __res
     for (; w0 * rpw < A.n_long; w0 += NW) {
       const int32_t lr = w0 * rpw + lane / group, i0 = lane & (group - 1);
       const bool has = lr < A.n_long;
-      const int32_t s0 = has ? A.rrow_ptr[A.n_short + lr] : 0;
-      const int32_t len = has ? A.rrow_ptr[A.n_short + lr + 1] - s0 : 0;
-      const uint32_t c0 = A.long_cell0 + uint32_t(has ? s0 - A.n_entries_short : 0);
+      const int2 d = has ? A.long_row[lr] : make_int2(0, 0);
+      const uint32_t c0 = uint32_t(d.x);
+      const int32_t len = d.y;
       auto value = [&](int32_t i) { return cell_lambda<R>(A, cells, t, c0 + uint32_t(i), A.word[c0 + uint32_t(i)], R(0)); };
       R lv[SMALL_LREG];
-      MinState<R> st;
-      st.m = st.m2 = rinf<R>();
-      st.s = R(0);
-      st.a = INT32_MAX;
-      auto take = [&](int32_t i, R v) {
-        MinState<R> one;
-        one.m = v;
-        one.m2 = rinf<R>();
-        one.s = R(0);
-        one.a = i;
-        st = ms_combine<R, false>(st, one, R(0));
-      };
+      TwoMin<R> st{rinf<R>(), rinf<R>()};
 #pragma unroll
       for (int u = 0; u < SMALL_LREG; ++u) {
         const int32_t i = i0 + u * group;
         lv[u] = i < len ? value(i) : rinf<R>();
       }
 #pragma unroll
-      for (int u = 0; u < SMALL_LREG; ++u) {
-        const int32_t i = i0 + u * group;
-        if (i < len) take(i, lv[u]);
-      }
-      for (int32_t i = i0 + SMALL_LREG * group; i < len; i += group) take(i, value(i));
-      for (int off = group / 2; off > 0; off >>= 1) st = ms_combine<R, false>(st, ms_shfl_xor<R, false>(st, off), R(0));
+      for (int u = 0; u < SMALL_LREG; ++u) st.take(lv[u]);
+      for (int32_t i = i0 + SMALL_LREG * group; i < len; i += group) st.take(value(i));
+      st.join_group(group);
       auto finish = [&](int32_t i, R v) {
-        cells[c0 + uint32_t(i)] = fma_r<R>(-omega, v - (i == st.a ? st.m2 : st.m), v);
+        cells[c0 + uint32_t(i)] = fma_r<R>(-omega, v - (v == st.m ? st.m2 : st.m), v);
       };
 #pragma unroll
       for (int u = 0; u < SMALL_LREG; ++u) {
@@ -1308,7 +1391,7 @@ __global__ __launch_bounds__(NT) void k_small(SweepArgs A, const uint32_t* __res
       if (has && i0 == 0) sum += double(st.m);
     }
     if (trace) {
-      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+      sum = wave_sum(sum);
       if (lane == 0) part[it & 1][wave] = sum;
     }
     __syncthreads();
@@ -1644,7 +1727,7 @@ static void hard_args(const dm_ctx* ctx, SweepArgs& A) {
   A.chunk_neg = ctx->chunk_neg.p;
   A.chunk_b = ctx->chunk_b.p;
   A.n_long_y = ctx->n_long_y;
-  A.n_entries_short = int32_t(ctx->nnz_short);
+  A.long_row = ctx->long_row.p;
   A.long_ent = ctx->long_ent.p;
   hard_blocks(ctx, A.per);
 }

@@ -315,6 +315,15 @@ __global__ void k_long_keys(const int32_t* rrow_ptr, const int32_t* rrow_orig, c
   if (y) atomicAdd(n_y, 1);
 }
 
+// first cell and length of the projection rows in launch order
+__global__ void k_long_rows(const int32_t* perm, const int32_t* rrow_ptr, int64_t n_short, int64_t n_long,
+                            uint32_t cell0, int2* row) {
+  const int64_t l = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (l >= n_long) return;
+  const int64_t j = n_short + perm[l];
+  row[l] = make_int2(int32_t(cell0 + uint32_t(rrow_ptr[j] - rrow_ptr[n_short])), rrow_ptr[j + 1] - rrow_ptr[j]);
+}
+
 // ---------------------------------------------------------------- short rows left to the chunks
 __global__ void k_perm_len(const int32_t* perm, const int32_t* rrow_ptr, const int32_t* rrow_b, int64_t n,
                            int32_t* len, int32_t* pb) {
@@ -614,7 +623,10 @@ dm_status sweep_layout(dm_ctx* ctx) {
   // the same XCD gathers at nearly the same time.  A generic problem's
   // variables are in the order of its rows as they are.
   const int64_t nl = rnnz - ctx->nnz_short;
+  DM_ALLOC(ctx, ctx->long_row, size_t(std::max<int64_t>(nlong, 1)));
   if (nl > 0) {
+    k_long_rows<<<grid_for(nlong, 256), 256, 0, st>>>(ctx->long_perm.p, ctx->rrow_ptr.p, nshort, nlong,
+                                                      uint32_t(long0), ctx->long_row.p);
     if (mesh) {
       DM_ALLOC(ctx, ctx->long_ent, size_t(nl));
       const int bb = bits_for(uint64_t(RANK_BINS - 1));
