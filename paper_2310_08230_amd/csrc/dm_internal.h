@@ -2,6 +2,7 @@
 // buffers and the entry points of each translation unit.
 #pragma once
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -205,11 +206,41 @@ __device__ inline void rec_lambdas(const R* __restrict__ rec, size_t i, R lam[5]
   lam[4] = s4 + corr;
 }
 
-// FP64 sum of a 256-thread block in a fixed order: an xor butterfly inside
-// each wave (every lane ends with the same value, since a + b == b + a
-// exactly), then the four wave sums in index order.  red: 4 doubles of LDS.
+// One DPP lane move (a VALU operation): ctrl 0xB1 swaps neighbours (quad
+// permutation 1,0,3,2), 0x4E swaps pairs (2,3,0,1), 0x141 mirrors each group of
+// eight lanes, 0x140 each row of sixteen; 0x138 shifts the whole wave by one
+// lane (lane i reads lane i - 1), 0x130 the other way (lane i reads i + 1).
+// A lane whose source is missing reads 0; callers mask those lanes.
+template <int CTRL, typename R>
+__device__ inline R dpp_move(R v) {
+  if constexpr (sizeof(R) == 4) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+  } else {
+    const long long bits = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp(int(bits & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(int(bits >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((static_cast<long long>(hi) << 32) | (static_cast<long long>(lo) & 0xFFFFFFFFll));
+  }
+}
+
+// FP64 sum of a full wave, the same value in every lane: lanes 32, 16, 8, 4, 2 and
+// 1 apart in turn (a + b == b + a exactly).  Two exchanges through the LDS; once
+// lanes 16 apart agree, the rotations inside rows of sixteen lanes, register
+// moves, fetch the same values as an exchange would.
+__device__ inline double wave_sum(double v) {
+  v += __shfl_xor(v, 32);
+  v += __shfl_xor(v, 16);
+  v += dpp_move<0x128>(v);   // rotate by 8
+  v += dpp_move<0x124>(v);   // by 4: lanes 8 apart agree
+  v += dpp_move<0x4E>(v);
+  v += dpp_move<0xB1>(v);
+  return v;
+}
+
+// FP64 sum of a 256-thread block in a fixed order: the four wave sums in index
+// order.  red: 4 doubles of LDS.
 __device__ inline double block_sum_256(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   const double r = ((red[0] + red[1]) + red[2]) + red[3];
@@ -242,7 +273,7 @@ __device__ inline double sum_partials_1024(const double* p, int n, double* red) 
       if (i + 1024 * u < n) a[u] += p[i + 1024 * u];
   }
   double v = ((((((a[0] + a[1]) + a[2]) + a[3]) + a[4]) + a[5]) + a[6]) + a[7];
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = 0.0;
@@ -345,6 +376,16 @@ struct dm_ctx {
   int32_t long_wpr = 1;       // waves per projection row: 1 or 4 (4 rows or 1 row per block)
   int32_t n_long_y = 0;       // Y projection rows, the first in long_perm
   DArr<int32_t> long_perm;    // n_rows - n_short: projection rows (relative to n_short) in launch order
+  DArr<uint32_t> vkey;        // mesh key of every reduced variable (bound_order)
+  DArr<int32_t> short_perm;   // short rows in cell order: the tile forms, then the chunks
+  int32_t tile_rows[TILE_FORMS] = {0};   // rows of each tile form
+  // order of the bound's terms in FP64 (bound_order; made on first use)
+  bool has_bound_order = false;
+  int32_t term_tiles = 0, term_chunks = 0;   // blocks of 256 tile rows, of four chunks
+  DArr<unsigned char> term_mem;
+  int32_t *term_row = nullptr, *term_long = nullptr;   // place of every tile row (cell order), projection row
+  double *terms = nullptr, *term_part = nullptr;       // the terms of one sweep, their sums per block
+  uint32_t* cpos = nullptr;                            // vpos with the variables in canonical order
   DArr<int2> long_row;        // first cell and length of each, in launch order
   DArr<int32_t> long_ent;     // entry of each projection-row cell, relative to the first (none: in order)
   DArr<int32_t> soft_row;     // short rows sorted (stably) by length, for the smoothed sweep
@@ -443,6 +484,40 @@ dm_status corner_lists(dm_ctx* ctx);  // corners per candidate pair (built once 
 void fill_info(dm_ctx* ctx, dm_space_info* info);   // sizes of the current (reduced) problem
 dm_status presolve_reduce(dm_ctx* ctx, const int8_t* fix);  // presolve from fixings, reduced problem
 dm_status sweep_layout(dm_ctx* ctx);   // cells, variable order and launch order of the hard sweep
+// Several arrays in one allocation: add() every size, then allocate base bytes
+// and take() the arrays in the same order.  What a first call allocates counts
+// (a block from the pool costs about 10 us of host time).
+struct Slab {
+  size_t bytes = 0;
+  unsigned char* at = nullptr;
+  static size_t room(size_t b) { return (std::max<size_t>(b, 1) + 255) / 256 * 256; }
+  template <typename T>
+  void add(int64_t n) { bytes += room(sizeof(T) * size_t(n)); }
+  template <typename T>
+  T* take(int64_t n) {
+    T* q = reinterpret_cast<T*>(at);
+    at += room(sizeof(T) * size_t(n));
+    return q;
+  }
+};
+// The terms of a bound in an order of the problem's own (bound_order): those of
+// the short rows in blocks of 256, then those of the projection rows in blocks
+// of rpb rows.
+struct TermSums {
+  const double* terms = nullptr;   // NULL: not used
+  int32_t n_blocks = 0, n_long = 0, rpb = 1, n_long_blocks = 0;
+  __device__ double long_block(int32_t q) const {
+    const double* t = terms + size_t(n_blocks) * 256;
+    double s = t[q * rpb];
+    for (int u = 1; u < rpb; ++u) s += q * rpb + u < n_long ? t[q * rpb + u] : 0.0;
+    return s;
+  }
+};
+dm_status bound_order(dm_ctx* ctx);
+TermSums term_sums(const dm_ctx* ctx);
+// sums per block into ctx->term_part; nothing is done when *skip (device, may be
+// NULL) is nonzero
+dm_status sum_terms(dm_ctx* ctx, const TermSums& T, const int32_t* skip);
 
 // Sweeps over all rows of the presolved problem (dual.hip).  Modes: update the
 // multipliers, write min-marginals (or soft marginals), bound only, or write
@@ -457,6 +532,7 @@ struct SweepExt {
   const double* gamma = nullptr;
   const int32_t* skip = nullptr;
   uint8_t* gsub = nullptr;
+  double* terms = nullptr;   // FP64 SWEEP_BOUND and SWEEP_SUBGRAD: every row's term to its place (bound_order)
 };
 // hard sweep: state from multipliers in entry order (two: both buffers), t of
 // every variable (after every change of the cells), a row pass, and back

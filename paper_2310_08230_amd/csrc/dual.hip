@@ -122,23 +122,6 @@ __device__ inline R smin2u(R a, R b) {
   return fmin(a, b) - SoftUnits<R>::L1p(SoftUnits<R>::E(-fabs(ac - bc)));
 }
 
-// One DPP lane move (a VALU operation): ctrl 0xB1 swaps neighbours (quad
-// permutation 1,0,3,2), 0x4E swaps pairs (2,3,0,1), 0x141 mirrors each group of
-// eight lanes, 0x140 each row of sixteen; 0x138 shifts the whole wave by one
-// lane (lane i reads lane i - 1), 0x130 the other way (lane i reads i + 1).
-// A lane whose source is missing reads 0; callers mask those lanes.
-template <int CTRL, typename R>
-__device__ inline R dpp_move(R v) {
-  if constexpr (sizeof(R) == 4) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
-  } else {
-    const long long bits = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp(int(bits & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(int(bits >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double((static_cast<long long>(hi) << 32) | (static_cast<long long>(lo) & 0xFFFFFFFFll));
-  }
-}
-
 // min / sum over the W lanes (W = 8, 16 or 32) of an aligned segment, the same
 // value in every lane: DPP steps within each sixteen-lane row (every pairing
 // is symmetric, so all lanes form the same sums), one shuffle joins two rows
@@ -238,18 +221,6 @@ __device__ inline void write_out(R* __restrict__ out, uint32_t w, R v) {
   out[size_t(w & W_VAR_MASK) * REC + ((w >> W_SLOT_SHIFT) & 7u)] = v;
 }
 
-// FP64 sum of a wave in a fixed order, the same value in every lane: DPP moves
-// inside rows of sixteen lanes (every pairing is symmetric), two shuffles across
-__device__ inline double wave_sum(double v) {
-  v += dpp_move<0xB1>(v);
-  v += dpp_move<0x4E>(v);
-  v += dpp_move<0x141>(v);
-  v += dpp_move<0x140>(v);
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
-}
-
 // block-wide FP64 sum of a 256-thread block in a fixed order (the waves in
 // index order); red is not reused after it
 __device__ inline double block_sum(double v, double* red) {
@@ -293,6 +264,10 @@ struct SweepArgs {
   const double* gamma;
   const int32_t* skip;
   uint8_t* gsub;
+  // FP64 bounds of the quasi-Newton search: every row's term goes to its place
+  double* terms;
+  const int32_t *term_row, *term_long;
+  int32_t tile_rows[TILE_FORMS], term_chunk0, term_long0;
   // ---- smoothed: records
   const uint32_t* ent_word;   // per entry: sign, slot, variable
   const int32_t* soft_row;  // short rows in order of length
@@ -1213,6 +1188,15 @@ __global__ __launch_bounds__(256) void k_vars(const uint32_t* __restrict__ vpos,
   t[v] = c - ((((s[0] + s[1]) + s[2]) + s[3]) + s[4]);
 }
 
+// the terms of the tile rows of a block to their places
+__device__ inline void tile_term(const SweepArgs& A, double part, int form, int32_t item) {
+  if (!A.terms) return;   // uniform
+  int32_t row0 = 0;
+  for (int f = 0; f < form; ++f) row0 += A.tile_rows[f];
+  const int32_t r = item * 256 + int32_t(threadIdx.x);
+  if (r < A.tile_rows[form]) A.terms[A.term_row[row0 + r]] = part;
+}
+
 template <typename R, bool SOFT, int MODE>
 __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const R* __restrict__ t, R* out, R omega,
                                                R T) {
@@ -1229,6 +1213,7 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
     // neighbouring rows need neighbouring ones of them.)
     const R gam = A.gamma ? R(*A.gamma) : R(0);
     const int wave = threadIdx.x >> 6;
+    constexpr bool TERMS = sizeof(R) == 8 && (MODE == MODE_BOUND || MODE == MODE_SUBGRAD);
     double part = 0.0;
     int32_t k = k0;
     if (k < A.per[0] + A.per[1]) {
@@ -1237,15 +1222,25 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
       const int32_t item = yrow ? x * A.per[0] + k : x * A.per[1] + (k - A.per[0]);
       const int32_t r = item * rpb + wave / A.long_wpr;
       const int32_t lr = yrow ? r : A.n_long_y + r;
-      part = long_cells<R, MODE>(A, rin, t, out, omega, gam, lr, lr < (yrow ? A.n_long_y : A.n_long));
+      const bool has = lr < (yrow ? A.n_long_y : A.n_long);
+      part = long_cells<R, MODE>(A, rin, t, out, omega, gam, lr, has);
+      if constexpr (TERMS)
+        if (A.terms && has && (threadIdx.x & (64 * A.long_wpr - 1)) == 0) A.terms[A.term_long0 + A.term_long[lr]] = part;
     } else if ((k -= A.per[0] + A.per[1]) < A.per[2]) {
       part = chunk_block<R, MODE>(A, rin, t, out, omega, gam, smem, x * A.per[2] + k);
+      if constexpr (TERMS) {
+        const int32_t c = (x * A.per[2] + k) * 4 + wave;
+        if (A.terms && c < A.n_chunks) A.terms[A.term_chunk0 + c * 64 + int32_t(threadIdx.x & 63)] = part;
+      }
     } else if ((k -= A.per[2]) < A.per[3]) {
       part = tile_block<R, MODE, 2>(A, rin, t, out, omega, gam, x * A.per[3] + k);
+      if constexpr (TERMS) tile_term(A, part, 2, x * A.per[3] + k);
     } else if ((k -= A.per[3]) < A.per[4]) {
       part = tile_block<R, MODE, 1>(A, rin, t, out, omega, gam, x * A.per[4] + k);
+      if constexpr (TERMS) tile_term(A, part, 1, x * A.per[4] + k);
     } else {
       part = tile_block<R, MODE, 0>(A, rin, t, out, omega, gam, x * A.per[5] + (k - A.per[4]));
+      if constexpr (TERMS) tile_term(A, part, 0, x * A.per[5] + (k - A.per[4]));
     }
     store_partial(block_sum(part, red), A.partial, int32_t(blockIdx.x));
   } else {
@@ -1745,6 +1740,14 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
     A.gamma = ext->gamma;
     A.skip = ext->skip;
     A.gsub = ext->gsub;
+    if (ext->terms) {
+      A.terms = ext->terms;
+      A.term_row = ctx->term_row;
+      A.term_long = ctx->term_long;
+      for (int f = 0; f < TILE_FORMS; ++f) A.tile_rows[f] = ctx->tile_rows[f];
+      A.term_chunk0 = ctx->term_tiles * 256;
+      A.term_long0 = (ctx->term_tiles + ctx->term_chunks) * 256;
+    }
   }
   const int64_t grid = hard_grid(ctx);
   if (grid == 0) return empty_sweep(ctx, bound_out);

@@ -464,6 +464,153 @@ dm_status mesh_ranks(dm_ctx* ctx, MeshDev& M, DArr<int32_t>& frank, DArr<int32_t
   return DM_OK;
 }
 
+// ---------------------------------------------------------------- order of the bound's terms
+// A quasi-Newton search compares bounds.  Where the relaxation is tight these
+// differ in their last bits only, so the order in which the rows' terms are
+// added decides the steps that the search takes.  In FP32 it does not (a term
+// has 24 bits, the sums 53); in FP64 the terms are therefore added in an order
+// of the problem's own, which no change of the launch layout touches: the tile
+// rows by their smallest X rank and row number, 256 to a block; the chunks,
+// four to a block; the projection rows by (region, key), where the regions are
+// the eighths of all entries in key order, an X row has the key of its face and
+// the Y rows are dealt to the regions in turn.
+constexpr int NREG = 8;
+
+// what needs no order yet, in one launch: vpos with the variables in canonical
+// order, the row counts in variable order, the inverses of the two row orders,
+// empty regions, and zeros in the places past the last row
+__global__ void k_term_start(const uint32_t* vpos, const int32_t* vinv, const uint8_t* vdeg, int64_t n, uint32_t* cpos,
+                             int32_t* deg, const int32_t* short_perm, int64_t n_short, int32_t* short_slot,
+                             const int32_t* long_perm, int64_t n_long, int32_t* long_slot, int64_t n_terms,
+                             double* terms, int32_t* bounds) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) {
+    const int32_t v = vinv[i];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) cpos[q * n + i] = vpos[q * n + v];
+    deg[i] = vdeg[i];
+  }
+  if (i < n_short) short_slot[short_perm[i]] = int32_t(i);
+  if (i < n_long) long_slot[long_perm[i]] = int32_t(i);
+  if (i < n_terms) terms[i] = 0.0;
+  if (i < 2 * NREG) bounds[i] = (i & 1) ? -2 : -1;
+}
+
+// pre[k]: entries of the variables of keys below k, for k = 0 .. nkeys, from
+// their running sum in variable order
+__global__ void k_key_prefix(const uint32_t* vkey, const int32_t* vperm, const int32_t* sum, int ybits, int64_t n,
+                             int32_t nkeys, int32_t* pre) {
+  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (v > n) return;
+  const int32_t hi = v < n ? int32_t(vkey[vperm[v]] >> ybits) : nkeys;
+  int32_t lo = v > 0 ? int32_t(vkey[vperm[v - 1]] >> ybits) : -1;
+  while (lo < hi) pre[++lo] = sum[v];
+}
+
+// region of a key: the eighth in which the middle of its own entries falls
+__device__ inline int32_t key_region(const int32_t* pre, int32_t k, int64_t total) {
+  const int64_t mid2 = int64_t(pre[k]) + pre[k + 1];
+  const int64_t r = total > 0 ? (NREG * mid2) / (2 * total) : 0;
+  return int32_t(r < 0 ? 0 : (r >= NREG ? NREG - 1 : r));
+}
+
+// first and last key of every region (bounds[2 r], bounds[2 r + 1]; k_term_start
+// wrote -1 and -2); regions never decrease with the key
+__global__ void k_region_keys(const int32_t* pre, int32_t nkeys, int64_t total, int32_t* bounds) {
+  const int32_t k = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (k >= nkeys) return;
+  const int32_t r = key_region(pre, k, total);
+  if (k == 0 || key_region(pre, k - 1, total) != r) bounds[2 * r] = k;
+  if (k == nkeys - 1 || key_region(pre, k + 1, total) != r) bounds[2 * r + 1] = k;
+}
+
+// tile rows first (their place in cell order, slot, is below n_tile), by the
+// smallest X rank of their entries
+__global__ void k_term_keys(const int32_t* rrow_ptr, const uint32_t* word, const uint32_t* vkey, const int32_t* slot,
+                            int64_t n_short, int64_t n_tile, int ybits, int kbits, uint32_t* key, int32_t* val) {
+  const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (j >= n_short) return;
+  const bool tile = slot[j] < n_tile;
+  uint32_t m = tile ? 0xFFFFFFFFu : 0u;
+  if (tile)
+    for (int32_t e = rrow_ptr[j]; e < rrow_ptr[j + 1]; ++e) m = min(m, vkey[word[e] & W_VAR_MASK] >> ybits);
+  if (rrow_ptr[j] == rrow_ptr[j + 1]) m = 0u;
+  key[j] = (tile ? 0u : (1u << kbits)) | m;
+  val[j] = int32_t(j);
+}
+
+// projection rows: (region, key); first_y_full as in k_long_keys, n_y Y rows,
+// which are the last of the projection rows; a generic problem's rows all take
+// their smallest key (one wave per row)
+__global__ void k_term_long_keys(const int32_t* rrow_ptr, const int32_t* rrow_orig, const uint32_t* word,
+                                 const uint32_t* vkey, int64_t n_short, int64_t n_long, int64_t first_y_full,
+                                 int64_t n_y, int ybits, int kbits, const int32_t* pre, int64_t total,
+                                 const int32_t* bounds, uint32_t* key, int32_t* val) {
+  const int64_t l = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (l >= n_long) return;   // uniform across the wave
+  const int64_t j = n_short + l;
+  int32_t r, k;
+  if (rrow_orig[j] < first_y_full) {
+    uint32_t m = 0x7FFFFFFFu;
+    for (int32_t e = rrow_ptr[j] + int32_t(threadIdx.x & 63); e < rrow_ptr[j + 1]; e += 64)
+      m = min(m, vkey[word[e] & W_VAR_MASK] >> ybits);
+    for (int off = 32; off > 0; off >>= 1) m = min(m, uint32_t(__shfl_xor(int(m), off)));
+    k = m == 0x7FFFFFFFu ? 0 : int32_t(m);
+    r = key_region(pre, k, total);
+  } else {
+    const int64_t o = l - (n_long - n_y);
+    r = int32_t(o % NREG);
+    const int64_t per = (n_y - r + NREG - 1) / NREG;   // Y rows of region r
+    const int32_t lo = bounds[2 * r], hi = bounds[2 * r + 1];
+    const int64_t span = hi >= lo ? int64_t(hi) - lo + 1 : 1;
+    k = int32_t((hi >= lo ? lo : 0) + ((o / NREG) * span) / (per > 0 ? per : 1));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    key[l] = (uint32_t(r) << kbits) | uint32_t(k);
+    val[l] = int32_t(l);
+  }
+}
+
+// place[slot of the k-th row in order] = k: slot is the row's number in the
+// order that the sweep counts in
+__global__ void k_term_place(const int32_t* order, const int32_t* slot, int64_t n, int32_t* place) {
+  const int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (k < n) place[slot[order[k]]] = int32_t(k);
+}
+
+// The same for few rows without the sort: one wave counts the rows before its
+// own by (key, row number).  4000 rows 11 us, 16384 rows 92 us, the sort's
+// dozen launches 150 us at either size.
+constexpr int64_t RANK_BY_COUNT = 16384;
+
+__global__ __launch_bounds__(256) void k_rank_place(const uint32_t* key, const int32_t* slot, int32_t n,
+                                                    int32_t n_place, int32_t* place) {
+  const int32_t j = int32_t(blockIdx.x) * 4 + int32_t(threadIdx.x >> 6);
+  if (j >= n) return;   // uniform across the wave
+  const uint32_t mine = key[j];
+  int32_t before = 0;
+  for (int32_t m = int32_t(threadIdx.x & 63); m < n; m += 64) {
+    const uint32_t k = key[m];
+    before += (k < mine || (k == mine && m < j)) ? 1 : 0;
+  }
+  for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+  if ((threadIdx.x & 63) == 0 && before < n_place) place[slot[j]] = before;
+}
+
+// terms of the short rows 256 to a block, then of the projection rows per
+// block of 4 / wpr rows (one thread each)
+__global__ __launch_bounds__(256) void k_sum_terms(TermSums T, const int32_t* skip, double* part) {
+  __shared__ double red[4];
+  if (skip && *skip) return;   // uniform
+  if (int32_t(blockIdx.x) < T.n_blocks) {
+    const double s = block_sum_256(T.terms[size_t(blockIdx.x) * 256 + threadIdx.x], red);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
+    return;
+  }
+  const int32_t q = (int32_t(blockIdx.x) - T.n_blocks) * 256 + int32_t(threadIdx.x);
+  if (q < T.n_long_blocks) part[T.n_blocks + q] = T.long_block(q);
+}
+
 }  // namespace
 
 // mean projection-row length above which a projection row gets a whole block
@@ -479,8 +626,10 @@ dm_status sweep_layout(dm_ctx* ctx) {
   // 2^31 slots, so the two ranks of an element together fit 32 bits
   const int xbits = bits_for(mesh ? uint64_t(ctx->X.nf) : uint64_t(std::max<int64_t>(nfree, 1)));
   const int ybits = mesh ? bits_for(uint64_t(ctx->Y.nf)) : 0;
-  DArr<uint32_t> vkey, vsort;
+  DArr<uint32_t> vsort;
+  DArr<uint32_t>& vkey = ctx->vkey;
   DM_ALLOC(ctx, vkey, nf1);
+  ctx->has_bound_order = false;
   DM_ALLOC(ctx, ctx->vperm, nf1);
   DM_ALLOC(ctx, ctx->vinv, nf1);
   DM_ALLOC(ctx, ctx->vdeg, nf1);
@@ -509,7 +658,8 @@ dm_status sweep_layout(dm_ctx* ctx) {
   const int ydrop = full > 32 ? full - 32 : (full > 24 && full <= 26 && ybits > 2 ? full - 24 : 0);
   const int kbits = xbits + ybits - ydrop;
   DArr<uint32_t> skey, lkey;
-  DArr<int32_t> perm, count;
+  DArr<int32_t> count;
+  DArr<int32_t>& perm = ctx->short_perm;
   DM_ALLOC(ctx, skey, size_t(std::max<int64_t>(nshort, 1)));
   DM_ALLOC(ctx, perm, size_t(std::max<int64_t>(nshort, 1)));
   DM_ALLOC(ctx, lkey, size_t(std::max<int64_t>(nlong, 1)));
@@ -592,6 +742,7 @@ dm_status sweep_layout(dm_ctx* ctx) {
   ctx->n_chunks = n_chunks;
   int64_t chunk0 = 0;
   for (int f = 0; f < TILE_FORMS; ++f) {
+    ctx->tile_rows[f] = n_tile_rows[f];
     ctx->n_tiles[f] = (n_tile_rows[f] + 63) / 64;
     ctx->tile_cell0[f] = chunk0;
     chunk0 += int64_t(ctx->n_tiles[f]) * 128 * TILE_HALF[f];
@@ -640,6 +791,114 @@ dm_status sweep_layout(dm_ctx* ctx) {
                                                    uint32_t(long0), ctx->vinv.p, ctx->var_deg.p, nfree,
                                                    ctx->cell_word.p, ctx->ent_cell.p, ctx->vpos.p);
   }
+  DM_LAUNCH_CHECK(ctx);
+  return DM_OK;
+}
+
+// place[slot[row]] for the first n_place of n rows in order of (key, row number);
+// order: the row numbers, and scratch
+static dm_status place_rows(dm_ctx* ctx, uint32_t* key, int32_t* order, const int32_t* slot, int64_t n,
+                            int64_t n_place, int bits, int32_t* place) {
+  if (n <= RANK_BY_COUNT) {
+    k_rank_place<<<grid_for(n, 4), 256, 0, ctx->stream>>>(key, slot, int32_t(n), int32_t(n_place), place);
+  } else {
+    DM_TRY(sort_pairs_u32(ctx, key, order, size_t(n), bits));
+    k_term_place<<<grid_for(n_place, 256), 256, 0, ctx->stream>>>(order, slot, n_place, place);
+  }
+  DM_LAUNCH_CHECK(ctx);
+  return DM_OK;
+}
+
+dm_status bound_order(dm_ctx* ctx) {
+  if (ctx->has_bound_order) return DM_OK;
+  hipStream_t st = ctx->stream;
+  const int64_t nfree = ctx->n_free, nshort = ctx->n_short, nlong = ctx->n_rows - nshort, total = ctx->nnz;
+  const bool mesh = !ctx->generic && ctx->X.nf > 0;
+  const int32_t nkeys = mesh ? ctx->X.nf : int32_t(std::max<int64_t>(nfree, 1));
+  const int ybits = mesh ? bits_for(uint64_t(ctx->Y.nf)) : 0, kbits = bits_for(uint64_t(nkeys));
+  const int64_t ntile = int64_t(ctx->tile_rows[0]) + ctx->tile_rows[1] + ctx->tile_rows[2];
+  ctx->term_tiles = int32_t((ntile + 255) / 256);
+  ctx->term_chunks = (ctx->n_chunks + 3) / 4;
+  const int32_t nb = ctx->term_tiles + ctx->term_chunks;
+  DArr<unsigned char> tmp;
+  uint32_t *skey = nullptr, *lkey = nullptr;
+  int32_t *sorder = nullptr, *lorder = nullptr, *sslot = nullptr, *lslot = nullptr;
+  int32_t *deg = nullptr, *wsum = nullptr, *pre = nullptr, *bounds = nullptr;
+  {
+    Slab k;
+    k.add<double>(int64_t(nb) * 256 + nlong);
+    k.add<double>(nb + nlong);
+    k.add<int32_t>(ntile);
+    k.add<int32_t>(nlong);
+    k.add<uint32_t>(5 * nfree);
+    DM_ALLOC(ctx, ctx->term_mem, k.bytes);
+    k.at = ctx->term_mem.p;
+    ctx->terms = k.take<double>(int64_t(nb) * 256 + nlong);
+    ctx->term_part = k.take<double>(nb + nlong);
+    ctx->term_row = k.take<int32_t>(ntile);
+    ctx->term_long = k.take<int32_t>(nlong);
+    ctx->cpos = k.take<uint32_t>(5 * nfree);
+    Slab w;
+    for (int q = 0; q < 3; ++q) w.add<int32_t>(nshort);
+    for (int q = 0; q < 3; ++q) w.add<int32_t>(nlong);
+    w.add<int32_t>(nfree);
+    w.add<int32_t>(nfree + 1);
+    w.add<int32_t>(nkeys + 1);
+    w.add<int32_t>(2 * NREG);
+    DM_ALLOC(ctx, tmp, w.bytes);
+    w.at = tmp.p;
+    skey = w.take<uint32_t>(nshort);
+    sorder = w.take<int32_t>(nshort);
+    sslot = w.take<int32_t>(nshort);
+    lkey = w.take<uint32_t>(nlong);
+    lorder = w.take<int32_t>(nlong);
+    lslot = w.take<int32_t>(nlong);
+    deg = w.take<int32_t>(nfree);
+    wsum = w.take<int32_t>(nfree + 1);
+    pre = w.take<int32_t>(nkeys + 1);
+    bounds = w.take<int32_t>(2 * NREG);
+  }
+  const int64_t most = std::max({nfree, nshort, nlong, int64_t(nb) * 256, int64_t(2 * NREG)});
+  k_term_start<<<grid_for(most, 256), 256, 0, st>>>(ctx->vpos.p, ctx->vinv.p, ctx->vdeg.p, nfree, ctx->cpos, deg,
+                                                    ctx->short_perm.p, nshort, sslot, ctx->long_perm.p, nlong,
+                                                    lslot, int64_t(nb) * 256, ctx->terms, bounds);
+  DM_LAUNCH_CHECK(ctx);
+  if (ntile > 0) {
+    k_term_keys<<<grid_for(nshort, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rent_word.p, ctx->vkey.p, sslot, nshort,
+                                                       ntile, ybits, kbits, skey, sorder);
+    DM_LAUNCH_CHECK(ctx);
+    DM_TRY(place_rows(ctx, skey, sorder, sslot, nshort, ntile, kbits + 1, ctx->term_row));
+  }
+  if (nlong > 0) {
+    DM_TRY(scan_i32(ctx, deg, wsum, size_t(nfree)));
+    k_key_prefix<<<grid_for(nfree + 1, 256), 256, 0, st>>>(ctx->vkey.p, ctx->vperm.p, wsum, ybits, nfree, nkeys,
+                                                           pre);
+    k_region_keys<<<grid_for(nkeys, 256), 256, 0, st>>>(pre, nkeys, total, bounds);
+    k_term_long_keys<<<grid_for(nlong, 4), 256, 0, st>>>(
+        ctx->rrow_ptr.p, ctx->rrow_orig.p, ctx->rent_word.p, ctx->vkey.p, nshort, nlong,
+        mesh ? ctx->n_closed_full + ctx->X.nf : INT64_MAX, ctx->n_long_y, ybits, kbits, pre, total, bounds, lkey,
+        lorder);
+    DM_LAUNCH_CHECK(ctx);
+    DM_TRY(place_rows(ctx, lkey, lorder, lslot, nlong, nlong, kbits + 3, ctx->term_long));
+  }
+  DM_LAUNCH_CHECK(ctx);
+  ctx->has_bound_order = true;
+  return DM_OK;
+}
+
+TermSums term_sums(const dm_ctx* ctx) {
+  TermSums T;
+  T.terms = ctx->terms;
+  T.n_blocks = ctx->term_tiles + ctx->term_chunks;
+  T.n_long = int32_t(ctx->n_rows - ctx->n_short);
+  T.rpb = 4 / ctx->long_wpr;
+  T.n_long_blocks = (T.n_long + T.rpb - 1) / T.rpb;
+  return T;
+}
+
+dm_status sum_terms(dm_ctx* ctx, const TermSums& T, const int32_t* skip) {
+  k_sum_terms<<<unsigned(T.n_blocks + (T.n_long_blocks + 255) / 256), 256, 0, ctx->stream>>>(T, skip,
+                                                                                            ctx->term_part);
   DM_LAUNCH_CHECK(ctx);
   return DM_OK;
 }

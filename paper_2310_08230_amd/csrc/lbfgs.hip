@@ -3,14 +3,18 @@
 //
 // Vectors with one value per multiplier (the subgradient g, the history pairs
 // s and y, the direction q / d) are five slot planes of n_free values: slot k
-// of variable i (i counts in variable order, layout.hip; slots at or above the
-// variable's row count are zero) at k * n_free + i, so every pass reads and
+// of variable i (slots at or above the variable's row count are zero) at
+// k * n_free + i, so every pass reads and
 // writes whole planes coalesced.  What the row passes read and write (the
 // direction, the row minimisers) is one value per cell: the last direction
 // pass also scatters d to the cells, which up to seven row passes then read in
 // order, and the history pass gathers the new g.  g and y only take the values 0/1 and -1/0/1 and
 // are stored as bytes, so a history pair costs 5 reals and 5 bytes per
-// variable.
+// variable.  In FP32 i counts in variable order (layout.hip), where the gathers
+// are cheapest.  In FP64 i is canonical and the bounds are summed in an order
+// of the problem's own (bound_order): where the relaxation is tight the search
+// compares sums that differ in their last bits only, and its steps should not
+// hang on how the launch deals the rows.
 //
 // One iteration, as launched by the host loop below:
 //  1. direction: 2h + 1 variable-major passes over the last h accepted pairs.
@@ -214,14 +218,16 @@ __device__ inline R restored(R s, R t, R rd) {
 // new g comes from the cells and goes to its planes
 template <typename R>
 __global__ __launch_bounds__(VB) void k_qn_hist_pass(const R* cell_old, const R* t_old, const R* cell_new,
-                                                     const R* t_new, const uint32_t* vpos, const uint8_t* g_old,
-                                                     const uint8_t* gcell, const uint8_t* deg, int64_t n, uint8_t* g_new,
-                                                     R* s_out, int8_t* y_out, double* part_sy, double* part_yy) {
+                                                     const R* t_new, const int32_t* vinv, const uint32_t* vpos,
+                                                     const uint8_t* g_old, const uint8_t* gcell,
+                                                     const uint8_t* deg, int64_t n, uint8_t* g_new, R* s_out,
+                                                     int8_t* y_out, double* part_sy, double* part_yy) {
   __shared__ double red[4];
   double a_sy = 0.0, a_yy = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * VB + threadIdx.x; i < n; i += int64_t(gridDim.x) * VB) {
     const int d = deg[i];
-    const R rd = R(1) / R(d), to = t_old[i], tn = t_new[i];
+    const int64_t v = vinv ? int64_t(vinv[i]) : i;
+    const R rd = R(1) / R(d), to = t_old[v], tn = t_new[v];
     uint32_t p[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) p[k] = vpos[k * n + i];
@@ -286,12 +292,42 @@ __global__ __launch_bounds__(1024) void k_qn_pair_fin(const double* part_sy, con
 }
 
 // ---------------------------------------------------------------- one-block decisions
+// Sum of a sweep's bound by a 1024-thread block: of the n block sums p, or (T.terms)
+// of the terms themselves where they are few: a thread takes up to FOLD_BLOCKS / 4
+// terms, and what a launch of k_sum_terms would write stays in LDS.  One launch
+// of a search over few rows fewer per trial (100-face pair, 22k entries, FP64:
+// 1.20 against 1.12 ms for 6 iterations); more blocks than FOLD_BLOCKS take one
+// workgroup longer than the launch.
+constexpr int FOLD_BLOCKS = 32, FOLD_LONG = 1024;
+
+__device__ inline double bound_sum(const TermSums& T, const double* p, int n, double* red) {
+  __shared__ double part[FOLD_BLOCKS + FOLD_LONG];
+  __shared__ double waves[4 * FOLD_BLOCKS];
+  if (!T.terms) return sum_partials_1024(p, n, red);   // uniform
+  constexpr int PER = FOLD_BLOCKS / 4;
+  const int t = int(threadIdx.x);
+  double v[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) v[u] = 4 * u + t / 256 < T.n_blocks ? T.terms[u * 1024 + t] : 0.0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (4 * u >= T.n_blocks) break;   // uniform
+    v[u] = wave_sum(v[u]);
+    if ((t & 63) == 0) waves[u * 16 + t / 64] = v[u];
+  }
+  for (int q = t; q < T.n_long_blocks; q += 1024) part[T.n_blocks + q] = T.long_block(q);
+  __syncthreads();
+  if (t < T.n_blocks) part[t] = ((waves[4 * t] + waves[4 * t + 1]) + waves[4 * t + 2]) + waves[4 * t + 3];
+  __syncthreads();
+  return sum_partials_1024(part, T.n_blocks + T.n_long_blocks, red);
+}
+
 // start of a call: the bound at the imported lambda; a fresh search also
 // resets the step size and Delta_min (a resumed one keeps them)
-__global__ __launch_bounds__(1024) void k_qn_begin(const double* sp, int32_t sn, double offset, QnState* st,
+__global__ __launch_bounds__(1024) void k_qn_begin(TermSums T, const double* sp, int32_t sn, double offset, QnState* st,
                                                  double* etrace, double gamma0, int32_t resume) {
   __shared__ double red[16];
-  const double E = offset + sum_partials_1024(sp, sn, red);
+  const double E = offset + bound_sum(T, sp, sn, red);
   if (threadIdx.x == 0) {
     etrace[0] = E;
     if (!resume) {
@@ -310,12 +346,13 @@ __global__ __launch_bounds__(1024) void k_qn_begin(const double* sp, int32_t sn,
 // FindStepSize after probe t (t = 0: the previous step size; t = 1..K: the
 // rescaled ones): keep the best trial, stop after a gain of Delta_min or at
 // t = K, otherwise rescale gamma by the verdict of this trial against E(lambda)
-__global__ __launch_bounds__(1024) void k_qn_probe(const double* sp, int32_t sn, double offset, int32_t t, int32_t K,
+__global__ __launch_bounds__(1024) void k_qn_probe(TermSums T, const double* sp, int32_t sn, double offset, int32_t t,
+                                                 int32_t K,
                                                  double up, double down, QnState* st, double* gtrace,
                                                  int32_t* taken) {
   __shared__ double red[16];
   if (st->done) return;   // uniform
-  const double E = offset + sum_partials_1024(sp, sn, red);
+  const double E = offset + bound_sum(T, sp, sn, red);
   if (threadIdx.x != 0) return;
   if (t == 0 || E >= st->Em) {
     st->gm = st->gamma;
@@ -336,12 +373,13 @@ __global__ __launch_bounds__(1024) void k_qn_probe(const double* sp, int32_t sn,
 
 // after the subgradient sweep at lambda_{k+1} and the history pass: the bound
 // E(lambda_{k+1}), Delta_min after the first iteration, the curvature test
-__global__ __launch_bounds__(1024) void k_qn_hist(const double* sp, int32_t sn, double offset, const double* part_sy,
-                                                const double* part_yy, int32_t hn, int32_t k, int32_t set_dmin,
+__global__ __launch_bounds__(1024) void k_qn_hist(TermSums T, const double* sp, int32_t sn, double offset,
+                                                const double* part_sy, const double* part_yy, int32_t hn, int32_t k,
+                                                int32_t set_dmin,
                                                 double eps, QnState* st, double* etrace, double* sy_out,
                                                 double* yy_out, int32_t* accepted) {
   __shared__ double red[16];
-  const double E = offset + sum_partials_1024(sp, sn, red);
+  const double E = offset + bound_sum(T, sp, sn, red);
   const double sy = sum_partials_1024(part_sy, hn, red);
   const double yy = sum_partials_1024(part_yy, hn, red);
   if (threadIdx.x != 0) return;
@@ -363,13 +401,17 @@ __global__ __launch_bounds__(1024) void k_qn_hist(const double* sp, int32_t sn, 
 template <typename T>
 __global__ void k_scatter(const T* v, const uint32_t* word, const int32_t* vinv, int64_t nnz, int64_t n, T* planes) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e < nnz) planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + vinv[word[e] & W_VAR_MASK]] = v[e];
+  if (e >= nnz) return;
+  const int32_t i = int32_t(word[e] & W_VAR_MASK);
+  planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + (vinv ? vinv[i] : i)] = v[e];
 }
 
 template <typename T>
 __global__ void k_gather(const T* planes, const uint32_t* word, const int32_t* vinv, int64_t nnz, int64_t n, T* v) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e < nnz) v[e] = planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + vinv[word[e] & W_VAR_MASK]];
+  if (e >= nnz) return;
+  const int32_t i = int32_t(word[e] & W_VAR_MASK);
+  v[e] = planes[int64_t((word[e] >> W_SLOT_SHIFT) & 7u) * n + (vinv ? vinv[i] : i)];
 }
 
 // entry order from cells
@@ -397,6 +439,27 @@ struct Scal {
   double* alpha(int b) const { return p + 2 * nb + b; }
 };
 
+// the numbering of the variables in the planes: cells of variable i, its row
+// count; its place in variable order (NULL: i itself) and in the planes from the
+// canonical index (NULL: the index itself)
+struct Numbering {
+  const uint32_t* pos;
+  const uint8_t* deg;
+  const int32_t* to_v;
+  const int32_t* from_i;
+};
+
+template <typename R>
+dm_status numbering(dm_ctx* ctx, Numbering& N) {
+  if constexpr (sizeof(R) == 8) {
+    DM_TRY(bound_order(ctx));
+    N = {ctx->cpos, ctx->var_deg.p, ctx->vinv.p, nullptr};
+  } else {
+    N = {ctx->vpos.p, ctx->vdeg.p, nullptr, ctx->vinv.p};
+  }
+  return DM_OK;
+}
+
 unsigned vgrid(int64_t n) {
   return unsigned(std::max<int64_t>(1, std::min<int64_t>(VGRID, (n + VB - 1) / VB)));
 }
@@ -405,14 +468,14 @@ unsigned vgrid(int64_t n) {
 // holds two VGRID halves; dcell (optional) takes d per cell as well
 template <typename R>
 dm_status direction(dm_ctx* ctx, const std::vector<int>& order, R* const* S, int8_t* const* Y, const uint8_t* g8,
-                    R* q, const Scal& sc, double* part, R* dcell) {
+                    R* q, const Scal& sc, double* part, R* dcell, const Numbering& N) {
   const int64_t n = ctx->n_free;
   const unsigned G = vgrid(n);
-  const uint8_t* deg = ctx->vdeg.p;
+  const uint8_t* deg = N.deg;
   hipStream_t st = ctx->stream;
   const int h = int(order.size());
   if (h == 0) {
-    k_qn_project_g<R><<<G, VB, 0, st>>>(g8, deg, n, q, ctx->vpos.p, dcell);
+    k_qn_project_g<R><<<G, VB, 0, st>>>(g8, deg, n, q, N.pos, dcell);
     DM_LAUNCH_CHECK(ctx);
     return DM_OK;
   }
@@ -433,7 +496,7 @@ dm_status direction(dm_ctx* ctx, const std::vector<int>& order, R* const* S, int
     const int8_t* y_next = i + 1 < h ? Y[order[i + 1]] : nullptr;
     k_qn_loop2<R><<<G, VB, 0, st>>>(q, S[b], y_next, pin, int32_t(G), sc.sy(b), sc.alpha(b),
                                      i == 0 ? sc.sy(newest) : nullptr, i == 0 ? sc.yy(newest) : nullptr, deg, n,
-                                     q, pout, ctx->vpos.p, y_next ? nullptr : dcell);
+                                     q, pout, N.pos, y_next ? nullptr : dcell);
     std::swap(pin, pout);
   }
   DM_LAUNCH_CHECK(ctx);
@@ -442,35 +505,41 @@ dm_status direction(dm_ctx* ctx, const std::vector<int>& order, R* const* S, int
 
 template <typename R>
 struct QnBuffers {
-  DArr<R> S, q;
-  DArr<int8_t> Y;
-  DArr<uint8_t> g[2];
-  DArr<double> part, scal;
+  DArr<unsigned char> mem;   // everything below
+  R* q = nullptr;
+  uint8_t* g[2] = {nullptr, nullptr};
+  double *part = nullptr, *scal = nullptr;
   std::vector<R*> Sp;
   std::vector<int8_t*> Yp;
 };
 
+// zeroed buffers of nb pairs
 template <typename R>
 dm_status qn_alloc(dm_ctx* ctx, int nb, QnBuffers<R>& B) {
-  const size_t rec = size_t(std::max<int64_t>(ctx->n_free, 1)) * 5;   // five slot planes
-  DM_ALLOC(ctx, B.S, rec * nb);
-  DM_ALLOC(ctx, B.Y, rec * nb);
-  DM_ALLOC(ctx, B.q, rec);
-  DM_ALLOC(ctx, B.g[0], rec);
-  DM_ALLOC(ctx, B.g[1], rec);
-  DM_ALLOC(ctx, B.part, 4 * VGRID);
-  DM_ALLOC(ctx, B.scal, 3 * size_t(nb));
-  DM_HIP(ctx, hipMemsetAsync(B.S.p, 0, rec * nb * sizeof(R), ctx->stream));
-  DM_HIP(ctx, hipMemsetAsync(B.Y.p, 0, rec * nb, ctx->stream));
-  DM_HIP(ctx, hipMemsetAsync(B.q.p, 0, rec * sizeof(R), ctx->stream));
-  DM_HIP(ctx, hipMemsetAsync(B.g[0].p, 0, rec, ctx->stream));
-  DM_HIP(ctx, hipMemsetAsync(B.g[1].p, 0, rec, ctx->stream));
-  DM_HIP(ctx, hipMemsetAsync(B.scal.p, 0, 3 * size_t(nb) * sizeof(double), ctx->stream));
+  const int64_t rec = std::max<int64_t>(ctx->n_free, 1) * 5;   // five slot planes
+  Slab k;
+  k.add<R>(rec * nb);
+  k.add<int8_t>(rec * nb);
+  k.add<R>(rec);
+  k.add<uint8_t>(rec);
+  k.add<uint8_t>(rec);
+  k.add<double>(4 * VGRID);
+  k.add<double>(3 * nb);
+  DM_ALLOC(ctx, B.mem, k.bytes);
+  DM_HIP(ctx, hipMemsetAsync(B.mem.p, 0, k.bytes, ctx->stream));
+  k.at = B.mem.p;
+  R* S = k.take<R>(rec * nb);
+  int8_t* Y = k.take<int8_t>(rec * nb);
+  B.q = k.take<R>(rec);
+  B.g[0] = k.take<uint8_t>(rec);
+  B.g[1] = k.take<uint8_t>(rec);
+  B.part = k.take<double>(4 * VGRID);
+  B.scal = k.take<double>(3 * nb);
   B.Sp.resize(nb);
   B.Yp.resize(nb);
   for (int b = 0; b < nb; ++b) {
-    B.Sp[b] = B.S.p + rec * b;
-    B.Yp[b] = B.Y.p + rec * b;
+    B.Sp[b] = S + rec * b;
+    B.Yp[b] = Y + rec * b;
   }
   return DM_OK;
 }
@@ -538,39 +607,60 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
   }
   QnBuffers<R>& B = S.B;
   QnState* st = S.st.p;
-  DArr<double> etrace;
-  DM_ALLOC(ctx, etrace, size_t(iters) + 1);
-  const Scal sc{B.scal.p, nb};
+  const Scal sc{B.scal, nb};
   const int64_t n = ctx->n_free;
   const unsigned G = vgrid(n);
   DM_TRY(dual_flush(ctx));
   CellState& C = ctx->cells;
   DM_TRY(cells_import<R>(ctx, lam, C, true));
-  DArr<uint8_t> gcell;   // row minimisers and direction, one value per cell
-  DArr<R> dcell;
-  DM_ALLOC(ctx, gcell, size_t(ctx->n_cells) + 1);
-  DM_ALLOC(ctx, dcell, size_t(ctx->n_cells) + 1);
+  // row minimisers and direction, one value per cell; the bounds
+  Slab slab;
+  slab.add<uint8_t>(ctx->n_cells + 1);
+  slab.add<R>(ctx->n_cells + 1);
+  slab.add<double>(int64_t(iters) + 1);
+  DArr<unsigned char> mem;
+  DM_ALLOC(ctx, mem, slab.bytes);
+  slab.at = mem.p;
+  uint8_t* gcell = slab.take<uint8_t>(ctx->n_cells + 1);
+  R* dcell = slab.take<R>(ctx->n_cells + 1);
+  double* etrace = slab.take<double>(int64_t(iters) + 1);
   int cur = 0, gc = 0;
   R* none = nullptr;
+  Numbering N;
+  DM_TRY(numbering<R>(ctx, N));
+  // the bound of the last sweep: its block sums, or in FP64 the terms (few) or their sums
+  constexpr bool ordered = sizeof(R) == 8;
+  const TermSums all = ordered ? term_sums(ctx) : TermSums();
+  const bool fold = all.n_blocks <= FOLD_BLOCKS && all.n_long_blocks <= FOLD_LONG;
+  const TermSums T = fold ? all : TermSums();
+  const double* sp = nullptr;
+  int32_t sn = 0;
+  auto block_sums = [&](const int32_t* skip) -> dm_status {
+    sp = ordered ? ctx->term_part : ctx->pend_partial;
+    sn = ordered ? all.n_blocks + all.n_long_blocks : ctx->pend_n;
+    return ordered && !fold ? sum_terms(ctx, all, skip) : DM_OK;
+  };
   SweepExt sub;
-  sub.gsub = gcell.p;
+  sub.gsub = gcell;
+  sub.terms = ordered ? ctx->terms : nullptr;
   DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), false));
   DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(0), C.ts<R>(0), none, R(0), nullptr, &sub));
-  k_qn_begin<<<1, 1024, 0, stream>>>(ctx->pend_partial, ctx->pend_n, ctx->offset, st, etrace.p, P.gamma0,
-                                   resume ? 1 : 0);
-  k_qn_gather_g<<<G, VB, 0, stream>>>(gcell.p, ctx->vpos.p, ctx->vdeg.p, n, B.g[0].p);
+  DM_TRY(block_sums(nullptr));
+  k_qn_begin<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, st, etrace, P.gamma0, resume ? 1 : 0);
+  k_qn_gather_g<<<G, VB, 0, stream>>>(gcell, N.pos, N.deg, n, B.g[0]);
   DM_LAUNCH_CHECK(ctx);
   for (int32_t k = 0; k < iters; ++k) {
-    DM_TRY(direction<R>(ctx, S.order, B.Sp.data(), B.Yp.data(), B.g[gc].p, B.q.p, sc, B.part.p, dcell.p));
+    DM_TRY(direction<R>(ctx, S.order, B.Sp.data(), B.Yp.data(), B.g[gc], B.q, sc, B.part, dcell, N));
     SweepExt pe;
-    pe.dir = dcell.p;
+    pe.dir = dcell;
     pe.gamma = &st->gamma;
     pe.skip = &st->done;
+    pe.terms = sub.terms;
     for (int t = 0; t <= P.max_search; ++t) {
       DM_TRY(cells_rows<R>(ctx, SWEEP_BOUND, C.cells<R>(cur), C.ts<R>(cur), none, R(0), nullptr, &pe));
-      k_qn_probe<<<1, 1024, 0, stream>>>(ctx->pend_partial, ctx->pend_n, ctx->offset, t, P.max_search, P.step_up,
-                                         P.step_down, st, gamma_trace ? gamma_trace + k : nullptr,
-                                         taken ? taken + k : nullptr);
+      DM_TRY(block_sums(pe.skip));
+      k_qn_probe<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, t, P.max_search, P.step_up, P.step_down, st,
+                                         gamma_trace ? gamma_trace + k : nullptr, taken ? taken + k : nullptr);
       DM_LAUNCH_CHECK(ctx);
       // the search usually stops at the second trial: one read of the flag
       // then spares launching the remaining probes (a skipped launch still
@@ -583,25 +673,24 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
       }
     }
     SweepExt me;
-    me.dir = dcell.p;
+    me.dir = dcell;
     me.gamma = &st->step;
     const int nxt = cur ^ 1;
     DM_TRY(cells_rows<R>(ctx, SWEEP_UPDATE, C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), R(P.omega), nullptr, &me));
     DM_TRY(cells_vars<R>(ctx, C.cells<R>(nxt), C.costs<R>(), C.ts<R>(nxt), false));
     DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(nxt), C.ts<R>(nxt), none, R(0), nullptr, &sub));
-    const double* sp = ctx->pend_partial;
-    const int32_t sn = ctx->pend_n;
-    double* psy = B.part.p + 2 * VGRID;
-    double* pyy = B.part.p + 3 * VGRID;
+    DM_TRY(block_sums(nullptr));
+    double* psy = B.part + 2 * VGRID;
+    double* pyy = B.part + 3 * VGRID;
     const int spare = S.spare;
     if (m > 0)
-      k_qn_hist_pass<R><<<G, VB, 0, stream>>>(C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), C.ts<R>(nxt), ctx->vpos.p,
-                                               B.g[gc].p, gcell.p, ctx->vdeg.p, n, B.g[gc ^ 1].p, B.Sp[spare],
+      k_qn_hist_pass<R><<<G, VB, 0, stream>>>(C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), C.ts<R>(nxt), N.to_v, N.pos,
+                                               B.g[gc], gcell, N.deg, n, B.g[gc ^ 1], B.Sp[spare],
                                                B.Yp[spare], psy, pyy);
     else
-      k_qn_gather_g<<<G, VB, 0, stream>>>(gcell.p, ctx->vpos.p, ctx->vdeg.p, n, B.g[gc ^ 1].p);
-    k_qn_hist<<<1, 1024, 0, stream>>>(sp, sn, ctx->offset, psy, pyy, m > 0 ? int32_t(G) : 0, k,
-                                    (k == 0 && !resume) ? 1 : 0, P.eps, st, etrace.p, sc.sy(spare),
+      k_qn_gather_g<<<G, VB, 0, stream>>>(gcell, N.pos, N.deg, n, B.g[gc ^ 1]);
+    k_qn_hist<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, psy, pyy, m > 0 ? int32_t(G) : 0, k,
+                                    (k == 0 && !resume) ? 1 : 0, P.eps, st, etrace, sc.sy(spare),
                                     sc.yy(spare), S.flag.p);
     DM_LAUNCH_CHECK(ctx);
     cur ^= 1;
@@ -626,7 +715,7 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
     }
   }
   if (lb_trace)
-    DM_HIP(ctx, hipMemcpyAsync(lb_trace, etrace.p, (size_t(iters) + 1) * sizeof(double), hipMemcpyDeviceToDevice,
+    DM_HIP(ctx, hipMemcpyAsync(lb_trace, etrace, (size_t(iters) + 1) * sizeof(double), hipMemcpyDeviceToDevice,
                                stream));
   DM_TRY(cells_export<R>(ctx, C.cells<R>(cur), C.ts<R>(cur), lam));
   // the per-call trace buffer is freed on return: wait for the queued work
@@ -664,22 +753,24 @@ dm_status direction_impl(dm_ctx* ctx, int32_t h, const R* S, const int8_t* Y, co
   if (nnz == 0) return DM_OK;
   QnBuffers<R> B;
   DM_TRY(qn_alloc<R>(ctx, std::max(h, 1), B));
-  const Scal sc{B.scal.p, std::max(h, 1)};
+  const Scal sc{B.scal, std::max(h, 1)};
   const unsigned G = vgrid(n);
   const unsigned E = grid_for(nnz, 256);
+  Numbering N;
+  DM_TRY(numbering<R>(ctx, N));
   std::vector<int> order;
-  k_scatter<uint8_t><<<E, 256, 0, ctx->stream>>>(g, ctx->rent_word.p, ctx->vinv.p, nnz, n, B.g[0].p);
+  k_scatter<uint8_t><<<E, 256, 0, ctx->stream>>>(g, ctx->rent_word.p, N.from_i, nnz, n, B.g[0]);
   for (int b = 0; b < h; ++b) {
-    k_scatter<R><<<E, 256, 0, ctx->stream>>>(S + size_t(b) * nnz, ctx->rent_word.p, ctx->vinv.p, nnz, n, B.Sp[b]);
-    k_scatter<int8_t><<<E, 256, 0, ctx->stream>>>(Y + size_t(b) * nnz, ctx->rent_word.p, ctx->vinv.p, nnz, n, B.Yp[b]);
-    k_qn_pair_dots<R><<<G, VB, 0, ctx->stream>>>(B.Sp[b], B.Yp[b], n, B.part.p, B.part.p + VGRID);
-    k_qn_pair_fin<<<1, 1024, 0, ctx->stream>>>(B.part.p, B.part.p + VGRID, int32_t(G), sc.sy(b), sc.yy(b));
+    k_scatter<R><<<E, 256, 0, ctx->stream>>>(S + size_t(b) * nnz, ctx->rent_word.p, N.from_i, nnz, n, B.Sp[b]);
+    k_scatter<int8_t><<<E, 256, 0, ctx->stream>>>(Y + size_t(b) * nnz, ctx->rent_word.p, N.from_i, nnz, n, B.Yp[b]);
+    k_qn_pair_dots<R><<<G, VB, 0, ctx->stream>>>(B.Sp[b], B.Yp[b], n, B.part, B.part + VGRID);
+    k_qn_pair_fin<<<1, 1024, 0, ctx->stream>>>(B.part, B.part + VGRID, int32_t(G), sc.sy(b), sc.yy(b));
     order.push_back(b);
   }
   DM_LAUNCH_CHECK(ctx);
-  DM_TRY(direction<R>(ctx, order, B.Sp.data(), B.Yp.data(), B.g[0].p, B.q.p, sc, B.part.p,
-                         static_cast<R*>(nullptr)));
-  k_gather<R><<<E, 256, 0, ctx->stream>>>(B.q.p, ctx->rent_word.p, ctx->vinv.p, nnz, n, d);
+  DM_TRY(direction<R>(ctx, order, B.Sp.data(), B.Yp.data(), B.g[0], B.q, sc, B.part,
+                         static_cast<R*>(nullptr), N));
+  k_gather<R><<<E, 256, 0, ctx->stream>>>(B.q, ctx->rent_word.p, N.from_i, nnz, n, d);
   DM_LAUNCH_CHECK(ctx);
   DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
   return DM_OK;
