@@ -95,7 +95,7 @@ template <typename R>
 struct SoftUnits;
 template <>
 struct SoftUnits<float> {
-  static constexpr float big = 3.40282347e+38f;   // largest finite value
+  static constexpr float none = 1e37f, lim = 1e36f;   // a state that cannot be reached; every value is below lim
   static __device__ float unit(float T) { return T * 0.693147180559945309f; }   // x = u * unit
   static __device__ float E(float x) { return __builtin_amdgcn_exp2f(x); }
   static __device__ float L(float x) { return __builtin_amdgcn_logf(x); }
@@ -103,107 +103,19 @@ struct SoftUnits<float> {
 };
 template <>
 struct SoftUnits<double> {
-  static constexpr double big = 1.7976931348623157e+308;
+  static constexpr double none = 1e307, lim = 1e306;
   static __device__ double unit(double T) { return T; }
   static __device__ double E(double x) { return exp(x); }
   static __device__ double L(double x) { return log(x); }
   static __device__ double L1p(double x) { return log1p(x); }
 };
 
-// soft-min of two values in scaled units, without branches: with the smaller
-// value clamped to the largest finite one, an infinite larger value gives
-// E(-inf) = 0 and the result is the smaller value (inf when both are inf)
+// soft-min of two values in scaled units, without branches.  Neither is +inf and
+// both at once: a state that cannot be reached holds SoftUnits::none, so large
+// that E of its distance to any value is 0, and finite.
 template <typename R>
 __device__ inline R smin2u(R a, R b) {
-  // with both operands clamped to the largest finite value, -|a - b| is the
-  // exponent m - M of two finite values, -huge when one is infinite and 0
-  // when both are (then m is inf and so is the result)
-  const R ac = fmin(a, SoftUnits<R>::big), bc = fmin(b, SoftUnits<R>::big);
-  return fmin(a, b) - SoftUnits<R>::L1p(SoftUnits<R>::E(-fabs(ac - bc)));
-}
-
-// min / sum over the W lanes (W = 8, 16 or 32) of an aligned segment, the same
-// value in every lane: DPP steps within each sixteen-lane row (every pairing
-// is symmetric, so all lanes form the same sums), one shuffle joins two rows
-// min of v and its DPP-moved copy (values are never NaN); adding +0 to the
-// moved value (-0 becomes +0, nothing else changes) gives an arithmetic
-// result, which needs no NaN canonicalisation before the min, and the move
-// folds into that add
-template <int CTRL, typename R>
-__device__ inline R min_dpp(R v) {
-  return fmin(v, dpp_move<CTRL, R>(v) + R(0));
-}
-
-// FP32 values as integers of the same order (the sign-magnitude bits with
-// the magnitude flipped for negative values; every non-NaN value, infinities
-// included, keeps its place), so a segment minimum runs on integer DPP mins,
-// which need no NaN canonicalisation of the moved operand
-__device__ inline int32_t ordered_bits(float f) {
-  const int32_t i = __float_as_int(f);
-  return i ^ ((i >> 31) & 0x7FFFFFFF);
-}
-__device__ inline float from_ordered_bits(int32_t k) { return __int_as_float(k ^ ((k >> 31) & 0x7FFFFFFF)); }
-
-template <int CTRL>
-__device__ inline int32_t imin_dpp(int32_t v) {
-  const int32_t o = __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
-  return o < v ? o : v;
-}
-
-// ordered bits of the FP32 segment minimum
-template <int W>
-__device__ inline int32_t seg_min_bits(float v) {
-  int32_t k = ordered_bits(v);
-  k = imin_dpp<0xB1>(k);
-  k = imin_dpp<0x4E>(k);
-  k = imin_dpp<0x141>(k);
-  if constexpr (W >= 16) k = imin_dpp<0x140>(k);
-  if constexpr (W == 32) {
-    const int32_t o = __shfl_xor(k, 16, 32);
-    k = o < k ? o : k;
-  }
-  return k;
-}
-
-template <int W, typename R>
-__device__ inline R seg_min(R v) {
-  if constexpr (sizeof(R) == 4) {
-    return from_ordered_bits(seg_min_bits<W>(v));
-  } else {
-    v = min_dpp<0xB1>(v);
-    v = min_dpp<0x4E>(v);
-    v = min_dpp<0x141>(v);
-    if constexpr (W >= 16) v = min_dpp<0x140>(v);
-    if constexpr (W == 32) v = fmin(v, __shfl_xor(v, 16, 32) + R(0));
-    return v;
-  }
-}
-
-template <int W, typename R>
-__device__ inline R seg_sum(R v) {
-  v += dpp_move<0xB1>(v);
-  v += dpp_move<0x4E>(v);
-  v += dpp_move<0x141>(v);
-  if constexpr (W >= 16) v += dpp_move<0x140>(v);
-  if constexpr (W == 32) v += __shfl_xor(v, 16, 32);
-  return v;
-}
-
-// soft-min over the W lanes of a segment in scaled units, as the two parts
-// every lane gets: the hard minimum mc and the sum e of one exponential per
-// lane; the soft-min is mc - L(e), left to the caller so that only the lane
-// that needs it takes the logarithm.  With the minimum clamped to the largest
-// finite value, lanes holding inf add E(-inf) = 0, and a segment of infs
-// gives L(0) = -inf, so inf.
-template <int W, typename R>
-__device__ inline void seg_softmin_parts(R x, R& mc, R& e) {
-  if constexpr (sizeof(R) == 4) {   // the clamp on the ordered bits: no NaN canonicalisation
-    mc = from_ordered_bits(min(seg_min_bits<W>(x), ordered_bits(SoftUnits<R>::big)));
-  } else {
-    const R m = seg_min<W, R>(x);
-    mc = m < SoftUnits<R>::big ? m : SoftUnits<R>::big;
-  }
-  e = seg_sum<W, R>(SoftUnits<R>::E(mc - x));
+  return fmin(a, b) - SoftUnits<R>::L1p(SoftUnits<R>::E(-fabs(a - b)));
 }
 
 // multiplier of entry word w from the previous record buffer, with dual
@@ -736,10 +648,19 @@ __device__ __forceinline__ double tile_block(const SweepArgs& A, const R* cells,
 // ---------------------------------------------------------------- short rows, soft min
 // One W-lane segment per row (W = 8, 16, 32 for rows of at most 7, 15, 24
 // entries; the rows are taken in order of length from soft_row; a block holds
-// soft_rpb<W>() rows, so the forward table fits SOFT_FTAB values); lane j holds
-// the partial sum sigma = j - N of the recursion
-// F_{l+1}(sigma) = smin(F_l(sigma), F_l(sigma - a_l) + lam_l),
-// B_l(sigma) = smin(B_{l+1}(sigma), B_{l+1}(sigma + a_l) + lam_l).
+// soft_rpb<W>() rows).  In the two recursions lane j holds the partial sum
+// sigma = j - N:
+//   F_{l+1}(sigma) = smin(F_l(sigma), F_l(sigma - a_l) + lam_l),
+//   B_l(sigma) = smin(B_{l+1}(sigma), B_{l+1}(sigma + a_l) + lam_l).
+// Their tables pass through one LDS table, F first, and then lane l holds entry
+// l: its soft-mins for x_l = 0 and 1 run over the states in its own registers,
+//   min_sigma F_l(sigma) + B_{l+1}(sigma),  lam_l + min_sigma F_l(sigma) + B_{l+1}(sigma + a_l).
+// Bound by vector instructions and, the longest rows first, evenly spread: 1000-
+// face pair, a launch 93 us with 46.6 M of them; 119 us with 69.5 M where every
+// entry's two soft-mins were reductions over the segment's lanes, entry after
+// entry (FP64: 485 and 615 us).  A table each for F and B leaves a CU fewer
+// blocks (FP32 119 us against 92, FP64 661 against 592, in one launch order).
+// Every sum is formed as those reductions formed it: pairs, fours, eights.
 // Rows [row0, row1) of soft_row belong to this width; blk counts the blocks of
 // this width, item is the block's index among all blocks.
 template <int W>
@@ -750,26 +671,38 @@ template <int W>
 constexpr int soft_nmax() {  // entries per row at most
   return W == 32 ? SOFT_MAX_ROW : W - 1;
 }
-// forward-table values per block: the largest of the three widths
-constexpr int SOFT_FTAB = 16 * 15 * 16;
-static_assert(soft_rpb<8>() * soft_nmax<8>() * 8 <= SOFT_FTAB && soft_rpb<32>() * soft_nmax<32>() * 32 <= SOFT_FTAB,
-              "forward table too small");
+template <int W>
+constexpr int soft_stride() {   // values per table row: 16 lanes' 16-byte reads of 16 rows touch every bank once
+  return W == 32 ? 28 : W + 4;
+}
+// values of one table per block: the largest of the three widths
+constexpr int SOFT_TAB = 16 * 15 * 20;
+static_assert(soft_rpb<8>() * soft_nmax<8>() * soft_stride<8>() <= SOFT_TAB &&
+                  soft_rpb<32>() * soft_nmax<32>() * soft_stride<32>() <= SOFT_TAB && SOFT_MAX_ROW < soft_stride<32>(),
+              "table too small");
+
+// orders this wave's LDS accesses (a row's lanes are in one wave)
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 template <typename R, int MODE, int W>
 __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out, R omega,
                                 R T, unsigned char* smem, double* red, int32_t item, int32_t blk, int32_t row0,
                                 int32_t row1) {
-  constexpr int RPB = soft_rpb<W>(), NMAX = soft_nmax<W>();
+  using U = SoftUnits<R>;
+  constexpr int RPB = soft_rpb<W>(), NMAX = soft_nmax<W>(), ST = soft_stride<W>();
   const int seg = threadIdx.x / W, lane = threadIdx.x % W;
-  R* Ftab = reinterpret_cast<R*>(smem) + seg * (NMAX * W);
-  R* lamL = reinterpret_cast<R*>(smem) + SOFT_FTAB + seg * W;
-  int8_t* aL = reinterpret_cast<int8_t*>(reinterpret_cast<R*>(smem) + SOFT_FTAB + 256) + seg * W;
+  R* tab = reinterpret_cast<R*>(smem) + seg * (NMAX * ST);
+  R* lamL = reinterpret_cast<R*>(smem) + SOFT_TAB + seg * W;
   const int32_t r = row0 + blk * RPB + seg;
   const bool act = seg < RPB && r < row1;
   int32_t s = 0, n = 0, b = 0;
   uint32_t w = 0;
   R mylam = R(0);
-  const R unit = SoftUnits<R>::unit(T), inv_unit = R(1) / unit;
+  const R unit = U::unit(T), inv_unit = R(1) / unit;
   if (act) {
     const int32_t j = A.soft_row[r];
     s = A.rrow_ptr[j];
@@ -778,63 +711,124 @@ __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R
     if (lane < n) {
       w = A.ent_word[s + lane];
       mylam = cur_lambda<R>(rin, w);
-      lamL[lane] = mylam * inv_unit;
-      aL[lane] = (w >> 31) ? int8_t(-1) : int8_t(1);
     }
   }
-  __syncthreads();
-  double rowpart = 0.0;
-  if (act) {
-    int32_t N = 0;
-    for (int32_t l = 0; l < n; ++l) N += aL[l] < 0;
-    const int32_t P = n - N;
-    const int32_t sigma = lane - N;
-    const bool valid = lane <= P + N;
-    R F = (valid && sigma == 0) ? R(0) : rinf<R>();
-    for (int32_t l = 0; l < n; ++l) {
-      Ftab[l * W + lane] = F;   // read back below by the same lane only
-      const int a = aL[l];
-      const R from_lo = dpp_move<0x138>(F), from_hi = dpp_move<0x130>(F);   // F[lane - 1], F[lane + 1]
-      R sh = a > 0 ? from_lo : from_hi;                                       // F[lane - a]
-      if ((unsigned(lane - a) >= unsigned(W)) | !valid) sh = rinf<R>();
-      F = smin2u<R>(F, sh + lamL[l]);
-      if (!valid) F = rinf<R>();
+  lamL[lane] = lane < n ? mylam * inv_unit : rinf<R>();   // past the row's end a step changes nothing
+  // signs of the row's entries, and the longest row of the wave (the rows are
+  // in order of length, so they hardly differ)
+  const unsigned long long neg_wave = __ballot(lane < n && (w >> 31) != 0u);
+  const int32_t N = __popc(uint32_t(neg_wave >> ((threadIdx.x & 63u) / W * W)) & (W == 32 ? ~0u : (1u << (W & 31)) - 1u));
+  int32_t nm = n;
+  for (int off = W; off < 64; off <<= 1) nm = max(nm, __shfl_xor(nm, off));
+  nm = __builtin_amdgcn_readfirstlane(nm);
+  wave_lds_fence();
+  // per entry the lanes whose row has it negative, as a mask of the wave
+  constexpr unsigned long long LOW = W == 8 ? 0x0101010101010101ull : (W == 16 ? 0x0001000100010001ull : 0x0000000100000001ull);
+  unsigned long long neg[NMAX];
+#pragma unroll
+  for (int l = 0; l < NMAX; ++l) {
+    const unsigned long long t = (neg_wave >> l) & LOW;
+    neg[l] = (t << W) - t;
+  }
+  // value of the state above (lanes of up) or below, none past the segment's ends
+  auto beside = [&](R v, unsigned long long up) {
+    const R lo = dpp_move<0x138>(v), hi = dpp_move<0x130>(v);   // v[lane - 1], v[lane + 1]
+    const R x = __builtin_amdgcn_inverse_ballot_w64(up) ? hi : lo;
+    return __builtin_amdgcn_inverse_ballot_w64((up & (LOW << (W - 1))) | (~up & LOW)) ? U::none : x;
+  };
+  constexpr int Q = (W == 32 ? ST : W) / 4;   // states in fours
+  R f[4 * Q];   // the entry's F_l of every state
+  auto load4 = [](const R* p, R* v) {
+    using Vec = typename LdsVec<R>::type;
+    constexpr int V = 16 / int(sizeof(R));
+#pragma unroll
+    for (int g = 0; g < 4; g += V) {
+      const Vec x = *reinterpret_cast<const Vec*>(p + g);
+#pragma unroll
+      for (int u = 0; u < V; ++u) v[g + u] = LdsVec<R>::get(x, u);
     }
-    R Bv = (valid && sigma == b) ? R(0) : rinf<R>();
-    // lane l keeps the parts of its entry's two soft-mins (x_l = 1 and
-    // x_l = 0); the logarithms are taken once, after the recursion
-    R m1 = R(0), e1 = R(1), m0 = R(0), e0 = R(1);
-    for (int32_t l = n - 1; l >= 0; --l) {
-      const int a = aL[l];
-      const R Fl = Ftab[l * W + lane];
-      const R from_lo = dpp_move<0x138>(Bv), from_hi = dpp_move<0x130>(Bv);
-      R sh = a > 0 ? from_hi : from_lo;                                       // Bv[lane + a]
-      if ((unsigned(lane + a) >= unsigned(W)) | !valid) sh = rinf<R>();
-      // inf + finite and inf + inf stay inf
-      R pm1, pe1, pm0, pe0;
-      seg_softmin_parts<W, R>(Fl + lamL[l] + sh, pm1, pe1);
-      seg_softmin_parts<W, R>(Fl + Bv, pm0, pe0);
-      if (lane == l) {
-        m1 = pm1;
-        e1 = pe1;
-        m0 = pm0;
-        e0 = pe0;
-      }
-      Bv = smin2u<R>(Bv, sh + lamL[l]);
-      if (!valid) Bv = rinf<R>();
+  };
+  if (MODE != MODE_BOUND) {
+    R F = lane == N ? R(0) : U::none;
+#pragma unroll
+    for (int l = 0; l < NMAX; ++l) {
+      if (l >= nm) break;   // uniform
+      if (W < 32 || lane < ST) tab[l * ST + lane] = F;
+      F = smin2u<R>(F, beside(F, neg[l]) + lamL[l]);
     }
-    const R my1 = m1 - SoftUnits<R>::L(e1);
-    const R myM = (my1 - (m0 - SoftUnits<R>::L(e0))) * unit;
-    // soft row value B_0(0) sits on lane N
-    const R rowv = __shfl(Bv, N, W);
+    wave_lds_fence();
     if (lane < n) {
-      if (MODE == MODE_UPDATE) write_out<R>(out, w, mylam - omega * myM);
-      if (MODE == MODE_EVAL) write_out<R>(out, w, SoftUnits<R>::E(rowv - my1));
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (4 * q > nm) break;   // uniform: no row of the wave has such states
+        load4(tab + lane * ST + 4 * q, f + 4 * q);
+      }
     }
-    if (lane == 0) rowpart = double(rowv * unit);
+    wave_lds_fence();   // the table now takes B
   }
-  double part = block_sum(rowpart, red);
-  store_partial(part, A.partial, item);
+  R Bv = lane - N == b && lane <= n ? R(0) : U::none;
+#pragma unroll
+  for (int l = NMAX - 1; l >= 0; --l) {
+    if (l < nm) {   // uniform
+      if (MODE != MODE_BOUND && (W < 32 || lane < ST)) tab[l * ST + lane] = Bv;
+      Bv = smin2u<R>(Bv, beside(Bv, ~neg[l]) + lamL[l]);
+    }
+  }
+  // the soft row value B_0(0) sits on lane N
+  R rowv = __shfl(Bv, N, W);
+  rowv = rowv < U::lim ? rowv : rinf<R>();
+  if (MODE != MODE_BOUND) {
+    wave_lds_fence();
+    if (lane < n) {
+      const bool up = !(w >> 31);
+      const R* Bl = tab + lane * ST;
+      const R mine = lamL[lane];
+      R x1[4 * Q];   // the sums for x = 1; f becomes those for x = 0
+      R m0 = U::none, m1 = U::none;
+      R below = U::none;   // B of the state below the four
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (4 * q > nm) break;
+        R B[6];
+        B[0] = below;
+        load4(Bl + 4 * q, B + 1);
+        B[5] = q + 1 < Q ? Bl[4 * q + 4] : U::none;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          R& x = f[4 * q + u];
+          x1[4 * q + u] = (x + mine) + (up ? B[u + 2] : B[u]);
+          x = x + B[u + 1];
+          m0 = fmin(m0, x);
+          m1 = fmin(m1, x1[4 * q + u]);
+        }
+        below = B[4];
+      }
+      // one exponential per state, added in pairs, fours, eights, ...
+      R e0[8], e1[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        e0[q] = e1[q] = R(0);
+        if (q < Q && 4 * q <= nm) {
+          const R *x = f + 4 * (q < Q ? q : 0), *y = x1 + 4 * (q < Q ? q : 0);
+          e0[q] = (U::E(m0 - x[0]) + U::E(m0 - x[1])) + (U::E(m0 - x[2]) + U::E(m0 - x[3]));
+          e1[q] = (U::E(m1 - y[0]) + U::E(m1 - y[1])) + (U::E(m1 - y[2]) + U::E(m1 - y[3]));
+        }
+      }
+#pragma unroll
+      for (int h = 1; h < W / 4; h *= 2)
+#pragma unroll
+        for (int q = 0; q < W / 4; q += 2 * h) {
+          e0[q] += e0[q + h];
+          e1[q] += e1[q + h];
+        }
+      const R my1 = m1 < U::lim ? m1 - U::L(e1[0]) : rinf<R>();
+      const R my0 = m0 < U::lim ? m0 - U::L(e0[0]) : rinf<R>();
+      if (MODE == MODE_UPDATE) write_out<R>(out, w, mylam - omega * ((my1 - my0) * unit));
+      if (MODE == MODE_EVAL) write_out<R>(out, w, U::E(rowv - my1));
+    }
+  }
+  const double rowpart = act && lane == 0 ? double(rowv * unit) : 0.0;
+  store_partial(block_sum(rowpart, red), A.partial, item);
 }
 
 // a multiplier record as loaded (two 16-byte loads for FP32, four for FP64)
@@ -1156,7 +1150,7 @@ __device__ double long_records(const SweepArgs& A, const R* __restrict__ src, R*
 
 template <typename R, bool SOFT>
 constexpr size_t smem_bytes() {
-  return SOFT ? (SOFT_FTAB + 256) * sizeof(R) + 256 : 768 * sizeof(R);
+  return SOFT ? (SOFT_TAB + 256) * sizeof(R) : 768 * sizeof(R);
 }
 
 // First pass of a hard iteration: t_i = c_i - sum_k s_k, one thread per
@@ -1244,25 +1238,26 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
     }
     store_partial(block_sum(part, red), A.partial, int32_t(blockIdx.x));
   } else {
-    // The smoothed form gives each XCD a contiguous range of short-row blocks
-    // and projection-row blocks in groups of LONG_GROUP consecutive blocks,
-    // group g on XCD g % 8, the heavier projection-row blocks first.
+    // The smoothed form deals the projection-row blocks in groups of LONG_GROUP,
+    // group g to XCD g % 8, then the short rows' blocks one by one, the widest
+    // rows first.  Each width is dealt by itself and in order of length, so that
+    // a wave's rows are equally long and the XCDs get equal work (contiguous
+    // eighths of all short rows in order of length: half the chip was idle at the
+    // end, 1000-face pair 119 us a launch against 90).
     int32_t item;
     const int32_t n_long_blocks = A.n_items - A.n_short_blocks;
     const int32_t lx = (n_long_blocks + 8 * LONG_GROUP - 1) / (8 * LONG_GROUP) * LONG_GROUP;
+    const int32_t nb8 = (A.soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>();
+    const int32_t nb16 = (A.soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>();
     if (k0 < lx) {
       const int32_t li = ((k0 / LONG_GROUP) * 8 + x) * LONG_GROUP + k0 % LONG_GROUP;
       if (li >= n_long_blocks) return;
       item = A.n_short_blocks + li;
     } else {
-      const int32_t pc = (A.n_short_blocks + 7) / 8;
-      const int32_t c = x * pc + (k0 - lx);
-      if (k0 - lx >= pc || c >= A.n_short_blocks) return;
-      item = c;
+      item = A.n_short_blocks - 1 - ((k0 - lx) * 8 + x);   // in order of length: the longest are the last
+      if (item < 0) return;
     }
     if (item < A.n_short_blocks) {
-      const int32_t nb8 = (A.soft_c8 + soft_rpb<8>() - 1) / soft_rpb<8>();
-      const int32_t nb16 = (A.soft_c16 + soft_rpb<16>() - 1) / soft_rpb<16>();
       const int32_t c816 = A.soft_c8 + A.soft_c16;
       if (item < nb8)
         short_rows_soft<R, MODE, 8>(A, rin, out, omega, T, smem, red, item, item, 0, A.soft_c8);
