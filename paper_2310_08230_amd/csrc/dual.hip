@@ -1463,7 +1463,10 @@ __global__ void k_init_lambda(const uint32_t* word, const R* share, int64_t nnz,
   if (e < nnz) lam[e] = share[word[e] & W_VAR_MASK];
 }
 
-__global__ void k_write_offset(double* out, double v) { *out = v; }
+__global__ void k_write_offset(double* out, int32_t n, double v) {
+  const int32_t i = int32_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = v;
+}
 
 __global__ __launch_bounds__(256) void k_reduce_last(const double* partial, int n, double offset, double* out) {
   __shared__ double red[256];
@@ -1698,7 +1701,7 @@ static void common_args(const dm_ctx* ctx, SweepArgs& A) {
 // no rows: the bound is the constant
 static dm_status empty_sweep(dm_ctx* ctx, double* bound_out) {
   DM_TRY(dual_flush(ctx));
-  if (bound_out) k_write_offset<<<1, 1, 0, ctx->stream>>>(bound_out, ctx->offset);
+  if (bound_out) k_write_offset<<<1, 1, 0, ctx->stream>>>(bound_out, 1, ctx->offset);
   DM_LAUNCH_CHECK(ctx);
   return DM_OK;
 }
@@ -1781,8 +1784,15 @@ static size_t small_lds(const dm_ctx* ctx) {
 template <typename R>
 dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, double* trace) {
   R *cells = S.cells<R>(0), *t = S.ts<R>(0);
+  if (hard_grid(ctx) == 0) {   // presolve left no rows: every bound is the constant
+    DM_TRY(dual_flush(ctx));
+    if (trace && iters > 0)
+      k_write_offset<<<grid_for(iters, 256), 256, 0, ctx->stream>>>(trace, iters, ctx->offset);
+    DM_LAUNCH_CHECK(ctx);
+    return DM_OK;
+  }
   const size_t lds = small_lds<R>(ctx);
-  if (lds > 0 && iters > 0 && hard_grid(ctx) > 0) {
+  if (lds > 0 && iters > 0) {
     DM_TRY(dual_flush(ctx));
     SweepArgs A;
     hard_args(ctx, A);

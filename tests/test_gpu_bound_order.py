@@ -59,3 +59,17 @@ def test_every_term_is_added_once(n_rows, b1_rows, long_len):
     end = np_(lam)
     tol = 2.0 ** -53 * (8 * len(ref) * np.abs(end).max() + ctx.info["n_rows"] * np.abs(end).sum())
     assert abs(np_(trace)[-1] - S.lower_bound(end)) <= tol
+
+
+@pytest.mark.parametrize("iters", [0, 1, 300])
+def test_no_rows_left(iters):
+    """Presolve fixes every variable: each bound is the constant, exactly."""
+    ctx = dm().Context(0)
+    ctx.build_ilp(2, np.array([0, 1, 3], np.int32), np.array([0, 0, 1], np.int32), np.ones(3, np.int8),
+                  np.ones(2, np.int32))
+    ctx.set_costs(torch.tensor([0.75, 5.0], dtype=torch.float64))
+    assert ctx.info["nnz"] == 0
+    for prec in ("fp64", "fp32"):
+        lam, trace = ctx.dual_solve(ctx.init_lambda(prec), iters)
+        assert lam.numel() == 0 and np.array_equal(np_(trace), np.full(iters, 0.75))
+        assert ctx.lower_bound(lam) == 0.75
