@@ -22,9 +22,9 @@
 // row pass streams its cells coalesced, in place, and every random access is a
 // 4-byte read of a small array (t: 4 bytes per variable) or of cells that
 // neighbouring variables share.  Measured, one iteration before and after:
-// 13.2 -> 10.0 us at the 500-face pair (two launches of 2.4 us each are half of
-// it), 41.6 -> 25.0 at 1000 faces, 253 -> 121 at 2000/3000 (row pass 75, variable
-// pass 46; 4.7 and 5.0 TB/s through the L2s, a plain copy reaches 4.7), 837 -> 381
+// 13.2 -> 9.1 us at the 500-face pair (two launches of 2.4 us each are half of
+// it), 41.6 -> 21.9 at 1000 faces, 253 -> 105 at 2000/3000 (row pass 65, variable
+// pass 40; 4.6 and 5.0 TB/s through the L2s, a plain copy reaches 4.7), 837 -> 308
 // with K = 144 candidates.
 //
 // Rows: closedness rows (short, coefficients +-1, right-hand side b) with b = 0
@@ -948,9 +948,9 @@ constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD
 // length, so that the words follow the descriptor at once).  A launch over few
 // blocks takes as long as its longest chain of loads and reductions: descriptor,
 // words, cells and residuals, six exchange steps of (m, m2), four of them as
-// register moves.  Against row number, offsets and an exchange of (m, m2, index)
-// through the LDS, an FP32 iteration takes 6.5-6.8 us (8.0) with 8k-30k entries,
-// 9.2 us (9.4) with 231k.  In place where
+// register moves.  With row number, offsets and an exchange of (m, m2, index)
+// through the LDS an FP32 iteration took 7.5-8.1 us with 8k-30k entries, 9.4 with
+// 231k; so 6.5-6.8 and 9.1.  In place where
 // cells and dst are one array: a lane reads its own cells before it writes them.
 // Returns the row minimum on one lane of the row.
 template <typename R, int MODE>
@@ -1156,7 +1156,7 @@ constexpr size_t smem_bytes() {
 // First pass of a hard iteration: t_i = c_i - sum_k s_k, one thread per
 // variable in variable order; unused slots read the zero cell.  Bound by the
 // index planes and the gathered lines (2000/3000-face pair: 20 + 16 bytes per
-// variable, 38 us, 5 TB/s; with the variables in canonical order 47 us).
+// variable, 40 us, 5 TB/s; 9 us more with the variables in canonical order).
 // Blocks 8 and up take the variables, each XCD a contiguous eighth; block 0
 // sums the previous row pass's partials, so that no other launch has to.
 template <typename R>
@@ -1768,10 +1768,10 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
 }
 
 // LDS of the one-workgroup form, 0 where it does not apply.  One CU takes about
-// 1 us an iteration for every thousand entries on top of 2.4, the two launches
-// 7.1 to 7.5 us at any small size (measured, FP32 and FP64: 989 entries 3.7 and
-// 4.0 against 7.3 and 7.5 us, 2946 4.4 and 6.7 against 7.1 and 7.5, 7695 7.4 and
-// 9.1 against 7.3 and 7.5), so the line lies at SMALL_NNZ entries.
+// 1 us an iteration for every thousand entries on top of 2, the two launches 6.5
+// to 7 us at any small size (FP32 and FP64: 989 entries 2.9 and 3.0 us in one
+// workgroup, 2946 3.1 and 4.7, 7695 about 7 and 9 against 6.6 and 6.7 in two
+// launches), so the line lies at SMALL_NNZ entries.
 template <typename R>
 static size_t small_lds(const dm_ctx* ctx) {
   constexpr int64_t NW = SMALL_THREADS<R> / 64;

@@ -20,9 +20,8 @@
 // entries, so that 64 neighbouring rows share most of their variables, a
 // wave's gathers fall into few cache lines, and each XCD, which takes a
 // contiguous eighth of either order, holds nearly all of what it reads in its
-// own L2 (2000/3000-face pair, both passes: 123 us so, 134 us with the
-// canonical order inside each X face).  A
-// generic problem without meshes keys a variable by its index.
+// own L2 (2000/3000-face pair, both passes: 11 us more with the canonical order
+// inside each X face; they take 105).  A generic problem without meshes keys a variable by its index.
 #include <algorithm>
 #include <climits>
 
@@ -670,8 +669,8 @@ dm_status sweep_layout(dm_ctx* ctx) {
   if (nshort > 0) {
     // the narrowest tiles only where one workgroup sweeps the problem from LDS
     // and its arithmetic counts: rows of one place spread over more tiles cost
-    // the variable pass cache lines (2000/3000-face pair 110 us an iteration
-    // without them, 117 with; 1000 faces 22.7 and 23.3)
+    // the variable pass cache lines (2000/3000-face pair 7 us more of 105
+    // an iteration with them, 1000 faces 0.6 of 22)
     const uint32_t form0 = rnnz <= SMALL_NNZ ? 0u : 1u;
     k_short_keys<<<grid_for(nshort, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rrow_b.p, ctx->rent_word.p, vkey.p,
                                                         nshort, ybits, ydrop, kbits, form0, skey.p, perm.p, count.p);
