@@ -21,7 +21,8 @@
 // wave's gathers fall into few cache lines, and each XCD, which takes a
 // contiguous eighth of either order, holds nearly all of what it reads in its
 // own L2 (2000/3000-face pair, both passes: 11 us more with the canonical order
-// inside each X face; they take 105).  A generic problem without meshes keys a variable by its index.
+// inside each X face; they take 105).  A generic problem without meshes keys a
+// variable by its index.
 #include <algorithm>
 #include <climits>
 
