@@ -616,12 +616,17 @@ __global__ __launch_bounds__(256) void k_sum_terms(TermSums T, const int32_t* sk
 // mean projection-row length above which a projection row gets a whole block
 constexpr int64_t LONG_BLOCK_ROW = 512;
 
+// largest X mesh: the size up to which the library answers for the layout
+constexpr int32_t MAX_KEY_FACES = 16384;
+
 dm_status sweep_layout(dm_ctx* ctx) {
   hipStream_t st = ctx->stream;
   const int64_t nfree = ctx->n_free, nr = ctx->n_rows, nshort = ctx->n_short, rnnz = ctx->nnz;
   const int64_t nlong = nr - nshort;
   const size_t nf1 = size_t(std::max<int64_t>(nfree, 1));
   const bool mesh = !ctx->generic && ctx->X.nf > 0;
+  if (mesh && nfree > 0 && ctx->X.nf > MAX_KEY_FACES)
+    return dm_fail(ctx, DM_ERR_WORKSPACE, "sweep layout: %d faces exceed %d key bins", ctx->X.nf, MAX_KEY_FACES);
   // ---- variable keys and the variable order; a product space has fewer than
   // 2^31 slots, so the two ranks of an element together fit 32 bits
   const int xbits = bits_for(mesh ? uint64_t(ctx->X.nf) : uint64_t(std::max<int64_t>(nfree, 1)));
