@@ -169,7 +169,7 @@ constexpr int REC_RDEG = 6;
 constexpr int MAX_SHORT_ROW = 64;
 constexpr int SOFT_MAX_ROW = 24;
 constexpr int64_t SMALL_LDS = 150 * 1024;   // the one-workgroup form: at most so many bytes of state
-constexpr int64_t SMALL_NNZ = 5000;         // and entries
+constexpr int64_t SMALL_NNZ = 8000, SMALL_NNZ64 = 6400;   // and entries, FP32 and FP64
 constexpr uint32_t CHUNK_PAD = 0xFFFFFFFFu;   // cell word of an unused cell
 
 // Multipliers of free variable i from its record (slots 0-4 hold s_k, slot 5

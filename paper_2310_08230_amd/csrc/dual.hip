@@ -1767,16 +1767,16 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
   return DM_OK;
 }
 
-// LDS of the one-workgroup form, 0 where it does not apply.  One CU takes about
-// 1 us an iteration for every thousand entries on top of 2, the two launches 6.5
-// to 7 us at any small size (FP32 and FP64: 989 entries 2.9 and 3.0 us in one
-// workgroup, 2946 3.1 and 4.7, 7695 about 7 and 9 against 6.6 and 6.7 in two
-// launches), so the line lies at SMALL_NNZ entries.
+// LDS of the one-workgroup form, 0 where it does not apply.  An iteration of it
+// against one of two launches, in us, of 200 in one call: FP32 989 entries 2.9 and
+// 6.5, 3782 4.1 and 6.5, 7695 5.0 and 6.8, 10433 13.0 and 6.9 (the waves no longer
+// keep their rows' words); FP64 989 3.0 and 6.7, 3782 6.6 and 6.9, 6334 6.8 and
+// 7.0, 7695 7.8 and 7.0.  So the lines lie at SMALL_NNZ and SMALL_NNZ64 entries.
 template <typename R>
 static size_t small_lds(const dm_ctx* ctx) {
   constexpr int64_t NW = SMALL_THREADS<R> / 64;
   const int64_t reals = ctx->n_cells + 1 + ctx->n_free + (ctx->n_chunks > 0 ? NW * 192 : 0);
-  return ctx->nnz <= SMALL_NNZ && reals * int64_t(sizeof(R)) <= SMALL_LDS ? size_t(reals) * sizeof(R) : 0;
+  return ctx->nnz <= (sizeof(R) == 4 ? SMALL_NNZ : SMALL_NNZ64) && reals * int64_t(sizeof(R)) <= SMALL_LDS ? size_t(reals) * sizeof(R) : 0;
 }
 
 // iters hard iterations in place on S (their t is left to the next cells_vars);
