@@ -95,7 +95,9 @@ template <typename R>
 struct SoftUnits;
 template <>
 struct SoftUnits<float> {
-  static constexpr float none = 1e37f, lim = 1e36f;   // a state that cannot be reached; every value is below lim
+  // a state that cannot be reached holds none; while a row's values are at most
+  // most, every sum of them is below lim and every such state above it
+  static constexpr float none = 1e37f, lim = 1e36f, most = 1e34f, big = 3.402823466e+38f;
   static __device__ float unit(float T) { return T * 0.693147180559945309f; }   // x = u * unit
   static __device__ float E(float x) { return __builtin_amdgcn_exp2f(x); }
   static __device__ float L(float x) { return __builtin_amdgcn_logf(x); }
@@ -103,7 +105,7 @@ struct SoftUnits<float> {
 };
 template <>
 struct SoftUnits<double> {
-  static constexpr double none = 1e307, lim = 1e306;
+  static constexpr double none = 1e307, lim = 1e306, most = 1e304, big = 1.7976931348623157e+308;
   static __device__ double unit(double T) { return T; }
   static __device__ double E(double x) { return exp(x); }
   static __device__ double L(double x) { return log(x); }
@@ -116,6 +118,14 @@ struct SoftUnits<double> {
 template <typename R>
 __device__ inline R smin2u(R a, R b) {
   return fmin(a, b) - SoftUnits<R>::L1p(SoftUnits<R>::E(-fabs(a - b)));
+}
+
+// The same where a state that cannot be reached holds +inf: clamped to the
+// largest finite value, an infinite operand leaves the other, and two give +inf.
+template <typename R>
+__device__ inline R smin2u_inf(R a, R b) {
+  constexpr R big = SoftUnits<R>::big;
+  return fmin(a, b) - SoftUnits<R>::L1p(SoftUnits<R>::E(-fabs(fmin(a, big) - fmin(b, big))));
 }
 
 // multiplier of entry word w from the previous record buffer, with dual
@@ -688,6 +698,56 @@ __device__ inline void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The recursions of one row per W-lane segment where a multiplier passes
+// SoftUnits::most in units (1e34 temperatures in FP32): the states that cannot be
+// reached are +inf, so that every finite sum counts, and each entry's soft-mins
+// are reductions over the lanes, for few registers rather than speed.  Kept out
+// of the sweep's own code (1000-face pair, which never comes here: 93.2 us a
+// launch against 93.0 without it and 93.9 with it inlined).  lamL: the row's n
+// multipliers in units, +inf behind them; neg: its signs; N negative ones, nm
+// entries in the wave's longest row.  Returns the row's value; lane l gets entry
+// l's soft-mins for x = 1 and 0.
+template <typename R, int W>
+__device__ __attribute__((noinline)) R soft_states_wide(R* tab, const R* lamL, int lane, int32_t n, int32_t b, uint32_t neg, int32_t N,
+                                     int32_t nm, R* my1, R* my0) {
+  using U = SoftUnits<R>;
+  constexpr int ST = soft_stride<W>();
+  auto shifted = [&](R v, int from) {   // v of the segment's lane from, none outside
+    const R x = __shfl(v, from & (W - 1), W);
+    return from >= 0 && from <= n ? x : rinf<R>();
+  };
+  auto softmin = [&](R x) {
+    R m = x, e;
+#pragma unroll 1
+    for (int o = 1; o < W; o <<= 1) m = fmin(m, __shfl_xor(m, o, W));
+    m = fmin(m, U::big);
+    e = U::E(m - x);
+#pragma unroll 1
+    for (int o = 1; o < W; o <<= 1) e += __shfl_xor(e, o, W);
+    return m - U::L(e);
+  };
+  R F = lane == N ? R(0) : rinf<R>();
+#pragma unroll 1
+  for (int l = 0; l < nm; ++l) {
+    if (W < 32 || lane < ST) tab[l * ST + lane] = F;
+    F = smin2u_inf<R>(F, shifted(F, lane - ((neg >> l) & 1u ? -1 : 1)) + lamL[l]);
+  }
+  wave_lds_fence();
+  R Bv = lane - N == b && lane <= n ? R(0) : rinf<R>();
+#pragma unroll 1
+  for (int l = nm - 1; l >= 0; --l) {
+    const R Fl = W < 32 || lane < ST ? tab[l * ST + lane] : rinf<R>();
+    const R sh = shifted(Bv, lane + ((neg >> l) & 1u ? -1 : 1));
+    const R one = softmin((Fl + lamL[l]) + sh), zero = softmin(Fl + Bv);
+    if (lane == l) {
+      *my1 = one;
+      *my0 = zero;
+    }
+    Bv = smin2u_inf<R>(Bv, sh + lamL[l]);
+  }
+  return __shfl(Bv, N, W);
+}
+
 template <typename R, int MODE, int W>
 __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R* __restrict__ out, R omega,
                                 R T, unsigned char* smem, double* red, int32_t item, int32_t blk, int32_t row0,
@@ -702,6 +762,7 @@ __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R
   int32_t s = 0, n = 0, b = 0;
   uint32_t w = 0;
   R mylam = R(0);
+  double rowpart = 0.0;
   const R unit = U::unit(T), inv_unit = R(1) / unit;
   if (act) {
     const int32_t j = A.soft_row[r];
@@ -722,112 +783,121 @@ __device__ void short_rows_soft(const SweepArgs& A, const R* __restrict__ rin, R
   for (int off = W; off < 64; off <<= 1) nm = max(nm, __shfl_xor(nm, off));
   nm = __builtin_amdgcn_readfirstlane(nm);
   wave_lds_fence();
-  // per entry the lanes whose row has it negative, as a mask of the wave
-  constexpr unsigned long long LOW = W == 8 ? 0x0101010101010101ull : (W == 16 ? 0x0001000100010001ull : 0x0000000100000001ull);
-  unsigned long long neg[NMAX];
-#pragma unroll
-  for (int l = 0; l < NMAX; ++l) {
-    const unsigned long long t = (neg_wave >> l) & LOW;
-    neg[l] = (t << W) - t;
-  }
-  // value of the state above (lanes of up) or below, none past the segment's ends
-  auto beside = [&](R v, unsigned long long up) {
-    const R lo = dpp_move<0x138>(v), hi = dpp_move<0x130>(v);   // v[lane - 1], v[lane + 1]
-    const R x = __builtin_amdgcn_inverse_ballot_w64(up) ? hi : lo;
-    return __builtin_amdgcn_inverse_ballot_w64((up & (LOW << (W - 1))) | (~up & LOW)) ? U::none : x;
-  };
-  constexpr int Q = (W == 32 ? ST : W) / 4;   // states in fours
-  R f[4 * Q];   // the entry's F_l of every state
-  auto load4 = [](const R* p, R* v) {
-    using Vec = typename LdsVec<R>::type;
-    constexpr int V = 16 / int(sizeof(R));
-#pragma unroll
-    for (int g = 0; g < 4; g += V) {
-      const Vec x = *reinterpret_cast<const Vec*>(p + g);
-#pragma unroll
-      for (int u = 0; u < V; ++u) v[g + u] = LdsVec<R>::get(x, u);
-    }
-  };
-  if (MODE != MODE_BOUND) {
-    R F = lane == N ? R(0) : U::none;
+  if (__builtin_expect(__any(fabs(mylam) > U::most * unit), 0)) {   // uniform across the wave
+    R my1 = R(0), my0 = R(0);
+    const R rowv = soft_states_wide<R, W>(tab, lamL, lane, n, b, uint32_t(neg_wave >> ((threadIdx.x & 63u) / W * W)), N, nm,
+                                          &my1, &my0);
+    if (MODE == MODE_UPDATE && lane < n) write_out<R>(out, w, mylam - omega * ((my1 - my0) * unit));
+    if (MODE == MODE_EVAL && lane < n) write_out<R>(out, w, U::E(rowv - my1));
+    rowpart = act && lane == 0 ? double(rowv * unit) : 0.0;
+  } else {
+    // per entry the lanes whose row has it negative, as a mask of the wave
+    constexpr unsigned long long LOW = W == 8 ? 0x0101010101010101ull : (W == 16 ? 0x0001000100010001ull : 0x0000000100000001ull);
+    unsigned long long neg[NMAX];
 #pragma unroll
     for (int l = 0; l < NMAX; ++l) {
-      if (l >= nm) break;   // uniform
-      if (W < 32 || lane < ST) tab[l * ST + lane] = F;
-      F = smin2u<R>(F, beside(F, neg[l]) + lamL[l]);
+      const unsigned long long t = (neg_wave >> l) & LOW;
+      neg[l] = (t << W) - t;
     }
-    wave_lds_fence();
-    if (lane < n) {
+    // value of the state above (lanes of up) or below, none past the segment's ends
+    auto beside = [&](R v, unsigned long long up) {
+      const R lo = dpp_move<0x138>(v), hi = dpp_move<0x130>(v);   // v[lane - 1], v[lane + 1]
+      const R x = __builtin_amdgcn_inverse_ballot_w64(up) ? hi : lo;
+      return __builtin_amdgcn_inverse_ballot_w64((up & (LOW << (W - 1))) | (~up & LOW)) ? U::none : x;
+    };
+    constexpr int Q = (W == 32 ? ST : W) / 4;   // states in fours
+    R f[4 * Q];   // the entry's F_l of every state
+    auto load4 = [](const R* p, R* v) {
+      using Vec = typename LdsVec<R>::type;
+      constexpr int V = 16 / int(sizeof(R));
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (4 * q > nm) break;   // uniform: no row of the wave has such states
-        load4(tab + lane * ST + 4 * q, f + 4 * q);
+      for (int g = 0; g < 4; g += V) {
+        const Vec x = *reinterpret_cast<const Vec*>(p + g);
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[g + u] = LdsVec<R>::get(x, u);
       }
-    }
-    wave_lds_fence();   // the table now takes B
-  }
-  R Bv = lane - N == b && lane <= n ? R(0) : U::none;
+    };
+    if (MODE != MODE_BOUND) {
+      R F = lane == N ? R(0) : U::none;
 #pragma unroll
-  for (int l = NMAX - 1; l >= 0; --l) {
-    if (l < nm) {   // uniform
-      if (MODE != MODE_BOUND && (W < 32 || lane < ST)) tab[l * ST + lane] = Bv;
-      Bv = smin2u<R>(Bv, beside(Bv, ~neg[l]) + lamL[l]);
-    }
-  }
-  // the soft row value B_0(0) sits on lane N
-  R rowv = __shfl(Bv, N, W);
-  rowv = rowv < U::lim ? rowv : rinf<R>();
-  if (MODE != MODE_BOUND) {
-    wave_lds_fence();
-    if (lane < n) {
-      const bool up = !(w >> 31);
-      const R* Bl = tab + lane * ST;
-      const R mine = lamL[lane];
-      R x1[4 * Q];   // the sums for x = 1; f becomes those for x = 0
-      R m0 = U::none, m1 = U::none;
-      R below = U::none;   // B of the state below the four
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        if (4 * q > nm) break;
-        R B[6];
-        B[0] = below;
-        load4(Bl + 4 * q, B + 1);
-        B[5] = q + 1 < Q ? Bl[4 * q + 4] : U::none;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          R& x = f[4 * q + u];
-          x1[4 * q + u] = (x + mine) + (up ? B[u + 2] : B[u]);
-          x = x + B[u + 1];
-          m0 = fmin(m0, x);
-          m1 = fmin(m1, x1[4 * q + u]);
-        }
-        below = B[4];
+      for (int l = 0; l < NMAX; ++l) {
+        if (l >= nm) break;   // uniform
+        if (W < 32 || lane < ST) tab[l * ST + lane] = F;
+        F = smin2u<R>(F, beside(F, neg[l]) + lamL[l]);
       }
-      // one exponential per state, added in pairs, fours, eights, ...
-      R e0[8], e1[8];
+      wave_lds_fence();
+      if (lane < n) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        e0[q] = e1[q] = R(0);
-        if (q < Q && 4 * q <= nm) {
-          const R *x = f + 4 * (q < Q ? q : 0), *y = x1 + 4 * (q < Q ? q : 0);
-          e0[q] = (U::E(m0 - x[0]) + U::E(m0 - x[1])) + (U::E(m0 - x[2]) + U::E(m0 - x[3]));
-          e1[q] = (U::E(m1 - y[0]) + U::E(m1 - y[1])) + (U::E(m1 - y[2]) + U::E(m1 - y[3]));
+        for (int q = 0; q < Q; ++q) {
+          if (4 * q > nm) break;   // uniform: no row of the wave has such states
+          load4(tab + lane * ST + 4 * q, f + 4 * q);
         }
       }
-#pragma unroll
-      for (int h = 1; h < W / 4; h *= 2)
-#pragma unroll
-        for (int q = 0; q < W / 4; q += 2 * h) {
-          e0[q] += e0[q + h];
-          e1[q] += e1[q + h];
-        }
-      const R my1 = m1 < U::lim ? m1 - U::L(e1[0]) : rinf<R>();
-      const R my0 = m0 < U::lim ? m0 - U::L(e0[0]) : rinf<R>();
-      if (MODE == MODE_UPDATE) write_out<R>(out, w, mylam - omega * ((my1 - my0) * unit));
-      if (MODE == MODE_EVAL) write_out<R>(out, w, U::E(rowv - my1));
+      wave_lds_fence();   // the table now takes B
     }
+    R Bv = lane - N == b && lane <= n ? R(0) : U::none;
+#pragma unroll
+    for (int l = NMAX - 1; l >= 0; --l) {
+      if (l < nm) {   // uniform
+        if (MODE != MODE_BOUND && (W < 32 || lane < ST)) tab[l * ST + lane] = Bv;
+        Bv = smin2u<R>(Bv, beside(Bv, ~neg[l]) + lamL[l]);
+      }
+    }
+    // the soft row value B_0(0) sits on lane N
+    R rowv = __shfl(Bv, N, W);
+    rowv = rowv < U::lim ? rowv : rinf<R>();
+    if (MODE != MODE_BOUND) {
+      wave_lds_fence();
+      if (lane < n) {
+        const bool up = !(w >> 31);
+        const R* Bl = tab + lane * ST;
+        const R mine = lamL[lane];
+        R x1[4 * Q];   // the sums for x = 1; f becomes those for x = 0
+        R m0 = U::none, m1 = U::none;
+        R below = U::none;   // B of the state below the four
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          if (4 * q > nm) break;
+          R B[6];
+          B[0] = below;
+          load4(Bl + 4 * q, B + 1);
+          B[5] = q + 1 < Q ? Bl[4 * q + 4] : U::none;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            R& x = f[4 * q + u];
+            x1[4 * q + u] = (x + mine) + (up ? B[u + 2] : B[u]);
+            x = x + B[u + 1];
+            m0 = fmin(m0, x);
+            m1 = fmin(m1, x1[4 * q + u]);
+          }
+          below = B[4];
+        }
+        // one exponential per state, added in pairs, fours, eights, ...
+        R e0[8], e1[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          e0[q] = e1[q] = R(0);
+          if (q < Q && 4 * q <= nm) {
+            const R *x = f + 4 * (q < Q ? q : 0), *y = x1 + 4 * (q < Q ? q : 0);
+            e0[q] = (U::E(m0 - x[0]) + U::E(m0 - x[1])) + (U::E(m0 - x[2]) + U::E(m0 - x[3]));
+            e1[q] = (U::E(m1 - y[0]) + U::E(m1 - y[1])) + (U::E(m1 - y[2]) + U::E(m1 - y[3]));
+          }
+        }
+#pragma unroll
+        for (int h = 1; h < W / 4; h *= 2)
+#pragma unroll
+          for (int q = 0; q < W / 4; q += 2 * h) {
+            e0[q] += e0[q + h];
+            e1[q] += e1[q + h];
+          }
+        const R my1 = m1 < U::lim ? m1 - U::L(e1[0]) : rinf<R>();
+        const R my0 = m0 < U::lim ? m0 - U::L(e0[0]) : rinf<R>();
+        if (MODE == MODE_UPDATE) write_out<R>(out, w, mylam - omega * ((my1 - my0) * unit));
+        if (MODE == MODE_EVAL) write_out<R>(out, w, U::E(rowv - my1));
+      }
+    }
+    rowpart = act && lane == 0 ? double(rowv * unit) : 0.0;
   }
-  const double rowpart = act && lane == 0 ? double(rowv * unit) : 0.0;
   store_partial(block_sum(rowpart, red), A.partial, item);
 }
 
