@@ -45,6 +45,7 @@
 #include <cmath>
 
 #include "dm_internal.h"
+#include "small_layout.h"
 
 namespace {
 
@@ -501,7 +502,7 @@ template <typename R, int MODE>
 __device__ __forceinline__ double chunk_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega, R gam,
                               unsigned char* smem, int32_t item) {
   const int wave = threadIdx.x >> 6;
-  R* wave_vals = reinterpret_cast<R*>(smem) + wave * 192;   // three 64-value slices per wave
+  R* wave_vals = reinterpret_cast<R*>(smem) + wave * CHUNK_SLICE;
   [[clang::always_inline]] return short_chunk_hard<R, MODE>(A, cells, t, out, omega, gam, item * 4 + wave, wave_vals);
 }
 
@@ -1220,7 +1221,7 @@ __device__ double long_records(const SweepArgs& A, const R* __restrict__ src, R*
 
 template <typename R, bool SOFT>
 constexpr size_t smem_bytes() {
-  return SOFT ? (SOFT_TAB + 256) * sizeof(R) : 768 * sizeof(R);
+  return SOFT ? (SOFT_TAB + 256) * sizeof(R) : 4 * CHUNK_SLICE * sizeof(R);
 }
 
 // First pass of a hard iteration: t_i = c_i - sum_k s_k, one thread per
@@ -1365,7 +1366,7 @@ __global__ __launch_bounds__(NT) void k_small(SweepArgs A, const uint32_t* __res
   __shared__ double part[2][NT / 64];
   R* cells = reinterpret_cast<R*>(lds);
   R* t = cells + n_cells + 1;
-  R* wave_vals = t + n + (threadIdx.x >> 6) * 192;   // chunks only
+  R* wave_vals = cells + small_slices_at<R>(n_cells, n) + (threadIdx.x >> 6) * CHUNK_SLICE;   // chunks only
   constexpr int NW = NT / 64;
   const int tid = int(threadIdx.x), wave = tid >> 6, lane = tid & 63;
   for (uint32_t c = uint32_t(tid); c <= n_cells; c += NT) cells[c] = gcells[c];
@@ -1844,8 +1845,7 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
 // 7.0, 7695 7.8 and 7.0.  So the lines lie at SMALL_NNZ and SMALL_NNZ64 entries.
 template <typename R>
 static size_t small_lds(const dm_ctx* ctx) {
-  constexpr int64_t NW = SMALL_THREADS<R> / 64;
-  const int64_t reals = ctx->n_cells + 1 + ctx->n_free + (ctx->n_chunks > 0 ? NW * 192 : 0);
+  const int64_t reals = small_reals<R>(ctx->n_cells, ctx->n_free, ctx->n_chunks > 0, SMALL_THREADS<R> / 64);
   return ctx->nnz <= (sizeof(R) == 4 ? SMALL_NNZ : SMALL_NNZ64) && reals * int64_t(sizeof(R)) <= SMALL_LDS ? size_t(reals) * sizeof(R) : 0;
 }
 
