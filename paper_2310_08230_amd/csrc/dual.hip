@@ -1869,9 +1869,11 @@ dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, doubl
     constexpr int NT = SMALL_THREADS<R>;
     const int64_t n_long = ctx->n_rows - ctx->n_short, mean = (ctx->nnz - ctx->nnz_short) / std::max<int64_t>(n_long, 1);
     const int32_t group = mean <= 16 ? 4 : (mean <= 64 ? 16 : 64);
+    // the most that any launch of it takes, whatever this one needs: the limit
+    // belongs to the function, which other threads' contexts launch too
     if (lds > 48 * 1024)
       DM_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small<R, NT>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(SMALL_LDS)));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1, iters));
     if (e0)
