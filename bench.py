@@ -214,8 +214,8 @@ def sweep_roofline(cfg, seed, iters=200, temperature=0.0, **over):
     at T = 0.1 (seed 0) its instructions per launch, from the committed SQ
     counter summary, are set against the VALU issue peak.
     ``over`` changes the pair's spec (e.g. ``k=96``).  A hard iteration is two
-    kernels (the variable pass and the row pass), timed from the start of the
-    first to the end of the second.  The working set is one multiplier, one
+    kernels (the variable pass and the row pass); its time is the sum of
+    their own durations, without the gap between them.  The working set is one multiplier, one
     variable word and one cell index per nonzero and the cost and residual of
     every variable (padding not counted)."""
     w = Workload(cfg, seed, **over)
@@ -646,7 +646,7 @@ def main():
     info = w.ctx.info
     log(f"[bench] timed: {ms_per_step:.2f} ms/step, {value:.0f} dual it/s, gap={r['gap']:.2e}")
 
-    # dominant kernels: one sweep (variable pass and row pass), timed with HIP events on its stream
+    # dominant kernels: one sweep (variable pass and row pass), each kernel timed with HIP events
     c = w.ctx
     lam = c.init_lambda(w.msg)
     c.dual_solve(lam, 20, w.spec.omega, w.spec.temperature, trace=False)
@@ -656,7 +656,7 @@ def main():
     c.dual_solve(lam, w.iters, w.spec.omega, w.spec.temperature)
     torch.cuda.synchronize()
     solve_s = time.perf_counter() - t1
-    # the same solve with start/stop events around every sweep launch
+    # the same solve with start/stop events of every sweep kernel
     c.timing(True)
     c.dual_solve(lam, w.iters, w.spec.omega, w.spec.temperature)
     torch.cuda.synchronize()
@@ -671,7 +671,7 @@ def main():
             "traffic": _traffic() if (a.config, a.seed, a.k) == (2, 0, None) and w.iters > 0 else None,
             "kernel": "k_vars<float> + k_sweep<float,false,MODE_UPDATE>", "avg_launch_us": round(avg_s * 1e6, 3),
             "bytes_per_launch": bytes_per_launch}
-    log(f"[bench] sweep kernel: {n_launch} launches, avg {avg_s * 1e6:.2f} us, {achieved:.0f} GB/s algorithmic")
+    log(f"[bench] sweep kernels: {n_launch} sweeps, avg {avg_s * 1e6:.2f} us, {achieved:.0f} GB/s algorithmic")
 
     out = {"metric": "dual iterations/sec + time-to-1% gap, plain FP32 vs mixed/diff form, 1 MI355X",
            "value": round(value, 2), "unit": "dual iterations/s", "n_gpus": 1, "steps": a.steps,

@@ -479,14 +479,17 @@ dm_status dm_smoothed_backward(dm_ctx* ctx, const void* lambda, double temperatu
  *  out [device] double [nv]. */
 dm_status dm_mixed_areas(dm_ctx* ctx, const dm_mesh* M, double* out);
 
-/* Measurement hook: while enabled, every dual-sweep kernel launch (of any
- * entry point) carries a pair of HIP events that record the kernel's own
- * start and end (hipExtLaunchKernelGGL) on the context's stream.
- * dm_timing_read synchronises the stream and returns the number of timed
- * launches and the sum of their durations in milliseconds [host], then
- * clears the record.  Off by default. */
+/* Measurement hook: while enabled, every dual-sweep kernel (of any entry
+ * point) carries a pair of HIP events that record the kernel's own start and
+ * end (hipExtLaunchKernelGGL) on the context's stream.  A sweep visits all rows
+ * once: an iteration, or an evaluation of the bound, the minimisers or the
+ * min-marginals.  It is one kernel, two (a variable pass and a row pass), or, in
+ * small problems, one of the iterations of a single kernel.  dm_timing_read
+ * synchronises the stream and returns the number of timed sweeps and the sum
+ * of their kernels' durations in milliseconds [host], then clears the record.
+ * Off by default. */
 dm_status dm_timing_enable(dm_ctx* ctx, int32_t enable);
-dm_status dm_timing_read(dm_ctx* ctx, int64_t* launches, double* total_ms);
+dm_status dm_timing_read(dm_ctx* ctx, int64_t* sweeps, double* total_ms);
 
 /* Version string of the library build. */
 const char* dm_version(void);

@@ -424,12 +424,11 @@ struct dm_ctx {
   DArr<float> gw;                // gradient per pair
   DArr<float> gcost_tmp;         // gradient per element
 
-  // optional per-launch event timing of the sweep kernel
+  // optional event timing of the sweep kernels
   bool timing = false;
-  bool timing_open = false;   // a start event waits for its row pass
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
-  int64_t ev_sweeps = 0;      // sweeps the recorded events span
+  int64_t ev_sweeps = 0;      // sweeps that the timed kernels made
 
   // quasi-Newton session kept between dm_lbfgs_solve calls (history, step
   // size, Delta_min), owned by lbfgs.hip; invalidated when the costs or the
@@ -539,7 +538,7 @@ struct SweepExt {
 template <typename R>
 dm_status cells_import(dm_ctx* ctx, const R* lam, CellState& S, bool two);
 template <typename R>
-dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool timed);
+dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool sweep);
 template <typename R>
 dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
                      const SweepExt* ext);

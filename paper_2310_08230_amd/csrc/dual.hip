@@ -1712,36 +1712,34 @@ static void pend(dm_ctx* ctx, double* mine, int64_t n, double* bound_out) {
   ctx->pend_out = bound_out;
 }
 
-// timing: a start event for the first kernel of a sweep, a stop event for its
-// last (the runtime records the kernels' own start and end)
-static dm_status timing_events(dm_ctx* ctx, hipEvent_t* e0, hipEvent_t* e1, int64_t sweeps = 1) {
+// timing: start and stop event of the next kernel (the runtime records the
+// kernel's own start and end), which ends so many sweeps
+static dm_status timing_events(dm_ctx* ctx, hipEvent_t* e0, hipEvent_t* e1, int64_t sweeps) {
   while (ctx->ev_pool.size() < ctx->ev_used + 2) {
     hipEvent_t e;
     DM_HIP(ctx, hipEventCreate(&e));
     ctx->ev_pool.push_back(e);
   }
-  if (e0) *e0 = ctx->ev_pool[ctx->ev_used];
-  if (e1) {
-    *e1 = ctx->ev_pool[ctx->ev_used + 1];
-    ctx->ev_used += 2;
-    ctx->ev_sweeps += sweeps;
-  }
+  *e0 = ctx->ev_pool[ctx->ev_used];
+  *e1 = ctx->ev_pool[ctx->ev_used + 1];
+  ctx->ev_used += 2;
+  ctx->ev_sweeps += sweeps;
   return DM_OK;
 }
 
 // t of every variable from the cells; takes over the bound of the last row
-// pass that has not been summed yet
+// pass that has not been summed yet.  sweep: a row pass follows, which counts it
+// as its own (timing)
 template <typename R>
-dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool timed) {
+dm_status cells_vars(dm_ctx* ctx, const R* cells, const R* cost, R* t, bool sweep) {
   const int64_t n = ctx->n_free;
   const int32_t per = int32_t((n + 8 * 256 - 1) / (8 * 256));
-  hipEvent_t e0 = nullptr;
-  if (ctx->timing && timed) DM_TRY(timing_events(ctx, &e0, nullptr));
-  ctx->timing_open = e0 != nullptr;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (ctx->timing && sweep && hard_grid(ctx) > 0) DM_TRY(timing_events(ctx, &e0, &e1, 0));
   const double* pp = ctx->pend_out ? ctx->pend_partial : nullptr;
   const unsigned grid = 8u * unsigned(per + 1);
   if (e0)
-    hipExtLaunchKernelGGL(k_vars<R>, dim3(grid), dim3(256), 0, ctx->stream, e0, nullptr, 0, ctx->vpos.p, cells, cost,
+    hipExtLaunchKernelGGL(k_vars<R>, dim3(grid), dim3(256), 0, ctx->stream, e0, e1, 0, ctx->vpos.p, cells, cost,
                           n, per, t, pp, ctx->pend_n, ctx->pend_offset, ctx->pend_out);
   else
     k_vars<R><<<grid, 256, 0, ctx->stream>>>(ctx->vpos.p, cells, cost, n, per, t, pp, ctx->pend_n, ctx->pend_offset,
@@ -1824,15 +1822,14 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
   double* mine = nullptr;
   DM_TRY(next_partials(ctx, sizeof(R), &mine));
   A.partial = mine;
-  hipEvent_t e1 = nullptr;
-  if (ctx->timing_open) DM_TRY(timing_events(ctx, nullptr, &e1));
-  ctx->timing_open = false;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1, 1));
   hipStream_t st = ctx->stream;
   const unsigned g = unsigned(grid);
-  if (mode == MODE_UPDATE) launch_sweep<R, false, MODE_UPDATE>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
-  else if (mode == MODE_EVAL) launch_sweep<R, false, MODE_EVAL>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
-  else if (mode == MODE_BOUND) launch_sweep<R, false, MODE_BOUND>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
-  else launch_sweep<R, false, MODE_SUBGRAD>(st, g, nullptr, e1, A, cells, t, out, omega, R(0));
+  if (mode == MODE_UPDATE) launch_sweep<R, false, MODE_UPDATE>(st, g, e0, e1, A, cells, t, out, omega, R(0));
+  else if (mode == MODE_EVAL) launch_sweep<R, false, MODE_EVAL>(st, g, e0, e1, A, cells, t, out, omega, R(0));
+  else if (mode == MODE_BOUND) launch_sweep<R, false, MODE_BOUND>(st, g, e0, e1, A, cells, t, out, omega, R(0));
+  else launch_sweep<R, false, MODE_SUBGRAD>(st, g, e0, e1, A, cells, t, out, omega, R(0));
   DM_LAUNCH_CHECK(ctx);
   pend(ctx, mine, grid, bound_out);
   return DM_OK;
@@ -1922,7 +1919,7 @@ dm_status soft_sweep(dm_ctx* ctx, int mode, const unsigned char* rin, unsigned c
   const int64_t long_slots = (nl + 8 * LONG_GROUP - 1) / (8 * LONG_GROUP) * LONG_GROUP;
   const unsigned g = unsigned(8 * (long_slots + (A.n_short_blocks + 7) / 8));
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1));
+  if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1, 1));
   const R* ri = reinterpret_cast<const R*>(rin);
   R* ro = reinterpret_cast<R*>(out);
   hipStream_t st = ctx->stream;
@@ -1950,8 +1947,8 @@ extern "C" dm_status dm_timing_enable(dm_ctx* ctx, int32_t enable) {
   return DM_OK;
 }
 
-extern "C" dm_status dm_timing_read(dm_ctx* ctx, int64_t* launches, double* total_ms) {
-  if (!ctx || !launches || !total_ms) return DM_ERR_INVALID_ARG;
+extern "C" dm_status dm_timing_read(dm_ctx* ctx, int64_t* sweeps, double* total_ms) {
+  if (!ctx || !sweeps || !total_ms) return DM_ERR_INVALID_ARG;
   DM_HIP(ctx, hipSetDevice(ctx->device));
   DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
   double tot = 0.0;
@@ -1960,7 +1957,7 @@ extern "C" dm_status dm_timing_read(dm_ctx* ctx, int64_t* launches, double* tota
     DM_HIP(ctx, hipEventElapsedTime(&ms, ctx->ev_pool[i], ctx->ev_pool[i + 1]));
     tot += ms;
   }
-  *launches = ctx->ev_sweeps;
+  *sweeps = ctx->ev_sweeps;
   *total_ms = tot;
   ctx->ev_used = 0;
   ctx->ev_sweeps = 0;
@@ -2051,7 +2048,7 @@ static dm_status bound_impl(dm_ctx* ctx, const R* lam, R T, double* out) {
   } else {
     CellState S;
     DM_TRY(cells_import<R>(ctx, lam, S, false));
-    DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), false));
+    DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), true));
     DM_TRY(cells_rows<R>(ctx, MODE_BOUND, S.cells<R>(0), S.ts<R>(0), static_cast<R*>(nullptr), R(0), ctx->scal.p,
                          nullptr));
     DM_TRY(dual_flush(ctx));

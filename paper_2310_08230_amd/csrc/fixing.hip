@@ -73,7 +73,7 @@ dm_status confident_impl(dm_ctx* ctx, const R* lam, double frac, int8_t* fix, in
     DM_TRY(cells_import<R>(ctx, lam, S, false));
     DM_ALLOC(ctx, ctx->mrec, size_t(ctx->n_cells + 1) * sizeof(R));
     R* m = reinterpret_cast<R*>(ctx->mrec.p);
-    DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), false));
+    DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), true));
     DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, S.cells<R>(0), S.ts<R>(0), m, R(0), nullptr, nullptr));
     DArr<uint8_t> flag;
     DArr<int8_t> pref;

@@ -643,7 +643,7 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
   SweepExt sub;
   sub.gsub = gcell;
   sub.terms = ordered ? ctx->terms : nullptr;
-  DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), false));
+  DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), true));
   DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(0), C.ts<R>(0), none, R(0), nullptr, &sub));
   DM_TRY(block_sums(nullptr));
   k_qn_begin<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, st, etrace, P.gamma0, resume ? 1 : 0);
@@ -677,7 +677,7 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
     me.gamma = &st->step;
     const int nxt = cur ^ 1;
     DM_TRY(cells_rows<R>(ctx, SWEEP_UPDATE, C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), R(P.omega), nullptr, &me));
-    DM_TRY(cells_vars<R>(ctx, C.cells<R>(nxt), C.costs<R>(), C.ts<R>(nxt), false));
+    DM_TRY(cells_vars<R>(ctx, C.cells<R>(nxt), C.costs<R>(), C.ts<R>(nxt), true));
     DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(nxt), C.ts<R>(nxt), none, R(0), nullptr, &sub));
     DM_TRY(block_sums(nullptr));
     double* psy = B.part + 2 * VGRID;
@@ -733,7 +733,7 @@ dm_status subgradient_impl(dm_ctx* ctx, const R* lam, uint8_t* g, double* lb) {
   DM_ALLOC(ctx, ctx->scal, 16);
   SweepExt sub;
   sub.gsub = gcell.p;
-  DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), false));
+  DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), true));
   DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(0), C.ts<R>(0), static_cast<R*>(nullptr), R(0), ctx->scal.p,
                        &sub));
   DM_TRY(dual_flush(ctx));

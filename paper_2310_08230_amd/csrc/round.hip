@@ -158,7 +158,7 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
   double delta = P.delta0;
   *feasible = 0;
   for (int32_t r = 0; r <= P.rounds; ++r) {
-    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, false));
+    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
     DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, cells, t, m, R(0), nullptr, nullptr));
     DM_HIP(ctx, hipMemsetAsync(ctx->icount.p, 0, sizeof(int64_t), st));
     const bool auto_delta = r == 0 && delta <= 0.0;

@@ -150,7 +150,7 @@ dm_status node_bound_and_branch(dm_ctx* ctx, const dm_search_params& P, DArr<uns
   DM_TRY(cells_import<R>(ctx, lam, S, false));
   DM_ALLOC(ctx, ctx->mrec, size_t(ctx->n_cells + 1) * sizeof(R));
   R* m = reinterpret_cast<R*>(ctx->mrec.p);
-  DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), false));
+  DM_TRY(cells_vars<R>(ctx, S.cells<R>(0), S.costs<R>(), S.ts<R>(0), true));
   DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, S.cells<R>(0), S.ts<R>(0), m, R(0), nullptr, nullptr));
   DArr<unsigned long long> key;
   DArr<int32_t> out;
