@@ -523,10 +523,17 @@ extern "C" dm_status dm_knn_candidates(dm_ctx* ctx, const float* FX, int32_t nvx
   ctx->err.clear();
   DM_TRY(knn_check_args(ctx, "dm_knn_candidates", FX, nvx, FY, nvy, D, K, prec, cand_xy, cand_yx));
   DM_HIP(ctx, hipSetDevice(ctx->device));
+  // the transposed distances where they are read and memory has room for both
   DArr<unsigned char> ws;
   KnnBufs w;
-  DM_ALLOC(ctx, ws, knn_layout(nvx, nvy, D, prec, true, true, nullptr, nullptr));
-  knn_layout(nvx, nvy, D, prec, true, true, ws.p, &w);
+  bool with_t = K <= TOPK_MAX / 2;
+  if (with_t && ws.resize(knn_layout(nvx, nvy, D, prec, true, true, nullptr, nullptr), ctx->stream, ctx->pool,
+                          &ctx->cache) != hipSuccess) {
+    (void)hipGetLastError();
+    with_t = false;
+  }
+  if (!with_t) DM_ALLOC(ctx, ws, knn_layout(nvx, nvy, D, prec, true, false, nullptr, nullptr));
+  knn_layout(nvx, nvy, D, prec, true, with_t, ws.p, &w);
   DM_TRY(knn_run(ctx, FX, nvx, FY, nvy, D, K, prec, cand_xy, cand_yx, w));
   return DM_OK;   // the temporaries are freed in stream order
 }
@@ -551,8 +558,9 @@ extern "C" dm_status dm_knn_candidates_noalloc(dm_ctx* ctx, const float* FX, int
                             ctx->device);
   DM_HIP(ctx, hipSetDevice(ctx->device));
   KnnBufs w;
-  // the transposed distances where the scratch has room for them
-  const bool with_t = knn_layout(nvx, nvy, D, prec, true, true, nullptr, nullptr) <= KNN_SCRATCH_BYTES;
+  // the transposed distances where they are read and the scratch has room for them
+  const bool with_t =
+      K <= TOPK_MAX / 2 && knn_layout(nvx, nvy, D, prec, true, true, nullptr, nullptr) <= KNN_SCRATCH_BYTES;
   knn_layout(nvx, nvy, D, prec, true, with_t, static_cast<unsigned char*>(base), &w);
   return knn_run(ctx, FX, nvx, FY, nvy, D, K, prec, cand_xy, cand_yx, w);
 }
