@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/discomatch.h"
@@ -131,6 +132,14 @@ struct DArr {
     cls = c;
     return hipSuccess;
   }
+  void swap(DArr& o) {
+    std::swap(p, o.p);
+    std::swap(n, o.n);
+    std::swap(s, o.s);
+    std::swap(view, o.view);
+    std::swap(cache, o.cache);
+    std::swap(cls, o.cls);
+  }
   void attach(T* ptr, size_t count) {
     release();
     p = ptr;
@@ -169,7 +178,8 @@ constexpr int REC_RDEG = 6;
 constexpr int MAX_SHORT_ROW = 64;
 constexpr int SOFT_MAX_ROW = 24;
 constexpr int64_t SMALL_LDS = 150 * 1024;   // the one-workgroup form: at most so many bytes of state
-constexpr int64_t SMALL_NNZ = 8000, SMALL_NNZ64 = 6400;   // and entries, FP32 and FP64
+constexpr int64_t SMALL_NNZ[2] = {6400, 3700};   // and entries (FP32, FP64)
+constexpr int64_t ONE_LAUNCH_NNZ = 180000;       // one launch per iteration: at most so many entries
 constexpr uint32_t CHUNK_PAD = 0xFFFFFFFFu;   // cell word of an unused cell
 
 // Multipliers of free variable i from its record (slots 0-4 hold s_k, slot 5
@@ -295,6 +305,7 @@ struct CellState {
   R* ts(int b) { return reinterpret_cast<R*>(t[b].p); }
   template <typename R>
   R* costs() { return reinterpret_cast<R*>(cost.p); }
+  void swap() { cell[0].swap(cell[1]); }
   void release() {
     for (int b = 0; b < 2; ++b) {
       cell[b].release();

@@ -27,6 +27,10 @@
 // pass 40; 4.6 and 5.0 TB/s through the L2s, a plain copy reaches 4.7), 837 -> 308
 // with K = 144 candidates.
 //
+// Problems of few entries take other forms of the same iteration, bit for bit: one
+// workgroup that runs all of them from LDS (k_small), or one launch each, in
+// which every entry sums its variable's cells itself (k_iterate); see hard_form.
+//
 // Rows: closedness rows (short, coefficients +-1, right-hand side b) with b = 0
 // and few entries run one lane per row (tiles), the others one lane per entry
 // in wave chunks, with the row minimum from sorted prefix sums: choosing k
@@ -238,11 +242,33 @@ __device__ inline R rdeg_of(uint32_t w) {
   return (w >> 31) ? rdeg_hi<R>(w) : lo;
 }
 
+// Where a row pass takes the residuals from: the array that the variable pass
+// wrote, or the variable's cost and cells, added in the variable pass's order.
+template <typename R>
+using Written = const R* __restrict__;
+
+template <typename R>
+struct Summed {
+  const uint32_t* __restrict__ vpos;
+  const R* __restrict__ cells;
+  const R* __restrict__ cost;
+  uint32_t n;
+  __device__ R operator[](uint32_t v) const {
+    uint32_t p[5];
+    R s[5];
+#pragma unroll
+    for (uint32_t q = 0; q < 5; ++q) p[q] = vpos[q * n + v];
+    const R c = cost[v];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) s[q] = cells[p[q]];
+    return c - ((((s[0] + s[1]) + s[2]) + s[3]) + s[4]);
+  }
+};
+
 // multiplier of cell c (word w, not padding) as the rows see it: feasible, and
 // moved along dir when one is set
-template <typename R>
-__device__ inline R cell_lambda(const SweepArgs& A, const R* cells, const R* __restrict__ t, uint32_t c, uint32_t w,
-                                R gam) {
+template <typename R, typename RT>
+__device__ inline R cell_lambda(const SweepArgs& A, const R* cells, RT t, uint32_t c, uint32_t w, R gam) {
   R v = feasible<R>(cells[c], t[w & W_VAR_MASK], rdeg_of<R>(w));
   if (A.dir) v = fma_r<R>(gam, static_cast<const R*>(A.dir)[c], v);
   return v;
@@ -286,9 +312,9 @@ __device__ inline R permute_to(int dst_lane, R v) {   // push v to lane dst_lane
   }
 }
 
-template <typename R, int MODE>
-__device__ inline double short_chunk_hard(const SweepArgs& A, const R* cells, const R* __restrict__ t_, R* out,
-                                          R omega, R gam, int32_t wc, R* wave_vals) {
+template <typename R, typename RT, int MODE>
+__device__ inline double short_chunk_hard(const SweepArgs& A, const R* cells, RT t_, R* out, R omega, R gam,
+                                          int32_t wc, R* wave_vals) {
   const int lane = threadIdx.x & 63;
   double rowpart = 0.0;
   if (wc < A.n_chunks) {   // uniform across the wave
@@ -300,7 +326,7 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* cells, co
     const int32_t b = A.chunk_b[size_t(wc) * 64 + lane];
     const bool act = w != CHUNK_PAD;
     const int32_t ne = __popcll(__ballot(act));
-    const R lam = act ? cell_lambda<R>(A, cells, t_, cell, w, gam) : R(0);
+    const R lam = act ? cell_lambda<R, RT>(A, cells, t_, cell, w, gam) : R(0);
     const int g = int((negm >> lane) & 1ull);
     // my row from the chunk's row-start mask: its start is the last set bit at
     // or below this lane, its end the next set bit (or the chunk's end)
@@ -498,12 +524,12 @@ __device__ inline double short_chunk_hard(const SweepArgs& A, const R* cells, co
 }
 
 // the four waves of a block take four adjacent chunks
-template <typename R, int MODE>
-__device__ __forceinline__ double chunk_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega, R gam,
-                              unsigned char* smem, int32_t item) {
+template <typename R, typename RT, int MODE>
+__device__ __forceinline__ double chunk_block(const SweepArgs& A, const R* cells, RT t, R* out, R omega, R gam,
+                                              unsigned char* smem, int32_t item) {
   const int wave = threadIdx.x >> 6;
   R* wave_vals = reinterpret_cast<R*>(smem) + wave * CHUNK_SLICE;
-  [[clang::always_inline]] return short_chunk_hard<R, MODE>(A, cells, t, out, omega, gam, item * 4 + wave, wave_vals);
+  [[clang::always_inline]] return short_chunk_hard<R, RT, MODE>(A, cells, t, out, omega, gam, item * 4 + wave, wave_vals);
 }
 
 // ---------------------------------------------------------------- short rows with b = 0, one lane per row
@@ -533,9 +559,8 @@ struct Pair2<double> {
   using type = double2;
 };
 
-template <typename R, int MODE, int H>
-__device__ inline double tile_rows(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega,
-                                   R gam, uint32_t cell0) {
+template <typename R, typename RT, int MODE, int H>
+__device__ inline double tile_rows(const SweepArgs& A, const R* cells, RT t, R* out, R omega, R gam, uint32_t cell0) {
   using P2 = typename Pair2<R>::type;
   const uint32_t c0 = cell0 + 2u * (threadIdx.x & 63u);
   uint2 wv[H];
@@ -644,16 +669,68 @@ __device__ inline double tile_rows(const SweepArgs& A, const R* cells, const R* 
 }
 
 // the four waves of a block take four adjacent tiles of one form
-template <typename R, int MODE, int FORM>
-__device__ __forceinline__ double tile_block(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* out, R omega,
-                                    R gam, int32_t item) {
+template <typename R, typename RT, int MODE, int FORM>
+__device__ __forceinline__ double tile_block(const SweepArgs& A, const R* cells, RT t, R* out, R omega, R gam,
+                                             int32_t item) {
   constexpr int H = TILE_HALF[FORM];
   const int32_t tile = item * 4 + int32_t(threadIdx.x >> 6);
   if (tile >= A.n_tiles[FORM]) return 0.0;   // uniform across the wave
   // inlined here whatever else calls it: as a function it costs the sweep 40
   // registers and 6 % of its time
-  [[clang::always_inline]] return tile_rows<R, MODE, H>(A, cells, t, out, omega, gam,
-                                                         A.tile_cell0[FORM] + uint32_t(tile) * (128u * H));
+  [[clang::always_inline]] return tile_rows<R, RT, MODE, H>(A, cells, t, out, omega, gam,
+                                                             A.tile_cell0[FORM] + uint32_t(tile) * (128u * H));
+}
+
+// The same rows with a lane per entry, for the form that has one launch per
+// iteration: a row's 2 H cells go to SPREAD lanes, so that each gathers one
+// residual, not 2 H of them one after the other.  The entries see each other by
+// lane exchange; every comparison is that of tile_rows.
+template <int H>
+constexpr int SPREAD = H <= 4 ? 8 : 16;
+
+template <typename R, typename RT, int H>
+__device__ inline double tile_spread(const SweepArgs& A, const R* cells, RT t, R* out, R omega, uint32_t cell0,
+                                     uint32_t row0) {
+  constexpr int W = SPREAD<H>;
+  static_assert(2 * H <= W, "a row's cells need a lane each");
+  const uint32_t lane = threadIdx.x & 63u, k = lane % W, j = k / 2;
+  const bool neg = k & 1u;
+  const uint32_t cell = cell0 + 128u * j + 2u * (row0 + lane / W) + (k & 1u);
+  const uint32_t w = k < 2 * H ? A.word[cell] : CHUNK_PAD;
+  const bool act = w != CHUNK_PAD;
+  const R lam = act ? cell_lambda<R, RT>(A, cells, t, cell, w, R(0)) : rinf<R>();
+  int32_t d = 0;   // count - rank
+#pragma unroll
+  for (uint32_t q = 0; q < 2 * H; ++q) {
+    const R other = __shfl(lam, int(q), W);
+    if (bool(q & 1u) != neg) d += lam + other < R(0) ? 1 : 0;
+    else if (q < k) d -= other <= lam ? 1 : 0;   // earlier: a tie ranks this one behind it
+    else if (q > k) d -= lam <= other ? 0 : 1;
+  }
+  const bool sel = d > 0;
+  // U: left +1 and taken -1 entries, V: left -1 and taken +1 entries
+  const R v = sel ? -lam : lam;
+  R U = sel == neg ? v : rinf<R>(), V = sel == neg ? rinf<R>() : v;
+  U = fmin(U, dpp_move<0xB1>(U)), V = fmin(V, dpp_move<0xB1>(V));
+  U = fmin(U, dpp_move<0x4E>(U)), V = fmin(V, dpp_move<0x4E>(V));
+  U = fmin(U, dpp_move<0x141>(U)), V = fmin(V, dpp_move<0x141>(V));
+  if (W > 8) U = fmin(U, dpp_move<0x140>(U)), V = fmin(V, dpp_move<0x140>(V));
+  if (act) {
+    const R B = sel == neg ? V : U;
+    out[cell] = fma_r<R>(-omega, sel ? lam - B : lam + B, lam);
+  }
+  return sel ? double(lam) : 0.0;
+}
+
+// the four waves of a block take adjacent rows of one tile
+template <typename R, typename RT, int FORM>
+__device__ __forceinline__ double spread_block(const SweepArgs& A, const R* cells, RT t, R* out, R omega,
+                                               int32_t item) {
+  constexpr int H = TILE_HALF[FORM], BPT = SPREAD<H> / 4, ROWS = 64 / SPREAD<H>;   // blocks per tile, rows per wave
+  const int32_t tile = item / BPT;
+  if (tile >= A.n_tiles[FORM]) return 0.0;   // uniform across the block
+  return tile_spread<R, RT, H>(A, cells, t, out, omega, A.tile_cell0[FORM] + uint32_t(tile) * (128u * H),
+                               uint32_t(item % BPT) * (4u * ROWS) + (threadIdx.x >> 6) * ROWS);
 }
 
 // ---------------------------------------------------------------- short rows, soft min
@@ -1024,9 +1101,9 @@ constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD
 // 231k; so 6.5-6.8 and 9.1.  In place where
 // cells and dst are one array: a lane reads its own cells before it writes them.
 // Returns the row minimum on one lane of the row.
-template <typename R, int MODE>
-__device__ __forceinline__ double long_cells(const SweepArgs& A, const R* cells, const R* __restrict__ t, R* dst,
-                                             R omega, R gam, int32_t lr, bool has) {
+template <typename R, typename RT, int MODE>
+__device__ __forceinline__ double long_cells(const SweepArgs& A, const R* cells, RT t, R* dst, R omega, R gam,
+                                             int32_t lr, bool has) {
   __shared__ R xm[4], xm2[4];
   __shared__ int32_t xa[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1054,13 +1131,13 @@ __device__ __forceinline__ double long_cells(const SweepArgs& A, const R* cells,
 #pragma unroll
     for (int u = u0; u < u0 + BATCH; ++u) {
       const int32_t i = i0 + step * u;
-      lv[u] = cell_lambda<R>(A, cells, t, c0 + uint32_t(i < n ? i : 0), wv[u], gam);
+      lv[u] = cell_lambda<R, RT>(A, cells, t, c0 + uint32_t(i < n ? i : 0), wv[u], gam);
     }
 #pragma unroll
     for (int u = u0; u < u0 + BATCH; ++u)
       if (i0 + step * u < n) st.take(lv[u]);
   }
-  auto value = [&](int32_t i) { return cell_lambda<R>(A, cells, t, c0 + uint32_t(i), words[i], gam); };
+  auto value = [&](int32_t i) { return cell_lambda<R, RT>(A, cells, t, c0 + uint32_t(i), words[i], gam); };
   for (int32_t i = i0 + step * LONG_REG; i < n; i += step) st.take(value(i));   // longer rows
   st.join_group(64);
   // which of several equal minima a row takes shows only in its assignment: the
@@ -1254,12 +1331,54 @@ __global__ __launch_bounds__(256) void k_vars(const uint32_t* __restrict__ vpos,
 }
 
 // the terms of the tile rows of a block to their places
-__device__ inline void tile_term(const SweepArgs& A, double part, int form, int32_t item) {
+template <int FORM>
+__device__ __forceinline__ void tile_term(const SweepArgs& A, double part, int32_t item) {
   if (!A.terms) return;   // uniform
-  int32_t row0 = 0;
-  for (int f = 0; f < form; ++f) row0 += A.tile_rows[f];
+  const int32_t row0 = (FORM > 0 ? A.tile_rows[0] : 0) + (FORM > 1 ? A.tile_rows[1] : 0);
   const int32_t r = item * 256 + int32_t(threadIdx.x);
-  if (r < A.tile_rows[form]) A.terms[A.term_row[row0 + r]] = part;
+  if (r < A.tile_rows[FORM]) A.terms[A.term_row[row0 + r]] = part;
+}
+
+// block k of XCD x of the hard row pass: the sum of its row minima, in parts
+template <typename R, typename RT, int MODE, bool SPREAD_TILES>
+__device__ __forceinline__ double hard_block(SweepArgs A, const R* cells, RT t, R* out, R omega, R gam,
+                                             unsigned char* smem, int32_t x, int32_t k) {
+  // Every XCD takes a contiguous eighth of each kind of rows, the heavier
+  // kinds first.  (Y projection rows too: they span all variables, but
+  // neighbouring rows need neighbouring ones of them.)
+  const int wave = threadIdx.x >> 6;
+  constexpr bool TERMS = sizeof(R) == 8 && (MODE == MODE_BOUND || MODE == MODE_SUBGRAD);
+  double part = 0.0;
+  if (k < A.per[0] + A.per[1]) {
+    const bool yrow = k < A.per[0];
+    const int32_t rpb = 4 / A.long_wpr;
+    const int32_t item = yrow ? x * A.per[0] + k : x * A.per[1] + (k - A.per[0]);
+    const int32_t r = item * rpb + wave / A.long_wpr;
+    const int32_t lr = yrow ? r : A.n_long_y + r;
+    const bool has = lr < (yrow ? A.n_long_y : A.n_long);
+    part = long_cells<R, RT, MODE>(A, cells, t, out, omega, gam, lr, has);
+    if constexpr (TERMS)
+      if (A.terms && has && (threadIdx.x & (64 * A.long_wpr - 1)) == 0) A.terms[A.term_long0 + A.term_long[lr]] = part;
+  } else if ((k -= A.per[0] + A.per[1]) < A.per[2]) {
+    part = chunk_block<R, RT, MODE>(A, cells, t, out, omega, gam, smem, x * A.per[2] + k);
+    if constexpr (TERMS) {
+      const int32_t c = (x * A.per[2] + k) * 4 + wave;
+      if (A.terms && c < A.n_chunks) A.terms[A.term_chunk0 + c * 64 + int32_t(threadIdx.x & 63)] = part;
+    }
+  } else if ((k -= A.per[2]) < A.per[3]) {
+    if constexpr (SPREAD_TILES) part = spread_block<R, RT, 2>(A, cells, t, out, omega, x * A.per[3] + k);
+    else part = tile_block<R, RT, MODE, 2>(A, cells, t, out, omega, gam, x * A.per[3] + k);
+    if constexpr (TERMS) tile_term<2>(A, part, x * A.per[3] + k);
+  } else if ((k -= A.per[3]) < A.per[4]) {
+    if constexpr (SPREAD_TILES) part = spread_block<R, RT, 1>(A, cells, t, out, omega, x * A.per[4] + k);
+    else part = tile_block<R, RT, MODE, 1>(A, cells, t, out, omega, gam, x * A.per[4] + k);
+    if constexpr (TERMS) tile_term<1>(A, part, x * A.per[4] + k);
+  } else {
+    if constexpr (SPREAD_TILES) part = spread_block<R, RT, 0>(A, cells, t, out, omega, x * A.per[5] + (k - A.per[4]));
+    else part = tile_block<R, RT, MODE, 0>(A, cells, t, out, omega, gam, x * A.per[5] + (k - A.per[4]));
+    if constexpr (TERMS) tile_term<0>(A, part, x * A.per[5] + (k - A.per[4]));
+  }
+  return part;
 }
 
 template <typename R, bool SOFT, int MODE>
@@ -1273,40 +1392,8 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
   // Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8).
   const int32_t x = int32_t(blockIdx.x % 8u), k0 = int32_t(blockIdx.x / 8u);
   if constexpr (!SOFT) {
-    // Every XCD takes a contiguous eighth of each kind of rows, the heavier
-    // kinds first.  (Y projection rows too: they span all variables, but
-    // neighbouring rows need neighbouring ones of them.)
     const R gam = A.gamma ? R(*A.gamma) : R(0);
-    const int wave = threadIdx.x >> 6;
-    constexpr bool TERMS = sizeof(R) == 8 && (MODE == MODE_BOUND || MODE == MODE_SUBGRAD);
-    double part = 0.0;
-    int32_t k = k0;
-    if (k < A.per[0] + A.per[1]) {
-      const bool yrow = k < A.per[0];
-      const int32_t rpb = 4 / A.long_wpr;
-      const int32_t item = yrow ? x * A.per[0] + k : x * A.per[1] + (k - A.per[0]);
-      const int32_t r = item * rpb + wave / A.long_wpr;
-      const int32_t lr = yrow ? r : A.n_long_y + r;
-      const bool has = lr < (yrow ? A.n_long_y : A.n_long);
-      part = long_cells<R, MODE>(A, rin, t, out, omega, gam, lr, has);
-      if constexpr (TERMS)
-        if (A.terms && has && (threadIdx.x & (64 * A.long_wpr - 1)) == 0) A.terms[A.term_long0 + A.term_long[lr]] = part;
-    } else if ((k -= A.per[0] + A.per[1]) < A.per[2]) {
-      part = chunk_block<R, MODE>(A, rin, t, out, omega, gam, smem, x * A.per[2] + k);
-      if constexpr (TERMS) {
-        const int32_t c = (x * A.per[2] + k) * 4 + wave;
-        if (A.terms && c < A.n_chunks) A.terms[A.term_chunk0 + c * 64 + int32_t(threadIdx.x & 63)] = part;
-      }
-    } else if ((k -= A.per[2]) < A.per[3]) {
-      part = tile_block<R, MODE, 2>(A, rin, t, out, omega, gam, x * A.per[3] + k);
-      if constexpr (TERMS) tile_term(A, part, 2, x * A.per[3] + k);
-    } else if ((k -= A.per[3]) < A.per[4]) {
-      part = tile_block<R, MODE, 1>(A, rin, t, out, omega, gam, x * A.per[4] + k);
-      if constexpr (TERMS) tile_term(A, part, 1, x * A.per[4] + k);
-    } else {
-      part = tile_block<R, MODE, 0>(A, rin, t, out, omega, gam, x * A.per[5] + (k - A.per[4]));
-      if constexpr (TERMS) tile_term(A, part, 0, x * A.per[5] + (k - A.per[4]));
-    }
+    const double part = hard_block<R, Written<R>, MODE, false>(A, rin, t, out, omega, gam, smem, x, k0);
     store_partial(block_sum(part, red), A.partial, int32_t(blockIdx.x));
   } else {
     // The smoothed form deals the projection-row blocks in groups of LONG_GROUP,
@@ -1342,6 +1429,31 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const R* rin, const 
       store_partial(block_sum(part, red), A.partial, item);
     }
   }
+}
+
+// ---------------------------------------------------------------- middle sizes: one launch per iteration
+// Hard iteration in one launch, from one cell buffer to the other: each entry
+// forms its variable's residual itself, from the cost and the old cells, with the
+// additions of the variable pass (same bits).  The gathers are five times as many,
+// but a launch less is what counts as long as the iteration is a chain of launches
+// (hard_form).  With a lane per row the gathers of a tile are one lane's chain:
+// 101k entries 16.4 us an iteration so, 5.9 with a lane per entry (tile_spread).
+// Blocks 8 and up take the rows; block 0 sums the previous launch's partials.
+template <typename R>
+__global__ __launch_bounds__(256) void k_iterate(SweepArgs A, const R* __restrict__ cells,
+                                                 const uint32_t* __restrict__ vpos, const R* __restrict__ cost,
+                                                 uint32_t n, R* __restrict__ out, R omega) {
+  __shared__ __align__(16) unsigned char smem[smem_bytes<R, false>()];
+  __shared__ double red[4];
+  if (blockIdx.x < 8) {
+    if (blockIdx.x == 0 && A.prev_partial)
+      reduce_partials(A.prev_partial, A.prev_n, A.prev_offset, A.prev_out, red);
+    return;
+  }
+  const Summed<R> t{vpos, cells, cost, n};
+  const double part = hard_block<R, Summed<R>, MODE_UPDATE, true>(A, cells, t, out, omega, R(0), smem,
+                                                                  int32_t(blockIdx.x % 8u), int32_t(blockIdx.x / 8u) - 1);
+  store_partial(block_sum(part, red), A.partial, int32_t(blockIdx.x) - 8);
 }
 
 // ---------------------------------------------------------------- small problems: one workgroup
@@ -1403,21 +1515,21 @@ __global__ __launch_bounds__(NT) void k_small(SweepArgs A, const uint32_t* __res
     int32_t w0 = wave;   // the waves take the items of all kinds in turn
 #pragma unroll 1
     for (; w0 < A.n_tiles[2]; w0 += NW)
-      sum += tile_rows<R, MODE_UPDATE, TILE_HALF[2]>(A, cells, t, cells, omega, R(0),
+      sum += tile_rows<R, Written<R>, MODE_UPDATE, TILE_HALF[2]>(A, cells, t, cells, omega, R(0),
                                                      A.tile_cell0[2] + uint32_t(w0) * (128u * TILE_HALF[2]));
     w0 -= A.n_tiles[2];
 #pragma unroll 1
     for (; w0 < A.n_chunks; w0 += NW)
-      sum += short_chunk_hard<R, MODE_UPDATE>(A, cells, t, cells, omega, R(0), w0, wave_vals);
+      sum += short_chunk_hard<R, Written<R>, MODE_UPDATE>(A, cells, t, cells, omega, R(0), w0, wave_vals);
     w0 -= A.n_chunks;
 #pragma unroll 1
     for (; w0 < A.n_tiles[1]; w0 += NW)
-      sum += tile_rows<R, MODE_UPDATE, TILE_HALF[1]>(A, cells, t, cells, omega, R(0),
+      sum += tile_rows<R, Written<R>, MODE_UPDATE, TILE_HALF[1]>(A, cells, t, cells, omega, R(0),
                                                      A.tile_cell0[1] + uint32_t(w0) * (128u * TILE_HALF[1]));
     w0 -= A.n_tiles[1];
 #pragma unroll 1
     for (; w0 < A.n_tiles[0]; w0 += NW)
-      sum += tile_rows<R, MODE_UPDATE, TILE_HALF[0]>(A, cells, t, cells, omega, R(0),
+      sum += tile_rows<R, Written<R>, MODE_UPDATE, TILE_HALF[0]>(A, cells, t, cells, omega, R(0),
                                                      A.tile_cell0[0] + uint32_t(w0) * (128u * TILE_HALF[0]));
     w0 -= A.n_tiles[0];
     const int32_t rpw = 64 / group;
@@ -1428,7 +1540,7 @@ __global__ __launch_bounds__(NT) void k_small(SweepArgs A, const uint32_t* __res
       const int2 d = has ? A.long_row[lr] : make_int2(0, 0);
       const uint32_t c0 = uint32_t(d.x);
       const int32_t len = d.y;
-      auto value = [&](int32_t i) { return cell_lambda<R>(A, cells, t, c0 + uint32_t(i), A.word[c0 + uint32_t(i)], R(0)); };
+      auto value = [&](int32_t i) { return cell_lambda<R, Written<R>>(A, cells, t, c0 + uint32_t(i), A.word[c0 + uint32_t(i)], R(0)); };
       R lv[SMALL_LREG];
       TwoMin<R> st{rinf<R>(), rinf<R>()};
 #pragma unroll
@@ -1498,22 +1610,28 @@ __global__ void k_rec_export(const R* rec, const uint32_t* word, int64_t nnz, R*
 template <typename R>
 __global__ void k_cell_import(const R* lam, const uint32_t* ent_cell, int64_t nnz, const int32_t* vperm,
                               const int32_t* free_var, const double* c64, int64_t n, uint32_t zero_cell, R* cells,
-                              R* cost) {
+                              R* other, R* cost) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e < nnz) cells[ent_cell[e]] = lam[e];
   if (e < n) cost[e] = R(c64[free_var[vperm[e]]]);
-  if (e == 0) cells[zero_cell] = R(0);
+  if (e == 0) {
+    cells[zero_cell] = R(0);
+    if (other) other[zero_cell] = R(0);   // its other cells are written before they are read
+  }
 }
 
-template <typename R>
-__global__ void k_zero_cell(R* cells, uint32_t zero_cell) {
-  cells[zero_cell] = R(0);
-}
-
-template <typename R>
-__global__ void k_cell_export(const R* cells, const R* t, const uint32_t* ent_cell, const uint32_t* word, int64_t nnz,
-                              R* lam) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// multipliers in entry order, with dual feasibility restored; block 0 sums the
+// previous launch's partials where there are any (the others then start behind it)
+template <typename R, typename RT>
+__global__ __launch_bounds__(256) void k_cell_export(const R* cells, RT t, const uint32_t* ent_cell, const uint32_t* word,
+                                                     int64_t nnz, R* lam, const double* prev_partial, int32_t prev_n,
+                                                     double prev_offset, double* prev_out) {
+  __shared__ double red[4];
+  if (prev_partial && blockIdx.x == 0) {
+    reduce_partials(prev_partial, prev_n, prev_offset, prev_out, red);
+    return;
+  }
+  const int64_t e = (int64_t(blockIdx.x) - (prev_partial ? 1 : 0)) * blockDim.x + threadIdx.x;
   if (e >= nnz) return;
   const uint32_t c = ent_cell[e], w = word[c];
   lam[e] = feasible<R>(cells[c], t[w & W_VAR_MASK], rdeg_of<R>(w));
@@ -1550,18 +1668,20 @@ __global__ __launch_bounds__(256) void k_reduce_last(const double* partial, int 
 // host side (shared with rounding, the quasi-Newton layer and the backward pass)
 // ============================================================================
 // blocks per XCD of each kind of rows of the hard sweep, in launch order
-static void hard_blocks(const dm_ctx* ctx, int32_t per[3 + TILE_FORMS]) {
+static void hard_blocks(const dm_ctx* ctx, bool spread, int32_t per[3 + TILE_FORMS]) {
   const int64_t n_long = ctx->n_rows - ctx->n_short, rpb = 4 / ctx->long_wpr;
   const auto xcd = [](int64_t items) { return int32_t((items + 7) / 8); };
   per[0] = xcd((ctx->n_long_y + rpb - 1) / rpb);
   per[1] = xcd((n_long - ctx->n_long_y + rpb - 1) / rpb);
   per[2] = xcd((ctx->n_chunks + 3) / 4);
-  for (int f = 0; f < TILE_FORMS; ++f) per[3 + f] = xcd((ctx->n_tiles[TILE_FORMS - 1 - f] + 3) / 4);
+  constexpr int BPT[TILE_FORMS] = {SPREAD<TILE_HALF[0]> / 4, SPREAD<TILE_HALF[1]> / 4, SPREAD<TILE_HALF[2]> / 4};
+  for (int f = TILE_FORMS - 1; f >= 0; --f)
+    per[2 + TILE_FORMS - f] = xcd(spread ? int64_t(ctx->n_tiles[f]) * BPT[f] : (ctx->n_tiles[f] + 3) / 4);
 }
 
-static int64_t hard_grid(const dm_ctx* ctx) {
+static int64_t hard_grid(const dm_ctx* ctx, bool spread = false) {
   int32_t per[3 + TILE_FORMS];
-  hard_blocks(ctx, per);
+  hard_blocks(ctx, spread, per);
   int64_t n = 0;
   for (int32_t p : per) n += p;
   return 8 * n;
@@ -1581,7 +1701,8 @@ static int64_t long_blocks(const dm_ctx* ctx) {
 // per-launch partials of one sweep (hard and smoothed forms): the partial
 // buffer holds two halves of this many doubles
 static int64_t sweep_partial_cap(const dm_ctx* ctx) {
-  return std::max<int64_t>(hard_grid(ctx), soft_short_blocks(ctx) + long_blocks(ctx));
+  const bool spread = ctx->nnz <= ONE_LAUNCH_NNZ;
+  return std::max<int64_t>(hard_grid(ctx, spread), soft_short_blocks(ctx) + long_blocks(ctx));
 }
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1610,9 +1731,34 @@ static dm_status solver_workspace(dm_ctx* ctx, size_t real_bytes, unsigned char*
   return DM_OK;
 }
 
+// Which form runs the hard iterations of a problem, by its entries.  An iteration
+// in us, of 190 in one call.  One workgroup against one launch per iteration: FP32
+// 1934 entries 2.8 and 4.5, 3782 4.1 and 4.4, 5844 4.5 and 4.6, 6983 5.7 and 4.5;
+// FP64 1934 3.9 and 4.8, 3649 4.9 and 5.0, 3782 5.7 and 5.1, 5844 6.7 and 4.9.  One
+// launch against two: FP32 10k 4.8 and 6.7 to 7.4, 45k 5.9 and 7.4, 101k 5.9 and
+// 7.8, 168k 7.1 and 8.1, 206k 10.4 and 8.7, 349k 9.9 and 8.9; FP64 10k 5.4 and 7.5,
+// 168k 8.2 and 9.0, 206k 10.7 and 9.5.  (Two launches are bound by the host, 3.6 us
+// each, up to some 100k entries; beside the launch one launch saves the last
+// variable pass of a call, and five gathers per entry are what it costs.)
+enum HardForm { ONE_WORKGROUP, ONE_LAUNCH, TWO_PASSES };
+
+// LDS of the one-workgroup form
+template <typename R>
+static int64_t small_lds(const dm_ctx* ctx) {
+  return small_reals<R>(ctx->n_cells, ctx->n_free, ctx->n_chunks > 0, SMALL_THREADS<R> / 64) * int64_t(sizeof(R));
+}
+
+template <typename R>
+static HardForm hard_form(const dm_ctx* ctx) {
+  constexpr int F = sizeof(R) == 4 ? 0 : 1;
+  if (ctx->nnz <= SMALL_NNZ[F] && small_lds<R>(ctx) <= SMALL_LDS) return ONE_WORKGROUP;
+  return ctx->nnz <= ONE_LAUNCH_NNZ ? ONE_LAUNCH : TWO_PASSES;
+}
+
 template <typename R>
 dm_status cells_import(dm_ctx* ctx, const R* lam, CellState& S, bool two) {
   const int64_t n = ctx->n_free;
+  two = two || hard_form<R>(ctx) == ONE_LAUNCH;   // whose iterations alternate
   const size_t cb = size_t(ctx->n_cells + 1) * sizeof(R), vb = size_t(std::max<int64_t>(n, 1)) * sizeof(R);
   unsigned char* ws = nullptr;
   SolverLayout L;
@@ -1631,9 +1777,7 @@ dm_status cells_import(dm_ctx* ctx, const R* lam, CellState& S, bool two) {
   const int64_t m = std::max<int64_t>(std::max<int64_t>(ctx->nnz, n), 1);
   k_cell_import<R><<<grid_for(m, 256), 256, 0, ctx->stream>>>(
       lam, ctx->ent_cell.p, ctx->nnz, ctx->vperm.p, ctx->free_var.p, ctx->cost64.p, n, uint32_t(ctx->n_cells),
-      S.cells<R>(0), S.costs<R>());
-  // the other buffer's zero cell: its other cells are written before they are read
-  if (two) k_zero_cell<R><<<1, 1, 0, ctx->stream>>>(S.cells<R>(1), uint32_t(ctx->n_cells));
+      S.cells<R>(0), two ? S.cells<R>(1) : nullptr, S.costs<R>());
   DM_LAUNCH_CHECK(ctx);
   return DM_OK;
 }
@@ -1641,8 +1785,8 @@ dm_status cells_import(dm_ctx* ctx, const R* lam, CellState& S, bool two) {
 template <typename R>
 dm_status cells_export(dm_ctx* ctx, const R* cells, const R* t, R* lam) {
   if (ctx->nnz > 0)
-    k_cell_export<R><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(cells, t, ctx->ent_cell.p, ctx->cell_word.p,
-                                                                       ctx->nnz, lam);
+    k_cell_export<R, const R*><<<grid_for(ctx->nnz, 256), 256, 0, ctx->stream>>>(
+        cells, t, ctx->ent_cell.p, ctx->cell_word.p, ctx->nnz, lam, nullptr, 0, 0.0, nullptr);
   DM_LAUNCH_CHECK(ctx);
   return DM_OK;
 }
@@ -1775,7 +1919,7 @@ static dm_status empty_sweep(dm_ctx* ctx, double* bound_out) {
   return DM_OK;
 }
 
-static void hard_args(const dm_ctx* ctx, SweepArgs& A) {
+static void hard_args(const dm_ctx* ctx, bool spread, SweepArgs& A) {
   common_args(ctx, A);
   A.word = ctx->cell_word.p;
   for (int f = 0; f < TILE_FORMS; ++f) {
@@ -1791,7 +1935,7 @@ static void hard_args(const dm_ctx* ctx, SweepArgs& A) {
   A.n_long_y = ctx->n_long_y;
   A.long_row = ctx->long_row.p;
   A.long_ent = ctx->long_ent.p;
-  hard_blocks(ctx, A.per);
+  hard_blocks(ctx, spread, A.per);
 }
 
 // one hard row pass: mode update cells -> out (which may be cells itself),
@@ -1801,7 +1945,7 @@ template <typename R>
 dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, R omega, double* bound_out,
                      const SweepExt* ext) {
   SweepArgs A;
-  hard_args(ctx, A);
+  hard_args(ctx, false, A);
   if (ext) {
     A.dir = ext->dir;
     A.gamma = ext->gamma;
@@ -1835,19 +1979,9 @@ dm_status cells_rows(dm_ctx* ctx, int mode, const R* cells, const R* t, R* out, 
   return DM_OK;
 }
 
-// LDS of the one-workgroup form, 0 where it does not apply.  An iteration of it
-// against one of two launches, in us, of 200 in one call: FP32 989 entries 2.9 and
-// 6.5, 3782 4.1 and 6.5, 7695 5.0 and 6.8, 10433 13.0 and 6.9 (the waves no longer
-// keep their rows' words); FP64 989 3.0 and 6.7, 3782 6.6 and 6.9, 6334 6.8 and
-// 7.0, 7695 7.8 and 7.0.  So the lines lie at SMALL_NNZ and SMALL_NNZ64 entries.
-template <typename R>
-static size_t small_lds(const dm_ctx* ctx) {
-  const int64_t reals = small_reals<R>(ctx->n_cells, ctx->n_free, ctx->n_chunks > 0, SMALL_THREADS<R> / 64);
-  return ctx->nnz <= (sizeof(R) == 4 ? SMALL_NNZ : SMALL_NNZ64) && reals * int64_t(sizeof(R)) <= SMALL_LDS ? size_t(reals) * sizeof(R) : 0;
-}
-
-// iters hard iterations in place on S (their t is left to the next cells_vars);
-// the bounds go to trace (device, may be NULL)
+// iters hard iterations on S, whose buffer 0 holds the result (their t is left to
+// the next cells_vars); the bounds go to trace (device, may be NULL), the last
+// one perhaps with the next launch
 template <typename R>
 dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, double* trace) {
   R *cells = S.cells<R>(0), *t = S.ts<R>(0);
@@ -1858,11 +1992,12 @@ dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, doubl
     DM_LAUNCH_CHECK(ctx);
     return DM_OK;
   }
-  const size_t lds = small_lds<R>(ctx);
-  if (lds > 0 && iters > 0) {
+  const HardForm form = hard_form<R>(ctx);
+  if (form == ONE_WORKGROUP && iters > 0) {
+    const size_t lds = size_t(small_lds<R>(ctx));
     DM_TRY(dual_flush(ctx));
     SweepArgs A;
-    hard_args(ctx, A);
+    hard_args(ctx, false, A);
     constexpr int NT = SMALL_THREADS<R>;
     const int64_t n_long = ctx->n_rows - ctx->n_short, mean = (ctx->nnz - ctx->nnz_short) / std::max<int64_t>(n_long, 1);
     const int32_t group = mean <= 16 ? 4 : (mean <= 64 ? 16 : 64);
@@ -1880,6 +2015,32 @@ dm_status cells_iterate(dm_ctx* ctx, CellState& S, int32_t iters, R omega, doubl
       k_small<R, NT><<<1, NT, lds, ctx->stream>>>(A, ctx->vpos.p, cells, S.costs<R>(), int32_t(ctx->n_free),
                                                   uint32_t(ctx->n_cells), iters, omega, ctx->offset, group, trace);
     DM_LAUNCH_CHECK(ctx);
+    return DM_OK;
+  }
+  if (form == ONE_LAUNCH) {
+    SweepArgs A;
+    hard_args(ctx, true, A);
+    const int64_t grid = hard_grid(ctx, true);
+    for (int32_t k = 0; k < iters; ++k) {
+      double* mine = nullptr;
+      DM_TRY(next_partials(ctx, sizeof(R), &mine));
+      A.partial = mine;
+      A.prev_partial = ctx->pend_out ? ctx->pend_partial : nullptr;
+      A.prev_n = ctx->pend_n;
+      A.prev_offset = ctx->pend_offset;
+      A.prev_out = ctx->pend_out;
+      hipEvent_t e0 = nullptr, e1 = nullptr;
+      if (ctx->timing) DM_TRY(timing_events(ctx, &e0, &e1, 1));
+      if (e0)
+        hipExtLaunchKernelGGL(k_iterate<R>, dim3(unsigned(grid + 8)), dim3(256), 0, ctx->stream, e0, e1, 0, A,
+                              S.cells<R>(0), ctx->vpos.p, S.costs<R>(), uint32_t(ctx->n_free), S.cells<R>(1), omega);
+      else
+        k_iterate<R><<<unsigned(grid + 8), 256, 0, ctx->stream>>>(A, S.cells<R>(0), ctx->vpos.p, S.costs<R>(),
+                                                                  uint32_t(ctx->n_free), S.cells<R>(1), omega);
+      DM_LAUNCH_CHECK(ctx);
+      pend(ctx, mine, grid, trace ? trace + k : nullptr);
+      S.swap();
+    }
     return DM_OK;
   }
   for (int32_t k = 0; k < iters; ++k) {
@@ -1997,10 +2158,20 @@ static dm_status solve_impl(dm_ctx* ctx, int32_t iters, R omega, R T, R* lam, do
   }
   CellState& S = ctx->cells;
   DM_TRY(cells_import<R>(ctx, lam, S, false));
-  R *cells = S.cells<R>(0), *t = S.ts<R>(0);
   DM_TRY(cells_iterate<R>(ctx, S, iters, omega, trace));
-  DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, false));   // also sums the last bound
-  return cells_export<R>(ctx, cells, t, lam);
+  const R* cells = S.cells<R>(0);
+  if (hard_form<R>(ctx) == TWO_PASSES) {
+    DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), S.ts<R>(0), false));   // also sums the last bound
+    return cells_export<R>(ctx, cells, S.ts<R>(0), lam);
+  }
+  if (ctx->nnz == 0) return DM_OK;
+  const Summed<R> t{ctx->vpos.p, cells, S.costs<R>(), uint32_t(ctx->n_free)};
+  const double* prev = ctx->pend_out ? ctx->pend_partial : nullptr;
+  k_cell_export<R, Summed<R>><<<grid_for(ctx->nnz, 256) + (prev ? 1u : 0u), 256, 0, ctx->stream>>>(
+      cells, t, ctx->ent_cell.p, ctx->cell_word.p, ctx->nnz, lam, prev, ctx->pend_n, ctx->pend_offset, ctx->pend_out);
+  DM_LAUNCH_CHECK(ctx);
+  ctx->pend_out = nullptr;
+  return DM_OK;
 }
 
 extern "C" dm_status dm_dual_solve(dm_ctx* ctx, int32_t iters, double omega, double temperature,

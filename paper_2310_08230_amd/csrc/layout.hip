@@ -673,11 +673,11 @@ dm_status sweep_layout(dm_ctx* ctx) {
   DM_ALLOC(ctx, count, NC);
   DM_HIP(ctx, hipMemsetAsync(count.p, 0, NC * sizeof(int32_t), st));
   if (nshort > 0) {
-    // the narrowest tiles only where one workgroup sweeps the problem from LDS
+    // the narrowest tiles only where one workgroup may sweep the problem from LDS
     // and its arithmetic counts: rows of one place spread over more tiles cost
     // the variable pass cache lines (2000/3000-face pair 7 us more of 105
     // an iteration with them, 1000 faces 0.6 of 22)
-    const uint32_t form0 = rnnz <= SMALL_NNZ ? 0u : 1u;
+    const uint32_t form0 = rnnz <= SMALL_NNZ[0] ? 0u : 1u;
     k_short_keys<<<grid_for(nshort, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rrow_b.p, ctx->rent_word.p, vkey.p,
                                                         nshort, ybits, ydrop, kbits, form0, skey.p, perm.p, count.p);
     DM_LAUNCH_CHECK(ctx);

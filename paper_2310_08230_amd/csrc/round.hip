@@ -147,7 +147,7 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
   CellState& S = ctx->rcells;
   DM_TRY(dual_flush(ctx));
   DM_TRY(cells_import<R>(ctx, lam, S, false));
-  R *cells = S.cells<R>(0), *t = S.ts<R>(0);
+  R* t = S.ts<R>(0);
   DM_ALLOC(ctx, ctx->mrec, size_t(ctx->n_cells + 1) * sizeof(R));
   R* m = reinterpret_cast<R*>(ctx->mrec.p);
   DM_ALLOC(ctx, ctx->pref, size_t(std::max<int64_t>(nfree, 1)));
@@ -158,6 +158,7 @@ static dm_status round_impl(dm_ctx* ctx, const dm_round_params& P, const R* lam,
   double delta = P.delta0;
   *feasible = 0;
   for (int32_t r = 0; r <= P.rounds; ++r) {
+    const R* cells = S.cells<R>(0);
     DM_TRY(cells_vars<R>(ctx, cells, S.costs<R>(), t, true));
     DM_TRY(cells_rows<R>(ctx, SWEEP_EVAL, cells, t, m, R(0), nullptr, nullptr));
     DM_HIP(ctx, hipMemsetAsync(ctx->icount.p, 0, sizeof(int64_t), st));
