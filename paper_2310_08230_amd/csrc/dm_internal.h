@@ -396,6 +396,7 @@ struct dm_ctx {
   DArr<unsigned char> term_mem;
   int32_t *term_row = nullptr, *term_long = nullptr;   // place of every tile row (cell order), projection row
   double *terms = nullptr, *term_part = nullptr;       // the terms of one sweep, their sums per block
+  uint32_t* term_arrived = nullptr;
   uint32_t* cpos = nullptr;                            // vpos with the variables in canonical order
   DArr<int2> long_row;        // first cell and length of each, in launch order
   DArr<int32_t> long_ent;     // entry of each projection-row cell, relative to the first (none: in order)
@@ -516,6 +517,8 @@ struct Slab {
 struct TermSums {
   const double* terms = nullptr;   // NULL: not used
   int32_t n_blocks = 0, n_long = 0, rpb = 1, n_long_blocks = 0;
+  double* part = nullptr;          // a sum per block
+  uint32_t* arrived = nullptr;     // workgroups that have written theirs; 0 between launches
   __device__ double long_block(int32_t q) const {
     const double* t = terms + size_t(n_blocks) * 256;
     double s = t[q * rpb];
@@ -525,9 +528,6 @@ struct TermSums {
 };
 dm_status bound_order(dm_ctx* ctx);
 TermSums term_sums(const dm_ctx* ctx);
-// sums per block into ctx->term_part; nothing is done when *skip (device, may be
-// NULL) is nonzero
-dm_status sum_terms(dm_ctx* ctx, const TermSums& T, const int32_t* skip);
 
 // Sweeps over all rows of the presolved problem (dual.hip).  Modes: update the
 // multipliers, write min-marginals (or soft marginals), bound only, or write

@@ -482,7 +482,7 @@ constexpr int NREG = 8;
 __global__ void k_term_start(const uint32_t* vpos, const int32_t* vinv, const uint8_t* vdeg, int64_t n, uint32_t* cpos,
                              int32_t* deg, const int32_t* short_perm, int64_t n_short, int32_t* short_slot,
                              const int32_t* long_perm, int64_t n_long, int32_t* long_slot, int64_t n_terms,
-                             double* terms, int32_t* bounds) {
+                             double* terms, int32_t* bounds, uint32_t* arrived) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) {
     const int32_t v = vinv[i];
@@ -494,6 +494,7 @@ __global__ void k_term_start(const uint32_t* vpos, const int32_t* vinv, const ui
   if (i < n_long) long_slot[long_perm[i]] = int32_t(i);
   if (i < n_terms) terms[i] = 0.0;
   if (i < 2 * NREG) bounds[i] = (i & 1) ? -2 : -1;
+  if (i == 0) *arrived = 0u;
 }
 
 // pre[k]: entries of the variables of keys below k, for k = 0 .. nkeys, from
@@ -595,20 +596,6 @@ __global__ __launch_bounds__(256) void k_rank_place(const uint32_t* key, const i
   }
   for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
   if ((threadIdx.x & 63) == 0 && before < n_place) place[slot[j]] = before;
-}
-
-// terms of the short rows 256 to a block, then of the projection rows per
-// block of 4 / wpr rows (one thread each)
-__global__ __launch_bounds__(256) void k_sum_terms(TermSums T, const int32_t* skip, double* part) {
-  __shared__ double red[4];
-  if (skip && *skip) return;   // uniform
-  if (int32_t(blockIdx.x) < T.n_blocks) {
-    const double s = block_sum_256(T.terms[size_t(blockIdx.x) * 256 + threadIdx.x], red);
-    if (threadIdx.x == 0) part[blockIdx.x] = s;
-    return;
-  }
-  const int32_t q = (int32_t(blockIdx.x) - T.n_blocks) * 256 + int32_t(threadIdx.x);
-  if (q < T.n_long_blocks) part[T.n_blocks + q] = T.long_block(q);
 }
 
 }  // namespace
@@ -836,6 +823,7 @@ dm_status bound_order(dm_ctx* ctx) {
     k.add<int32_t>(ntile);
     k.add<int32_t>(nlong);
     k.add<uint32_t>(5 * nfree);
+    k.add<uint32_t>(1);
     DM_ALLOC(ctx, ctx->term_mem, k.bytes);
     k.at = ctx->term_mem.p;
     ctx->terms = k.take<double>(int64_t(nb) * 256 + nlong);
@@ -843,6 +831,7 @@ dm_status bound_order(dm_ctx* ctx) {
     ctx->term_row = k.take<int32_t>(ntile);
     ctx->term_long = k.take<int32_t>(nlong);
     ctx->cpos = k.take<uint32_t>(5 * nfree);
+    ctx->term_arrived = k.take<uint32_t>(1);
     Slab w;
     for (int q = 0; q < 3; ++q) w.add<int32_t>(nshort);
     for (int q = 0; q < 3; ++q) w.add<int32_t>(nlong);
@@ -866,7 +855,7 @@ dm_status bound_order(dm_ctx* ctx) {
   const int64_t most = std::max({nfree, nshort, nlong, int64_t(nb) * 256, int64_t(2 * NREG)});
   k_term_start<<<grid_for(most, 256), 256, 0, st>>>(ctx->vpos.p, ctx->vinv.p, ctx->vdeg.p, nfree, ctx->cpos, deg,
                                                     ctx->short_perm.p, nshort, sslot, ctx->long_perm.p, nlong,
-                                                    lslot, int64_t(nb) * 256, ctx->terms, bounds);
+                                                    lslot, int64_t(nb) * 256, ctx->terms, bounds, ctx->term_arrived);
   DM_LAUNCH_CHECK(ctx);
   if (ntile > 0) {
     k_term_keys<<<grid_for(nshort, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rent_word.p, ctx->vkey.p, sslot, nshort,
@@ -898,12 +887,7 @@ TermSums term_sums(const dm_ctx* ctx) {
   T.n_long = int32_t(ctx->n_rows - ctx->n_short);
   T.rpb = 4 / ctx->long_wpr;
   T.n_long_blocks = (T.n_long + T.rpb - 1) / T.rpb;
+  T.part = ctx->term_part;
+  T.arrived = ctx->term_arrived;
   return T;
-}
-
-dm_status sum_terms(dm_ctx* ctx, const TermSums& T, const int32_t* skip) {
-  k_sum_terms<<<unsigned(T.n_blocks + (T.n_long_blocks + 255) / 256), 256, 0, ctx->stream>>>(T, skip,
-                                                                                            ctx->term_part);
-  DM_LAUNCH_CHECK(ctx);
-  return DM_OK;
 }

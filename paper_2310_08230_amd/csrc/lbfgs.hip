@@ -292,34 +292,66 @@ __global__ __launch_bounds__(1024) void k_qn_pair_fin(const double* part_sy, con
 }
 
 // ---------------------------------------------------------------- one-block decisions
-// Sum of a sweep's bound by a 1024-thread block: of the n block sums p, or (T.terms)
-// of the terms themselves where they are few: a thread takes up to FOLD_BLOCKS / 4
-// terms, and what a launch of k_sum_terms would write stays in LDS.  One launch
-// of a search over few rows fewer per trial (100-face pair, 22k entries, FP64:
-// 1.20 against 1.12 ms for 6 iterations); more blocks than FOLD_BLOCKS take one
-// workgroup longer than the launch.
+// Sum of a sweep's bound: of the n block sums p, or (T.terms) of the terms in their
+// own order.  Up to FOLD_BLOCKS blocks of terms one workgroup adds all; more are
+// dealt out, four to a workgroup, and the last workgroup to arrive adds their sums
+// (in index order, so it does not matter which).  Returns false in the others, which
+// are done: whatever the launch changes, it changes after all have arrived.
+// 320-face pair (12k rows, 100k entries), FP64, a call of six iterations: 996 us; with
+// a launch of its own for the block sums, 39 a call, 1023 (and up to 1180 where the
+// host is slower); with all of it in one workgroup 1078; with every thread
+// fencing, not one, 1267.  At 4k rows one workgroup is as good.
 constexpr int FOLD_BLOCKS = 32, FOLD_LONG = 1024;
 
-__device__ inline double bound_sum(const TermSums& T, const double* p, int n, double* red) {
+inline unsigned sum_grid(const TermSums& T) {
+  if (!T.terms || (T.n_blocks <= FOLD_BLOCKS && T.n_long_blocks <= FOLD_LONG)) return 1u;
+  return unsigned(std::max((T.n_blocks + 3) / 4, (T.n_long_blocks + 1023) / 1024));
+}
+
+__device__ inline bool bound_sum(const TermSums& T, const double* p, int n, double* red, double* E) {
   __shared__ double part[FOLD_BLOCKS + FOLD_LONG];
   __shared__ double waves[4 * FOLD_BLOCKS];
-  if (!T.terms) return sum_partials_1024(p, n, red);   // uniform
+  __shared__ bool last;
+  if (!T.terms) {   // uniform across the grid
+    *E = sum_partials_1024(p, n, red);
+    return true;
+  }
   constexpr int PER = FOLD_BLOCKS / 4;
   const int t = int(threadIdx.x);
-  double v[PER];
+  if (gridDim.x == 1) {
+    double v[PER];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) v[u] = 4 * u + t / 256 < T.n_blocks ? T.terms[u * 1024 + t] : 0.0;
+    for (int u = 0; u < PER; ++u) v[u] = 4 * u + t / 256 < T.n_blocks ? T.terms[u * 1024 + t] : 0.0;
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    if (4 * u >= T.n_blocks) break;   // uniform
-    v[u] = wave_sum(v[u]);
-    if ((t & 63) == 0) waves[u * 16 + t / 64] = v[u];
+    for (int u = 0; u < PER; ++u) {
+      if (4 * u >= T.n_blocks) break;   // uniform
+      v[u] = wave_sum(v[u]);
+      if ((t & 63) == 0) waves[u * 16 + t / 64] = v[u];
+    }
+    for (int q = t; q < T.n_long_blocks; q += 1024) part[T.n_blocks + q] = T.long_block(q);
+    __syncthreads();
+    if (t < T.n_blocks) part[t] = ((waves[4 * t] + waves[4 * t + 1]) + waves[4 * t + 2]) + waves[4 * t + 3];
+    __syncthreads();
+    *E = sum_partials_1024(part, T.n_blocks + T.n_long_blocks, red);
+    return true;
   }
-  for (int q = t; q < T.n_long_blocks; q += 1024) part[T.n_blocks + q] = T.long_block(q);
+  const int b0 = 4 * int(blockIdx.x);
+  const double v = wave_sum(b0 + t / 256 < T.n_blocks ? T.terms[size_t(b0) * 256 + t] : 0.0);
+  if ((t & 63) == 0) waves[t / 64] = v;
+  for (int q = int(blockIdx.x) * 1024 + t; q < T.n_long_blocks; q += int(gridDim.x) * 1024)
+    T.part[T.n_blocks + q] = T.long_block(q);
   __syncthreads();
-  if (t < T.n_blocks) part[t] = ((waves[4 * t] + waves[4 * t + 1]) + waves[4 * t + 2]) + waves[4 * t + 3];
+  if (t < 4 && b0 + t < T.n_blocks)
+    T.part[b0 + t] = ((waves[4 * t] + waves[4 * t + 1]) + waves[4 * t + 2]) + waves[4 * t + 3];
+  __syncthreads();   // the workgroup's sums are in its L2; one thread hands them on
+  if (t == 0) {
+    last = __hip_atomic_fetch_add(T.arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
+    if (last) *T.arrived = 0u;   // for the next launch
+  }
   __syncthreads();
-  return sum_partials_1024(part, T.n_blocks + T.n_long_blocks, red);
+  if (!last) return false;   // uniform
+  *E = sum_partials_1024(T.part, T.n_blocks + T.n_long_blocks, red);
+  return true;
 }
 
 // start of a call: the bound at the imported lambda; a fresh search also
@@ -327,7 +359,9 @@ __device__ inline double bound_sum(const TermSums& T, const double* p, int n, do
 __global__ __launch_bounds__(1024) void k_qn_begin(TermSums T, const double* sp, int32_t sn, double offset, QnState* st,
                                                  double* etrace, double gamma0, int32_t resume) {
   __shared__ double red[16];
-  const double E = offset + bound_sum(T, sp, sn, red);
+  double E = 0.0;
+  if (!bound_sum(T, sp, sn, red, &E)) return;   // uniform
+  E += offset;
   if (threadIdx.x == 0) {
     etrace[0] = E;
     if (!resume) {
@@ -351,8 +385,10 @@ __global__ __launch_bounds__(1024) void k_qn_probe(TermSums T, const double* sp,
                                                  double up, double down, QnState* st, double* gtrace,
                                                  int32_t* taken) {
   __shared__ double red[16];
-  if (st->done) return;   // uniform
-  const double E = offset + bound_sum(T, sp, sn, red);
+  if (st->done) return;   // uniform across the grid
+  double E = 0.0;
+  if (!bound_sum(T, sp, sn, red, &E)) return;   // uniform
+  E += offset;
   if (threadIdx.x != 0) return;
   if (t == 0 || E >= st->Em) {
     st->gm = st->gamma;
@@ -379,7 +415,9 @@ __global__ __launch_bounds__(1024) void k_qn_hist(TermSums T, const double* sp, 
                                                 double eps, QnState* st, double* etrace, double* sy_out,
                                                 double* yy_out, int32_t* accepted) {
   __shared__ double red[16];
-  const double E = offset + bound_sum(T, sp, sn, red);
+  double E = 0.0;
+  if (!bound_sum(T, sp, sn, red, &E)) return;   // uniform
+  E += offset;
   const double sy = sum_partials_1024(part_sy, hn, red);
   const double yy = sum_partials_1024(part_yy, hn, red);
   if (threadIdx.x != 0) return;
@@ -628,25 +666,16 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
   R* none = nullptr;
   Numbering N;
   DM_TRY(numbering<R>(ctx, N));
-  // the bound of the last sweep: its block sums, or in FP64 the terms (few) or their sums
+  // the bound of a sweep: its block sums, or in FP64 the terms
   constexpr bool ordered = sizeof(R) == 8;
-  const TermSums all = ordered ? term_sums(ctx) : TermSums();
-  const bool fold = all.n_blocks <= FOLD_BLOCKS && all.n_long_blocks <= FOLD_LONG;
-  const TermSums T = fold ? all : TermSums();
-  const double* sp = nullptr;
-  int32_t sn = 0;
-  auto block_sums = [&](const int32_t* skip) -> dm_status {
-    sp = ordered ? ctx->term_part : ctx->pend_partial;
-    sn = ordered ? all.n_blocks + all.n_long_blocks : ctx->pend_n;
-    return ordered && !fold ? sum_terms(ctx, all, skip) : DM_OK;
-  };
+  const TermSums T = ordered ? term_sums(ctx) : TermSums();
+  const unsigned SG = sum_grid(T);
   SweepExt sub;
   sub.gsub = gcell;
   sub.terms = ordered ? ctx->terms : nullptr;
   DM_TRY(cells_vars<R>(ctx, C.cells<R>(0), C.costs<R>(), C.ts<R>(0), true));
   DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(0), C.ts<R>(0), none, R(0), nullptr, &sub));
-  DM_TRY(block_sums(nullptr));
-  k_qn_begin<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, st, etrace, P.gamma0, resume ? 1 : 0);
+  k_qn_begin<<<SG, 1024, 0, stream>>>(T, ctx->pend_partial, ctx->pend_n, ctx->offset, st, etrace, P.gamma0, resume ? 1 : 0);
   k_qn_gather_g<<<G, VB, 0, stream>>>(gcell, N.pos, N.deg, n, B.g[0]);
   DM_LAUNCH_CHECK(ctx);
   for (int32_t k = 0; k < iters; ++k) {
@@ -658,9 +687,9 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
     pe.terms = sub.terms;
     for (int t = 0; t <= P.max_search; ++t) {
       DM_TRY(cells_rows<R>(ctx, SWEEP_BOUND, C.cells<R>(cur), C.ts<R>(cur), none, R(0), nullptr, &pe));
-      DM_TRY(block_sums(pe.skip));
-      k_qn_probe<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, t, P.max_search, P.step_up, P.step_down, st,
-                                         gamma_trace ? gamma_trace + k : nullptr, taken ? taken + k : nullptr);
+      k_qn_probe<<<SG, 1024, 0, stream>>>(T, ctx->pend_partial, ctx->pend_n, ctx->offset, t, P.max_search, P.step_up,
+                                          P.step_down, st, gamma_trace ? gamma_trace + k : nullptr,
+                                          taken ? taken + k : nullptr);
       DM_LAUNCH_CHECK(ctx);
       // the search usually stops at the second trial: one read of the flag
       // then spares launching the remaining probes (a skipped launch still
@@ -679,7 +708,6 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
     DM_TRY(cells_rows<R>(ctx, SWEEP_UPDATE, C.cells<R>(cur), C.ts<R>(cur), C.cells<R>(nxt), R(P.omega), nullptr, &me));
     DM_TRY(cells_vars<R>(ctx, C.cells<R>(nxt), C.costs<R>(), C.ts<R>(nxt), true));
     DM_TRY(cells_rows<R>(ctx, SWEEP_SUBGRAD, C.cells<R>(nxt), C.ts<R>(nxt), none, R(0), nullptr, &sub));
-    DM_TRY(block_sums(nullptr));
     double* psy = B.part + 2 * VGRID;
     double* pyy = B.part + 3 * VGRID;
     const int spare = S.spare;
@@ -689,7 +717,7 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
                                                B.Yp[spare], psy, pyy);
     else
       k_qn_gather_g<<<G, VB, 0, stream>>>(gcell, N.pos, N.deg, n, B.g[gc ^ 1]);
-    k_qn_hist<<<1, 1024, 0, stream>>>(T, sp, sn, ctx->offset, psy, pyy, m > 0 ? int32_t(G) : 0, k,
+    k_qn_hist<<<SG, 1024, 0, stream>>>(T, ctx->pend_partial, ctx->pend_n, ctx->offset, psy, pyy, m > 0 ? int32_t(G) : 0, k,
                                     (k == 0 && !resume) ? 1 : 0, P.eps, st, etrace, sc.sy(spare),
                                     sc.yy(spare), S.flag.p);
     DM_LAUNCH_CHECK(ctx);
