@@ -725,8 +725,7 @@ dm_status lbfgs_impl(dm_ctx* ctx, int32_t iters, const dm_lbfgs_params& P, R* la
     gc ^= 1;
     if (m > 0) {
       int32_t ok = 0;
-      DM_HIP(ctx, hipMemcpyAsync(&ok, S.flag.p, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-      DM_HIP(ctx, hipStreamSynchronize(stream));
+      DM_TRY(read_i32(ctx, S.flag.p, &ok));
       if (ok) {
         S.order.push_back(spare);
         if (int(S.order.size()) > m) {
