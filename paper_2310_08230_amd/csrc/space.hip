@@ -186,9 +186,13 @@ __global__ void k_max_degree(const uint64_t* dkey, int32_t nv, int32_t n, int* o
   if (i >= n) return;
   const uint64_t a = dkey[i] / uint64_t(nv);
   if (i > 0 && dkey[i - 1] / uint64_t(nv) == a) return;   // one thread per vertex: its first edge
-  int32_t d = 1;
-  while (i + d < n && dkey[i + d] / uint64_t(nv) == a) ++d;
-  atomicMax(out, d);
+  int32_t lo = i + 1, hi = n;   // the first edge of a later vertex (a hub may have thousands)
+  while (lo < hi) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (dkey[mid] < (a + 1) * uint64_t(nv)) lo = mid + 1;
+    else hi = mid;
+  }
+  atomicMax(out, lo - i);
 }
 
 // first directed edge of every vertex, and the edges' far ends: the sorted
@@ -208,9 +212,14 @@ __global__ void k_neighbours(const uint64_t* dkey, int32_t nv, int32_t n, int32_
 
 // place of b among a and its neighbours, in order (b is a or one of them)
 __device__ inline uint32_t near_rank(const int32_t* nbr, const int32_t* start, int32_t a, int32_t b) {
-  uint32_t r = b > a ? 1u : 0u;
-  for (int32_t i = start[a]; i < start[a + 1] && nbr[i] < b; ++i) ++r;
-  return r;
+  const int32_t s = start[a];
+  int32_t lo = s, hi = start[a + 1];
+  while (lo < hi) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (nbr[mid] < b) lo = mid + 1;
+    else hi = mid;
+  }
+  return uint32_t(lo - s) + (b > a ? 1u : 0u);
 }
 
 // Sort keys of the product edges, in the order of (smaller, larger) product
