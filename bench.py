@@ -413,37 +413,44 @@ TRAFFIC_PROFILES = {(2, 0, ()): "sweep_plain_fp32_500_hbm_traffic.json",
                     (5, 0, (("k", 144),)): "sweep_k144_hbm_point_hbm_traffic.json"}
 
 
-def _traffic(name="sweep_plain_fp32_500_hbm_traffic.json"):
-    """HBM bytes per sweep launch from a committed rocprofv3 counter summary
-    (FETCH_SIZE and WRITE_SIZE per dispatch, each scaled by its reading on a
-    plain copy kernel), used only while the sweep source is the one that was
-    profiled; otherwise None."""
+# what decides a sweep's instructions and traffic: its kernels, the orders of its
+# cells and variables, and the widths of its forms
+SWEEP_SOURCES = ("dual.hip", "layout.hip", "dm_internal.h")
+
+
+def _sweep_sources():
+    """SHA-256 of every sweep source in the tree."""
     import hashlib
+    src = os.path.join(ROOT, "paper_2310_08230_amd", "csrc")
+    return {f: hashlib.sha256(open(os.path.join(src, f), "rb").read()).hexdigest()
+            for f in SWEEP_SOURCES if os.path.exists(os.path.join(src, f))}
+
+
+def _profiled(name):
+    """A committed counter summary, or None unless it was taken on the present
+    sweep sources, every one of them."""
     path = os.path.join(ROOT, "profiles", name)
-    src = os.path.join(ROOT, "paper_2310_08230_amd", "csrc", "dual.hip")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    h = hashlib.sha256(open(src, "rb").read()).hexdigest()
-    if rec.get("dual_hip_sha256") != h:
-        return None
-    return rec.get("bytes_per_launch")
+    return rec if rec.get("sources_sha256", {"dual.hip": rec.get("dual_hip_sha256")}) == _sweep_sources() else None
+
+
+def _traffic(name="sweep_plain_fp32_500_hbm_traffic.json"):
+    """HBM bytes per sweep launch from a committed rocprofv3 counter summary
+    (FETCH_SIZE and WRITE_SIZE per dispatch, each scaled by its reading on a
+    plain copy kernel), used only while the sweep sources are those that were
+    profiled; otherwise None."""
+    rec = _profiled(name)
+    return rec.get("bytes_per_launch") if rec else None
 
 
 def _smoothed_valu():
     """VALU and transcendental wave-instructions per launch of the smoothed
     sweep on the 1000-face pair at T = 0.1, from the committed rocprofv3 SQ
-    counter summary, used only while the sweep source is the one that was
+    counter summary, used only while the sweep sources are those that were
     profiled; otherwise None."""
-    import hashlib
-    path = os.path.join(ROOT, "profiles", "sweep_smoothed_t0.1_1000_valu.json")
-    src = os.path.join(ROOT, "paper_2310_08230_amd", "csrc", "dual.hip")
-    if not os.path.exists(path):
-        return None
-    rec = json.load(open(path))
-    if rec.get("dual_hip_sha256") != hashlib.sha256(open(src, "rb").read()).hexdigest():
-        return None
-    return rec
+    return _profiled("sweep_smoothed_t0.1_1000_valu.json")
 
 
 def summarize_valu(counter_csv, out_json, workload, command=""):
@@ -452,7 +459,6 @@ def summarize_valu(counter_csv, out_json, workload, command=""):
     rocprofv3 --pmc collection; writes the summary the smoothed entry's
     roofline reads."""
     import csv
-    import hashlib
     import statistics
     rows = [r for r in csv.DictReader(open(counter_csv)) if "k_sweep<float, true, 0" in r["Kernel_Name"]]
 
@@ -463,11 +469,11 @@ def summarize_valu(counter_csv, out_json, workload, command=""):
     valu, n = med("SQ_INSTS_VALU")
     trans, _ = med("SQ_INSTS_VALU_TRANS_F32")
     waves, _ = med("SQ_WAVES")
-    src = os.path.join(ROOT, "paper_2310_08230_amd", "csrc", "dual.hip")
+    sources = _sweep_sources()
     rec = {"kernel": sorted({r["Kernel_Name"].strip() for r in rows})[0] if rows else "", "workload": workload,
            "dispatches": n, "waves_per_launch": waves, "valu_insts_per_launch": valu,
            "trans_insts_per_launch": trans, "valu_issue_peak_G_per_s": VALU_ISSUE_PEAK_G, "commands": command,
-           "dual_hip_sha256": hashlib.sha256(open(src, "rb").read()).hexdigest()}
+           "dual_hip_sha256": sources["dual.hip"], "sources_sha256": sources}
     with open(out_json, "w") as fh:
         json.dump(rec, fh, indent=1)
     print(json.dumps(rec, indent=1))
@@ -545,44 +551,48 @@ def copy_calibration(nbytes, reps=5):
 
 
 def summarize_counters(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, out_json, copy_bytes,
-                       command="", workload="plain_fp32_500 (config 2, seed 0)"):
+                       command="", workload="plain_fp32_500 (config 2, seed 0)", two_passes=False):
     """Turn rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE collections (KiB per
     dispatch) of the sweep kernels and of a plain copy of ``copy_bytes`` bytes
     into HBM bytes per sweep (the row pass and, where the collection has one,
-    the variable pass before it); writes the summary JSON used by the
-    roofline's ``traffic`` field."""
+    the variable pass before it; ``two_passes``: it must); writes the summary
+    JSON used by the roofline's ``traffic`` field.  Raises when the sweep or
+    the copy is missing from a collection."""
     import csv
-    import hashlib
     import statistics
 
     names = set()
 
-    def per_kernel(path, counter, name_has):
+    def per_kernel(path, counter, name_has, needed=True):
         rows = [r for r in csv.DictReader(open(path))
                 if r["Counter_Name"] == counter and name_has in r["Kernel_Name"]]
         if name_has.startswith("k_"):
             names.update(r["Kernel_Name"].strip() for r in rows)
-        return statistics.median([float(r["Counter_Value"]) for r in rows] or [0.0]), len(rows)
+        if not rows:
+            if needed:
+                raise ValueError(f"{path}: no {counter} of {name_has}")
+            return 0.0, 0
+        return statistics.median(float(r["Counter_Value"]) for r in rows), len(rows)
 
     cf, _ = per_kernel(copy_fetch_csv, "FETCH_SIZE", "copyBuffer")
     cw, _ = per_kernel(copy_write_csv, "WRITE_SIZE", "copyBuffer")
     # the hard FP32 update sweep, k_sweep<float, false, 0, ...>, and its variable pass
     f, nf = per_kernel(fetch_csv, "FETCH_SIZE", "k_sweep<float, false, 0")
     wv, nw = per_kernel(write_csv, "WRITE_SIZE", "k_sweep<float, false, 0")
-    f += per_kernel(fetch_csv, "FETCH_SIZE", "k_vars<float>")[0]
-    wv += per_kernel(write_csv, "WRITE_SIZE", "k_vars<float>")[0]
+    f += per_kernel(fetch_csv, "FETCH_SIZE", "k_vars<float>", two_passes)[0]
+    wv += per_kernel(write_csv, "WRITE_SIZE", "k_vars<float>", two_passes)[0]
     kib = copy_bytes / 1024.0
     ffac, wfac = kib / cf, kib / cw
     fetch_b = f * ffac * 1024.0
     write_b = wv * wfac * 1024.0
-    src = os.path.join(ROOT, "paper_2310_08230_amd", "csrc", "dual.hip")
+    sources = _sweep_sources()
     rec = {"kernel": " / ".join(sorted(names)), "workload": workload,
            "fetch_kib_median": f, "write_kib_median": wv, "dispatches": [nf, nw],
            "copy_calibration": {"bytes": copy_bytes, "fetch_kib": cf, "write_kib": cw,
                                 "fetch_factor": ffac, "write_factor": wfac},
            "bytes_per_launch": int(fetch_b + write_b), "fetch_bytes": int(fetch_b), "write_bytes": int(write_b),
            "commands": command,
-           "dual_hip_sha256": hashlib.sha256(open(src, "rb").read()).hexdigest()}
+           "dual_hip_sha256": sources["dual.hip"], "sources_sha256": sources}
     with open(out_json, "w") as fh:
         json.dump(rec, fh, indent=1)
     print(json.dumps(rec, indent=1))
@@ -609,7 +619,8 @@ def summarize_trace(stats_csv, out_txt, command):
 def main():
     if len(sys.argv) > 1 and sys.argv[1] == "--summarize-counters":
         # fetch write copy_fetch copy_write out_json copy_bytes workload command...
-        summarize_counters(*sys.argv[2:7], int(sys.argv[7]), " ".join(sys.argv[9:]), sys.argv[8])
+        summarize_counters(*sys.argv[2:7], int(sys.argv[7]), " ".join(sys.argv[9:]), sys.argv[8],
+                           two_passes=True)
         return
     if len(sys.argv) > 1 and sys.argv[1] == "--copy-calibration":
         copy_calibration(int(sys.argv[2]))
