@@ -67,10 +67,14 @@ MIDDLE = [([40] * 145, 60),              # just over what one workgroup takes
           ([520, 1500] * 12, 120),       # a block per exactly-one row, entries beyond the registers
           ([], 1500),                    # none of them
           ([250] * 640, 900)]            # 170k entries, the largest such problems
+# one workgroup: 4, 16 and 64 lanes per exactly-one row, entries beyond a lane's registers
+SMALL = [([10] * 40, 60), ([30] * 30, 40), ([5, 7, 160] * 8, 10), ([300] * 8, 0), ([300, 70] * 6, 40), ([100, 400] * 4, 60),
+         ([], 300)]
+LARGE = [([260] * 700, 900)]             # two passes
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
-@pytest.mark.parametrize("lens,n_side", MIDDLE)
+@pytest.mark.parametrize("lens,n_side", MIDDLE + SMALL + LARGE)
 def test_steps_match_the_oracle(lens, n_side, prec):
     n, ptr, cols, coefs, rhs, cost = mixed(lens, n_side, 1)
     S = O.Space.from_ilp(n, ptr, cols, coefs, rhs)
