@@ -511,7 +511,7 @@ struct Slab {
     return q;
   }
 };
-// The terms of a bound in an order of the problem's own (bound_order): those of
+// The terms of a bound in their fixed order (bound_order): those of
 // the short rows in blocks of 256, then those of the projection rows in blocks
 // of rpb rows.
 struct TermSums {

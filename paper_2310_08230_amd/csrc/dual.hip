@@ -21,11 +21,11 @@
 // bytes through the L2 at the 2000/3000-face pair, 253 us).  Split in two, the
 // row pass streams its cells coalesced, in place, and every random access is a
 // 4-byte read of a small array (t: 4 bytes per variable) or of cells that
-// neighbouring variables share.  Measured, one iteration before and after:
-// 13.2 -> 9.1 us at the 500-face pair (two launches of 2.4 us each are half of
-// it), 41.6 -> 21.9 at 1000 faces, 253 -> 105 at 2000/3000 (row pass 65, variable
-// pass 40; 4.6 and 5.0 TB/s through the L2s, a plain copy reaches 4.7), 837 -> 308
-// with K = 144 candidates.
+// neighbouring variables share.  Measured, one iteration of a long solve before
+// and after: 13.2 -> 9.2 to 9.7 us at the 500-face pair (two launches of 2.4 us
+// each are half of it), 41.6 -> 22.6 at 1000 faces, 253 -> 108 at 2000/3000 (row
+// pass 66, variable pass 43; 5.0 TB/s through the L2s, a plain copy reaches 4.7 to
+// 4.9), 837 -> 342 with K = 144 candidates.
 //
 // Problems of few entries take other forms of the same iteration, bit for bit: one
 // workgroup that runs all of them from LDS (k_small), or one launch each, in
@@ -73,23 +73,6 @@ template <>
 __device__ inline float r_log<float>(float x) { return logf(x); }
 template <>
 __device__ inline double r_log<double>(double x) { return log(x); }
-template <typename R>
-__device__ inline R r_log1p(R x);
-template <>
-__device__ inline float r_log1p<float>(float x) { return log1pf(x); }
-template <>
-__device__ inline double r_log1p<double>(double x) { return log1p(x); }
-
-// soft-min of two values (hard min when T == 0):
-// -T log(e^{-a/T} + e^{-b/T}) = min(a, b) - T log1p(e^{-|a-b|/T})
-template <typename R, bool SOFT>
-__device__ inline R smin2(R a, R b, R T) {
-  if (!SOFT) return a < b ? a : b;
-  if (a == rinf<R>()) return b;
-  if (b == rinf<R>()) return a;
-  const R m = a < b ? a : b, d = a < b ? b - a : a - b;
-  return m - T * r_log1p<R>(r_exp<R>(-d / T));
-}
 
 // Scaled soft-min arithmetic for the short-row recursion.  Values are kept in
 // units u = x / (T ln 2) (FP32) or u = x / T (FP64), so that the soft-min of
@@ -276,12 +259,14 @@ __device__ inline R cell_lambda(const SweepArgs& A, const R* cells, RT t, uint32
 
 // ---------------------------------------------------------------- short rows, hard min
 // One wave per chunk of whole closedness rows (<= 64 entries, one per lane),
-// four chunks per block, no LDS and no barrier until the bound.  Every
-// cross-lane step runs in a wave-uniform loop, so no lane ever reads from an
-// inactive lane:
-//  1. lane e holds entry e (multiplier, sign, word); the first lanes hold the
-//     row starts, and each lane finds its row with a 5-step binary search;
-//  2. rank inside the row's sign group by comparing with the row's lanes;
+// four chunks per block, with an LDS slice per wave and no barrier until the
+// bound.  Every cross-lane step runs in a wave-uniform loop, so no lane ever
+// reads from an inactive lane:
+//  1. lane e holds entry e (multiplier, sign, word) and finds its row in the
+//     chunk's mask of row starts;
+//  2. rank inside the row's sign group by comparing with the row's values, which
+//     the wave's slice holds; if every row of the chunk has b = 0, a closed form
+//     of the ranks gives the rest;
 //  3. ds_permute moves every value to its sorted position;
 //  4. a segmented inclusive scan gives S(k), the sum of the k smallest of a
 //     group, at the lane of the k-th smallest;
@@ -1097,9 +1082,9 @@ constexpr int32_t LONG_GROUP = 8;   // consecutive projection-row blocks per XCD
 // blocks takes as long as its longest chain of loads and reductions: descriptor,
 // words, cells and residuals, six exchange steps of (m, m2), four of them as
 // register moves.  With row number, offsets and an exchange of (m, m2, index)
-// through the LDS an FP32 iteration took 7.5-8.1 us with 8k-30k entries, 9.4 with
-// 231k; so 6.5-6.8 and 9.1.  In place where
-// cells and dst are one array: a lane reads its own cells before it writes them.
+// through the LDS an FP32 iteration of two launches took 7.5-8.1 us with 8k-30k
+// entries, 9.4 with 231k; so 6.5-6.8 and 9.1.  In place where cells and dst are
+// one array: a lane reads its own cells before it writes them.
 // Returns the row minimum on one lane of the row.
 template <typename R, typename RT, int MODE>
 __device__ __forceinline__ double long_cells(const SweepArgs& A, const R* cells, RT t, R* dst, R omega, R gam,
@@ -1304,7 +1289,7 @@ constexpr size_t smem_bytes() {
 // First pass of a hard iteration: t_i = c_i - sum_k s_k, one thread per
 // variable in variable order; unused slots read the zero cell.  Bound by the
 // index planes and the gathered lines (2000/3000-face pair: 20 + 16 bytes per
-// variable, 40 us, 5 TB/s; 9 us more with the variables in canonical order).
+// variable, 43 us, 5 TB/s; 9 us more with the variables in canonical order).
 // Blocks 8 and up take the variables, each XCD a contiguous eighth; block 0
 // sums the previous row pass's partials, so that no other launch has to.
 template <typename R>

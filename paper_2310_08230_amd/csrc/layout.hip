@@ -21,7 +21,7 @@
 // wave's gathers fall into few cache lines, and each XCD, which takes a
 // contiguous eighth of either order, holds nearly all of what it reads in its
 // own L2 (2000/3000-face pair, both passes: 11 us more with the canonical order
-// inside each X face; they take 105).  A generic problem without meshes keys a
+// inside each X face; they take 108).  A generic problem without meshes keys a
 // variable by its index.
 #include <algorithm>
 #include <climits>
@@ -467,13 +467,16 @@ dm_status mesh_ranks(dm_ctx* ctx, MeshDev& M, DArr<int32_t>& frank, DArr<int32_t
 // ---------------------------------------------------------------- order of the bound's terms
 // A quasi-Newton search compares bounds.  Where the relaxation is tight these
 // differ in their last bits only, so the order in which the rows' terms are
-// added decides the steps that the search takes.  In FP32 it does not (a term
-// has 24 bits, the sums 53); in FP64 the terms are therefore added in an order
-// of the problem's own, which no change of the launch layout touches: the tile
-// rows by their smallest X rank and row number, 256 to a block; the chunks,
-// four to a block; the projection rows by (region, key), where the regions are
-// the eighths of all entries in key order, an X row has the key of its face and
-// the Y rows are dealt to the regions in turn.
+// added decides the steps that the search takes.  In FP64 the terms are therefore
+// added in one order, whichever way the rows are launched: the one in which the
+// earlier sweep over records dealt them to the eight XCDs, so that searches take
+// the steps that they took with it.  The tile rows by their smallest X rank and
+// row number, 256 to a block; the chunks, four to a block; the projection rows by
+// (region, key), where the regions are the eighths of all entries in key order, an
+// X row has the key of its face and the Y rows are dealt to the regions in turn.
+// In FP32 the blocks' sums are added as launched: what the order changes there,
+// the last bits of an FP64 sum, lies far below the terms' own rounding of 2^-24, and
+// a step that hangs on it may change with the layout.
 constexpr int NREG = 8;
 
 // what needs no order yet, in one launch: vpos with the variables in canonical
@@ -662,7 +665,7 @@ dm_status sweep_layout(dm_ctx* ctx) {
   if (nshort > 0) {
     // the narrowest tiles only where one workgroup may sweep the problem from LDS
     // and its arithmetic counts: rows of one place spread over more tiles cost
-    // the variable pass cache lines (2000/3000-face pair 7 us more of 105
+    // the variable pass cache lines (2000/3000-face pair 7 us more of 108
     // an iteration with them, 1000 faces 0.6 of 22)
     const uint32_t form0 = rnnz <= SMALL_NNZ[0] ? 0u : 1u;
     k_short_keys<<<grid_for(nshort, 256), 256, 0, st>>>(ctx->rrow_ptr.p, ctx->rrow_b.p, ctx->rent_word.p, vkey.p,

@@ -11,10 +11,10 @@
 // order, and the history pass gathers the new g.  g and y only take the values 0/1 and -1/0/1 and
 // are stored as bytes, so a history pair costs 5 reals and 5 bytes per
 // variable.  In FP32 i counts in variable order (layout.hip), where the gathers
-// are cheapest.  In FP64 i is canonical and the bounds are summed in an order
-// of the problem's own (bound_order): where the relaxation is tight the search
-// compares sums that differ in their last bits only, and its steps should not
-// hang on how the launch deals the rows.
+// are cheapest.  In FP64 i is canonical and the bounds' terms are added in one
+// fixed order (bound_order): where the relaxation is tight the search compares
+// sums that differ in their last bits only, and its steps should not hang on how
+// the launch deals the rows.
 //
 // One iteration, as launched by the host loop below:
 //  1. direction: 2h + 1 variable-major passes over the last h accepted pairs.
