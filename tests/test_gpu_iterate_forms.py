@@ -104,3 +104,33 @@ def test_steps_match_the_oracle(lens, n_side, prec):
             assert abs(float(trace[k]) - S.lower_bound(a)) <= (10 + 8 * 3 ** k) * u * np.abs(a).sum()
         again = ctx.dual_solve(at[0].clone(), iters, trace=False)[0]
         assert torch.equal(again, lam)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_both_buffers_in_a_workspace(prec):
+    """One launch per iteration alternates between two cell buffers, the context's
+    own or those of a workspace, here full of NaN, of which nothing is used once it
+    is detached."""
+    n, ptr, cols, coefs, rhs, cost = mixed([40] * 145, 60, 2)
+    ctx = dm().Context(0)
+    ctx.build_ilp(n, ptr, cols, coefs, rhs)
+    ctx.set_costs(torch.from_numpy(cost))
+    start = ctx.init_lambda(prec)
+    none = ctx.dual_solve(start.clone(), 0)[0]
+    bound = ctx.lower_bound(start)
+    own = {k: ctx.dual_solve(start.clone(), k) for k in (1, 2, 5)}
+    assert float(own[1][1][0]) == pytest.approx(bound, rel=1e-12)
+    ws = torch.full((ctx.workspace_bytes(prec),), 255, dtype=torch.uint8, device="cuda")
+    ctx.set_workspace(prec, ws)
+    for k in (5, 1, 2):
+        lam, trace = ctx.dual_solve(start.clone(), k)
+        assert torch.equal(lam, own[k][0]) and torch.equal(trace, own[k][1])
+    ctx.set_workspace(prec, None)
+    torch.cuda.synchronize()
+    kept = ws.fill_(255).clone()
+    assert torch.equal(ctx.dual_solve(start.clone(), 0)[0], none)
+    for k in (2, 5, 1):
+        lam, trace = ctx.dual_solve(start.clone(), k)
+        assert torch.equal(lam, own[k][0]) and torch.equal(trace, own[k][1])
+    torch.cuda.synchronize()
+    assert torch.equal(ws, kept)
